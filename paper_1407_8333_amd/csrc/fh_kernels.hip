@@ -1452,6 +1452,27 @@ __device__ Best block_best(Best m, Best *red) {
     return r;
 }
 
+// Value and critical ratio of a cell holding `val` (a count, or a fixed-point
+// weighted sum when ws is given).
+__device__ __forceinline__ void cell_value(uint32_t val, int32_t n_fft, double theta,
+                                           const WeightStats *__restrict__ ws, float *value, float *cr) {
+    const double p0 = exp(-theta) - exp(-2.0 * theta) + exp(-3.0 * theta) / 3.0;
+    double mu, sd, v;
+    if (ws != nullptr) {
+        const WeightStats st = *ws;
+        const double scale = ldexp(1.0, -st.frac_bits);
+        mu = p0 * st.sum_w;
+        sd = sqrt(p0 * (1.0 - p0) * st.sum_w2);
+        v = (double)(float)((float)val * (float)scale);
+    } else {
+        mu = (double)n_fft * p0;
+        sd = sqrt((double)n_fft * p0 * (1.0 - p0));
+        v = (double)val;
+    }
+    *value = (float)v;
+    *cr = (float)((v - mu) / sd);
+}
+
 __global__ void __launch_bounds__(256) k_select(const unsigned long long *__restrict__ colmax,
                                                 int32_t nf, fh_select sel, int32_t sky_base,
                                                 int32_t n_fft, const WeightStats *__restrict__ ws,
@@ -1484,18 +1505,6 @@ __global__ void __launch_bounds__(256) k_select(const unsigned long long *__rest
     }
     const Best b2 = block_best(m, red);
     if (threadIdx.x == 0) {
-        const double th = sel.theta;
-        const double p0 = exp(-th) - exp(-2.0 * th) + exp(-3.0 * th) / 3.0;
-        double scale = 1.0, mu, sd;
-        if (ws != nullptr) {
-            const WeightStats st = ws[(int64_t)slot * ws_stride];
-            scale = ldexp(1.0, -st.frac_bits);
-            mu = p0 * st.sum_w;
-            sd = sqrt(p0 * (1.0 - p0) * st.sum_w2);
-        } else {
-            mu = (double)n_fft * p0;
-            sd = sqrt((double)n_fft * p0 * (1.0 - p0));
-        }
         fh_candidate *o = out + ((int64_t)(sky_base + slot) * n_sb + sb) * 2;
         const Best bs[2] = {b1, b2};
         for (int r = 0; r < 2; ++r) {
@@ -1510,12 +1519,10 @@ __global__ void __launch_bounds__(256) k_select(const unsigned long long *__rest
             }
             c.valid = valid ? 1 : 0;
             if (valid) {
-                const double value = ws != nullptr ? (double)(float)((float)bs[r].val * (float)scale)
-                                                   : (double)bs[r].val;
                 c.bin = bs[r].bin;
                 c.row = bs[r].row;
-                c.value = (float)value;
-                c.cr = (float)((value - mu) / sd);
+                cell_value(bs[r].val, n_fft, sel.theta, ws != nullptr ? ws + (int64_t)slot * ws_stride : nullptr,
+                           &c.value, &c.cr);
             } else {
                 c.bin = -1;
                 c.row = -1;
@@ -1772,8 +1779,11 @@ static hipError_t launch_tiles_t(const TileArgs &a, bool persistent, int32_t n_t
     return hipGetLastError();
 }
 
+static hipError_t set_refine_attributes();
+
 hipError_t init_kernel_attributes() {
     hipError_t e;
+    if ((e = set_refine_attributes()) != hipSuccess) return e;
     if ((e = set_tile_attrs<true, true, true>()) != hipSuccess) return e;
     if ((e = set_tile_attrs<true, true, false>()) != hipSuccess) return e;
     if ((e = set_tile_attrs<true, false, true>()) != hipSuccess) return e;
@@ -1849,6 +1859,183 @@ __global__ void k_slice_pack(const int64_t *__restrict__ first, const int32_t *_
     const int i = blockIdx.x;
     const int64_t src = first[i], dst = offsets[i];
     for (int k = threadIdx.x; k < counts[i]; k += blockDim.x) out[dst + k] = bins[src + k];
+}
+
+// ----------------------------------------------------------------------------
+// refinement of many coarse candidates.  A refined volume is small (2 K_f + 1
+// bins x 4 K_fdot rows), so per (candidate, direction) only a few peaks of
+// each FFT can reach it: the tiles' machinery (stripe edges of a sliced
+// peakmap, sorted windows, tiles) costs eleven launches per candidate, each
+// far too small for the GPU.  Here all candidates run in two launches.
+
+// Per (candidate, FFT): the run of peaks with natural bin in [klo, khi).
+// grid.y = candidate.
+__global__ void __launch_bounds__(256) k_refine_runs(int32_t n_fft, const int64_t *__restrict__ offsets,
+                                                     const int32_t *__restrict__ bins,
+                                                     const RefineCand *__restrict__ rc, int2 *__restrict__ runs) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n_fft) return;
+    const RefineCand q = rc[blockIdx.y];
+    const int32_t p0 = (int32_t)offsets[i], p1 = (int32_t)offsets[i + 1];
+    // both lower bounds in lockstep
+    int32_t a = p0, b = p0;
+    int32_t top = 1;
+    while (top <= (p1 - p0) >> 1) top <<= 1;
+    for (int32_t st = top; st > 0; st >>= 1) {
+        const int32_t ta = a + st - 1, tb = b + st - 1;
+        const int32_t va = ta < p1 ? bins[ta] : 0x7fffffff, vb = tb < p1 ? bins[tb] : 0x7fffffff;
+        if (va < q.k_lo) a += st;
+        if (vb < q.k_hi) b += st;
+    }
+    runs[(int64_t)blockIdx.y * n_fft + i] = make_int2(a, b);
+}
+
+// One workgroup per (direction, candidate): grid (n_dir, n_cand).  Threads
+// own FFTs: the FFT's peaks whose stripes meet the volume are a contiguous
+// part of its run (Y ascends; the shifts' extremes over the rows are those of
+// the first and last row).  These peaks (0.1-2 per FFT) are compacted into an
+// LDS list, so that the (peak, row) pairs then spread evenly over the
+// threads, one LDS atomic each; window sums and the maximum follow in LDS.
+// Bound by the chain of dependent loads per FFT (run, then the edges of its
+// binary search), which several workgroups per CU hide.  Measured on 22
+// candidates x 25 directions (3140 FFTs of 8192 s at 100 Hz, 20 rows): the
+// whole call 2290 us with a slice and a tile search per candidate, 133 us so.
+constexpr int kRefineThreads = 512;
+constexpr int kRefineList = 1024;  // listed peaks per pass
+
+struct RefinePeak {
+    int64_t y;    // stripe edge Y
+    double tau;   // t_i - t0
+};
+
+__global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
+    int32_t n_fft, const int32_t *__restrict__ bins, const double *__restrict__ t, const double *__restrict__ v,
+    const double *__restrict__ sky, const RefineCand *__restrict__ rc, const int2 *__restrict__ runs, int32_t kf,
+    int32_t nf, int32_t ns, double dfdot, double t0, double S, double theta, const float *__restrict__ w,
+    const WeightStats *__restrict__ ws, int32_t shift_mode, fh_candidate *__restrict__ out) {
+    extern __shared__ uint32_t cells[];  // [ns][nf + kf - 1] stripe starts
+    __shared__ RefinePeak s_peak[kRefineList];
+    __shared__ uint32_t s_w[kRefineList];
+    __shared__ int s_wave[kRefineThreads / 64];
+    __shared__ unsigned long long s_best;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int cand = blockIdx.y, dir = blockIdx.x, n_dir = gridDim.x;
+    const RefineCand q = rc[cand];
+    const double *n = sky + 3 * ((int64_t)cand * n_dir + dir);
+    const double n0 = n[0], n1 = n[1], n2 = n[2];
+    const int wc = nf + kf - 1;
+    const int n_cells = ns * wc;
+    for (int x = tid; x < n_cells; x += kRefineThreads) cells[x] = 0u;
+    if (tid == 0) s_best = 0ull;
+    bool bad = false;
+    int frac = 0;
+    if (w != nullptr) {
+        bad = ws->bad != 0;
+        frac = ws->frac_bits;
+    }
+    const int2 *__restrict__ run = runs + (int64_t)cand * n_fft;
+    const int64_t ybase = -q.b0 * kQ - (int64_t)kf * (kQ / 2) + (kQ - 1);
+    for (int i0 = 0; i0 < n_fft; i0 += kRefineThreads) {
+        const int i = i0 + tid;
+        int pa = 0, pe = 0;
+        double r = 1.0, tau = 0.0;
+        int64_t c = ybase;
+        auto edge = [&](int p) -> int64_t {
+            const int32_t k = bins[p];
+            if (shift_mode) return (int64_t)(kf * k) * kQ + c;
+            double x = (double)(kf * k) * r;
+            x = x * kQd;
+            return (int64_t)floor(x) + c;
+        };
+        if (i < n_fft) {
+            const int2 ab = run[i];
+            const double *vi = v + 3 * (int64_t)i;
+            double d = vi[0] * n0;
+            d = d + vi[1] * n1;
+            d = d + vi[2] * n2;
+            d = 1.0 + d;
+            r = 1.0 / d;
+            if (shift_mode) c -= llrint((q.q * (1.0 - r)) * kQd);
+            tau = t[i] - t0;
+            const int64_t ga = row_shift(tau, S, q.fdot0, dfdot, 0), gb = row_shift(tau, S, q.fdot0, dfdot, ns - 1);
+            // some row's start lies in columns [0, wc), column = start + K_f - 1
+            const int64_t y_lo = -(int64_t)(kf - 1) * kQ + (ga < gb ? ga : gb);
+            const int64_t y_hi = (int64_t)nf * kQ + (ga < gb ? gb : ga);
+            pa = pe = ab.x;
+            int top = 1;
+            while (top <= (ab.y - ab.x) >> 1) top <<= 1;
+            for (int st = top; st > 0; st >>= 1) {
+                const int ta = pa + st - 1, te = pe + st - 1;
+                if (ta < ab.y && edge(ta) < y_lo) pa += st;
+                if (te < ab.y && edge(te) < y_hi) pe += st;
+            }
+        }
+        // places of the thread's peaks in the list: exclusive scan of the counts
+        const int cnt = pe - pa;
+        int incl = cnt;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(incl, o);
+            if (lane >= o) incl += u;
+        }
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int first = incl - cnt, total = 0;
+        for (int k = 0; k < kRefineThreads / 64; ++k) {
+            const int u = s_wave[k];
+            first += k < wave ? u : 0;
+            total += u;
+        }
+        uint32_t wq = 1u;
+        if (w != nullptr && cnt > 0) wq = bad ? 0u : (uint32_t)rint(ldexp((double)w[i], frac));
+        for (int base = 0; base < total; base += kRefineList) {
+            const int b0 = max(0, base - first), b1 = min(cnt, base + kRefineList - first);
+            for (int u = b0; u < b1; ++u) {
+                s_peak[first + u - base] = {edge(pa + u), tau};
+                s_w[first + u - base] = wq;
+            }
+            __syncthreads();
+            const int n_pairs = min(total - base, kRefineList) * ns;
+            for (int e = tid; e < n_pairs; e += kRefineThreads) {
+                const int p = e / ns, s = e - p * ns;
+                const RefinePeak pk = s_peak[p];
+                const int64_t g = row_shift(pk.tau, S, q.fdot0, dfdot, s);
+                const int64_t col = shrq(pk.y - g) + (kf - 1);
+                if (col >= 0 && col < wc) atomicAdd(&cells[s * wc + (int)col], s_w[p]);
+            }
+            __syncthreads();
+        }
+        if (total == 0) __syncthreads();  // s_wave is rewritten by the next round
+    }
+    __syncthreads();
+    // window sums and their maximum (larger value, smaller bin, smaller row)
+    unsigned long long best = 0ull;
+    for (int e = tid; e < nf * ns; e += kRefineThreads) {
+        const int s = e / nf, b = e - s * nf;
+        const uint32_t *P = cells + s * wc + b;
+        uint32_t h = 0;
+        for (int k = 0; k < kf; ++k) h += P[k];
+        const unsigned long long key = ((unsigned long long)h << 32) | (0xFFFFFFFFull - (unsigned)(b * ns + s));
+        best = key > best ? key : best;
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        const unsigned long long u = __shfl_xor(best, o);
+        best = u > best ? u : best;
+    }
+    if (lane == 0) atomicMax(&s_best, best);
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned long long k = s_best;
+        const uint32_t at = 0xFFFFFFFFu - (uint32_t)k;
+        fh_candidate x;
+        x.sky = dir;
+        x.subband = 0;
+        x.rank = 0;
+        x.bin = (int32_t)(at / (uint32_t)ns);
+        x.row = (int32_t)(at % (uint32_t)ns);
+        cell_value((uint32_t)(k >> 32), n_fft, theta, ws, &x.value, &x.cr);
+        x.valid = 1;
+        out[2 * ((int64_t)cand * n_dir + dir)] = x;
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -2109,6 +2296,37 @@ hipError_t launch_slice(int32_t n_fft, const int64_t *offsets, const int32_t *bi
     k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_slice_pack<<<n_fft, 256, 0, st>>>(first, counts, out_offsets, bins, out_bins);
+    return hipGetLastError();
+}
+
+static hipError_t set_refine_attributes() {
+    const int fixed = (int)sizeof(RefinePeak) * kRefineList + 4 * kRefineList + 1024;
+    return hipFuncSetAttribute((const void *)k_refine_cells, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kLdsBytes - fixed);
+}
+
+// The line lies where the volume and the peak list fill the LDS of a CU (up to
+// 4 x 46 rows at K_f = 64, 4 x 296 at K_f = 10); beyond it the cells have no
+// place and the volume is searched with the tiles, candidate by candidate.
+int refine_cell_bytes(int kf, int nf, int ns) {
+    const int64_t n = 4ll * ns * (nf + kf - 1);
+    const int64_t fixed = (int64_t)sizeof(RefinePeak) * kRefineList + 4 * kRefineList + 1024;
+    return n + fixed <= kLdsBytes ? (int)n : 0;
+}
+
+hipError_t launch_refine_cells(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const double *t,
+                               const double *v, int32_t n_cand, int32_t n_dir, const double *sky,
+                               const RefineCand *rc, int2 *runs, int32_t kf, int32_t nf, int32_t ns, double dfdot,
+                               double t0, double t_fft, double theta, const float *w, const WeightStats *ws,
+                               int32_t shift_mode, fh_candidate *out, hipStream_t st) {
+    const int lds = refine_cell_bytes(kf, nf, ns);
+    if (lds == 0 || n_cand > 65535) return hipErrorInvalidValue;
+    k_refine_runs<<<dim3(grid_for(n_fft, 256), n_cand), 256, 0, st>>>(n_fft, offsets, bins, rc, runs);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const double S = ((double)kf * t_fft) * kQd;
+    k_refine_cells<<<dim3(n_dir, n_cand), kRefineThreads, lds, st>>>(n_fft, bins, t, v, sky, rc, runs, kf, nf, ns,
+                                                                     dfdot, t0, S, theta, w, ws, shift_mode, out);
     return hipGetLastError();
 }
 

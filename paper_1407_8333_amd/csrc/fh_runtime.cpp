@@ -172,8 +172,8 @@ struct fh_ctx {
     int32_t doppler_mode = 0;
     double doppler_fref = 0.0;
     DevBuf err;
-    // refinement: sliced peakmap and per-call scratch
-    DevBuf rf_offsets, rf_bins, rf_t, rf_v, rf_first, rf_counts, rf_cands, rf_aux;
+    // refinement: sliced peakmap (volumes larger than the LDS) and per-call scratch
+    DevBuf rf_offsets, rf_bins, rf_first, rf_counts, rf_cands, rf_aux;
     // cleaning: robust-statistic histogram, its rank sum and results
     DevBuf cl_hist, cl_s2, cl_out;
     // autotuned tile width per problem shape (shared by weighted and
@@ -771,7 +771,7 @@ void fh_ctx_destroy(fh_ctx *ctx) {
     ctx->graphs.clear();
     ctx->main_ws.release();
     ctx->err.release();
-    for (DevBuf *b : {&ctx->rf_offsets, &ctx->rf_bins, &ctx->rf_t, &ctx->rf_v, &ctx->rf_first, &ctx->rf_counts,
+    for (DevBuf *b : {&ctx->rf_offsets, &ctx->rf_bins, &ctx->rf_first, &ctx->rf_counts,
                       &ctx->rf_cands, &ctx->rf_aux, &ctx->cl_hist, &ctx->cl_s2, &ctx->cl_out})
         b->release();
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
@@ -1107,50 +1107,80 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
                 for (int k = 0; k < 3; ++k) sky[3 * ((size_t)c * n_dir + d) + k] = n[k] / r;
             }
     }
-    // the sliced peakmap (context-owned arrays, reused by every candidate)
     const int32_t N = pm->n_fft;
     const int64_t cap = std::min<int64_t>((int64_t)N * width, pm->n_peaks);
-    if ((s = ctx->rf_offsets.ensure(8 * (size_t)(N + 1), st)) || (s = ctx->rf_bins.ensure(4 * (size_t)cap + 4, st)) ||
-        (s = ctx->rf_t.ensure(8 * (size_t)N, st)) || (s = ctx->rf_v.ensure(24 * (size_t)N, st)) ||
-        (s = ctx->rf_first.ensure(8 * (size_t)N, st)) || (s = ctx->rf_counts.ensure(4 * (size_t)N, st)) ||
-        (s = ctx->rf_cands.ensure(sizeof(fh_candidate) * 2 * (size_t)n_cand * n_dir, st)) ||
-        (s = ctx->rf_aux.ensure(8 * aux.size(), st)))
-        return s;
-    fh_peakmap sub(*pm);
-    sub.d_offsets = (int64_t *)ctx->rf_offsets.ptr;
-    sub.d_bins = (int32_t *)ctx->rf_bins.ptr;
-    sub.d_t = (double *)ctx->rf_t.ptr;
-    sub.d_v = (double *)ctx->rf_v.ptr;
+    fh_peakmap sub(*pm);  // the widest candidate's part of the peakmap
     sub.n_peaks = cap;
     sub.k_min = kmin;
     sub.k_max = kmax;
     sub.max_per_fft = std::min<int32_t>(pm->max_per_fft, width);
     for (int c = 0; c < n_cand; ++c)
         if ((s = check_grid(&sub, &grids[c]))) return s;
-    HIP_OK(hipMemcpyAsync(sub.d_t, pm->d_t, 8 * (size_t)N, hipMemcpyDeviceToDevice, st));
-    HIP_OK(hipMemcpyAsync(sub.d_v, pm->d_v, 24 * (size_t)N, hipMemcpyDeviceToDevice, st));
     const bool weighted = d_w != nullptr;
-    const Plan p = make_plan(grids[0], choose_tile_bins(ctx, &sub, &grids[0], 0));
-    ChunkBufs b;
-    if ((s = ensure_workspace(ctx, &sub, &grids[0], p, n_dir, n_cand * n_dir, weighted, st, b))) return s;
-    if ((s = upload_sky(ctx, sky.data(), n_cand * n_dir, b, st))) return s;
-    // the auxiliary arrays go through the (now idle) pinned sky buffer
-    if ((s = ctx->cur->h_sky.ensure(8 * aux.size(), st))) return s;
+    // one upload: parameters and sky points of the pick, refined directions,
+    // and the candidates' grids
+    std::vector<RefineCand> rc((size_t)n_cand);
+    for (int c = 0; c < n_cand; ++c)
+        rc[c] = {grids[c].b0, grids[c].fdot0, ctx->doppler_mode ? shift_reference_bins(ctx, &sub, &grids[c]) : 0.0,
+                 klo[c], khi[c]};
+    const size_t b_aux = 8 * aux.size(), b_sky = 8 * sky.size(), b_rc = sizeof(RefineCand) * rc.size();
+    if ((s = ctx->rf_cands.ensure(sizeof(fh_candidate) * 2 * (size_t)n_cand * n_dir, st)) ||
+        (s = ctx->rf_aux.ensure(b_aux + b_sky + b_rc, st)) ||
+        (s = ctx->cur->h_sky.ensure(b_aux + b_sky + b_rc, st)))
+        return s;
+    // the pinned buffer may still feed an earlier copy on this stream
     HIP_OK(hipStreamSynchronize(st));
-    std::memcpy(ctx->cur->h_sky.ptr, aux.data(), 8 * aux.size());
-    HIP_OK(hipMemcpyAsync(ctx->rf_aux.ptr, ctx->cur->h_sky.ptr, 8 * aux.size(), hipMemcpyHostToDevice, st));
-    fh_select sel{nf, nf, -1, o->theta};
-    fh_candidate *dc = (fh_candidate *)ctx->rf_cands.ptr;
-    for (int c = 0; c < n_cand; ++c) {
-        HIP_OK(launch_slice(N, pm->d_offsets, pm->d_bins, klo[c], khi[c], (int64_t *)ctx->rf_first.ptr,
-                            (int32_t *)ctx->rf_counts.ptr, sub.d_offsets, sub.d_bins, st));
-        ChunkBufs bc = b;
-        bc.sky = b.sky + 3 * (int64_t)c * n_dir;
-        if ((s = run_search(ctx, &sub, &grids[c], p, n_dir, n_dir, d_w, 0, FH_SCHED_PERSISTENT, &sel,
-                            dc + 2 * (int64_t)c * n_dir, bc, st)))
-            return s;
-    }
+    char *h = (char *)ctx->cur->h_sky.ptr;
+    std::memcpy(h, aux.data(), b_aux);
+    std::memcpy(h + b_aux, sky.data(), b_sky);
+    std::memcpy(h + b_aux + b_sky, rc.data(), b_rc);
+    HIP_OK(hipMemcpyAsync(ctx->rf_aux.ptr, h, b_aux + b_sky + b_rc, hipMemcpyHostToDevice, st));
     const double *daux = (const double *)ctx->rf_aux.ptr;
+    double *d_sky = (double *)((char *)ctx->rf_aux.ptr + b_aux);
+    const RefineCand *d_rc = (const RefineCand *)((char *)ctx->rf_aux.ptr + b_aux + b_sky);
+    fh_candidate *dc = (fh_candidate *)ctx->rf_cands.ptr;
+    if (refine_cell_bytes(kf, nf, ns) > 0) {
+        // a volume that fits the LDS: all candidates at once (in chunks whose
+        // peak runs take at most 64 MiB)
+        const int chunk = (int)std::min<int64_t>(std::min(n_cand, 65535),
+                                                 std::max<int64_t>(1, ((int64_t)64 << 20) / (8 * (int64_t)N)));
+        if ((s = ctx->rf_first.ensure(8 * (size_t)chunk * N, st)) ||
+            (s = ctx->cur->ws.ensure(sizeof(WeightStats), st)))
+            return s;
+        WeightStats *ws = weighted ? (WeightStats *)ctx->cur->ws.ptr : nullptr;
+        Timed timed(ctx, st, kSpanTiles);
+        if (weighted)
+            HIP_OK(launch_weight_stats(N, 1, d_w, 0, pm->adjacent ? 2 : 1, ws, (int32_t *)ctx->err.ptr, st));
+        for (int c = 0; c < n_cand; c += chunk) {
+            const int nc = std::min(chunk, n_cand - c);
+            HIP_OK(launch_refine_cells(N, pm->d_offsets, pm->d_bins, pm->d_t, pm->d_v, nc, n_dir,
+                                       d_sky + 3 * (size_t)c * n_dir, d_rc + c, (int2 *)ctx->rf_first.ptr, kf, nf, ns,
+                                       dfd, o->t0, T, o->theta, d_w, ws, ctx->doppler_mode,
+                                       dc + 2 * (size_t)c * n_dir, st));
+        }
+        if (ctx->profiling) ctx->prof_updates += cap * (int64_t)ns * n_dir * n_cand;
+    } else {
+        // a larger one: candidate by candidate, the sliced peakmap (context-owned
+        // arrays) searched with the tiles
+        if ((s = ctx->rf_offsets.ensure(8 * (size_t)(N + 1), st)) || (s = ctx->rf_bins.ensure(4 * (size_t)cap + 4, st)) ||
+            (s = ctx->rf_first.ensure(8 * (size_t)N, st)) || (s = ctx->rf_counts.ensure(4 * (size_t)N, st)))
+            return s;
+        sub.d_offsets = (int64_t *)ctx->rf_offsets.ptr;
+        sub.d_bins = (int32_t *)ctx->rf_bins.ptr;
+        const Plan p = make_plan(grids[0], choose_tile_bins(ctx, &sub, &grids[0], 0));
+        ChunkBufs b;
+        if ((s = ensure_workspace(ctx, &sub, &grids[0], p, n_dir, 1, weighted, st, b))) return s;
+        fh_select sel{nf, nf, -1, o->theta};
+        for (int c = 0; c < n_cand; ++c) {
+            HIP_OK(launch_slice(N, pm->d_offsets, pm->d_bins, klo[c], khi[c], (int64_t *)ctx->rf_first.ptr,
+                                (int32_t *)ctx->rf_counts.ptr, sub.d_offsets, sub.d_bins, st));
+            ChunkBufs bc = b;
+            bc.sky = d_sky + 3 * (size_t)c * n_dir;
+            if ((s = run_search(ctx, &sub, &grids[c], p, n_dir, n_dir, d_w, 0, FH_SCHED_PERSISTENT, &sel,
+                                dc + 2 * (int64_t)c * n_dir, bc, st)))
+                return s;
+        }
+    }
     HIP_OK(launch_refine_pick(n_cand, n_dir, dc, daux, daux + 4 * (size_t)n_cand, d_out, st));
     return FH_OK;
 }

@@ -189,3 +189,48 @@ def test_refine_edge_cases(ctx):
         with pytest.raises(FHError):
             api.refine(ctx, dpm, [cand], **args)
     dpm.release()
+
+
+@pytest.mark.parametrize("kf,k_fdot,k_sky,n_fft,t_fft,density,mode,weighted", [
+    (10, 1, 1, 130, 2048.0, 0.07, "exact", False),   # smallest volume, one direction, a partial round of FFTs
+    (10, 5, 3, 1037, 2048.0, 0.07, "exact", True),   # several rounds of FFTs, the last one partial
+    (4, 3, 3, 512, 2048.0, 0.45, "shift", True),     # exactly one round; dense peaks, more than one list pass
+    (64, 46, 1, 60, 1024.0, 0.07, "exact", False),   # the largest volume that fits the LDS ...
+    (64, 47, 1, 60, 1024.0, 0.07, "exact", False),   # ... and one searched with the tiles
+])
+def test_refined_volumes_of_every_route(ctx, kf, k_fdot, k_sky, n_fft, t_fft, density, mode, weighted):
+    """Volumes searched in one workgroup's LDS and those too large for it, at
+    the edges of the rounds of FFTs, against the oracle's best cell."""
+    import torch
+    from paper_1407_8333_amd import api
+    rng = synth.rng_for(91 + kf + k_fdot)
+    pm = synth.random_peakmap(n_fft, t_fft, int(90.0 * t_fft), int(90.2 * t_fft), density, rng)
+    dfdot = 1.0 / (t_fft * 0.5 * n_fft * t_fft)
+    t0 = 0.5 * (pm.t[0] + pm.t[-1])
+    cands = [[90.1, -1.5 * dfdot, 1.0, 0.3, 0.05, 0.04], [90.03, 2.0 * dfdot, 4.0, -1.1, 0.03, 0.02]]
+    w = synth.fft_weights(n_fft, rng) if weighted else None
+    dpm = ctx.upload(pm)
+    ctx.set_doppler(mode)
+    try:
+        out = api.decode_refined(api.refine(ctx, dpm, cands, kf, k_fdot, k_sky, dfdot, t0,
+                                            weights=None if w is None else torch.as_tensor(w, device="cuda")))
+    finally:
+        ctx.set_doppler("exact")
+    for o, cand in zip(out, cands):
+        rgrid = synth.Grid(kf=kf, b0=int(round(cand[0] * kf * t_fft)) - kf, nf=2 * kf + 1, ns=4 * k_fdot,
+                           fdot0=cand[1] - 2 * dfdot, dfdot=dfdot / k_fdot, t0=t0)
+        best = None
+        for d, (_, _, n) in enumerate(_reference_directions(*cand[2:], k_sky)):
+            m = oracle.hough_map(pm, rgrid, np.array(n), weights=None if w is None else w.astype(np.float64),
+                                 doppler=mode)
+            rows, bins = np.nonzero(m == m.max())
+            k = np.lexsort((rows, bins))[0]
+            if best is None or m.max() > best[0]:
+                best = (float(m.max()), d, int(bins[k]), int(rows[k]))
+        if w is None:
+            assert (float(o["value"]), int(o["sky"]), int(o["bin"]), int(o["row"])) == best
+        else:
+            # every cell is within 1e-5 of its exact sum, so the chosen one is
+            # within twice that of the best
+            assert float(o["value"]) == pytest.approx(best[0], abs=2e-5 * max(best[0], float(np.mean(w))))
+    dpm.release()
