@@ -179,8 +179,8 @@ struct FilterSpec {
 };
 hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const FilterSpec &spec,
                          int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, hipStream_t st);
-hipError_t launch_bin_counts(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_lo,
-                             int32_t k_hi, int32_t *counts, hipStream_t st);
+hipError_t launch_bin_counts(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
+                             int32_t k_lo, int32_t k_hi, int32_t *counts, hipStream_t st);
 // robust statistic: hist needs 2 x_max + 1 entries; out[0] = m1, out[1] = m2
 hipError_t launch_robust(const int32_t *x, int32_t n, int32_t x_max, int32_t *hist, int64_t *s2, double *out,
                          int32_t *err, hipStream_t st);

@@ -1224,7 +1224,8 @@ fh_status fh_bin_counts(fh_ctx *ctx, const fh_peakmap *pm, int32_t k_lo, int32_t
     if (!pm) return fail(FH_E_INVALID, "peakmap is NULL");
     if (k_lo < 0 || k_hi <= k_lo) return fail(FH_E_INVALID, "need 0 <= k_lo < k_hi");
     if (!d_counts) return fail(FH_E_INVALID, "counts pointer is NULL");
-    HIP_OK(launch_bin_counts(pm->n_fft, pm->d_offsets, pm->d_bins, k_lo, k_hi, d_counts, (hipStream_t)stream));
+    HIP_OK(launch_bin_counts(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, k_lo, k_hi, d_counts,
+                             (hipStream_t)stream));
     return FH_OK;
 }
 

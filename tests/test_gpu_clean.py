@@ -151,3 +151,44 @@ def test_cleaning_an_empty_peakmap(ctx):
     assert not clean.bin_counts(ctx, dpm, 1000, 2000).cpu().numpy().any()
     out.release()
     dpm.release()
+
+
+@pytest.fixture(scope="module")
+def wide_band():
+    """37 FFTs over 140 000 natural bins, with a run of popular bins."""
+    pm = synth.random_peakmap(37, 1024.0, 5000, 145000, 0.05, synth.rng_for(3), min_gap=2)
+    return pm
+
+
+@pytest.mark.parametrize("width", [1, 1023, 32768, 32769, 131072, 131073])
+def test_bin_counts_at_the_edges_of_the_lds_segments(ctx, wide_band, width):
+    from paper_1407_8333_amd import clean
+    dpm = ctx.upload(wide_band)
+    for k_lo in (5003, 0):
+        c = clean.bin_counts(ctx, dpm, k_lo, k_lo + width)
+        np.testing.assert_array_equal(c.cpu().numpy(), oclean.bin_counts(wide_band, k_lo, k_lo + width))
+    dpm.release()
+
+
+@pytest.mark.parametrize("n_f", [1, 8192, 8193])
+def test_gross_histogram_at_the_edges_of_the_lds_row(ctx, wide_band, n_f):
+    """Rows that fit the LDS and longer ones; time cells that change inside
+    and at the ends of a workgroup's 16 FFTs, FFTs outside the histogram."""
+    from paper_1407_8333_amd import clean
+    dpm = ctx.upload(wide_band)
+    step = 0.5 * wide_band.t_fft
+    for dt_h, t0 in [(16 * step, 0.0), (5 * step, 3 * step), (1e9, 0.0)]:
+        geo = (t0, dt_h, 5, 16.0 / wide_band.t_fft, 5000 // 16, n_f)
+        np.testing.assert_array_equal(clean.gross_histogram(ctx, dpm, geo).cpu().numpy(),
+                                      oclean.gross_histogram(wide_band, *geo))
+    dpm.release()
+
+
+@pytest.mark.parametrize("n,x_max", [(1, 0), (2, 1), (4599, 6286), (65536, 36863), (65537, 36863), (3000, 36864)])
+def test_robust_statistic_of_every_route(ctx, n, x_max):
+    import torch
+    from paper_1407_8333_amd import clean
+    rng = np.random.default_rng(n + x_max)
+    for x in (rng.integers(0, x_max + 1, n), rng.binomial(x_max, 0.07, n), np.full(n, x_max)):
+        x = x.astype(np.int32)
+        assert clean.robust_stats(ctx, torch.as_tensor(x, device="cuda"), x_max) == oclean.robust_stats(x)
