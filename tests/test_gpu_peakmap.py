@@ -54,3 +54,32 @@ def test_built_peakmap_feeds_the_hough_map():
         assert torch.equal(a, b)
         built.release()
         up.release()
+
+
+@pytest.mark.parametrize("n_fft,n_bins", [(5, 4), (5, 66), (5, 513), (5, 514), (5, 515), (3, 2049), (3, 2050),
+                                          (3, 2051), (3, 4099), (8191, 5), (8192, 5), (8200, 5), (16385, 4)])
+@pytest.mark.parametrize("with_ar", [False, True])
+def test_rows_at_the_edges_of_a_waves_run_and_of_the_scan(n_fft, n_bins, with_ar):
+    """Rows that end around a wave's 512 bins and a workgroup's 2048, FFT
+    counts around the scan's 8192, rows with a pitch, dense peaks, and
+    infinities and NaN among the values."""
+    import torch
+    from paper_1407_8333_amd import api
+    rng = synth.rng_for(n_fft * 7 + n_bins)
+    ld = n_bins + 3
+    sp = (4.0 * rng.standard_exponential((n_fft, ld))).astype(np.float32)
+    sp[rng.random(sp.shape) < 0.02] = np.inf
+    sp[rng.random(sp.shape) < 0.02] = np.nan
+    ar = rng.uniform(0.5, 2.0, (n_fft, ld)).astype(np.float32)
+    t = synth.fft_times(n_fft, 1024.0)
+    with api.Context(0) as ctx:
+        dsp = torch.as_tensor(sp, device="cuda")[:, :n_bins]
+        dar = torch.as_tensor(ar, device="cuda")[:, :n_bins] if with_ar else None
+        dpm = api.DevicePeakmap.from_spectra(ctx, dsp, 77, 2.5, t, np.zeros((n_fft, 3)), 1024.0, sar=dar)
+        off, bins = dpm.download()
+        with np.errstate(invalid="ignore"):
+            ref_off, ref_bins = peakmap.peakmap_from_spectra(sp[:, :n_bins], ar[:, :n_bins] if with_ar else None,
+                                                             77, 2.5)
+        np.testing.assert_array_equal(off, ref_off)
+        np.testing.assert_array_equal(bins, ref_bins)
+        dpm.release()
