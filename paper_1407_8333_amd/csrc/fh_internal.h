@@ -134,13 +134,14 @@ hipError_t launch_select(const unsigned long long *colmax, int32_t nf, int32_t n
 hipError_t launch_pm_rows(int32_t n_fft, int32_t n_bins, int64_t ld, const float *sp, const float *sar,
                           int32_t k0, float theta, int32_t cap, int32_t *scratch, int32_t *counts,
                           hipStream_t st);
-hipError_t launch_pm_scan(int32_t n_fft, const int32_t *counts, int64_t *offsets, hipStream_t st);
+// meta (optional): the total and the largest count
+hipError_t launch_pm_scan(int32_t n_fft, const int32_t *counts, int64_t *offsets, int64_t *meta, hipStream_t st);
 hipError_t launch_pm_pack(int32_t n_fft, int32_t cap, const int32_t *scratch, const int64_t *offsets,
                           int32_t *bins, hipStream_t st);
 // peaks of each FFT with natural bin in [k_lo, k_hi) into a new CSR
 hipError_t launch_slice(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_lo, int32_t k_hi,
                         int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
-                        hipStream_t st);
+                        int64_t *meta, hipStream_t st);
 // one coarse candidate's refined grid: fine bin 0, first row's spin-down, shift
 // reference (shift mode), natural bins [k_lo, k_hi) whose peaks can reach it
 struct RefineCand {
@@ -178,10 +179,12 @@ struct FilterSpec {
     double thr;
 };
 hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const FilterSpec &spec,
-                         int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, hipStream_t st);
+                         int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, int64_t *meta,
+                         hipStream_t st);
 hipError_t launch_bin_counts(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
                              int32_t k_lo, int32_t k_hi, int32_t *counts, hipStream_t st);
-// robust statistic: hist needs 2 x_max + 1 entries; out[0] = m1, out[1] = m2
+// robust statistic: hist needs 2 x_max + 1 entries; out[0] = m1, out[1] = m2,
+// out[2] = 1 (and *err = 1) if a value lies outside [0, x_max], else 0
 hipError_t launch_robust(const int32_t *x, int32_t n, int32_t x_max, int32_t *hist, int64_t *s2, double *out,
                          int32_t *err, hipStream_t st);
 // decoded column maxima of n_slots directions: value [slot][nf], row [slot][nf]

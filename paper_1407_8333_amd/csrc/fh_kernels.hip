@@ -2361,7 +2361,7 @@ __global__ void k_value_hist(const int32_t *__restrict__ x, int32_t n, int32_t x
 // for pass 1, m2 = sum / 4 / 0.6745 to out[1].
 __global__ void __launch_bounds__(1024) k_rank_pick(const int32_t *__restrict__ hist, int32_t m, int64_t ra,
                                                     int64_t rb, int pass, int64_t *__restrict__ s2,
-                                                    double *__restrict__ out) {
+                                                    double *__restrict__ out, const int32_t *__restrict__ err) {
     __shared__ int64_t part[1024];
     __shared__ int32_t val[2];
     const int tid = threadIdx.x;
@@ -2401,6 +2401,7 @@ __global__ void __launch_bounds__(1024) k_rank_pick(const int32_t *__restrict__ 
         } else {
             // median of |x - m1| = (t / 2) / 2: both halves exact
             out[1] = 0.5 * (0.5 * (double)val[0] + 0.5 * (double)val[1]) / 0.6745;
+            out[2] = (double)*err;  // a value outside [0, x_max]
         }
     }
 }
@@ -2410,7 +2411,8 @@ __global__ void __launch_bounds__(1024) k_rank_pick(const int32_t *__restrict__ 
 // ranks of |2 x - s| from the same prefix sums (values at most d away are those
 // in [ceil((s - d) / 2), floor((s + d) / 2)]), found by bisection.  It replaces
 // two fills, two histograms and two rank searches, 40 us of launches on 4600
-// counts of 6286 FFTs.  *err reports a value outside [0, x_max].
+// counts of 6286 FFTs.  out[2] (as a number) and *err report a value outside
+// [0, x_max].
 constexpr int kRobustBins = 36 * 1024;  // 144 KB of LDS
 
 __global__ void __launch_bounds__(1024) k_robust_lds(const int32_t *__restrict__ x, int32_t n, int32_t x_max,
@@ -2474,6 +2476,7 @@ __global__ void __launch_bounds__(1024) k_robust_lds(const int32_t *__restrict__
     out[0] = 0.5 * (double)s;
     // median of |x - m1| = (t / 2) / 2: both halves exact
     out[1] = 0.5 * (0.5 * (double)deviation_at(ra) + 0.5 * (double)deviation_at(rb)) / 0.6745;
+    out[2] = (double)s_bad;
     *err = s_bad;
 }
 
@@ -2516,11 +2519,11 @@ hipError_t launch_colmax_decode(const unsigned long long *colmax, int32_t nf, in
 
 hipError_t launch_slice(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_lo, int32_t k_hi,
                         int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
-                        hipStream_t st) {
+                        int64_t *meta, hipStream_t st) {
     k_slice_count<<<grid_for(n_fft, 256), 256, 0, st>>>(n_fft, offsets, bins, k_lo, k_hi, first, counts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets, nullptr);
+    k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets, meta);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     k_slice_pack<<<n_fft, 256, 0, st>>>(first, counts, out_offsets, bins, out_bins);
     return hipGetLastError();
@@ -2595,7 +2598,8 @@ hipError_t launch_gross_hist(int32_t n_fft, const int64_t *offsets, const int32_
 }
 
 hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const FilterSpec &spec,
-                         int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, hipStream_t st) {
+                         int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, int64_t *meta,
+                         hipStream_t st) {
     PeakFilter f{};
     f.mode = spec.mode;
     f.t = spec.t;
@@ -2618,7 +2622,7 @@ hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *b
         k_filter_count<<<(n_fft + 3) / 4, 256, 0, st>>>(n_fft, offsets, bins, f, counts);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets, nullptr);
+        k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets, meta);
     } else {
         k_filter_pack<<<(n_fft + 3) / 4, 256, 0, st>>>(n_fft, offsets, bins, f, out_offsets, out_bins);
     }
@@ -2653,13 +2657,15 @@ hipError_t launch_robust(const int32_t *x, int32_t n, int32_t x_max, int32_t *hi
         k_robust_lds<<<1, 1024, 4 * ((size_t)x_max + 1), st>>>(x, n, x_max, ra, rb, out, err);
         return hipGetLastError();
     }
+    hipError_t e = launch_fill_i32(err, 1, 0, st);
+    if (e != hipSuccess) return e;
     for (int pass = 0; pass < 2; ++pass) {
         const int32_t m = pass == 0 ? x_max + 1 : 2 * x_max + 1;
-        hipError_t e = launch_fill_i32(hist, m, 0, st);
+        e = launch_fill_i32(hist, m, 0, st);
         if (e != hipSuccess) return e;
         k_value_hist<<<grid_for(n, 256), 256, 0, st>>>(x, n, x_max, pass, s2, hist, err);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_rank_pick<<<1, 1024, 0, st>>>(hist, m, ra, rb, pass, s2, out);
+        k_rank_pick<<<1, 1024, 0, st>>>(hist, m, ra, rb, pass, s2, out, err);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -2670,8 +2676,8 @@ hipError_t launch_colmax_values(const unsigned long long *colmax, int32_t nf, in
     return hipGetLastError();
 }
 
-hipError_t launch_pm_scan(int32_t n_fft, const int32_t *counts, int64_t *offsets, hipStream_t st) {
-    k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, offsets, nullptr);
+hipError_t launch_pm_scan(int32_t n_fft, const int32_t *counts, int64_t *offsets, int64_t *meta, hipStream_t st) {
+    k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, offsets, meta);
     return hipGetLastError();
 }
 

@@ -125,6 +125,63 @@ struct PinnedBuf {
     }
 };
 
+// Device blocks of released peakmaps, kept for the next ones: building or
+// filtering a peakmap otherwise spends several times its kernels' time in
+// hipMalloc and hipFree (which maps and unmaps the pages): 700 us of calls
+// around 70 us of kernels for a band of 2.1 M peaks.  At most kMaxBlocks
+// blocks of kMaxBytes together; a block serves requests of half its size or
+// more; given back when an allocation fails and with the context.
+struct BlockPool {
+    static constexpr size_t kMaxBlocks = 8;
+    static constexpr size_t kMaxBytes = (size_t)256 << 20;
+    struct Block { void *ptr; size_t bytes; };
+    std::vector<Block> free_;
+    size_t held = 0;
+    // a block of at least n bytes and its size, or nullptr
+    void *take(size_t n, size_t *bytes) {
+        n = (std::max(n, (size_t)1) + 4095) / 4096 * 4096;
+        size_t at = free_.size();
+        for (size_t k = 0; k < free_.size(); ++k)
+            if (free_[k].bytes >= n && free_[k].bytes <= 2 * n &&
+                (at == free_.size() || free_[k].bytes < free_[at].bytes))
+                at = k;
+        if (at < free_.size()) {
+            const Block b = free_[at];
+            free_.erase(free_.begin() + (long)at);
+            held -= b.bytes;
+            *bytes = b.bytes;
+            return b.ptr;
+        }
+        void *p = nullptr;
+        if (hipMalloc(&p, n) != hipSuccess) {
+            trim();
+            if (hipMalloc(&p, n) != hipSuccess) return nullptr;
+        }
+        *bytes = n;
+        return p;
+    }
+    // no enqueued work uses the block any more
+    void give(void *p, size_t bytes) {
+        if (!p) return;
+        if (bytes > kMaxBytes) {
+            (void)hipFree(p);
+            return;
+        }
+        free_.push_back({p, bytes});
+        held += bytes;
+        while (held > kMaxBytes || free_.size() > kMaxBlocks) {
+            (void)hipFree(free_.front().ptr);
+            held -= free_.front().bytes;
+            free_.erase(free_.begin());
+        }
+    }
+    void trim() {
+        for (const Block &b : free_) (void)hipFree(b.ptr);
+        free_.clear();
+        held = 0;
+    }
+};
+
 }  // namespace
 
 struct fh_peakmap {
@@ -136,6 +193,10 @@ struct fh_peakmap {
     int32_t k_min = 0, k_max = 0;
     int32_t adjacent = 0;  // 1 if some FFT holds two peaks one natural bin apart
     int32_t max_per_fft = 0;
+    // two device blocks: the head, t [N] | v [N][3] | offsets [N+1], and the bins
+    void *head = nullptr;
+    size_t head_bytes = 0, bins_bytes = 0;  // sizes of the two blocks
+    int32_t device = 0;
     int64_t *d_offsets = nullptr;
     int32_t *d_bins = nullptr;
     double *d_t = nullptr;
@@ -176,6 +237,11 @@ struct fh_ctx {
     DevBuf rf_offsets, rf_bins, rf_first, rf_counts, rf_cands, rf_aux;
     // cleaning: robust-statistic histogram, its rank sum and results
     DevBuf cl_hist, cl_s2, cl_out;
+    // peakmap construction: row scratch, peaks per FFT, {total, largest} of the
+    // counts; pinned memory for small results and staged times and velocities
+    DevBuf pm_rows, pm_counts, pm_meta;
+    PinnedBuf h_small, h_stage;
+    BlockPool blocks;
     // autotuned tile width per problem shape (shared by weighted and
     // unweighted searches: the two kernels differ only in the added value)
     std::map<std::tuple<int, int, int, int>, int> tuned;
@@ -251,6 +317,47 @@ fh_status check_ctx(fh_ctx *ctx) {
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return fail(FH_E_DEVICE, "hipSetDevice(%d): %s", ctx->device, hipGetErrorString(e));
     return FH_OK;
+}
+
+// The head block of a peakmap of pm->n_fft FFTs.
+bool alloc_head(fh_ctx *ctx, fh_peakmap *pm) {
+    const size_t N = (size_t)pm->n_fft;
+    pm->device = ctx->device;
+    pm->head = ctx->blocks.take(32 * N + 8 * (N + 1), &pm->head_bytes);
+    if (!pm->head) return false;
+    pm->d_t = (double *)pm->head;
+    pm->d_v = pm->d_t + N;
+    pm->d_offsets = (int64_t *)(pm->d_v + 3 * N);
+    return true;
+}
+
+bool alloc_bins(fh_ctx *ctx, fh_peakmap *pm, int64_t n) {
+    pm->d_bins = (int32_t *)ctx->blocks.take(4 * (size_t)std::max<int64_t>(1, n), &pm->bins_bytes);
+    return pm->d_bins != nullptr;
+}
+
+// A new peakmap with pm's FFTs (times, velocities, metadata) and no blocks.
+fh_peakmap *like(const fh_peakmap *pm) {
+    fh_peakmap *q = new fh_peakmap(*pm);
+    q->head = nullptr;
+    q->d_offsets = nullptr;
+    q->d_bins = nullptr;
+    q->d_t = q->d_v = nullptr;
+    q->head_bytes = q->bins_bytes = 0;
+    return q;
+}
+
+// {total, largest} of a scan's counts, read back from ctx->pm_meta; waits for
+// the stream.
+hipError_t read_meta(fh_ctx *ctx, hipStream_t st, int64_t *total, int32_t *most) {
+    int64_t *h = (int64_t *)ctx->h_small.ptr;
+    hipError_t e = hipMemcpyAsync(h, ctx->pm_meta.ptr, 16, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) {
+        *total = h[0];
+        *most = (int32_t)h[1];
+    }
+    return e;
 }
 
 // Largest spin-down step of one row, in fine bins: |dfdot tau| K_f T_FFT
@@ -392,8 +499,8 @@ int64_t edge_bytes_per_sky(const fh_ctx *ctx, const fh_peakmap *pm) {
     return (needs_full_edges(ctx, pm) ? 12 : 4) * y_stride(pm->n_peaks, pm->n_fft);
 }
 
-fh_status ensure_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
-                           int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
+fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
+                         int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
     const int64_t N = pm->n_fft;
     fh_status s;
     const ShiftLayout sl = shift_layout(N, p.nrb_tab, p.nrbg);
@@ -424,6 +531,14 @@ fh_status ensure_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, 
     b.qctr = (int32_t *)ctx->cur->qctr.ptr;
     b.err = (int32_t *)ctx->err.ptr;
     return FH_OK;
+}
+
+fh_status ensure_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
+                           int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
+    const fh_status s = grow_workspace(ctx, pm, g, p, slots, n_sky, weighted, st, b);
+    if (s != FH_E_NOMEM || ctx->blocks.held == 0) return s;
+    ctx->blocks.trim();
+    return grow_workspace(ctx, pm, g, p, slots, n_sky, weighted, st, b);
 }
 
 TileArgs tile_args(const fh_peakmap *pm, const fh_grid *g, const Plan &p, int slots,
@@ -678,44 +793,28 @@ fh_status filter_peakmap(fh_ctx *ctx, const fh_peakmap *pm, const FilterSpec &sp
     fh_status s;
     const int32_t N = pm->n_fft;
     if ((s = ctx->rf_counts.ensure(4 * (size_t)std::max(1, N), st))) return s;
-    fh_peakmap *q = new fh_peakmap(*pm);
-    q->d_offsets = nullptr;
-    q->d_bins = nullptr;
-    q->d_t = nullptr;
-    q->d_v = nullptr;
-    const size_t b_off = 8 * (size_t)(N + 1);
-    if (hipMalloc(&q->d_offsets, b_off) != hipSuccess || hipMalloc(&q->d_t, 8 * (size_t)N) != hipSuccess ||
-        hipMalloc(&q->d_v, 24 * (size_t)N) != hipSuccess) {
+    fh_peakmap *q = like(pm);
+    if (!alloc_head(ctx, q)) {
         fh_peakmap_release(ctx, q);
         return fail(FH_E_NOMEM, "device allocation for the cleaned peakmap failed");
     }
-    std::vector<int64_t> h_off((size_t)N + 1, 0);
-    hipError_t e = hipSuccess;
-    if (N > 0) {
-        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, (int32_t *)ctx->rf_counts.ptr, q->d_offsets,
-                          nullptr, 0, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(h_off.data(), q->d_offsets, b_off, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-    } else {
-        e = hipMemcpyAsync(q->d_offsets, h_off.data(), b_off, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-    }
-    const int64_t P = e == hipSuccess ? h_off[N] : 0;
-    if (e == hipSuccess && hipMalloc(&q->d_bins, 4 * (size_t)std::max<int64_t>(1, P)) != hipSuccess)
-        e = hipErrorOutOfMemory;
-    if (e == hipSuccess && N > 0)
-        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, nullptr, q->d_offsets, q->d_bins, 1, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(q->d_t, pm->d_t, 8 * (size_t)N, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(q->d_v, pm->d_v, 24 * (size_t)N, hipMemcpyDeviceToDevice, st);
+    // times and velocities lie next to each other in both heads
+    hipError_t e = hipMemcpyAsync(q->d_t, pm->d_t, 32 * (size_t)N, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess)
+        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, (int32_t *)ctx->rf_counts.ptr, q->d_offsets, nullptr, 0,
+                          (int64_t *)ctx->pm_meta.ptr, st);
+    int64_t P = 0;
+    if (e == hipSuccess) e = read_meta(ctx, st, &P, &q->max_per_fft);
+    if (e == hipSuccess && !alloc_bins(ctx, q, P)) e = hipErrorOutOfMemory;
+    if (e == hipSuccess)
+        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, nullptr, q->d_offsets, q->d_bins, 1, nullptr, st);
     if (e != hipSuccess) {
         fh_peakmap_release(ctx, q);
         return fail(e == hipErrorOutOfMemory ? FH_E_NOMEM : FH_E_DEVICE, "filtering the peakmap failed: %s",
                     hipGetErrorString(e));
     }
     q->n_peaks = P;
-    q->max_per_fft = 0;
-    for (int32_t i = 0; i < N; ++i) q->max_per_fft = std::max<int32_t>(q->max_per_fft, (int32_t)(h_off[i + 1] - h_off[i]));
-    q->bytes = (int64_t)(b_off + 4 * (size_t)std::max<int64_t>(1, P) + 32 * (size_t)N);
+    q->bytes = (int64_t)(8 * (size_t)(N + 1) + 4 * (size_t)std::max<int64_t>(1, P) + 32 * (size_t)N);
     *out = q;
     return FH_OK;
 }
@@ -747,12 +846,18 @@ fh_status fh_ctx_create(int32_t device, fh_ctx **out) {
     c->device = device;
     c->n_cu = prop.multiProcessorCount;
     fh_status s = c->err.ensure(4, nullptr);
+    if (!s) s = c->pm_meta.ensure(16, nullptr);
+    if (!s) s = c->h_small.ensure(256, nullptr);
     if (s) {
+        c->err.release();
+        c->pm_meta.release();
         delete c;
         return s;
     }
     if (hipMemset(c->err.ptr, 0, 4) != hipSuccess) {
         c->err.release();
+        c->pm_meta.release();
+        c->h_small.release();
         delete c;
         return fail(FH_E_DEVICE, "hipMemset failed");
     }
@@ -772,8 +877,12 @@ void fh_ctx_destroy(fh_ctx *ctx) {
     ctx->main_ws.release();
     ctx->err.release();
     for (DevBuf *b : {&ctx->rf_offsets, &ctx->rf_bins, &ctx->rf_first, &ctx->rf_counts,
-                      &ctx->rf_cands, &ctx->rf_aux, &ctx->cl_hist, &ctx->cl_s2, &ctx->cl_out})
+                      &ctx->rf_cands, &ctx->rf_aux, &ctx->cl_hist, &ctx->cl_s2, &ctx->cl_out, &ctx->pm_rows, &ctx->pm_counts,
+                      &ctx->pm_meta})
         b->release();
+    ctx->h_small.release();
+    ctx->h_stage.release();
+    ctx->blocks.trim();
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
     delete ctx;
 }
@@ -868,8 +977,7 @@ fh_status fh_peakmap_upload(fh_ctx *ctx, const fh_peakmap_desc *d, void *stream,
     hipStream_t st = (hipStream_t)stream;
     const size_t b_off = 8 * (size_t)(N + 1), b_bins = 4 * (size_t)std::max<int64_t>(1, d->n_peaks);
     const size_t b_t = 8 * (size_t)N, b_v = 24 * (size_t)N;
-    if (hipMalloc(&pm->d_offsets, b_off) != hipSuccess || hipMalloc(&pm->d_bins, b_bins) != hipSuccess ||
-        hipMalloc(&pm->d_t, b_t) != hipSuccess || hipMalloc(&pm->d_v, b_v) != hipSuccess) {
+    if (!alloc_head(ctx, pm) || !alloc_bins(ctx, pm, d->n_peaks)) {
         fh_peakmap_release(ctx, pm);
         return fail(FH_E_NOMEM, "device allocation for the peakmap failed");
     }
@@ -921,30 +1029,40 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
     }
     hipStream_t st = (hipStream_t)stream;
     const int32_t cap = n_bins / 2 + 1;  // strict local maxima are never adjacent
-    int32_t *rows_buf = nullptr, *counts = nullptr;
     const size_t b_off = 8 * (size_t)(n_fft + 1), b_t = 8 * (size_t)n_fft, b_v = 24 * (size_t)n_fft;
-    if (hipMalloc(&rows_buf, 4 * (size_t)n_fft * cap) != hipSuccess || hipMalloc(&counts, 4 * (size_t)n_fft) != hipSuccess ||
-        hipMalloc(&pm->d_offsets, b_off) != hipSuccess || hipMalloc(&pm->d_t, b_t) != hipSuccess ||
-        hipMalloc(&pm->d_v, b_v) != hipSuccess) {
-        if (rows_buf) (void)hipFree(rows_buf);
-        if (counts) (void)hipFree(counts);
+    s = ctx->pm_rows.ensure(4 * (size_t)n_fft * cap, st);
+    if (s == FH_E_NOMEM && ctx->blocks.held) {
+        ctx->blocks.trim();
+        s = ctx->pm_rows.ensure(4 * (size_t)n_fft * cap, st);
+    }
+    if (s || (s = ctx->pm_counts.ensure(4 * (size_t)n_fft, st)) ||
+        (s = ctx->h_stage.ensure(b_t + b_v, st))) {
+        delete pm;
+        return s;
+    }
+    if (!alloc_head(ctx, pm)) {
         fh_peakmap_release(ctx, pm);
         return fail(FH_E_NOMEM, "device allocation for the peakmap failed");
     }
-    std::vector<int64_t> h_off(n_fft + 1);
+    // (every use of the staging buffer ends with a wait for its copy)
+    std::memcpy(ctx->h_stage.ptr, t, b_t);
+    std::memcpy((char *)ctx->h_stage.ptr + b_t, v, b_v);
+    int32_t *rows_buf = (int32_t *)ctx->pm_rows.ptr, *counts = (int32_t *)ctx->pm_counts.ptr;
+    int64_t P = 0;
     hipError_t e = launch_pm_rows(n_fft, n_bins, ld, d_sp, d_sar, k0, theta, cap, rows_buf, counts, st);
-    if (e == hipSuccess) e = launch_pm_scan(n_fft, counts, pm->d_offsets, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(h_off.data(), pm->d_offsets, b_off, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    const int64_t P = e == hipSuccess ? h_off[n_fft] : 0;
-    if (e == hipSuccess && hipMalloc(&pm->d_bins, 4 * (size_t)std::max<int64_t>(1, P)) != hipSuccess)
-        e = hipErrorOutOfMemory;
+    if (e == hipSuccess) e = launch_pm_scan(n_fft, counts, pm->d_offsets, (int64_t *)ctx->pm_meta.ptr, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(pm->d_t, ctx->h_stage.ptr, b_t + b_v, hipMemcpyHostToDevice, st);
+    const hipError_t e2 = read_meta(ctx, st, &P, &pm->max_per_fft);
+    if (e == hipSuccess) e = e2;
+    if (e == hipSuccess && !alloc_bins(ctx, pm, P)) e = hipErrorOutOfMemory;
     if (e == hipSuccess) e = launch_pm_pack(n_fft, cap, rows_buf, pm->d_offsets, pm->d_bins, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(pm->d_t, t, b_t, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(pm->d_v, v, b_v, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(rows_buf);
-    (void)hipFree(counts);
+    // the scratch of a usual band stays; that of a large one (14 MB per 1000
+    // FFTs x 7000 bins) goes back
+    if (ctx->pm_rows.bytes > BlockPool::kMaxBytes) {
+        if (e != hipSuccess) (void)hipStreamSynchronize(st);
+        ctx->pm_rows.release();
+    }
     if (e != hipSuccess) {
         fh_peakmap_release(ctx, pm);
         return fail(e == hipErrorOutOfMemory ? FH_E_NOMEM : FH_E_DEVICE, "peakmap construction failed: %s",
@@ -954,8 +1072,6 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
     pm->k_min = k0 + 1;
     pm->k_max = k0 + n_bins - 2;
     pm->adjacent = 0;
-    for (int32_t i = 0; i < n_fft; ++i)
-        pm->max_per_fft = std::max<int32_t>(pm->max_per_fft, (int32_t)(h_off[i + 1] - h_off[i]));
     pm->bytes = (int64_t)(b_off + 4 * (size_t)std::max<int64_t>(1, P) + b_t + b_v);
     *out = pm;
     return FH_OK;
@@ -981,10 +1097,15 @@ fh_status fh_peakmap_shape(const fh_peakmap *pm, int32_t *n_fft, int64_t *n_peak
 void fh_peakmap_release(fh_ctx *ctx, fh_peakmap *pm) {
     if (!pm) return;
     if (ctx) (void)hipSetDevice(ctx->device);
-    if (pm->d_offsets) (void)hipFree(pm->d_offsets);
-    if (pm->d_bins) (void)hipFree(pm->d_bins);
-    if (pm->d_t) (void)hipFree(pm->d_t);
-    if (pm->d_v) (void)hipFree(pm->d_v);
+    if (ctx && ctx->device == pm->device) {
+        // as hipFree does: no block is handed on while the device may use it
+        if (pm->head || pm->d_bins) (void)hipDeviceSynchronize();
+        ctx->blocks.give(pm->head, pm->head_bytes);
+        ctx->blocks.give(pm->d_bins, pm->bins_bytes);
+    } else {
+        if (pm->head) (void)hipFree(pm->head);
+        if (pm->d_bins) (void)hipFree(pm->d_bins);
+    }
     delete pm;
 }
 
@@ -1003,37 +1124,25 @@ fh_status fh_peakmap_slice(fh_ctx *ctx, const fh_peakmap *pm, int32_t k_lo, int3
     const int64_t cap = std::min<int64_t>((int64_t)N * (k_hi - k_lo), pm->n_peaks);
     if ((s = ctx->rf_first.ensure(8 * (size_t)N, st)) || (s = ctx->rf_counts.ensure(4 * (size_t)N, st)))
         return s;
-    fh_peakmap *q = new fh_peakmap(*pm);
-    q->d_offsets = nullptr;
-    q->d_bins = nullptr;
-    q->d_t = nullptr;
-    q->d_v = nullptr;
-    q->n_peaks = cap;
+    fh_peakmap *q = like(pm);
     q->k_min = k_lo;
     q->k_max = k_hi - 1;
-    q->max_per_fft = std::min<int32_t>(pm->max_per_fft, k_hi - k_lo);
     const size_t b_off = 8 * (size_t)(N + 1), b_bins = 4 * (size_t)std::max<int64_t>(1, cap);
-    if (hipMalloc(&q->d_offsets, b_off) != hipSuccess || hipMalloc(&q->d_bins, b_bins) != hipSuccess ||
-        hipMalloc(&q->d_t, 8 * (size_t)N) != hipSuccess || hipMalloc(&q->d_v, 24 * (size_t)N) != hipSuccess) {
+    if (!alloc_head(ctx, q) || !alloc_bins(ctx, q, cap)) {
         fh_peakmap_release(ctx, q);
         return fail(FH_E_NOMEM, "device allocation for the sliced peakmap failed");
     }
     q->bytes = (int64_t)(b_off + b_bins + 32 * (size_t)N);
-    hipError_t e = launch_slice(N, pm->d_offsets, pm->d_bins, k_lo, k_hi, (int64_t *)ctx->rf_first.ptr,
-                                (int32_t *)ctx->rf_counts.ptr, q->d_offsets, q->d_bins, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(q->d_t, pm->d_t, 8 * (size_t)N, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(q->d_v, pm->d_v, 24 * (size_t)N, hipMemcpyDeviceToDevice, st);
+    hipError_t e = hipMemcpyAsync(q->d_t, pm->d_t, 32 * (size_t)N, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess)
+        e = launch_slice(N, pm->d_offsets, pm->d_bins, k_lo, k_hi, (int64_t *)ctx->rf_first.ptr,
+                         (int32_t *)ctx->rf_counts.ptr, q->d_offsets, q->d_bins, (int64_t *)ctx->pm_meta.ptr, st);
     // exact peak count and longest FFT of the slice (the allocation keeps the bound)
-    std::vector<int64_t> h_off((size_t)N + 1);
-    if (e == hipSuccess) e = hipMemcpyAsync(h_off.data(), q->d_offsets, b_off, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = read_meta(ctx, st, &q->n_peaks, &q->max_per_fft);
     if (e != hipSuccess) {
         fh_peakmap_release(ctx, q);
         return fail(FH_E_DEVICE, "slicing the peakmap failed: %s", hipGetErrorString(e));
     }
-    q->n_peaks = h_off[N];
-    q->max_per_fft = 0;
-    for (int32_t i = 0; i < N; ++i) q->max_per_fft = std::max<int32_t>(q->max_per_fft, (int32_t)(h_off[i + 1] - h_off[i]));
     *out = q;
     return FH_OK;
 }
@@ -1173,7 +1282,7 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
         fh_select sel{nf, nf, -1, o->theta};
         for (int c = 0; c < n_cand; ++c) {
             HIP_OK(launch_slice(N, pm->d_offsets, pm->d_bins, klo[c], khi[c], (int64_t *)ctx->rf_first.ptr,
-                                (int32_t *)ctx->rf_counts.ptr, sub.d_offsets, sub.d_bins, st));
+                                (int32_t *)ctx->rf_counts.ptr, sub.d_offsets, sub.d_bins, nullptr, st));
             ChunkBufs bc = b;
             bc.sky = d_sky + 3 * (size_t)c * n_dir;
             if ((s = run_search(ctx, &sub, &grids[c], p, n_dir, n_dir, d_w, 0, FH_SCHED_PERSISTENT, &sel,
@@ -1238,20 +1347,16 @@ fh_status fh_robust_stats(fh_ctx *ctx, const int32_t *d_x, int32_t n, int32_t x_
     if (x_max < 0 || x_max > (1 << 28)) return fail(FH_E_INVALID, "x_max=%d outside 0..2^28", x_max);
     hipStream_t st = (hipStream_t)stream;
     if ((s = ctx->cl_hist.ensure(4 * (2 * (size_t)x_max + 1), st)) || (s = ctx->cl_s2.ensure(8, st)) ||
-        (s = ctx->cl_out.ensure(16, st)) || (s = ctx->err.ensure(4, st)))
+        (s = ctx->cl_out.ensure(24, st)) || (s = ctx->err.ensure(4, st)))
         return s;
-    int32_t *err = (int32_t *)ctx->err.ptr;
-    HIP_OK(launch_fill_i32(err, 1, 0, st));
     HIP_OK(launch_robust(d_x, n, x_max, (int32_t *)ctx->cl_hist.ptr, (int64_t *)ctx->cl_s2.ptr,
-                         (double *)ctx->cl_out.ptr, err, st));
-    int32_t h_err = 0;
-    double h_out[2];
-    HIP_OK(hipMemcpyAsync(&h_err, err, 4, hipMemcpyDeviceToHost, st));
-    HIP_OK(hipMemcpyAsync(h_out, ctx->cl_out.ptr, 16, hipMemcpyDeviceToHost, st));
+                         (double *)ctx->cl_out.ptr, (int32_t *)ctx->err.ptr, st));
+    double *h = (double *)ctx->h_small.ptr;  // m1, m2, error flag
+    HIP_OK(hipMemcpyAsync(h, ctx->cl_out.ptr, 24, hipMemcpyDeviceToHost, st));
     HIP_OK(hipStreamSynchronize(st));
-    if (h_err) return fail(FH_E_INVALID, "a value lies outside [0, x_max=%d]", x_max);
-    out[0] = h_out[0];
-    out[1] = h_out[1];
+    if (h[2] != 0.0) return fail(FH_E_INVALID, "a value lies outside [0, x_max=%d]", x_max);
+    out[0] = h[0];
+    out[1] = h[1];
     return FH_OK;
 }
 
@@ -1767,7 +1872,11 @@ fh_status fh_server_create(fh_ctx *ctx, int64_t hbm_budget, int32_t lanes, int32
     const int64_t budget = hbm_budget / 256 * 256;
     if (budget <= 0) return fail(FH_E_INVALID, "hbm_budget must be at least 256 bytes");
     void *mem = nullptr;
-    if (hipMalloc(&mem, (size_t)budget) != hipSuccess)
+    if (hipMalloc(&mem, (size_t)budget) != hipSuccess) {
+        ctx->blocks.trim();
+        mem = nullptr;
+    }
+    if (!mem && hipMalloc(&mem, (size_t)budget) != hipSuccess)
         return fail(FH_E_NOMEM, "allocating the server's %lld-byte arena failed", (long long)budget);
     fh_server *srv = new fh_server();
     srv->ctx = ctx;

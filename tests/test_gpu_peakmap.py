@@ -83,3 +83,38 @@ def test_rows_at_the_edges_of_a_waves_run_and_of_the_scan(n_fft, n_bins, with_ar
         np.testing.assert_array_equal(off, ref_off)
         np.testing.assert_array_equal(bins, ref_bins)
         dpm.release()
+
+
+def test_blocks_of_released_peakmaps_are_handed_on_safely():
+    """Peakmaps built, filtered and released in turn, through two contexts:
+    every live peakmap keeps its own peaks, and device memory goes back with
+    the contexts."""
+    import torch
+    from paper_1407_8333_amd import api
+    rng = synth.rng_for(99)
+    t = synth.fft_times(50, 1024.0)
+    v = synth.detector_velocity(t, rng)
+    torch.cuda.synchronize()
+    with api.Context(0) as a, api.Context(0) as b:
+        live = []
+        for turn in range(14):
+            ctx = (a, b)[turn % 2]
+            n_bins = int(rng.integers(40, 4000))
+            sp = rng.standard_exponential((50, n_bins)).astype(np.float32)
+            want = peakmap.peakmap_from_spectra(sp, None, 500, 2.5)
+            pm = api.DevicePeakmap.from_spectra(ctx, torch.as_tensor(sp, device="cuda"), 500, 2.5, t, v, 1024.0)
+            live.append((pm, want))
+            if turn % 3 == 2:
+                lo, hi = 500 + n_bins // 4, 500 + n_bins // 2 + 1
+                sub = pm.slice(lo, hi)
+                keep = (want[1] >= lo) & (want[1] < hi)
+                off = np.concatenate([[0], np.cumsum(keep)])[want[0]]
+                live.append((sub, (off, want[1][keep])))
+            if len(live) > 5:
+                live.pop(int(rng.integers(len(live))))[0].release()
+            for p, (off, bins) in live:
+                got = p.download()
+                np.testing.assert_array_equal(got[0], off)
+                np.testing.assert_array_equal(got[1], bins)
+        for p, _ in live:
+            p.release()
