@@ -174,8 +174,10 @@ fh_status fh_ctx_check(fh_ctx *ctx, void *stream);
  * depend on them.  Names: "window_method" (0 = two binary searches per peak
  * window, 1 = one sweep per FFT, 2 = stripe edges and windows in one kernel
  * with the edges of a few FFTs staged in LDS, default 2; it falls back to 1
- * when one FFT holds too many peaks for the LDS).  FH_E_INVALID for an
- * unknown name or value. */
+ * when one FFT holds too many peaks for the LDS); "tile_parts" (workgroups
+ * that share each tile of searches and maps with few tiles, 1 .. 64, capped
+ * by the peakmap's FFTs; 0, the default, chooses by a cost model).
+ * FH_E_INVALID for an unknown name or value. */
 fh_status fh_ctx_set_option(fh_ctx *ctx, const char *name, int64_t value);
 
 /* Doppler correction used by every later search of the context (Sec. "The
@@ -228,7 +230,9 @@ int64_t fh_peakmap_bytes(const fh_peakmap *pm);
 /* ---- planning ---------------------------------------------------------- */
 
 /* Tile shape and workspace size the library will use for (pm, grid);
- * tile_bins = 0 lets the library choose. */
+ * tile_bins = 0 lets the library choose: the autotuned or widest tile of a
+ * search of many directions, or the width of the shape's last search where
+ * that had so few tiles that it chose its own. */
 fh_status fh_plan_query(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *grid,
                         int32_t tile_bins, fh_plan_info *out);
 

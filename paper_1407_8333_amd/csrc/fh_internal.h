@@ -77,6 +77,10 @@ struct TileArgs {
     // persistent scheduling
     int32_t *queue_ctr;           // [kXcds] claimed positions of the tile queues
     int32_t tile_base;            // first tile id of a plain launch
+    // tiles of which several workgroups accumulate a part (parts > 1)
+    int32_t parts;
+    int64_t part_stride;          // words of a partial tile (part_words)
+    uint32_t *part;               // [tile][parts][part_stride]
 };
 
 // ---- launchers (fh_kernels.hip) ----
@@ -124,8 +128,10 @@ hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t
 hipError_t launch_windows(int32_t n_fft, const int64_t *offsets, const int64_t *Y, int64_t n_peaks,
                           const int64_t *gwin, int32_t nrbg, int32_t nbb, int32_t W,
                           int32_t kf, int32_t n_slots, int2 *win, int method, hipStream_t st);
-hipError_t launch_tiles(const TileArgs &a, bool weighted, bool want_map, bool want_colmax,
-                        bool persistent, int32_t n_tiles, int32_t grid_blocks, hipStream_t st);
+// map: the map of one direction; otherwise column maxima, by persistent
+// workgroups or one per tile.  a.parts > 1: partial tiles, then their merge.
+hipError_t launch_tiles(const TileArgs &a, bool weighted, bool map, bool persistent, int32_t n_tiles,
+                        int32_t grid_blocks, hipStream_t st);
 hipError_t launch_select(const unsigned long long *colmax, int32_t nf, int32_t n_slots,
                          const fh_select &sel, int32_t sky_base, int32_t n_fft,
                          const WeightStats *ws, int32_t ws_stride, fh_candidate *out,
@@ -191,6 +197,8 @@ hipError_t launch_robust(const int32_t *x, int32_t n, int32_t x_max, int32_t *hi
 hipError_t launch_colmax_decode(const unsigned long long *colmax, int32_t nf, int32_t n_slots, const WeightStats *ws,
                                 int32_t ws_stride, float *value, int32_t *row, hipStream_t st);
 hipError_t launch_colmax_values(const unsigned long long *colmax, int32_t nf, int32_t *out, hipStream_t st);
+// words of a partial tile of 16 + tail rows
+int64_t part_words(int W, int kf, int tail);
 // LDS bytes of a tile of 16 + tail rows
 int tile_lds_bytes(int W, int kf, int tail);
 // Raise the dynamic-LDS limit of the tile kernels (once per device).

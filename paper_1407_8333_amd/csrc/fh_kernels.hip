@@ -872,15 +872,20 @@ __device__ __forceinline__ int queue_tile(const TileArgs &A, int qi, int pos) {
 }
 
 // A tile from the first queue, starting at `home`, that is not exhausted; -1
-// when all are.
-__device__ int steal_tile(const TileArgs &A, int home) {
+// when all are.  *at: its position in the home queue, kNotHome elsewhere.
+constexpr int kNotHome = 0x3fffffff;
+
+__device__ int steal_tile(const TileArgs &A, int home, int *at) {
     for (int k = 0; k < kXcds; ++k) {
         const int qi = (home + k) % kXcds;
         const int len = queue_len(A, qi);
         if (__hip_atomic_load(A.queue_ctr + qi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= len)
             continue;
         const int pos = atomicAdd(A.queue_ctr + qi, 1);
-        if (pos < len) return queue_tile(A, qi, pos);
+        if (pos < len) {
+            *at = k == 0 ? pos : kNotHome;
+            return queue_tile(A, qi, pos);
+        }
     }
     return -1;
 }
@@ -903,17 +908,18 @@ __device__ __forceinline__ void tile_zero(const TileArgs &A, uint32_t *__restric
     }
 }
 
-// Output phase of tile (slot, rb, jb): per-row window sums of the start
-// histogram, written as a map and/or reduced to per-bin column maxima.
+// Output phase of tile (slot, rb, jb) for K_f > kHold + 1: per-row window sums
+// of the start histogram, written as a map or reduced to per-bin column maxima.
 // Column maxima: a lane group owns a segment [x0, x1) of columns.  Its first
 // K_f - 1 columns are still read by the previous group's window sums, so
 // their maxima are reduced across the group's 16 lanes at once (DPP); every
 // later column is read by its own group only, and its window sums replace
 // its start counts in place.  After a barrier one thread per such column
 // reduces the 16 rows in registers and updates the global maximum.
-template <bool WEIGHTED, bool MAP, bool COLMAX>
+template <bool WEIGHTED, bool MAP>
 __device__ __forceinline__ void tile_output(const TileArgs &A, int slot, int rb, int jb,
                                             uint32_t *__restrict__ lds) {
+    constexpr bool COLMAX = !MAP;
     const int tid = threadIdx.x;
     const int j = tid & 15;
     const int W = A.W, kf = A.kf;
@@ -989,16 +995,21 @@ __device__ __forceinline__ void tile_output(const TileArgs &A, int slot, int rb,
     }
 }
 
-// Column-maximum output of tile (slot, rb, jb) that also clears the tile for
-// the next one: the output of the candidate search for K_f <= kHold + 1.
+// Output of tile (slot, rb, jb) for K_f <= kHold + 1: column maxima (the
+// candidate search), or the map.
 // Phase 1, lane group = segment of columns, lane = row: the window sums H(x)
 // along each row.  The first K_f - 1 columns of a segment are still read by
 // the previous segment, so their sums wait in registers; the later ones are
 // rewritten in place, eight columns per round with every LDS read of a round
 // issued before the first is used.  After a barrier the held sums go back in
-// place, and after another one, phase 2: one thread per column reduces its
-// 16 rows, updates the global maximum and clears the column (dump columns
-// and columns past the map are only cleared).  `mid` runs between the
+// place, and after another one, phase 2: one thread per column either reduces
+// its 16 rows and updates the global maximum, or writes them to the map,
+// where consecutive lanes then write consecutive bins of a row (stores by the
+// lanes of phase 1, one row each, went to 64 lines per instruction: the tile
+// kernel of the 100 Hz map of 3140 FFTs and 118 rows took 140 us, now 89 us,
+// also through an even cut of the band).  A persistent
+// kernel also clears the column for its next tile (dump columns and columns
+// past the map are only cleared).  `mid` runs between the
 // phases (the caller's prefetch of the next tile); the caller's barrier then
 // separates the clearing from the next tile's updates.
 constexpr int kHold = 9;  // held columns per lane: K_f - 1 <= kHold
@@ -1034,9 +1045,9 @@ __device__ __forceinline__ int colmax_rounds(uint32_t *__restrict__ P, int x, in
     return x;
 }
 
-template <typename Mid>
-__device__ __forceinline__ void tile_colmax(const TileArgs &A, int slot, int rb, int jb,
-                                            uint32_t *__restrict__ lds, Mid mid) {
+template <bool WEIGHTED, bool MAP, bool CLEAR, typename Mid>
+__device__ __forceinline__ void tile_windows(const TileArgs &A, int slot, int rb, int jb,
+                                             uint32_t *__restrict__ lds, Mid mid) {
     const int tid = threadIdx.x;
     const int j = tid & 15;
     const int W = A.W, kf = A.kf;
@@ -1107,15 +1118,34 @@ __device__ __forceinline__ void tile_colmax(const TileArgs &A, int slot, int rb,
     // Phase 2.  Lane l reads the four 16-byte quarters of its column starting
     // at quarter (l >> 1) & 3: with columns 64 bytes apart, every eight lanes
     // then cover the 32 banks once.
-    const int ncols = W + kf - 1 + kDumpCols;
+    const int ncols = CLEAR ? W + kf - 1 + kDumpCols : xend;
     const int st = ((tid & 63) >> 1) & 3;
     int qo[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) qo[k] = (k + st) & 3;
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+    float scale = 1.0f;
+    if (MAP && WEIGHTED) scale = ldexpf(1.0f, -A.ws[(int64_t)slot * A.ws_stride].frac_bits);
     for (int c = tid; c < ncols; c += blockDim.x) {
         uint4 *q = reinterpret_cast<uint4 *>(lds + c * kTileRows);
-        if (c < xend) {
+        if (MAP && c < xend) {
+            uint4 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = q[qo[k]];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t h[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int s = s0 + 4 * qo[k] + r;
+                    if (s < A.ns) {
+                        const int64_t at = (int64_t)s * A.nf + bbase + c;
+                        if (WEIGHTED) A.map_f32[at] = (float)h[r] * scale;
+                        else A.map_i32[at] = (int32_t)h[r];
+                    }
+                }
+            }
+        } else if (c < xend) {
             uint4 v[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = q[qo[k]];
@@ -1132,19 +1162,22 @@ __device__ __forceinline__ void tile_colmax(const TileArgs &A, int slot, int rb,
             }
             atomicMax(cm + c, ((unsigned long long)top << 32) | (0xFFFFFFFFull - (unsigned)(s0 + r)));
         }
+        if (CLEAR) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) q[qo[k]] = z;
+            for (int k = 0; k < 4; ++k) q[qo[k]] = z;
+        }
     }
 }
 
 // Output of the tail rows of a tile (rows (rb + 1) 16 + r, r < A.tail): their
 // window sums, one thread per column summing K_f start counts per row, as a
-// map and/or raised into the column maxima; then, after a barrier, the tail
+// map or raised into the column maxima; then, after a barrier, the tail
 // region is cleared for the next tile.  Reads only the tail region, so it
 // may follow either output phase of the 16 rows without a barrier between.
-template <bool WEIGHTED, bool MAP, bool COLMAX>
+template <bool WEIGHTED, bool MAP>
 __device__ __forceinline__ void tail_output(const TileArgs &A, int slot, int rb, int jb,
                                             uint32_t *__restrict__ lt) {
+    constexpr bool COLMAX = !MAP;
     const int W = A.W, kf = A.kf;
     const int stride = W + kf - 1 + kTailDump;
     const int s_t = (rb + 1) * kTileRows;  // first tail row
@@ -1186,8 +1219,13 @@ __device__ __forceinline__ void tail_output(const TileArgs &A, int slot, int rb,
 // during the output phase of the current one.  Every load is issued on every
 // path so that the wait counts stay exact.  PERSISTENT: tiles come from the
 // XCD queues until all are exhausted; otherwise the workgroup runs tile
-// tile_base + blockIdx.x only.
-template <bool WEIGHTED, bool MAP, bool COLMAX, bool PERSISTENT, bool TAIL>
+// tile_base + blockIdx.x only.  OUT says what becomes of the tile: a map,
+// column maxima, or (kOutPart, not persistent) one of A.parts partial tiles:
+// workgroup u takes every A.parts-th block of tile u / A.parts, starting at
+// block u % A.parts, and copies its LDS tile to A.part for k_tiles_merge.
+enum { kOutColmax = 0, kOutMap = 1, kOutPart = 2 };
+
+template <bool WEIGHTED, int OUT, bool PERSISTENT, bool TAIL>
 __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restrict__ lds, int *s_next,
                                           int *s_cnt) {
     const int tid = threadIdx.x;
@@ -1208,6 +1246,8 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     const int total = kTileWaves * nblk;  // blocks of a tile
     const int i_last = A.n_fft - 1;
     const int home = blockIdx.x % kXcds;
+    const int parts = OUT == kOutPart ? A.parts : 1;
+    const int part = OUT == kOutPart ? (int)blockIdx.x % parts : 0;
     const __amdgpu_buffer_rsrc_t r_rec = buf(A.rec), r_step = buf(A.step);
     const uint32_t lane_code = 2u * (uint32_t)j;  // bit offset of this row's residual code
     // tail rows after the 16-row tile (row-major, rows of wc + kTailDump
@@ -1248,6 +1288,7 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     // after the counter ran out) read the row's last entry, an empty window.
     auto stage_w = [&](Quad &Q, int gv, const Bufs &B) {
         Q.g = __builtin_amdgcn_readfirstlane(gv);
+        if (OUT == kOutPart) Q.g = Q.g * parts + part;
         Q.run = Q.g & (kTileWaves - 1);
         const uint32_t e = (uint32_t)(Q.run * per + 4 * (Q.g >> 4) + grp);
         const auto w2 = __builtin_amdgcn_raw_buffer_load_b64(
@@ -1291,14 +1332,16 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         Q.y1 = ld_u32(B.y, (uint32_t)(Q.lo + Q.q2) * 4u);
     };
 
+    // (thread 0) position of the current tile in the home queue
+    int at = kNotHome;
     int t;
     if (PERSISTENT) {
-        if (tid == 0) s_next[0] = steal_tile(A, home);
+        if (tid == 0) s_next[0] = steal_tile(A, home, &at);
     }
     if (tid < 2) s_cnt[tid] = 0;
     tile_zero(A, lds);
     lds_barrier();
-    t = PERSISTENT ? s_next[0] : A.tile_base + (int)blockIdx.x;
+    t = PERSISTENT ? s_next[0] : OUT == kOutPart ? (int)blockIdx.x / parts : A.tile_base + (int)blockIdx.x;
     if (t < 0 || nblk == 0) return;  // nblk > 0 whenever there is an FFT
     Quad qa, qb, qc;
     Bufs cur = tile_bufs(t);
@@ -1307,8 +1350,13 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     stage_y(qa, cur);
     for (int it = 0;; ++it) {
         const int par = it & 1;  // block counter of this tile; the other is the next tile's
-        int pos = 0;
-        if (PERSISTENT && tid == 0) pos = atomicAdd(A.queue_ctr + home, 1);
+        // The next tile is claimed ahead while the home queue holds two more
+        // rounds of its workgroups; the last ones are claimed when they are
+        // needed, so that no workgroup holds a tile that an idle one could run
+        // (703 tiles on 256 CUs took four rounds of tiles instead of three).
+        int pos = kNotHome;
+        if (PERSISTENT && tid == 0 && at + 2 * (int)(gridDim.x / kXcds) < queue_len(A, home))
+            pos = atomicAdd(A.queue_ctr + home, 1);
         // the next tile's counter was last used by the previous tile, whose
         // claims all came before the barrier that ended its accumulation
         if (tid == 0) s_cnt[par ^ 1] = 0;
@@ -1362,8 +1410,14 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         }
         int tn = -1;
         if (PERSISTENT) {
-            if (tid == 0)
-                s_next[(it + 1) & 1] = pos < queue_len(A, home) ? queue_tile(A, home, pos) : steal_tile(A, home);
+            if (tid == 0) {
+                if (pos < queue_len(A, home)) {
+                    at = pos;
+                    s_next[(it + 1) & 1] = queue_tile(A, home, pos);
+                } else {
+                    s_next[(it + 1) & 1] = steal_tile(A, home, &at);
+                }
+            }
         }
         // Drain this wave's vector-memory queue here, where the workgroup
         // waits anyway: otherwise the compiler cannot tell that the tile
@@ -1378,17 +1432,29 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
             stage_w(qa, claim(par ^ 1, 1), nxt);
             stage_w(qb, claim(par ^ 1, 1), nxt);
         }
-        // candidate search: clearing fused into the output, and the next
+        if (OUT == kOutPart) {
+            uint32_t *__restrict__ dst = A.part + (int64_t)blockIdx.x * A.part_stride;
+            const int nwords = tile_words(A);
+            for (int x = tid * 4; x < nwords; x += blockDim.x * 4) {
+                if (x + 3 < nwords) {
+                    *reinterpret_cast<uint4 *>(dst + x) = *reinterpret_cast<const uint4 *>(lds + x);
+                } else {
+                    for (int y = x; y < nwords; ++y) dst[y] = lds[y];
+                }
+            }
+            break;
+        }
+        // K_f <= kHold + 1: clearing fused into the output, and the next
         // tile's stripe edges requested while the output still runs
-        const bool fused = COLMAX && !MAP && kf <= kHold + 1;
+        const bool fused = kf <= kHold + 1;
         if (fused) {
-            tile_colmax(A, slot, rb, jb, lds, [&] {
+            tile_windows<WEIGHTED, OUT == kOutMap, PERSISTENT>(A, slot, rb, jb, lds, [&] {
                 if (tn >= 0) stage_y(qa, nxt);
             });
         } else {
-            tile_output<WEIGHTED, MAP, COLMAX>(A, slot, rb, jb, lds);
+            tile_output<WEIGHTED, OUT == kOutMap>(A, slot, rb, jb, lds);
         }
-        if (TAIL && tailed) tail_output<WEIGHTED, MAP, COLMAX>(A, slot, rb, jb, ltail);
+        if (TAIL && tailed) tail_output<WEIGHTED, OUT == kOutMap>(A, slot, rb, jb, ltail);
         if (tn < 0) break;
         if (!fused) stage_y(qa, nxt);
         lds_barrier();
@@ -1401,23 +1467,113 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     }
 }
 
-template <bool WEIGHTED, bool MAP, bool COLMAX, bool TAIL>
+template <bool WEIGHTED, int OUT, bool TAIL>
 __global__ void __launch_bounds__(kTileThreads) k_tiles_plain(TileArgs A) {
     extern __shared__ uint32_t lds[];
     __shared__ int s_cnt[2];
-    run_tiles<WEIGHTED, MAP, COLMAX, false, TAIL>(A, lds, nullptr, s_cnt);
+    run_tiles<WEIGHTED, OUT, false, TAIL>(A, lds, nullptr, s_cnt);
 }
 
 // One workgroup per CU.  The next tile of the home queue is claimed when a
 // tile starts (its counter update overlaps the tile's work) and used when it
 // ends; an exhausted home queue sends the workgroup to the others.  Every
 // workgroup leaves the loop once all queues are exhausted.
-template <bool WEIGHTED, bool MAP, bool COLMAX, bool TAIL>
+template <bool WEIGHTED, bool TAIL>
 __global__ void __launch_bounds__(kTileThreads) k_tiles_persistent(TileArgs A) {
     extern __shared__ uint32_t lds[];
     __shared__ int s_next[2];
     __shared__ int s_cnt[2];
-    run_tiles<WEIGHTED, MAP, COLMAX, true, TAIL>(A, lds, s_next, s_cnt);
+    run_tiles<WEIGHTED, kOutColmax, true, TAIL>(A, lds, s_next, s_cnt);
+}
+
+// Sums of the partial tiles and their output: grid (column chunks of a tile,
+// tiles), kMergeCols columns per workgroup.  The A.parts partial tiles of the
+// chunk (and the K_f - 1 columns past it) are read with 16 bytes per lane,
+// added in registers and laid out row-major in LDS, where every output is
+// the sum of K_f consecutive words: one wave writes 64 consecutive bins of a
+// row of the map, or raises the column maxima (two threads per column, eight
+// rows each).  Bound by reading the partial tiles.
+constexpr int kMergeCols = 128;
+constexpr int kMergeThreads = 256;
+// words per row: kMergeCols + 63 (K_f = 64) and 4 modulo 16, so that the four
+// quarters of 16 columns that a wave stores together lie in 64 banks
+constexpr int kMergeStride = 196;
+
+template <bool WEIGHTED, bool MAP>
+__global__ void __launch_bounds__(kMergeThreads) k_tiles_merge(TileArgs A) {
+    __shared__ uint32_t h[(kTileRows + kTailRows) * kMergeStride];
+    const int tid = threadIdx.x;
+    const int t = blockIdx.y;
+    int slot, rb, jb;
+    decode_tile(A, t, slot, rb, jb);
+    const int W = A.W, kf = A.kf;
+    const int64_t bbase = (int64_t)jb * W;
+    const int xend = (int)min((int64_t)W, (int64_t)A.nf - bbase);
+    const int c0 = (int)blockIdx.x * kMergeCols;
+    if (c0 >= xend) return;  // (the whole workgroup)
+    const int ncol = min(kMergeCols, xend - c0);
+    const int nin = ncol + kf - 1;
+    const uint32_t *__restrict__ src = A.part + (int64_t)t * A.parts * A.part_stride;
+    for (int e = tid; e < nin * 4; e += kMergeThreads) {
+        const uint32_t *__restrict__ q = src + (int64_t)c0 * kTileRows + 4 * e;
+        uint4 sum = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll 4
+        for (int p = 0; p < A.parts; ++p) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(q + p * A.part_stride);
+            sum.x += v.x;
+            sum.y += v.y;
+            sum.z += v.z;
+            sum.w += v.w;
+        }
+        uint32_t *d = h + (e & 3) * 4 * kMergeStride + (e >> 2);
+        d[0] = sum.x;
+        d[kMergeStride] = sum.y;
+        d[2 * kMergeStride] = sum.z;
+        d[3 * kMergeStride] = sum.w;
+    }
+    const int tail = rb == A.nrb - 1 ? A.tail : 0;
+    const int wc = W + kf - 1;
+    for (int e = tid; e < tail * nin; e += kMergeThreads) {
+        const int r = e / nin, c = e - r * nin;
+        const uint32_t *__restrict__ q = src + kTileRows * (wc + kDumpCols) + r * (wc + kTailDump) + c0 + c;
+        uint32_t sum = 0;
+        for (int p = 0; p < A.parts; ++p) sum += q[p * A.part_stride];
+        h[(kTileRows + r) * kMergeStride + c] = sum;
+    }
+    __syncthreads();
+    const int s0 = rb * kTileRows;
+    const int rows = min(kTileRows, A.ns - s0) + tail;
+    const int c = tid & (kMergeCols - 1), half = tid / kMergeCols;
+    if (c >= ncol) return;
+    if (MAP) {
+        float scale = 1.0f;
+        if (WEIGHTED) scale = ldexpf(1.0f, -A.ws[(int64_t)slot * A.ws_stride].frac_bits);
+        for (int r = half; r < rows; r += kMergeThreads / kMergeCols) {
+            const uint32_t *P = h + r * kMergeStride + c;
+            uint32_t acc = 0;
+            for (int k = 0; k < kf; ++k) acc += P[k];
+            const int64_t at = (int64_t)(s0 + r) * A.nf + bbase + c0 + c;
+            if (WEIGHTED) A.map_f32[at] = (float)acc * scale;
+            else A.map_i32[at] = (int32_t)acc;
+        }
+    } else {
+        // rows 0-7, and 8 to the last (tail rows follow the 16 in the grid too)
+        const int r0 = half * 8, r1 = half == 0 ? min(rows, 8) : rows;
+        if (r0 >= r1) return;
+        uint32_t top = 0;
+        int at = r0;
+        for (int r = r0; r < r1; ++r) {
+            const uint32_t *P = h + r * kMergeStride + c;
+            uint32_t acc = 0;
+            for (int k = 0; k < kf; ++k) acc += P[k];
+            if (acc > top) {  // the smallest row holding the maximum
+                top = acc;
+                at = r;
+            }
+        }
+        atomicMax(A.colmax + (int64_t)slot * A.nf + bbase + c0 + c,
+                  ((unsigned long long)top << 32) | (0xFFFFFFFFull - (unsigned)(s0 + at)));
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -1698,6 +1854,8 @@ int tile_lds_bytes(int W, int kf, int tail) {
     return (kTileRows * (W + kf - 1 + kDumpCols) + tail * (W + kf - 1 + kTailDump)) * 4;
 }
 
+int64_t part_words(int W, int kf, int tail) { return (tile_lds_bytes(W, kf, tail) / 4 + 3) / 4 * 4; }
+
 int max_tile_bins(int kf, double step_bins, int rows) {
     // rows past 16 are tail rows, with kTailDump dump words each
     const int words = (kLdsBytes - kLdsReserve) / 4 - kDumpCols * kTileRows - kTailDump * (rows - kTileRows);
@@ -1807,41 +1965,40 @@ hipError_t launch_windows(int32_t n_fft, const int64_t *offsets, const int64_t *
     return hipGetLastError();
 }
 
-template <bool Wt, bool M, bool C, bool T>
-static hipError_t set_tile_attrs_t() {
-    const int lds = kLdsBytes - kLdsReserve;
-    hipError_t e = hipFuncSetAttribute((const void *)k_tiles_persistent<Wt, M, C, T>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void *)k_tiles_plain<Wt, M, C, T>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-}
-
-template <bool Wt, bool M, bool C>
+template <bool Wt, bool T>
 static hipError_t set_tile_attrs() {
-    const hipError_t e = set_tile_attrs_t<Wt, M, C, false>();
-    return e != hipSuccess ? e : set_tile_attrs_t<Wt, M, C, true>();
+    const int lds = kLdsBytes - kLdsReserve;
+    for (const void *f : {(const void *)k_tiles_persistent<Wt, T>, (const void *)k_tiles_plain<Wt, kOutColmax, T>,
+                          (const void *)k_tiles_plain<Wt, kOutMap, T>, (const void *)k_tiles_plain<Wt, kOutPart, T>}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Tiles with tail rows run the TAIL form of the kernels; without, the plain
 // form has no trace of them.
-template <bool Wt, bool M, bool C>
-static hipError_t launch_tiles_t(const TileArgs &a, bool persistent, int32_t n_tiles,
+template <bool Wt, bool T>
+static hipError_t launch_tiles_t(const TileArgs &a, bool map, bool persistent, int32_t n_tiles,
                                  int32_t grid_blocks, hipStream_t st) {
     if (a.tail < 0 || a.tail > kTailRows) return hipErrorInvalidValue;
     const int lds = tile_lds_bytes(a.W, a.kf, a.tail);
     if (lds > kLdsBytes - kLdsReserve) return hipErrorInvalidValue;
-    if (a.tail > 0) {
-        if (persistent)
-            k_tiles_persistent<Wt, M, C, true><<<grid_blocks, kTileThreads, lds, st>>>(a);
-        else
-            k_tiles_plain<Wt, M, C, true><<<n_tiles, kTileThreads, lds, st>>>(a);
-    } else {
-        if (persistent)
-            k_tiles_persistent<Wt, M, C, false><<<grid_blocks, kTileThreads, lds, st>>>(a);
-        else
-            k_tiles_plain<Wt, M, C, false><<<n_tiles, kTileThreads, lds, st>>>(a);
+    if (a.parts > 1) {
+        // (the launch grid below holds 65535 tiles)
+        if (a.part == nullptr || a.part_stride < part_words(a.W, a.kf, a.tail) || n_tiles > 65535)
+            return hipErrorInvalidValue;
+        k_tiles_plain<Wt, kOutPart, T><<<n_tiles * a.parts, kTileThreads, lds, st>>>(a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const dim3 grid((a.W + kMergeCols - 1) / kMergeCols, n_tiles);
+        if (map) k_tiles_merge<Wt, true><<<grid, kMergeThreads, 0, st>>>(a);
+        else k_tiles_merge<Wt, false><<<grid, kMergeThreads, 0, st>>>(a);
+        return hipGetLastError();
     }
+    if (map) k_tiles_plain<Wt, kOutMap, T><<<n_tiles, kTileThreads, lds, st>>>(a);
+    else if (persistent) k_tiles_persistent<Wt, T><<<grid_blocks, kTileThreads, lds, st>>>(a);
+    else k_tiles_plain<Wt, kOutColmax, T><<<n_tiles, kTileThreads, lds, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1852,12 +2009,10 @@ hipError_t init_kernel_attributes() {
     hipError_t e;
     if ((e = set_refine_attributes()) != hipSuccess) return e;
     if ((e = set_cleaning_attributes()) != hipSuccess) return e;
-    if ((e = set_tile_attrs<true, true, true>()) != hipSuccess) return e;
-    if ((e = set_tile_attrs<true, true, false>()) != hipSuccess) return e;
-    if ((e = set_tile_attrs<true, false, true>()) != hipSuccess) return e;
-    if ((e = set_tile_attrs<false, true, true>()) != hipSuccess) return e;
-    if ((e = set_tile_attrs<false, true, false>()) != hipSuccess) return e;
-    if ((e = set_tile_attrs<false, false, true>()) != hipSuccess) return e;
+    if ((e = set_tile_attrs<true, true>()) != hipSuccess) return e;
+    if ((e = set_tile_attrs<true, false>()) != hipSuccess) return e;
+    if ((e = set_tile_attrs<false, true>()) != hipSuccess) return e;
+    if ((e = set_tile_attrs<false, false>()) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute((const void *)k_sort_windows, hipFuncAttributeMaxDynamicSharedMemorySize,
                                  kSortStageBytes)) != hipSuccess)
         return e;
@@ -1865,17 +2020,14 @@ hipError_t init_kernel_attributes() {
                                kSortStageEntries * (int)sizeof(int2));
 }
 
-hipError_t launch_tiles(const TileArgs &a, bool weighted, bool want_map, bool want_colmax,
-                        bool persistent, int32_t n_tiles, int32_t grid_blocks, hipStream_t st) {
+hipError_t launch_tiles(const TileArgs &a, bool weighted, bool map, bool persistent, int32_t n_tiles,
+                        int32_t grid_blocks, hipStream_t st) {
     if (n_tiles <= 0) return hipSuccess;
-    if (weighted) {
-        if (want_map && want_colmax) return launch_tiles_t<true, true, true>(a, persistent, n_tiles, grid_blocks, st);
-        if (want_map) return launch_tiles_t<true, true, false>(a, persistent, n_tiles, grid_blocks, st);
-        return launch_tiles_t<true, false, true>(a, persistent, n_tiles, grid_blocks, st);
-    }
-    if (want_map && want_colmax) return launch_tiles_t<false, true, true>(a, persistent, n_tiles, grid_blocks, st);
-    if (want_map) return launch_tiles_t<false, true, false>(a, persistent, n_tiles, grid_blocks, st);
-    return launch_tiles_t<false, false, true>(a, persistent, n_tiles, grid_blocks, st);
+    if (weighted)
+        return a.tail > 0 ? launch_tiles_t<true, true>(a, map, persistent, n_tiles, grid_blocks, st)
+                          : launch_tiles_t<true, false>(a, map, persistent, n_tiles, grid_blocks, st);
+    return a.tail > 0 ? launch_tiles_t<false, true>(a, map, persistent, n_tiles, grid_blocks, st)
+                      : launch_tiles_t<false, false>(a, map, persistent, n_tiles, grid_blocks, st);
 }
 
 hipError_t launch_select(const unsigned long long *colmax, int32_t nf, int32_t n_slots,

@@ -207,16 +207,16 @@ struct fh_peakmap {
 // Device and pinned buffers of one in-flight search.  A context owns one;
 // each serving lane owns another.
 struct Workspace {
-    DevBuf sht, Y, Y64, win, wsort, colmax, wq, ws, sky, qctr;
+    DevBuf sht, Y, Y64, win, wsort, colmax, wq, ws, sky, qctr, part;
     PinnedBuf h_sky;
     size_t device_bytes() const {
         size_t n = 0;
-        for (const DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr})
+        for (const DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part})
             n += b->bytes;
         return n;
     }
     void release() {
-        for (DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr})
+        for (DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part})
             b->release();
         h_sky.release();
     }
@@ -228,6 +228,7 @@ struct fh_ctx {
     Workspace main_ws;
     Workspace *cur = &main_ws;  // workspace used by the launch sequences
     int32_t window_method = 2;  // peak windows: 0 binary searches, 1 sweep, 2 fused front
+    int32_t tile_parts = 0;     // workgroups per tile of small searches: 0 by rule (plan_parts)
     // Doppler correction: 0 exact per peak, 1 per-FFT shift at doppler_fref
     // (<= 0: each map's band centre)
     int32_t doppler_mode = 0;
@@ -245,6 +246,9 @@ struct fh_ctx {
     // autotuned tile width per problem shape (shared by weighted and
     // unweighted searches: the two kernels differ only in the added value)
     std::map<std::tuple<int, int, int, int>, int> tuned;
+    // width of a shape's last search where that was a small launch, which
+    // chooses its own (reported by fh_plan_query)
+    std::map<std::tuple<int, int, int, int>, int> used;
     // captured searches (fh_options.use_graph), keyed by every argument and
     // workspace pointer they bake in
     struct GraphEntry {
@@ -426,7 +430,7 @@ std::tuple<int, int, int, int> tune_key(const fh_peakmap *pm, const fh_grid *g) 
 // holds; a width too wide for the tail rows runs them as a row block of
 // their own), else the autotuned one, else the widest that also holds the
 // tail rows.
-int choose_tile_bins(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int requested) {
+int choose_tile_bins(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int requested) {
     const int wmax = tile_bins_limit(pm, g);
     if (requested > 0)
         return std::min(((requested + 63) / 64) * 64, max_tile_bins(g->kf, row_step_bins(pm, g), kTileRows));
@@ -486,7 +490,119 @@ struct ChunkBufs {
     WeightStats *ws;
     double *sky;
     int32_t *qctr, *err;
+    uint32_t *part = nullptr;  // partial tiles of searches with few tiles
+    size_t part_bytes = 0;
 };
+
+// Cost model of the tiles of small launches, in us, fitted to timed launches of
+// one and five directions at T_FFT = 1024 .. 8192 s, W = 256 .. 2496 and 1 .. 16
+// parts (single rounds; the model is within about 20 % of them).
+//   a tile's clearing, first loads and output: 4.2 + 2.5 per 1000 columns;
+//   its FFTs: 3.05 ns each (a quarter of a block's window, term and pattern
+//   set-up) and 0.43 ns per peak of the FFT's window, which is wider than the
+//   tile by the rows' spread; a third more where the tile has tail rows.
+double tile_fixed_us(int W) { return 4.2 + 2.5e-3 * W; }
+
+double tile_accum_us(const fh_peakmap *pm, const fh_grid *g, const Plan &p) {
+    const double density = (double)pm->n_peaks / pm->n_fft / ((double)g->kf * (pm->k_max - pm->k_min + 1));
+    const double spread = 0.5 * row_step_bins(pm, g) * std::min(kTileRows * kRowBlocksPerGroup, g->ns);
+    const double us = pm->n_fft * (3.05e-3 + 0.43e-3 * density * (p.W + g->kf + spread));
+    return p.tail ? us * (1.0 + 0.33 / p.nrb) : us;
+}
+
+// n_tiles tiles, each shared by `parts` workgroups: rounds over the CUs, and
+// the partial tiles written and read by the merge at 2.6 TB/s.
+double tiles_us(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int64_t n_tiles, int parts) {
+    const double rounds = (double)((n_tiles * parts + ctx->n_cu - 1) / ctx->n_cu);
+    const double us = rounds * (tile_fixed_us(p.W) + tile_accum_us(pm, g, p) / parts);
+    return parts == 1 ? us
+                      : us + 6.0 + 4.0e-6 * (double)part_words(p.W, g->kf, p.tail) * (double)(n_tiles * parts) / 2.6;
+}
+
+// Workgroups that share each of n_tiles tiles (each accumulates every
+// parts-th block of FFTs; a merge adds the partial tiles): more than one only
+// where the launch leaves CUs idle and the model finds the shorter
+// accumulation worth the partial tiles' way through memory.  One direction of
+// 31 rows at T_FFT = 2048 s (32 tiles of 1280 bins): 103 us by one workgroup
+// each, 35 us by eight.
+int plan_parts(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int64_t n_tiles) {
+    // a part keeps one round of the ring of blocks for each of its waves
+    const int64_t blocks = (int64_t)kTileWaves * (wave_ffts(pm->n_fft) / 4);
+    const int64_t most = std::min<int64_t>(64, std::max<int64_t>(1, blocks / (3 * kTileWaves)));
+    if (n_tiles < 1 || n_tiles > 65535) return 1;
+    if (ctx->tile_parts > 0) return (int)std::min<int64_t>(ctx->tile_parts, most);
+    int best = 1;
+    double best_us = tiles_us(ctx, pm, g, p, n_tiles, 1);
+    for (int64_t s = 2; s <= most && s * n_tiles <= 2 * ctx->n_cu; ++s) {
+        const double us = tiles_us(ctx, pm, g, p, n_tiles, (int)s);
+        if (us < best_us) {
+            best_us = us;
+            best = (int)s;
+        }
+    }
+    return best;
+}
+
+// Launches of at most this many rounds of tiles over the CUs choose their
+// width by the model: there the last, partly empty round and the parts decide
+// (a width tuned on many directions left a map of 264 tiles two rounds of 66 us
+// on 256 CUs).  Longer launches are tuned by timing.
+constexpr int kSmallRounds = 6;
+
+bool small_launch(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_dir) {
+    const Plan p = make_plan(*g, std::max(64, std::min(tile_bins_limit(pm, g), ((g->nf + 63) / 64) * 64)));
+    return p.tiles_per_sky * n_dir <= (int64_t)kSmallRounds * ctx->n_cu;
+}
+
+// Tile width of a small launch of n_dir directions: the band cut evenly into
+// n blocks, for every n up to tiles of 192 bins; besides the tiles' cost, a
+// window entry of the front and the window sort takes 12 ps.
+int small_tile_bins(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_dir) {
+    const int wmax = max_tile_bins(g->kf, row_step_bins(pm, g), kTileRows);
+    int best_w = 0;
+    double best_us = 0.0;
+    for (int n = std::max(1, (g->nf + wmax - 1) / wmax); ; n += 1 + n / 16) {
+        const int w = std::max(64, ((g->nf + n - 1) / n + 63) / 64 * 64);
+        const Plan p = make_plan(*g, w);
+        const int64_t n_tiles = p.tiles_per_sky * n_dir;
+        const double us = tiles_us(ctx, pm, g, p, n_tiles, plan_parts(ctx, pm, g, p, n_tiles)) +
+                          12e-6 * (double)p.nrbg * p.nbb * win_stride(pm->n_fft) * n_dir;
+        if (best_w == 0 || us < best_us) {
+            best_us = us;
+            best_w = w;
+        }
+        if (w <= 192) break;
+    }
+    return best_w;
+}
+
+size_t parts_bytes(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int slots) {
+    const int64_t n_tiles = p.tiles_per_sky * slots;
+    const int parts = plan_parts(ctx, pm, g, p, n_tiles);
+    return parts > 1 ? (size_t)4 * part_words(p.W, g->kf, p.tail) * parts * n_tiles : 0;
+}
+
+// bytes for the partial tiles of every launch of n_sky directions in chunks
+size_t search_parts_bytes(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int chunk,
+                          int n_sky) {
+    const int last = n_sky % chunk;
+    return std::max(n_sky >= chunk ? parts_bytes(ctx, pm, g, p, chunk) : 0,
+                    last ? parts_bytes(ctx, pm, g, p, last) : 0);
+}
+
+// The parts of a launch of n_tiles tiles that fit the buffers it was given.
+void set_parts(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int64_t n_tiles,
+               const ChunkBufs &b, TileArgs &a) {
+    a.parts = plan_parts(ctx, pm, g, p, n_tiles);
+    a.part_stride = part_words(p.W, g->kf, p.tail);
+    a.part = b.part;
+    if ((size_t)4 * a.part_stride * a.parts * n_tiles > b.part_bytes) a.parts = 1;
+}
+
+// Tile width of a launch sequence of n_dir directions.
+int search_tile_bins(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_dir) {
+    return small_launch(ctx, pm, g, n_dir) ? small_tile_bins(ctx, pm, g, n_dir) : choose_tile_bins(ctx, pm, g, 0);
+}
 
 // the unfused window methods (chosen, or forced when one FFT's edges do not
 // fit the fused front's LDS) search the full 64-bit edges in device memory
@@ -517,6 +633,10 @@ fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, co
     if ((s = ctx->cur->sky.ensure((size_t)24 * n_sky, st))) return s;
     if ((s = ctx->cur->qctr.ensure(4 * kXcds, st))) return s;
     if ((s = ctx->err.ensure(4, st))) return s;
+    const size_t pb = search_parts_bytes(ctx, pm, g, p, slots, n_sky);
+    if (pb && (s = ctx->cur->part.ensure(pb, st))) return s;
+    b.part = (uint32_t *)ctx->cur->part.ptr;
+    b.part_bytes = ctx->cur->part.bytes;
     b.gwin = reinterpret_cast<int64_t *>((char *)ctx->cur->sht.ptr + sl.gwin);
     b.rec = reinterpret_cast<uint2 *>((char *)ctx->cur->sht.ptr + sl.rec);
     b.step = reinterpret_cast<uint32_t *>((char *)ctx->cur->sht.ptr + sl.step);
@@ -629,7 +749,7 @@ fh_status hough_map_common(fh_ctx *ctx, const fh_peakmap *pm, const double nhat[
     if (!out) return fail(FH_E_INVALID, "output map pointer is NULL");
     hipStream_t st = (hipStream_t)stream;
     const bool weighted = d_w != nullptr;
-    const Plan p = make_plan(*g, choose_tile_bins(ctx, pm, g, 0));
+    const Plan p = make_plan(*g, search_tile_bins(ctx, pm, g, 1));
     ChunkBufs b;
     if ((s = ensure_workspace(ctx, pm, g, p, 1, 1, weighted, st, b))) return s;
     if ((s = upload_sky(ctx, nhat, 1, b, st))) return s;
@@ -648,7 +768,8 @@ fh_status enqueue_map(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const
     a.tile_base = 0;
     {
         Timed timed(ctx, st, kSpanTiles);
-        HIP_OK(launch_tiles(a, weighted, true, false, false, (int32_t)p.tiles_per_sky, 0, st));
+        set_parts(ctx, pm, g, p, p.tiles_per_sky, b, a);
+        HIP_OK(launch_tiles(a, weighted, true, false, (int32_t)p.tiles_per_sky, 0, st));
     }
     if (ctx->profiling) ctx->prof_updates += pm->n_peaks * (int64_t)g->ns;
     return FH_OK;
@@ -690,15 +811,17 @@ fh_status run_search(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const 
         HIP_OK(launch_fill_u64(b.colmax, (int64_t)slots * g->nf, 0ull, st));
         TileArgs a = tile_args(pm, g, p, slots, b, weighted, w_stride == 0 ? 0 : 1);
         const int64_t n_tiles = p.tiles_per_sky * slots;
-        if (schedule == FH_SCHED_PERSISTENT) {
-            HIP_OK(launch_fill_i32(b.qctr, kXcds, 0, st));
+        set_parts(ctx, pm, g, p, n_tiles, b, a);
+        // A single round of tiles is dispatched by the hardware: a persistent
+        // workgroup claims its next tile when it starts one, so early ones
+        // would take two tiles and late ones none (240 tiles of a 4096 s band:
+        // 165 us, against 90 us).
+        const bool persistent = schedule == FH_SCHED_PERSISTENT && a.parts == 1 && n_tiles > ctx->n_cu;
+        if (persistent) HIP_OK(launch_fill_i32(b.qctr, kXcds, 0, st));
+        {
             const int grid_blocks = (int)std::min<int64_t>(ctx->n_cu, n_tiles);
             Timed timed(ctx, st, kSpanTiles);
-            HIP_OK(launch_tiles(a, weighted, false, true, true, (int32_t)n_tiles, grid_blocks, st));
-        } else {
-            a.tile_base = 0;
-            Timed timed(ctx, st, kSpanTiles);
-            HIP_OK(launch_tiles(a, weighted, false, true, false, (int32_t)n_tiles, 0, st));
+            HIP_OK(launch_tiles(a, weighted, false, persistent, (int32_t)n_tiles, grid_blocks, st));
         }
         if (ctx->profiling) ctx->prof_updates += pm->n_peaks * (int64_t)g->ns * slots;
         if (cm_out.value)
@@ -770,6 +893,29 @@ fh_status autotune(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_sk
     if (s) return s;
     ctx->tuned[tune_key(pm, g)] = best_w;
     return FH_OK;
+}
+
+// Tile width of a search: the requested one, by the model where a launch has
+// few tiles, else the autotuned one (tuning it first if need be).
+fh_status plan_width(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_sky, const double *sky,
+                     const float *d_w, int w_stride, const fh_options &o, hipStream_t st, int *width) {
+    if (o.tile_bins > 0) {
+        *width = choose_tile_bins(ctx, pm, g, o.tile_bins);
+        return FH_OK;
+    }
+    // directions per launch (a plain schedule runs them one by one)
+    const int dirs = o.schedule == FH_SCHED_PLAIN ? 1 : o.sky_chunk > 0 ? std::min(o.sky_chunk, n_sky) : n_sky;
+    if (small_launch(ctx, pm, g, dirs)) {
+        *width = small_tile_bins(ctx, pm, g, dirs);
+        ctx->used[tune_key(pm, g)] = *width;
+        return FH_OK;
+    }
+    fh_status s = FH_OK;
+    if (ctx->tuned.find(tune_key(pm, g)) == ctx->tuned.end())
+        s = autotune(ctx, pm, g, n_sky, sky, d_w, w_stride, st);
+    *width = choose_tile_bins(ctx, pm, g, 0);
+    ctx->used.erase(tune_key(pm, g));
+    return s;
 }
 
 }  // namespace
@@ -904,6 +1050,11 @@ fh_status fh_ctx_set_option(fh_ctx *ctx, const char *name, int64_t value) {
     if (std::strcmp(name, "window_method") == 0) {
         if (value < 0 || value > 2) return fail(FH_E_INVALID, "window_method must be 0, 1 or 2");
         ctx->window_method = (int32_t)value;
+        return FH_OK;
+    }
+    if (std::strcmp(name, "tile_parts") == 0) {
+        if (value < 0 || value > 64) return fail(FH_E_INVALID, "tile_parts must be 0 .. 64");
+        ctx->tile_parts = (int32_t)value;
         return FH_OK;
     }
     return fail(FH_E_INVALID, "unknown option '%s'", name);
@@ -1366,7 +1517,7 @@ fh_status fh_line_counts(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, in
     if ((s = check_grid(pm, g))) return s;
     if (!d_out) return fail(FH_E_INVALID, "output pointer is NULL");
     hipStream_t st = (hipStream_t)stream;
-    const Plan p = make_plan(*g, choose_tile_bins(ctx, pm, g, 0));
+    const Plan p = make_plan(*g, search_tile_bins(ctx, pm, g, 1));
     ChunkBufs b;
     if ((s = ensure_workspace(ctx, pm, g, p, 1, 1, false, st, b))) return s;
     const double zero[3] = {0.0, 0.0, 0.0};  // v . n = 0: no Doppler correction
@@ -1406,7 +1557,10 @@ fh_status fh_plan_query(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int
     if ((s = check_grid(pm, g))) return s;
     if (!out) return fail(FH_E_INVALID, "out is NULL");
     if (tile_bins < 0) return fail(FH_E_INVALID, "tile_bins < 0");
-    const Plan p = make_plan(*g, choose_tile_bins(ctx, pm, g, tile_bins));
+    int width = choose_tile_bins(ctx, pm, g, tile_bins);
+    const auto used = ctx->used.find(tune_key(pm, g));
+    if (tile_bins == 0 && used != ctx->used.end()) width = used->second;
+    const Plan p = make_plan(*g, width);
     out->tile_rows = kTileRows;
     out->tile_bins = p.W;
     out->n_row_blocks = p.nrb;
@@ -1475,8 +1629,12 @@ fh_status fh_hough_map_i32_static(fh_ctx *ctx, const fh_peakmap *pm, const doubl
     if ((s = check_sky(nhat))) return s;
     if (!d_map) return fail(FH_E_INVALID, "output map pointer is NULL");
     hipStream_t st = (hipStream_t)stream;
-    const Plan p = make_plan(*g, choose_tile_bins(ctx, pm, g, 0));
-    const StaticLayout L = static_layout(ctx, pm, p);
+    Plan p = make_plan(*g, search_tile_bins(ctx, pm, g, 1));
+    StaticLayout L = static_layout(ctx, pm, p);
+    if (L.total > kStaticScratchBytes) {  // wider tiles need fewer windows
+        p = make_plan(*g, choose_tile_bins(ctx, pm, g, 0));
+        L = static_layout(ctx, pm, p);
+    }
     if (L.total > kStaticScratchBytes)
         return fail(FH_E_UNSUPPORTED, "this map needs %zu bytes of scratch; the static scratch holds %zu",
                     L.total, kStaticScratchBytes);
@@ -1495,6 +1653,8 @@ fh_status fh_hough_map_i32_static(fh_ctx *ctx, const fh_peakmap *pm, const doubl
     b.Y64 = reinterpret_cast<int64_t *>(c + L.y64);
     b.win = reinterpret_cast<int2 *>(c + L.win);
     b.wsort = reinterpret_cast<int2 *>(c + L.wsort);
+    b.part = reinterpret_cast<uint32_t *>(c + L.total);  // what is left holds partial tiles
+    b.part_bytes = kStaticScratchBytes - L.total;
     HIP_OK(launch_set_f64x3(b.sky, nhat[0], nhat[1], nhat[2], st));
     // no profiling spans here: recording one can create an event
     const bool was = ctx->profiling;
@@ -1527,9 +1687,9 @@ fh_status fh_hough_candidates(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, 
     if (o.tile_bins < 0 || o.sky_chunk < 0) return fail(FH_E_INVALID, "negative option");
     hipStream_t st = (hipStream_t)stream;
     const bool weighted = d_w != nullptr;
-    if (o.tile_bins == 0 && ctx->tuned.find(tune_key(pm, g)) == ctx->tuned.end())
-        if ((s = autotune(ctx, pm, g, n_sky, sky, d_w, w_stride, st))) return s;
-    const Plan p = make_plan(*g, choose_tile_bins(ctx, pm, g, o.tile_bins));
+    int width = 0;
+    if ((s = plan_width(ctx, pm, g, n_sky, sky, d_w, w_stride, o, st, &width))) return s;
+    const Plan p = make_plan(*g, width);
     int chunk = o.schedule == FH_SCHED_PLAIN ? 1 : default_chunk(ctx, pm, g, p, o.sky_chunk);
     chunk = std::min(chunk, n_sky);
     ChunkBufs b;
@@ -1553,6 +1713,7 @@ fh_status fh_hough_candidates(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, 
         (uint64_t)(uintptr_t)b.ws, (uint64_t)(uintptr_t)b.sky,
         (uint64_t)(uintptr_t)b.gwin,
         (uint64_t)(uintptr_t)b.qctr, (uint64_t)(uintptr_t)b.Y64, (uint64_t)ctx->window_method,
+        (uint64_t)ctx->tile_parts, (uint64_t)(uintptr_t)b.part, (uint64_t)b.part_bytes,
         (uint64_t)ctx->doppler_mode, bits(ctx->doppler_fref)};
     fh_ctx::GraphEntry *ge = nullptr;
     for (auto &e : ctx->graphs)
@@ -1612,9 +1773,9 @@ fh_status fh_hough_colmax(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, cons
     if (o.tile_bins < 0 || o.sky_chunk < 0) return fail(FH_E_INVALID, "negative option");
     hipStream_t st = (hipStream_t)stream;
     const bool weighted = d_w != nullptr;
-    if (o.tile_bins == 0 && ctx->tuned.find(tune_key(pm, g)) == ctx->tuned.end())
-        if ((s = autotune(ctx, pm, g, n_sky, sky, d_w, w_stride, st))) return s;
-    const Plan p = make_plan(*g, choose_tile_bins(ctx, pm, g, o.tile_bins));
+    int width = 0;
+    if ((s = plan_width(ctx, pm, g, n_sky, sky, d_w, w_stride, o, st, &width))) return s;
+    const Plan p = make_plan(*g, width);
     int chunk = o.schedule == FH_SCHED_PLAIN ? 1 : default_chunk(ctx, pm, g, p, o.sky_chunk);
     chunk = std::min(chunk, n_sky);
     ChunkBufs b;
@@ -1674,7 +1835,8 @@ double ms_between(Clock::time_point a, Clock::time_point b) {
 // Byte layout of one search's workspace inside a block of the server's
 // arena: the same buffers ensure_workspace provides, 256-byte aligned.
 struct SearchLayout {
-    size_t sht = 0, y = 0, y64 = 0, win = 0, wsort = 0, colmax = 0, wq = 0, ws = 0, sky = 0, qctr = 0, total = 0;
+    size_t sht = 0, y = 0, y64 = 0, win = 0, wsort = 0, colmax = 0, wq = 0, ws = 0, sky = 0, qctr = 0, part = 0, total = 0;
+    size_t part_bytes = 0;
     ShiftLayout shl{};
 };
 
@@ -1703,6 +1865,8 @@ SearchLayout search_layout(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gri
 
 ChunkBufs carve(char *base, const SearchLayout &L, int32_t *err) {
     ChunkBufs b{};
+    b.part = reinterpret_cast<uint32_t *>(base + L.part);
+    b.part_bytes = L.part_bytes;
     b.gwin = reinterpret_cast<int64_t *>(base + L.sht + L.shl.gwin);
     b.rec = reinterpret_cast<uint2 *>(base + L.sht + L.shl.rec);
     b.step = reinterpret_cast<uint32_t *>(base + L.sht + L.shl.step);
@@ -1918,17 +2082,29 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
     R.sky.assign(req->sky, req->sky + 3 * (int64_t)req->n_sky);
     R.r.sky = nullptr;
     R.t_submit = Clock::now();
-    R.W = choose_tile_bins(ctx, req->pm, &req->grid, 0);
-    const Plan p = make_plan(req->grid, R.W);
-    // the largest chunk whose footprint fits one lane's share of the budget
+    // the largest chunk whose footprint fits one lane's share of the budget,
+    // with the tile width and partial tiles of a launch of that many directions
     const bool weighted = req->d_w != nullptr;
     const int64_t share = srv->budget / (int64_t)srv->lanes.size();
-    int chunk = (int)std::min<int64_t>(std::min<int>(req->n_sky, 256), chunk_by_tiles(p));
-    while (chunk > 1 &&
-           (int64_t)search_layout(ctx, req->pm, &req->grid, p, chunk, req->n_sky, weighted).total > share)
-        chunk = (chunk + 1) / 2;
-    R.chunk = chunk;
-    R.layout = search_layout(ctx, req->pm, &req->grid, p, chunk, req->n_sky, weighted);
+    auto plan = [&](int chunk, int width, bool parts) {
+        const Plan p = make_plan(req->grid, width);
+        R.W = width;
+        R.chunk = (int)std::min<int64_t>(chunk, chunk_by_tiles(p));
+        R.layout = search_layout(ctx, req->pm, &req->grid, p, R.chunk, req->n_sky, weighted);
+        if (parts) {
+            R.layout.part = R.layout.total;
+            R.layout.part_bytes =
+                (search_parts_bytes(ctx, req->pm, &req->grid, p, R.chunk, req->n_sky) + 255) / 256 * 256;
+            R.layout.total += R.layout.part_bytes;
+        }
+        return (int64_t)R.layout.total;
+    };
+    int chunk = std::min<int>(req->n_sky, 256);
+    while (plan(chunk, search_tile_bins(ctx, req->pm, &req->grid, chunk), true) > share && R.chunk > 1)
+        chunk = (R.chunk + 1) / 2;
+    // one direction at a time, in the least memory
+    if ((int64_t)R.layout.total > srv->budget) plan(1, R.W, false);
+    if ((int64_t)R.layout.total > srv->budget) plan(1, choose_tile_bins(ctx, req->pm, &req->grid, 0), false);
     R.footprint = (int64_t)R.layout.total;
     if (R.footprint > srv->budget) {
         srv->next_id--;

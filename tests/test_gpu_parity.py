@@ -574,3 +574,53 @@ def test_degenerate_grids(ctx, n_fft, nf, ns, kf):
     idx, val = oracle.candidates(ref, sel.width, sel.excl, sel.sep)
     _check_candidates(dec, 0, idx, val, pm.n_fft, sel.theta)
     dpm.release()
+
+
+@pytest.mark.parametrize("kf,ns,parts,weighted", [
+    (10, 9, 2, False), (10, 16, 3, True), (10, 17, 5, True),   # one row block: partly empty, full, with a tail row
+    (10, 35, 7, False), (1, 33, 64, False),                    # two row blocks, the last with tail rows
+    (5, 40, 4, True), (11, 20, 2, True), (64, 18, 3, False),   # K_f on either side of the held columns
+])
+@pytest.mark.parametrize("nf", [1, 127, 1300, 2700])
+def test_tiles_shared_by_several_workgroups(ctx, kf, ns, parts, weighted, nf):
+    """Partial tiles and their merge: maps, column maxima and candidates with
+    every tile shared by `parts` workgroups equal those of unshared tiles, and
+    the map the oracle's; bands that end in and past a merge's 128 columns."""
+    import torch
+    from paper_1407_8333_amd import api
+    rng = synth.rng_for(kf * 100 + ns)
+    n, t_fft = 900, 1024.0
+    pm = synth.random_peakmap(n, t_fft, 50000, 50000 + 600, 0.07, rng)
+    dfdot = 1.0 / (t_fft * 0.5 * n * t_fft)
+    grid = synth.Grid(kf=kf, b0=kf * 50040, nf=nf, ns=ns, fdot0=-0.4 * ns * dfdot, dfdot=dfdot,
+                      t0=0.5 * (pm.t[0] + pm.t[-1]))
+    sel = synth.Selection(width=100)
+    sky = synth.sky_uniform(3, rng)
+    w = synth.fft_weights(n, rng) if weighted else None
+    wt = None if w is None else torch.as_tensor(w, device="cuda")
+    dpm = ctx.upload(pm)
+
+    def everything():
+        m = (api.fh_hough_map_i32(ctx, dpm, sky[0], grid) if wt is None
+             else api.fh_hough_map_f32(ctx, dpm, sky[0], wt, grid))
+        value, row = api.fh_hough_colmax(ctx, dpm, sky, grid, weights=wt)
+        wide = api.fh_hough_candidates(ctx, dpm, sky, grid, sel, weights=wt, tile_bins=2496)
+        return [m, value, row, api.fh_hough_candidates(ctx, dpm, sky, grid, sel, weights=wt), wide]
+
+    try:
+        got = []
+        for p in (1, parts, 0):
+            ctx.set_option("tile_parts", p)
+            got.append(everything())
+    finally:
+        ctx.set_option("tile_parts", 0)
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert torch.equal(a, b)
+    ref = oracle.hough_map(pm, grid, sky[0], weights=None if w is None else w.astype(np.float64))
+    m = got[1][0].cpu().numpy()
+    if w is None:
+        np.testing.assert_array_equal(m, ref.astype(np.int32))
+    else:
+        assert np.all(np.abs(m - ref) <= 1e-5 * np.maximum(np.abs(ref), w.mean()))
+    dpm.release()
