@@ -1178,19 +1178,25 @@ fh_status fh_peakmap_upload(fh_ctx *ctx, const fh_peakmap_desc *d, void *stream,
         if (vn >= 1e-2) { delete pm; return fail(FH_E_INVALID, "|v[%d]| = %g >= 1e-2", i, vn); }
         pm->v_max = std::max(pm->v_max, vn);
         pm->max_per_fft = std::max<int32_t>(pm->max_per_fft, (int32_t)(e - a));
-        for (int64_t p = a; p < e; ++p) {
-            const int32_t k = d->bins[p];
-            if (k < 0) { delete pm; return fail(FH_E_INVALID, "negative bin at peak %lld", (long long)p); }
-            if (p > a) {
-                if (k <= d->bins[p - 1]) {
-                    delete pm;
-                    return fail(FH_E_INVALID, "bins not strictly ascending in FFT %d", i);
-                }
-                if (k == d->bins[p - 1] + 1) pm->adjacent = 1;
-            }
-            pm->k_min = std::min(pm->k_min, k);
-            pm->k_max = std::max(pm->k_max, k);
+        if (e == a) continue;
+        // ascending bins: the first is the least, the last the largest
+        const int32_t *k = d->bins + a;
+        int32_t bad = 0, adjacent = 0;
+        for (int64_t p = 1; p < e - a; ++p) {
+            bad |= k[p] <= k[p - 1];
+            adjacent |= (int64_t)k[p] == (int64_t)k[p - 1] + 1;
         }
+        if (k[0] < 0) bad = 1;
+        for (int64_t p = 0; bad && p < e - a; ++p) {  // name the first bad peak
+            if (k[p] < 0) { delete pm; return fail(FH_E_INVALID, "negative bin at peak %lld", (long long)(a + p)); }
+            if (p > 0 && k[p] <= k[p - 1]) {
+                delete pm;
+                return fail(FH_E_INVALID, "bins not strictly ascending in FFT %d", i);
+            }
+        }
+        pm->adjacent |= adjacent;
+        pm->k_min = std::min(pm->k_min, k[0]);
+        pm->k_max = std::max(pm->k_max, k[e - a - 1]);
     }
     if (pm->n_peaks == 0) pm->k_min = pm->k_max = 0;
     hipStream_t st = (hipStream_t)stream;
