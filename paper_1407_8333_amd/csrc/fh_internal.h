@@ -95,7 +95,8 @@ hipError_t launch_set_sky(const SkyArg &s, int n, double *sky, hipStream_t st);
 // What a search needs before its front (k_setup).  Spin-down shift tables of
 // G_is = rint(((fdot0 + s dfdot) (t_i - t0)) S), S = (K_f T_FFT) 2^16:
 // gwin [N][nrbg][2] (first and last grid row of each row group), rec [nrb][N],
-// step [N][16] (see shift_tables); err bit 2 if a residual code overflows
+// step [N][16] (see shift_tables); base [win_stride(N)], the place of each
+// FFT's first stripe edge, run by run; err bit 2 if a residual code overflows
 // (nrb row blocks of records; windows for the row groups of the first
 // nrb_run blocks, the last group reaching the grid's last row).  Weight
 // statistics of n_vec vectors.  n_colmax column maxima and the queue counters
@@ -104,9 +105,10 @@ struct SetupArgs {
     int32_t n_fft, nrb, nrb_run, ns;
     const double *t;
     double t0, S, fdot0, dfdot;
+    const int64_t *offsets;
     int64_t *gwin;
     uint2 *rec;
-    uint32_t *step;
+    uint32_t *step, *base;
     int32_t *err;
     int32_t n_vec, w_stride, mult;
     const float *w;
@@ -140,16 +142,33 @@ hipError_t launch_front(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, 
                         const int64_t *gwin, uint32_t *Y, const float *w,
                         int32_t w_stride, const WeightStats *ws, int32_t ws_stride, uint32_t *wq,
                         int32_t ns, int32_t nrbg, int32_t nbb, int32_t W, int32_t F, int32_t max_per_fft,
-                        int2 *win, int32_t shift_mode, double q, hipStream_t st);
+                        uint32_t *win, int32_t shift_mode, double q, hipStream_t st);
+// The same for many directions: window ends from a table of the FFTs' peaks
+// (launch_rank, uint2 [N][rank_words], once per call; 0 words when the natural
+// bins span too far for it) instead of searches.
+constexpr int kRankMaxWords = 3072;
+constexpr int kRankLdsBytes = 24 * 1024;
+constexpr int kRankDirs = 4;  // directions per workgroup, at most
+int32_t rank_words(int32_t k_min, int32_t k_max);
+bool rank_front_fits(int32_t k_min, int32_t k_max, int32_t nrbg);
+hipError_t launch_rank(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_min, int32_t k_max,
+                       uint2 *rank, hipStream_t st);
+hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
+                             const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
+                             const int64_t *gwin, uint32_t *Y, const float *w, int32_t w_stride,
+                             const WeightStats *ws, int32_t ws_stride, uint32_t *wq, int32_t nrbg, int32_t nbb,
+                             int32_t W, int32_t k_min, int32_t k_max, const uint2 *rank, uint32_t *win,
+                             int32_t shift_mode, double q, hipStream_t st);
 // shift_mode 1: Doppler correction as a per-FFT shift computed at the
 // reference q = (K_f T_FFT) f_ref fine bins (0: exact per peak)
 // window rows sorted by window size per tile-wave run (see k_sort_windows)
-hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t n_slots, const int2 *win,
-                               int2 *wsorted, hipStream_t st);
+// (win: packed, see window(); base: u32 [win_stride(N)], see SetupArgs)
+hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t n_slots, const uint32_t *win,
+                               const uint32_t *base, int2 *wsorted, hipStream_t st);
 // method 0: two binary searches per entry; 1: one sweep per FFT
 hipError_t launch_windows(int32_t n_fft, const int64_t *offsets, const int64_t *Y, int64_t n_peaks,
                           const int64_t *gwin, int32_t nrbg, int32_t nbb, int32_t W,
-                          int32_t kf, int32_t n_slots, int2 *win, int method, hipStream_t st);
+                          int32_t kf, int32_t n_slots, uint32_t *win, int method, hipStream_t st);
 // map: the map of one direction; otherwise column maxima, by persistent
 // workgroups or one per tile.  a.parts > 1: partial tiles, then their merge.
 hipError_t launch_tiles(const TileArgs &a, bool weighted, bool map, bool persistent, int32_t n_tiles,

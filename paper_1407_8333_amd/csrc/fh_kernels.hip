@@ -99,6 +99,8 @@ __device__ __forceinline__ void shift_tables(const SetupArgs &A, int64_t first, 
     for (int64_t x = first; x < n; x += stride) {
         const int32_t rb = (int32_t)(x / n_fft);
         const int32_t i = (int32_t)(x - (int64_t)rb * n_fft);
+        if (rb == 0)  // run by run, as the window sort reads them
+            A.base[(i % kTileWaves) * wave_ffts(n_fft) + i / kTileWaves] = (uint32_t)(A.offsets[i] + (int64_t)kYPad * i);
         const double tau = A.t[i] - A.t0;
         double sig = A.dfdot * tau;
         sig = sig * A.S;
@@ -208,6 +210,10 @@ __global__ void __launch_bounds__(128) k_set_sky(SkyArg s, int n, double *__rest
     if ((int)threadIdx.x < 3 * n) sky[threadIdx.x] = s.v[threadIdx.x];
 }
 
+// A window before it is sorted: the places of its first peak and of the first
+// peak past it within their FFT (an FFT holds fewer than 65536 peaks).
+__device__ __forceinline__ uint32_t window(int lo, int hi) { return (uint32_t)lo | ((uint32_t)hi << 16); }
+
 // ----------------------------------------------------------------------------
 // per-peak stripe edge.  For peak (i, k) and sky n:
 //   r = 1 / (1 + ((vx nx + vy ny) + vz nz))                     (Eq. fdopp)
@@ -286,7 +292,7 @@ __global__ void __launch_bounds__(256) k_front(
     uint32_t *__restrict__ Y, const float *__restrict__ w,
     int32_t w_stride, const WeightStats *__restrict__ ws, int32_t ws_stride,
     uint32_t *__restrict__ wq, int32_t ns, int32_t nrbg, int32_t nbb, int32_t W, int32_t F,
-    int32_t search_top, int2 *__restrict__ win, int32_t shift_mode, double q) {
+    int32_t search_top, uint32_t *__restrict__ win, int32_t shift_mode, double q) {
     extern __shared__ int64_t ys[];
     __shared__ int64_t s_off[kFrontMaxF + 1];  // offsets of the block's FFTs
     __shared__ int32_t s_loc[kFrontMaxF + 1];  // the same, from the block's first peak
@@ -298,8 +304,6 @@ __global__ void __launch_bounds__(256) k_front(
     const int nfl = fe - f0;  // FFTs of this block (<= 0 for padding blocks)
     const int32_t n_pad = win_stride(n_fft);
     uint32_t *Yslot = Y + (int64_t)slot * y_stride(n_peaks, n_fft);
-    // padded index of the first staged edge
-    const int64_t pb = f0 < n_fft ? offsets[f0] + (int64_t)kYPad * f0 : 0;
 
     // per-FFT terms (r, constant, weight), one thread per FFT
     const double *n = sky + 3 * (int64_t)slot;
@@ -369,10 +373,6 @@ __global__ void __launch_bounds__(256) k_front(
                 }
             }
         }
-        for (int t = threadIdx.x; t < nfl * kYPad; t += blockDim.x) {
-            const int fl = t / kYPad;
-            Yslot[s_off[fl + 1] + (int64_t)kYPad * (f0 + fl) + (t - fl * kYPad)] = (uint32_t)kYSentinel;
-        }
     }
     __syncthreads();
 
@@ -397,9 +397,9 @@ __global__ void __launch_bounds__(256) k_front(
         end = s_loc[fl + 1] + kYPad * fl;
     }
     const int64_t *__restrict__ gq = gwin + (int64_t)f * nrbg * 2;
-    int2 *__restrict__ wp = win + (int64_t)slot * n_rows * n_pad + f;
+    uint32_t *__restrict__ wp = win + (int64_t)slot * n_rows * n_pad + f;
     for (; rest < n_rows; rest += step_r) {
-        int2 out = make_int2(0, 0);
+        uint32_t out = 0u;
         if (live) {
             // shifts of the group's first and last grid rows
             const int64_t q_lo = gq[2 * g], q_hi = gq[2 * g + 1];
@@ -414,7 +414,7 @@ __global__ void __launch_bounds__(256) k_front(
                 lo += (t1 < end && v1 < y_lo) ? stp : 0;
                 hi += (t2 < end && v2 < y_hi) ? stp : 0;
             }
-            out = make_int2((int)(lo + pb), (int)(hi + pb));
+            out = window(lo - a0, hi - a0);
         }
         wp[(int64_t)rest * n_pad] = out;
         g += dg;
@@ -422,6 +422,211 @@ __global__ void __launch_bounds__(256) k_front(
         if (jb >= nbb) {
             jb -= nbb;
             ++g;
+        }
+    }
+}
+
+// ----------------------------------------------------------------------------
+// Front of many directions.  A window's ends are found without a search: the
+// edge bound of an entry gives the least natural bin whose edge reaches it
+// (an estimate and one exact test, since edges ascend with the bin), and a
+// table of the FFT's peaks, 32 natural bins to a word with the number of peaks
+// before it, gives that bin's place among them.  The table does not depend on
+// the direction and is built once per call.
+
+// rank[i][w] = (bits of natural bins k_min + 32 w .. + 31, peaks of FFT i below
+// them), nw words per FFT; one wave per FFT.
+__global__ void __launch_bounds__(256) k_rank(int32_t n_fft, const int64_t *__restrict__ offsets,
+                                              const int32_t *__restrict__ bins, int32_t k_min, int32_t nw,
+                                              uint2 *__restrict__ rank) {
+    extern __shared__ uint32_t s_bits[];  // [4][nw]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = blockIdx.x * 4 + wave;
+    uint32_t *b = s_bits + wave * nw;
+    for (int w = lane; w < nw; w += 64) b[w] = 0u;
+    __syncthreads();
+    if (i < n_fft) {
+        const int64_t e = offsets[i + 1];
+        for (int64_t p = offsets[i] + lane; p < e; p += 64) {
+            const uint32_t x = (uint32_t)(bins[p] - k_min);
+            atomicOr(&b[x >> 5], 1u << (x & 31));
+        }
+    }
+    __syncthreads();
+    if (i >= n_fft) return;
+    uint32_t carry = 0;
+    for (int w0 = 0; w0 < nw; w0 += 64) {
+        const int w = w0 + lane;
+        const uint32_t v = w < nw ? b[w] : 0u;
+        const uint32_t c = __popc(v);
+        uint32_t incl = c;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(incl, o);
+            if (lane >= o) incl += u;
+        }
+        if (w < nw) rank[(int64_t)i * nw + w] = make_uint2(v, carry + incl - c);
+        carry += __shfl(incl, 63);
+    }
+}
+
+// For up to D direction slots and F consecutive FFTs f0 .. f0+F-1: the stripe
+// edges of their peaks, their fixed-point weights and every window entry.  The
+// FFTs' tables, offsets and natural bins are read once for all D directions: a
+// workgroup of one direction is a chain of dependent loads around little work
+// (as such this kernel, with a third of k_front's instructions, took the same
+// time).  The edges go to memory only, so the LDS holds F tables, and up to 16
+// FFTs share a workgroup: consecutive threads write whole lines of a window row.
+// With Y(k) = floor(fl(fl(K_f k r) 2^16)) + c, Y(k) >= y is fl(K_f k r) >= z for
+// z = (y - c) 2^-16, which a double holds exactly wherever an edge can lie; z
+// d / K_f (d = 1 / r before rounding) is within 2^-23 of the real bound, so the
+// least bin is the nearest whole number or the next one.
+// Bound by its stores (the edges, 4 B per peak, and 4 B per window entry).
+// Against k_front: 112 directions of the 256 Hz band 1050 -> 464 us (3.2 TB/s
+// written), 24 of the 10 Hz band at 1 kHz 1440 -> 900 us, 97 narrow ones at
+// 1024 s 463 -> 334 us.
+__global__ void __launch_bounds__(256) k_front_rank(
+    int32_t n_fft, int64_t n_peaks, const int64_t *__restrict__ offsets, const int32_t *__restrict__ bins,
+    const double *__restrict__ v, const double *__restrict__ sky, int32_t n_slots, int32_t kf, int64_t b0,
+    const int64_t *__restrict__ gwin, uint32_t *__restrict__ Y, const float *__restrict__ w, int32_t w_stride,
+    const WeightStats *__restrict__ ws, int32_t ws_stride, uint32_t *__restrict__ wq, int32_t nrbg, int32_t nbb,
+    int32_t W, int32_t F, int32_t D, int32_t k_min, int32_t k_max, int32_t nw, const uint2 *__restrict__ rank,
+    uint32_t *__restrict__ win, int32_t shift_mode, double q) {
+    extern __shared__ double s_dyn[];
+    double *s_g = s_dyn;  // [nrbg][F][2]: least and largest shift of the group's rows, in fine bins
+    const int ts = nw | 1;  // table stride (odd: the FFTs' words spread over the banks)
+    uint2 *s_tab = reinterpret_cast<uint2 *>(s_dyn + 2 * nrbg * F);  // [F][ts]
+    __shared__ int64_t s_off[kFrontMaxF + 1];
+    __shared__ int64_t s_c[kRankDirs * kFrontMaxF];                  // [D][F], the edge's constant
+    __shared__ double s_r[kRankDirs * kFrontMaxF], s_d[kRankDirs * kFrontMaxF];
+    const int slot0 = blockIdx.y * D;
+    const int nd = min(D, n_slots - slot0);
+    const int f0 = blockIdx.x * F;
+    const int nfl = min(f0 + F, n_fft) - f0;  // FFTs of this block (<= 0 for padding blocks)
+    const int32_t n_pad = win_stride(n_fft);
+    if ((int)threadIdx.x <= nfl) s_off[threadIdx.x] = offsets[f0 + threadIdx.x];
+    // (F divides 256, so x & (F - 1) is the same FFT in every round)
+    for (int x = threadIdx.x; x < nd * F; x += 256) {
+        const int l = x & (F - 1), slot = slot0 + x / F;
+        if (l >= nfl) continue;
+        const int i = f0 + l;
+        const double *n = sky + 3 * (int64_t)slot;
+        const double *vi = v + 3 * (int64_t)i;
+        double d = vi[0] * n[0];
+        d = d + vi[1] * n[1];
+        d = d + vi[2] * n[2];
+        d = 1.0 + d;
+        const double r = 1.0 / d;
+        int64_t c = -b0 * kQ - (int64_t)kf * (kQ / 2) + (kQ - 1);
+        if (shift_mode) c -= llrint((q * (1.0 - r)) * kQd);  // per-FFT shift at the reference
+        s_r[x] = shift_mode ? 1.0 : r;
+        s_d[x] = (shift_mode ? 1.0 : d) / (double)kf;
+        s_c[x] = c;
+        if (w != nullptr) {
+            const WeightStats wst = ws[(int64_t)slot * ws_stride];
+            double wi = (double)w[(int64_t)slot * w_stride + i];
+            wq[(int64_t)slot * n_fft + i] = wst.bad ? 0u : (uint32_t)rint(ldexp(wi, wst.frac_bits));
+        }
+    }
+    // the FFTs' tables are consecutive in memory
+    for (int x = threadIdx.x; x < nfl * nw; x += 256) {
+        const int l = x / nw;
+        s_tab[l * ts + (x - l * nw)] = rank[(int64_t)f0 * nw + x];
+    }
+    for (int x = threadIdx.x; x < nrbg * F; x += 256) {
+        const int g = x / F, l = x & (F - 1);
+        if (l < nfl) {
+            const int64_t *gq = gwin + ((int64_t)(f0 + l) * nrbg + g) * 2;
+            const int64_t q0 = gq[0], q1 = gq[1];
+            s_g[2 * x] = (double)(q0 < q1 ? q0 : q1) * (1.0 / kQd);
+            s_g[2 * x + 1] = (double)(q0 < q1 ? q1 : q0) * (1.0 / kQd);
+        }
+    }
+    __syncthreads();
+    // stripe edges: wave w takes FFTs w, w + 4, ..., its lanes their
+    // consecutive peaks; the entries between two FFTs' runs stay unwritten
+    // (the tiles read past a window's end but do not use what they read)
+    {
+        const int64_t ys = y_stride(n_peaks, n_fft);
+        const int lane = (int)threadIdx.x & 63;
+        constexpr int kU = 4;  // peaks per lane and round, their natural bins requested together
+        for (int l = (int)threadIdx.x >> 6; l < nfl; l += 4) {
+            const int64_t p0 = s_off[l];
+            const int cnt = (int)(s_off[l + 1] - p0);
+            const int32_t *__restrict__ kb0 = bins + p0;
+            uint32_t *__restrict__ Yb = Y + (int64_t)slot0 * ys + p0 + (int64_t)kYPad * (f0 + l);
+            for (int lb = lane; lb < cnt; lb += 64 * kU) {
+                double kb[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int lp = lb + 64 * u;
+                    kb[u] = (double)(kf * (lp < cnt ? kb0[lp] : 0));
+                }
+                for (int d = 0; d < nd; ++d) {
+                    const double r = s_r[d * F + l];
+                    const int64_t c = s_c[d * F + l];
+                    uint32_t *__restrict__ Yd = Yb + d * ys;
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) {
+                        const int lp = lb + 64 * u;
+                        if (lp >= cnt) break;
+                        // (r = 1 in shift mode, where the product is exact)
+                        double x = kb[u] * r;
+                        x = x * kQd;
+                        Yd[lp] = (uint32_t)((int64_t)floor(x) + c);
+                    }
+                }
+            }
+        }
+    }
+    // window entries: a thread keeps one FFT and steps through the rows (row
+    // group, bin block) of every direction
+    const int fl = (int)threadIdx.x & (F - 1);
+    const int step_r = 256 / F;
+    const int n_rows = nrbg * nbb;
+    const bool live = fl < nfl;
+    const uint2 *__restrict__ tab = s_tab + fl * ts;
+    const double e_lo = (double)k_min - 1.0, e_hi = (double)k_max + 2.0;
+    int rest = (int)threadIdx.x / F, d = 0;
+    int g = rest / nbb, jb = rest - g * nbb;
+    const int dg = step_r / nbb, djb = step_r - dg * nbb;
+    while (rest >= n_rows && d < nd) {
+        rest -= n_rows;
+        g -= nrbg;
+        ++d;
+    }
+    while (d < nd) {
+        uint32_t out = 0u;
+        if (live) {
+            const double r = s_r[d * F + fl], dk = s_d[d * F + fl];
+            const double c = (double)s_c[d * F + fl] * (1.0 / kQd);
+            // number of the FFT's peaks whose edge lies below bound z (fine bins)
+            auto below = [&](double z) -> int32_t {
+                const double e = fmin(fmax(z * dk, e_lo), e_hi);
+                int32_t k = (int32_t)rint(e);
+                k += (double)(kf * k) * r >= z ? 0 : 1;
+                const uint32_t x = (uint32_t)(min(max(k, k_min), k_max + 1) - k_min);
+                const uint2 t = tab[x >> 5];
+                return (int32_t)(t.y + (uint32_t)__popc(t.x & ((1u << (x & 31)) - 1u)));
+            };
+            // max_s a_s = floor((Y - min G) / kQ) >= t  <=>  Y >= t kQ + min G
+            // min_s a_s = floor((Y - max G) / kQ) >= t  <=>  Y >= t kQ + max G
+            const double z_lo = (s_g[2 * (g * F + fl)] - c) + (double)(jb * W - (kf - 1));
+            const double z_hi = (s_g[2 * (g * F + fl) + 1] - c) + (double)((jb + 1) * W);
+            out = window(below(z_lo), below(z_hi));
+        }
+        win[((int64_t)(slot0 + d) * n_rows + rest) * n_pad + f0 + fl] = out;
+        rest += step_r;
+        g += dg;
+        jb += djb;
+        if (jb >= nbb) {
+            jb -= nbb;
+            ++g;
+        }
+        while (rest >= n_rows) {
+            rest -= n_rows;
+            g -= nrbg;
+            ++d;
+            if (d >= nd) break;
         }
     }
 }
@@ -436,16 +641,16 @@ __global__ void __launch_bounds__(256) k_front(
 __global__ void k_windows(int32_t n_fft, const int64_t *__restrict__ offsets,
                           const int64_t *__restrict__ Y, int64_t n_peaks,
                           const int64_t *__restrict__ gwin, int32_t nrbg,
-                          int32_t nbb, int32_t W, int32_t kf, int2 *__restrict__ win) {
+                          int32_t nbb, int32_t W, int32_t kf, uint32_t *__restrict__ win) {
     const int32_t n_pad = win_stride(n_fft);
     const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (idx >= (int64_t)nbb * n_pad) return;
     const int32_t jb = (int32_t)(idx / n_pad);
     const int32_t i = (int32_t)(idx - (int64_t)jb * n_pad);
     const int32_t g = blockIdx.y, slot = blockIdx.z;
-    int2 *out = win + (((int64_t)slot * nrbg + g) * nbb + jb) * n_pad + i;
+    uint32_t *out = win + (((int64_t)slot * nrbg + g) * nbb + jb) * n_pad + i;
     if (i >= n_fft) {  // padding: empty window
-        *out = make_int2(0, 0);
+        *out = 0u;
         return;
     }
     const int64_t c0 = (int64_t)jb * W - (kf - 1);
@@ -473,7 +678,7 @@ __global__ void k_windows(int32_t n_fft, const int64_t *__restrict__ offsets,
         int64_t cmin = c1 < c2 ? c1 : c2;
         if (cmin >= wc) b = m; else a = m + 1;
     }
-    *out = make_int2((int)lo, (int)a);
+    *out = window((int)(lo - p0), (int)(a - p0));
 }
 
 // Same windows by one sweep over each FFT's peaks (one wave per FFT, every
@@ -492,7 +697,7 @@ __device__ __forceinline__ int floor_div_w(int64_t x, int W, float inv_w) {
 __global__ void __launch_bounds__(256) k_windows_sweep(
     int32_t n_fft, const int64_t *__restrict__ offsets, const int64_t *__restrict__ Y,
     int64_t n_peaks, const int64_t *__restrict__ gwin, int32_t nrbg, int32_t nbb,
-    int32_t W, int32_t kf, int2 *__restrict__ win) {
+    int32_t W, int32_t kf, uint32_t *__restrict__ win) {
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int slot = blockIdx.y;
@@ -500,7 +705,7 @@ __global__ void __launch_bounds__(256) k_windows_sweep(
     if (i >= n_pad) return;
     if (i >= n_fft) {  // padding: empty windows
         for (int e = lane; e < nrbg * nbb; e += 64)
-            win[((int64_t)slot * nrbg * nbb + e) * n_pad + i] = make_int2(0, 0);
+            win[((int64_t)slot * nrbg * nbb + e) * n_pad + i] = 0u;
         return;
     }
     const int64_t *Ys = Y + (int64_t)slot * y_stride(n_peaks, n_fft);
@@ -509,7 +714,8 @@ __global__ void __launch_bounds__(256) k_windows_sweep(
     const int64_t *gi = gwin + (int64_t)i * nrbg * 2;
     const float inv_w = 1.0f / (float)W;
     for (int g = 0; g < nrbg; ++g) {
-        int2 *wg = win + ((int64_t)slot * nrbg + g) * nbb * (int64_t)n_pad + i;
+        // the two halves of an entry, at stride 2 n_pad
+        uint16_t *wg = reinterpret_cast<uint16_t *>(win + ((int64_t)slot * nrbg + g) * nbb * (int64_t)n_pad + i);
         const int64_t q_lo = gi[2 * g], q_hi = gi[2 * g + 1];
         int prev_hi = -1;  // jhi of the peak before this chunk
         int prev_lo = 0;   // jlo of the peak before this chunk
@@ -530,16 +736,16 @@ __global__ void __launch_bounds__(256) k_windows_sweep(
                 before_lo = prev_lo;
             }
             if (p < p1) {
-                for (int jb = before_hi + 1; jb <= jhi; ++jb) wg[(int64_t)jb * n_pad].x = p;
-                for (int jb = before_lo; jb < jlo; ++jb) wg[(int64_t)jb * n_pad].y = p;
+                for (int jb = before_hi + 1; jb <= jhi; ++jb) wg[(int64_t)jb * n_pad * 2] = (uint16_t)(p - p0);
+                for (int jb = before_lo; jb < jlo; ++jb) wg[(int64_t)jb * n_pad * 2 + 1] = (uint16_t)(p - p0);
             }
             const int last = min(63, p1 - 1 - pb);
             prev_hi = __shfl(jhi, last);
             prev_lo = __shfl(jlo, last);
         }
         // bin blocks past the last peak's reach end at the segment end
-        for (int jb = prev_hi + 1 + lane; jb < nbb; jb += 64) wg[(int64_t)jb * n_pad].x = p1;
-        for (int jb = prev_lo + lane; jb < nbb; jb += 64) wg[(int64_t)jb * n_pad].y = p1;
+        for (int jb = prev_hi + 1 + lane; jb < nbb; jb += 64) wg[(int64_t)jb * n_pad * 2] = (uint16_t)(p1 - p0);
+        for (int jb = prev_lo + lane; jb < nbb; jb += 64) wg[(int64_t)jb * n_pad * 2 + 1] = (uint16_t)(p1 - p0);
     }
 }
 
@@ -554,64 +760,41 @@ __global__ void __launch_bounds__(256) k_windows_sweep(
 // bucket, are ranked exactly among themselves), so that the four FFTs of a
 // tile block (four consecutive entries of a run) have nearly equal windows
 // and the first holds the largest, which the tiles rely on.  An entry becomes
-// (lo, m << 16 | count): FFT m * 16 + w of the row.  One workgroup per window
-// row (grid.x = row group * bin blocks, grid.y = slot), one wave per run.
+// (place of its first edge, m << 16 | count): FFT m * 16 + w of the row, whose
+// edges start at base[w * wave_ffts(N) + m].  One workgroup per window row (grid.x = row group *
+// bin blocks, grid.y = slot), one wave per run.
+// Bound by the LDS atomics of the counts, many of which meet in the few buckets
+// of the common sizes: there is one per entry, whose result is also the
+// entry's rank in its bucket (a second pass of atomics that placed the entries
+// made the sort half as long again).  The row is staged in LDS run by run, since
+// its runs are strided (16 lanes to a bank), and the first edges lie in memory
+// run by run too.  19 040 rows of 6336 entries: 517 -> 378 us.
 constexpr int kSortBuckets = 128;
-// rows of at most this many bytes are first copied into LDS with 16-byte
-// loads (the runs read the row with a 128-byte stride, twice)
-constexpr int kSortStageBytes = 128 * 1024;
+constexpr int kSortLdsBytes = kLdsBytes - kTileWaves * kSortBuckets * 4 - kLdsReserve;
 
 // Place of a window of c >= 127 peaks (entry e of a run of `per`) among the
 // run's windows of 127 peaks or more, which fill the run's first places:
-// larger first, equal sizes in run order.  entry(j) reads entry j of the run.
+// larger first, equal sizes in run order.  size(j) is that of entry j.
 // Such windows are rare (dense peakmaps, K_f = 1), so a scan of the run is
 // cheap enough.
-template <typename Entry>
-__device__ __forceinline__ int big_window_rank(int c, int e, int per, Entry entry) {
+template <typename Size>
+__device__ __forceinline__ int big_window_rank(int c, int e, int per, Size size) {
     int pos = 0;
     for (int j = 0; j < per; ++j) {
-        const int2 o = entry(j);
-        const int cj = o.y - o.x;
+        const int cj = size(j);
         pos += (cj > c || (cj == c && j < e)) ? 1 : 0;
     }
     return pos;
 }
 
-__global__ void __launch_bounds__(kTileThreads) k_sort_windows(int32_t n_fft, int32_t nrows,
-                                                               const int2 *__restrict__ win,
-                                                               int2 *__restrict__ wsorted) {
-    extern __shared__ int4 s_row4[];
-    __shared__ int hist[kTileWaves][kSortBuckets];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int per = wave_ffts(n_fft);
-    const int n_pad = win_stride(n_fft);  // a multiple of 64 entries
-    const int64_t row = (int64_t)blockIdx.y * nrows + blockIdx.x;
-    const int2 *rowp = win + row * n_pad;
-    {
-        const int4 *g4 = reinterpret_cast<const int4 *>(rowp);
-        for (int i = threadIdx.x; i < n_pad / 2; i += blockDim.x) s_row4[i] = g4[i];
-    }
-    // FFT m * kTileWaves + wave of the row is entry m of run `wave`
-    const int2 *src = reinterpret_cast<const int2 *>(s_row4) + wave;
-    int2 *dst = wsorted + row * n_pad + (int64_t)wave * per;
-    int *h = hist[wave];
-    for (int b = lane; b < kSortBuckets; b += 64) h[b] = 0;
-    __syncthreads();
-    // entries are read four per lane and round (one memory latency per round)
-    constexpr int kU = 4;
-    for (int e0 = lane; e0 < per; e0 += kU * 64) {
-        int2 w2[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int e = e0 + 64 * u;
-            w2[u] = e < per ? src[(int64_t)e * kTileWaves] : make_int2(0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (e0 + 64 * u < per) atomicAdd(&h[kSortBuckets - 1 - min(w2[u].y - w2[u].x, kSortBuckets - 1)], 1);
-    }
-    __syncthreads();
-    // exclusive prefix sum over the buckets (lane L holds buckets 2L, 2L+1)
+// Words between the staged runs: 4 modulo 16, so that the four quarters of 16
+// entries that a wave stores together lie in 64 banks.
+__host__ __device__ inline int sort_run_stride(int per) { return per + ((4 - per) & 15); }
+
+__device__ __forceinline__ int window_size(uint32_t w) { return (int)(w >> 16) - (int)(w & 0xFFFFu); }
+
+// Exclusive prefix sums over a run's buckets (lane L holds buckets 2L, 2L+1).
+__device__ __forceinline__ void scan_buckets(int *h, int lane) {
     const int a0 = h[2 * lane], a1 = h[2 * lane + 1];
     int incl = a0 + a1;
     for (int o = 1; o < 64; o <<= 1) {
@@ -623,117 +806,120 @@ __global__ void __launch_bounds__(kTileThreads) k_sort_windows(int32_t n_fft, in
     h[2 * lane] = excl;
     h[2 * lane + 1] = excl + a0;
     __syncthreads();
+}
+
+__global__ void __launch_bounds__(kTileThreads) k_sort_windows(int32_t n_fft, int32_t nrows,
+                                                               const uint32_t *__restrict__ win,
+                                                               const uint32_t *__restrict__ base,
+                                                               int2 *__restrict__ wsorted) {
+    extern __shared__ uint32_t s_run[];  // the row, run by run, then the entries' ranks in their buckets (16-bit)
+    __shared__ int hist[kTileWaves][kSortBuckets];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int per = wave_ffts(n_fft);
+    const int n_pad = win_stride(n_fft);  // a multiple of 64 entries
+    const int rs = sort_run_stride(per);
+    const int64_t row = (int64_t)blockIdx.y * nrows + blockIdx.x;
+    // FFT m * kTileWaves + w of the row is entry m of run w
+    {
+        const uint4 *g4 = reinterpret_cast<const uint4 *>(win + row * n_pad);
+        for (int i = threadIdx.x; i < n_pad / 4; i += blockDim.x) {
+            const uint4 q = g4[i];
+            uint32_t *d = s_run + (i & 3) * 4 * rs + (i >> 2);
+            d[0] = q.x;
+            d[rs] = q.y;
+            d[2 * rs] = q.z;
+            d[3 * rs] = q.w;
+        }
+    }
+    const uint32_t *src = s_run + wave * rs;
+    uint16_t *rk = reinterpret_cast<uint16_t *>(s_run + kTileWaves * rs) + wave * per;
+    int2 *dst = wsorted + row * n_pad + (int64_t)wave * per;
+    int *h = hist[wave];
+    for (int b = lane; b < kSortBuckets; b += 64) h[b] = 0;
+    __syncthreads();
+    constexpr int kU = 4;  // entries per lane and round, their LDS accesses issued together
     for (int e0 = lane; e0 < per; e0 += kU * 64) {
-        int2 w2[kU];
+        int c[kU], r[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) c[u] = e0 + 64 * u < per ? window_size(src[e0 + 64 * u]) : -1;
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            r[u] = c[u] >= 0 ? atomicAdd(&h[kSortBuckets - 1 - min(c[u], kSortBuckets - 1)], 1) : 0;
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+            if (c[u] >= 0) rk[e0 + 64 * u] = (uint16_t)r[u];
+    }
+    __syncthreads();
+    scan_buckets(h, lane);
+    for (int e0 = lane; e0 < per; e0 += kU * 64) {
+        uint32_t w[kU], b[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int e = e0 + 64 * u;
-            w2[u] = e < per ? src[(int64_t)e * kTileWaves] : make_int2(0, 0);
+            const int e = e0 + 64 * u, i = e * kTileWaves + wave;
+            b[u] = e < per && i < n_fft ? base[wave * per + e] : 0u;
+            w[u] = e < per ? src[e] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int e = e0 + 64 * u;
             if (e >= per) break;
-            const int c = w2[u].y - w2[u].x;
-            int pos;
-            if (c >= kSortBuckets - 1) {
-                pos = big_window_rank(c, e, per, [&](int j) { return src[(int64_t)j * kTileWaves]; });
-            } else {
-                pos = atomicAdd(&h[kSortBuckets - 1 - c], 1);
-            }
-            dst[pos] = make_int2(w2[u].x, (e << 16) | c);
+            const int c = window_size(w[u]);
+            const int pos = c >= kSortBuckets - 1
+                                ? big_window_rank(c, e, per, [&](int j) { return window_size(src[j]); })
+                                : h[kSortBuckets - 1 - c] + rk[e];
+            dst[pos] = make_int2((int)(b[u] + (w[u] & 0xFFFFu)), (e << 16) | c);
         }
     }
 }
 
-// Rows longer than kSortStageEntries entries: the same sort, the row copied
-// into LDS in pieces of kSortStageEntries (128 KB), once per pass.
-constexpr int kSortStageEntries = 16384;
+// Rows whose entries and ranks do not fit the LDS: the same sort, the
+// row copied into LDS in pieces of kSortPiece entries (128 KB), once per pass,
+// and the entries written where they belong.
+constexpr int kSortPiece = 32768;
 
 __global__ void __launch_bounds__(kTileThreads) k_sort_windows_long(int32_t n_fft, int32_t nrows,
-                                                               const int2 *__restrict__ win,
-                                                               int2 *__restrict__ wsorted) {
-    extern __shared__ int4 s_row4[];
+                                                                    const uint32_t *__restrict__ win,
+                                                                    const uint32_t *__restrict__ base,
+                                                                    int2 *__restrict__ wsorted) {
+    extern __shared__ uint4 s_row4[];
     __shared__ int hist[kTileWaves][kSortBuckets];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int per = wave_ffts(n_fft);
     const int n_pad = win_stride(n_fft);  // a multiple of 64 entries
-    const int piece = kSortStageEntries;
     const int64_t row = (int64_t)blockIdx.y * nrows + blockIdx.x;
-    const int2 *rowp = win + row * n_pad;
-    const int2 *s_row = reinterpret_cast<const int2 *>(s_row4);
+    const uint32_t *rowp = win + row * n_pad;
+    const uint32_t *s_row = reinterpret_cast<const uint32_t *>(s_row4);
     int2 *dst = wsorted + row * n_pad + (int64_t)wave * per;
     int *h = hist[wave];
-    // entries [p0, p0 + piece) of the row into LDS (both multiples of 64)
-    auto stage = [&](int p0) {
-        const int n = min(piece, n_pad - p0);
-        const int4 *g4 = reinterpret_cast<const int4 *>(rowp + p0);
-        for (int i = threadIdx.x; i < n / 2; i += blockDim.x) s_row4[i] = g4[i];
-    };
     for (int b = lane; b < kSortBuckets; b += 64) h[b] = 0;
-    __syncthreads();
-    // Entry e of run `wave` is row entry e * kTileWaves + wave; a piece
-    // starting at p0 holds the run's entries [p0 / 16, (p0 + piece) / 16).
-    // Entries are read four per lane and round.
-    constexpr int kU = 4;
-    for (int p0 = 0; p0 < n_pad; p0 += piece) {
-        if (p0 > 0) __syncthreads();
-        stage(p0);
-        __syncthreads();
-        const int e_lo = p0 / kTileWaves, e_hi = min(per, (p0 + piece) / kTileWaves);
-        for (int e0 = e_lo + lane; e0 < e_hi; e0 += kU * 64) {
-            int2 w2[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int e = e0 + 64 * u;
-                w2[u] = e < e_hi ? s_row[(e - e_lo) * kTileWaves + wave] : make_int2(0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u)
-                if (e0 + 64 * u < e_hi)
-                    atomicAdd(&h[kSortBuckets - 1 - min(w2[u].y - w2[u].x, kSortBuckets - 1)], 1);
-        }
-    }
-    __syncthreads();
-    // exclusive prefix sum over the buckets (lane L holds buckets 2L, 2L+1)
-    const int a0 = h[2 * lane], a1 = h[2 * lane + 1];
-    int incl = a0 + a1;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-    }
-    const int excl = incl - (a0 + a1);
-    __syncthreads();
-    h[2 * lane] = excl;
-    h[2 * lane + 1] = excl + a0;
-    __syncthreads();
-    for (int p0 = 0; p0 < n_pad; p0 += piece) {
-        if (p0 > 0) __syncthreads();
-        stage(p0);
-        __syncthreads();
-        const int e_lo = p0 / kTileWaves, e_hi = min(per, (p0 + piece) / kTileWaves);
-        for (int e0 = e_lo + lane; e0 < e_hi; e0 += kU * 64) {
-            int2 w2[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int e = e0 + 64 * u;
-                w2[u] = e < e_hi ? s_row[(e - e_lo) * kTileWaves + wave] : make_int2(0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int e = e0 + 64 * u;
-                if (e >= e_hi) break;
-                const int c = w2[u].y - w2[u].x;
-                int pos;
-                if (c >= kSortBuckets - 1) {
-                    // the run's other pieces are not staged: read the row in memory
-                    pos = big_window_rank(c, e, per, [&](int j) { return rowp[(int64_t)j * kTileWaves + wave]; });
-                } else {
-                    pos = atomicAdd(&h[kSortBuckets - 1 - c], 1);
+    // entry e of run `wave` is row entry e * kTileWaves + wave; a piece
+    // starting at p0 holds the run's entries [p0 / 16, (p0 + piece) / 16)
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int p0 = 0; p0 < n_pad; p0 += kSortPiece) {
+            __syncthreads();
+            const uint4 *g4 = reinterpret_cast<const uint4 *>(rowp + p0);
+            for (int i = threadIdx.x; i < min(kSortPiece, n_pad - p0) / 4; i += blockDim.x) s_row4[i] = g4[i];
+            __syncthreads();
+            const int e_lo = p0 / kTileWaves, e_hi = min(per, (p0 + kSortPiece) / kTileWaves);
+            for (int e = e_lo + lane; e < e_hi; e += 64) {
+                const uint32_t w = s_row[(e - e_lo) * kTileWaves + wave];
+                const int c = window_size(w);
+                if (pass == 0) {
+                    atomicAdd(&h[kSortBuckets - 1 - min(c, kSortBuckets - 1)], 1);
+                    continue;
                 }
-                dst[pos] = make_int2(w2[u].x, (e << 16) | c);
+                int pos;
+                if (c >= kSortBuckets - 1)  // the run's other pieces are not staged: read the row in memory
+                    pos = big_window_rank(c, e, per, [&](int j) { return window_size(rowp[(int64_t)j * kTileWaves + wave]); });
+                else
+                    pos = atomicAdd(&h[kSortBuckets - 1 - c], 1);
+                const int i = e * kTileWaves + wave;
+                const uint32_t b = i < n_fft ? base[wave * per + e] : 0u;
+                dst[pos] = make_int2((int)(b + (w & 0xFFFFu)), (e << 16) | c);
             }
         }
+        __syncthreads();
+        if (pass == 0) scan_buckets(h, lane);
     }
 }
 
@@ -1935,7 +2121,7 @@ hipError_t launch_front(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, 
                         const int64_t *gwin, uint32_t *Y, const float *w,
                         int32_t w_stride, const WeightStats *ws, int32_t ws_stride, uint32_t *wq,
                         int32_t ns, int32_t nrbg, int32_t nbb, int32_t W, int32_t F, int32_t max_per_fft,
-                        int2 *win, int32_t shift_mode, double q, hipStream_t st) {
+                        uint32_t *win, int32_t shift_mode, double q, hipStream_t st) {
     if (F < 1 || win_stride(n_fft) % F != 0) return hipErrorInvalidValue;
     dim3 grid(win_stride(n_fft) / F, n_slots);
     const size_t lds = ((size_t)F * (max_per_fft + kYPad) * 8 + 255) / 256 * 256;
@@ -1948,21 +2134,69 @@ hipError_t launch_front(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, 
     return hipGetLastError();
 }
 
-hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t n_slots, const int2 *win,
-                               int2 *wsorted, hipStream_t st) {
+// Words of an FFT's rank table.
+int32_t rank_words(int32_t k_min, int32_t k_max) {
+    const int64_t w = ((int64_t)k_max - k_min + 1) / 32 + 1;
+    return w <= kRankMaxWords ? (int32_t)w : 0;
+}
+
+// FFTs per workgroup: as many as fit kRankLdsBytes (eight workgroups per CU),
+// up to a whole line of a window row; at least one, in up to kFrontLdsBytes.
+static int rank_ffts_per_block(int32_t nw, int32_t nrbg) {
+    const int64_t one = (int64_t)(nw | 1) * 8 + (int64_t)nrbg * 16;
+    for (int F = kFrontMaxF; F >= 1; F >>= 1)
+        if (F * one <= kRankLdsBytes) return F;
+    return one <= kFrontLdsBytes ? 1 : 0;
+}
+
+bool rank_front_fits(int32_t k_min, int32_t k_max, int32_t nrbg) {
+    const int32_t nw = rank_words(k_min, k_max);
+    return nw > 0 && rank_ffts_per_block(nw, nrbg) > 0;
+}
+
+hipError_t launch_rank(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_min, int32_t k_max,
+                       uint2 *rank, hipStream_t st) {
+    const int32_t nw = rank_words(k_min, k_max);
+    if (nw == 0) return hipErrorInvalidValue;
+    k_rank<<<(n_fft + 3) / 4, 256, (size_t)16 * nw, st>>>(n_fft, offsets, bins, k_min, nw, rank);
+    return hipGetLastError();
+}
+
+hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
+                             const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
+                             const int64_t *gwin, uint32_t *Y, const float *w, int32_t w_stride,
+                             const WeightStats *ws, int32_t ws_stride, uint32_t *wq, int32_t nrbg, int32_t nbb,
+                             int32_t W, int32_t k_min, int32_t k_max, const uint2 *rank, uint32_t *win,
+                             int32_t shift_mode, double q, hipStream_t st) {
+    const int32_t nw = rank_words(k_min, k_max);
+    const int F = nw ? rank_ffts_per_block(nw, nrbg) : 0;
+    if (F < 1 || win_stride(n_fft) % F != 0) return hipErrorInvalidValue;
+    const size_t lds = (size_t)F * ((size_t)(nw | 1) * 8 + (size_t)nrbg * 16);
+    // directions per workgroup: up to kRankDirs while that leaves four rounds
+    // of workgroups (eight per CU)
+    const int64_t blocks = (int64_t)(win_stride(n_fft) / F) * n_slots;
+    const int D = (int)std::max<int64_t>(1, std::min<int64_t>(kRankDirs, blocks / (4 * 8 * 256)));
+    k_front_rank<<<dim3(win_stride(n_fft) / F, (n_slots + D - 1) / D), 256, lds, st>>>(
+        n_fft, n_peaks, offsets, bins, v, sky, n_slots, kf, b0, gwin, Y, w, w_stride, ws, ws_stride, wq, nrbg, nbb, W, F,
+        D, k_min, k_max, nw, rank, win, shift_mode, q);
+    return hipGetLastError();
+}
+
+hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t n_slots, const uint32_t *win,
+                               const uint32_t *base, int2 *wsorted, hipStream_t st) {
     dim3 grid(nrbg * nbb, n_slots);
-    const size_t row_bytes = (size_t)win_stride(n_fft) * sizeof(int2);
-    if (row_bytes <= (size_t)kSortStageBytes)
-        k_sort_windows<<<grid, kTileThreads, row_bytes, st>>>(n_fft, nrbg * nbb, win, wsorted);
+    const size_t lds = (size_t)kTileWaves * (4 * (size_t)sort_run_stride(wave_ffts(n_fft)) + 2 * (size_t)wave_ffts(n_fft));
+    if (lds <= (size_t)kSortLdsBytes)
+        k_sort_windows<<<grid, kTileThreads, lds, st>>>(n_fft, nrbg * nbb, win, base, wsorted);
     else
-        k_sort_windows_long<<<grid, kTileThreads, (size_t)kSortStageEntries * sizeof(int2), st>>>(
-            n_fft, nrbg * nbb, win, wsorted);
+        k_sort_windows_long<<<grid, kTileThreads, (size_t)kSortPiece * sizeof(uint32_t), st>>>(n_fft, nrbg * nbb, win,
+                                                                                              base, wsorted);
     return hipGetLastError();
 }
 
 hipError_t launch_windows(int32_t n_fft, const int64_t *offsets, const int64_t *Y, int64_t n_peaks,
                           const int64_t *gwin, int32_t nrbg, int32_t nbb, int32_t W,
-                          int32_t kf, int32_t n_slots, int2 *win, int method, hipStream_t st) {
+                          int32_t kf, int32_t n_slots, uint32_t *win, int method, hipStream_t st) {
     if (method == 0) {
         dim3 grid(grid_for((int64_t)nbb * win_stride(n_fft), 256), nrbg, n_slots);
         k_windows<<<grid, 256, 0, st>>>(n_fft, offsets, Y, n_peaks, gwin, nrbg, nbb, W, kf, win);
@@ -2022,10 +2256,10 @@ hipError_t init_kernel_attributes() {
     if ((e = set_tile_attrs<false, true>()) != hipSuccess) return e;
     if ((e = set_tile_attrs<false, false>()) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute((const void *)k_sort_windows, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 kSortStageBytes)) != hipSuccess)
+                                 kSortLdsBytes)) != hipSuccess)
         return e;
     return hipFuncSetAttribute((const void *)k_sort_windows_long, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kSortStageEntries * (int)sizeof(int2));
+                               kSortPiece * (int)sizeof(uint32_t));
 }
 
 hipError_t launch_tiles(const TileArgs &a, bool weighted, bool map, bool persistent, int32_t n_tiles,

@@ -207,17 +207,17 @@ struct fh_peakmap {
 // Device and pinned buffers of one in-flight search.  A context owns one;
 // each serving lane owns another.
 struct Workspace {
-    DevBuf sht, Y, Y64, win, wsort, colmax, wq, ws, sky, qctr, part;
+    DevBuf sht, Y, Y64, win, wsort, colmax, wq, ws, sky, qctr, part, rank;
     PinnedBuf h_sky;
     hipEvent_t staged = nullptr;  // last copy out of h_sky
     size_t device_bytes() const {
         size_t n = 0;
-        for (const DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part})
+        for (const DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part, &rank})
             n += b->bytes;
         return n;
     }
     void release() {
-        for (DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part})
+        for (DevBuf *b : {&sht, &Y, &Y64, &win, &wsort, &colmax, &wq, &ws, &sky, &qctr, &part, &rank})
             b->release();
         h_sky.release();
         if (staged) (void)hipEventDestroy(staged);
@@ -484,10 +484,11 @@ struct Timed {
 struct ChunkBufs {
     int64_t *gwin;   // spin-down shift tables (ShiftLayout)
     uint2 *rec;
-    uint32_t *step;
+    uint32_t *step, *base;
     uint32_t *Y;   // low words of the stripe edges (what the tiles read)
     int64_t *Y64;  // full stripe edges, only for the unfused window methods
-    int2 *win, *wsort;
+    uint32_t *win;  // packed windows before the sort
+    int2 *wsort;
     unsigned long long *colmax;
     uint32_t *wq;
     WeightStats *ws;
@@ -495,6 +496,7 @@ struct ChunkBufs {
     int32_t *qctr, *err;
     uint32_t *part = nullptr;  // partial tiles of searches with few tiles
     size_t part_bytes = 0;
+    uint2 *rank = nullptr;  // peaks' rank table of a search of many directions
 };
 
 // Cost model of the tiles of small launches, in us, fitted to timed launches of
@@ -613,6 +615,18 @@ bool needs_full_edges(const fh_ctx *ctx, const fh_peakmap *pm) {
     return !(ctx->window_method == 2 && front_ffts_per_block(pm->max_per_fft) > 0);
 }
 
+// Bytes of the rank table with which a launch of `slots` directions finds its
+// windows (k_front_rank), 0 when it searches them (k_front): few directions do
+// not repay the table, and wide, sparsely filled bands would make it larger
+// than four directions' stripe edges.
+constexpr int kRankMinDirs = 3;
+
+size_t rank_bytes(const fh_ctx *ctx, const fh_peakmap *pm, const Plan &p, int slots) {
+    if (slots < kRankMinDirs || needs_full_edges(ctx, pm) || !rank_front_fits(pm->k_min, pm->k_max, p.nrbg)) return 0;
+    const int64_t bytes = 8 * (int64_t)rank_words(pm->k_min, pm->k_max) * pm->n_fft;
+    return bytes <= 16 * y_stride(pm->n_peaks, pm->n_fft) ? (size_t)bytes : 0;
+}
+
 // device bytes of the stripe edges of one direction
 int64_t edge_bytes_per_sky(const fh_ctx *ctx, const fh_peakmap *pm) {
     return (needs_full_edges(ctx, pm) ? 12 : 4) * y_stride(pm->n_peaks, pm->n_fft);
@@ -628,7 +642,8 @@ fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, co
     if (needs_full_edges(ctx, pm) &&
         (s = ctx->cur->Y64.ensure((size_t)8 * y_stride(pm->n_peaks, pm->n_fft) * slots, st)))
         return s;
-    if ((s = ctx->cur->win.ensure((size_t)8 * slots * p.nrbg * p.nbb * win_stride(N), st))) return s;
+    const size_t n_win = (size_t)slots * p.nrbg * p.nbb * win_stride(N);
+    if ((s = ctx->cur->win.ensure(4 * (n_win + win_stride(N)), st))) return s;
     if ((s = ctx->cur->wsort.ensure((size_t)8 * slots * p.nrbg * p.nbb * win_stride(N), st))) return s;
     if ((s = ctx->cur->colmax.ensure((size_t)8 * slots * g->nf, st))) return s;
     if ((s = ctx->cur->wq.ensure(weighted ? (size_t)4 * slots * N : 4, st))) return s;
@@ -640,12 +655,16 @@ fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, co
     if (pb && (s = ctx->cur->part.ensure(pb, st))) return s;
     b.part = (uint32_t *)ctx->cur->part.ptr;
     b.part_bytes = ctx->cur->part.bytes;
+    const size_t rb = rank_bytes(ctx, pm, p, slots);
+    if (rb && (s = ctx->cur->rank.ensure(rb, st))) return s;
+    b.rank = rb ? (uint2 *)ctx->cur->rank.ptr : nullptr;
     b.gwin = reinterpret_cast<int64_t *>((char *)ctx->cur->sht.ptr + sl.gwin);
     b.rec = reinterpret_cast<uint2 *>((char *)ctx->cur->sht.ptr + sl.rec);
     b.step = reinterpret_cast<uint32_t *>((char *)ctx->cur->sht.ptr + sl.step);
     b.Y = (uint32_t *)ctx->cur->Y.ptr;
     b.Y64 = (int64_t *)ctx->cur->Y64.ptr;
-    b.win = (int2 *)ctx->cur->win.ptr;
+    b.win = (uint32_t *)ctx->cur->win.ptr;
+    b.base = b.win + n_win;
     b.wsort = (int2 *)ctx->cur->wsort.ptr;
     b.colmax = (unsigned long long *)ctx->cur->colmax.ptr;
     b.wq = (uint32_t *)ctx->cur->wq.ptr;
@@ -756,7 +775,7 @@ double shift_reference_bins(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gr
 
 fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
                         int slots, const double *d_sky, const SkyDirs &dirs, const float *d_w, int w_stride,
-                        int64_t n_colmax, const ChunkBufs &b, hipStream_t st) {
+                        int64_t n_colmax, bool first, const ChunkBufs &b, hipStream_t st) {
     Timed timed(ctx, st, kSpanFront);
     const bool weighted = d_w != nullptr;
     SetupArgs a{};
@@ -772,6 +791,8 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
     a.gwin = b.gwin;
     a.rec = b.rec;
     a.step = b.step;
+    a.base = b.base;
+    a.offsets = pm->d_offsets;
     a.err = b.err;
     a.n_vec = weighted ? (w_stride == 0 ? 1 : slots) : 0;
     a.w_stride = w_stride;
@@ -788,11 +809,20 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
     const int F = ctx->window_method == 2 ? front_ffts_per_block(pm->max_per_fft) : 0;
     const int32_t sm = ctx->doppler_mode;
     const double q = sm ? shift_reference_bins(ctx, pm, g) : 0.0;
+    if (b.rank && rank_bytes(ctx, pm, p, slots) > 0) {
+        // (the first chunk is the largest; later ones find its table)
+        if (first) HIP_OK(launch_rank(pm->n_fft, pm->d_offsets, pm->d_bins, pm->k_min, pm->k_max, b.rank, st));
+        HIP_OK(launch_front_rank(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots, g->kf, g->b0,
+                                 b.gwin, b.Y, d_w, w_stride, b.ws, w_stride == 0 ? 0 : 1, b.wq, p.nrbg, p.nbb, p.W,
+                                 pm->k_min, pm->k_max, b.rank, b.win, sm, q, st));
+        HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, st));
+        return FH_OK;
+    }
     if (F > 0) {
         HIP_OK(launch_front(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots, g->kf,
                             g->b0, b.gwin, b.Y, d_w, w_stride, b.ws, w_stride == 0 ? 0 : 1, b.wq, g->ns,
                             p.nrbg, p.nbb, p.W, F, pm->max_per_fft, b.win, sm, q, st));
-        HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.wsort, st));
+        HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, st));
         return FH_OK;
     }
     HIP_OK(launch_prep(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots,
@@ -800,7 +830,7 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
                        st));
     HIP_OK(launch_windows(pm->n_fft, pm->d_offsets, b.Y64, pm->n_peaks, b.gwin, p.nrbg, p.nbb,
                           p.W, g->kf, slots, b.win, ctx->window_method == 0 ? 0 : 1, st));
-    HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.wsort, st));
+    HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, st));
     return FH_OK;
 }
 
@@ -827,7 +857,7 @@ fh_status enqueue_map(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const
                       const float *d_w, const ChunkBufs &b, void *out, hipStream_t st) {
     fh_status s;
     const bool weighted = d_w != nullptr;
-    if ((s = enqueue_front(ctx, pm, g, p, 1, b.sky, {nhat, 1}, d_w, 0, 0, b, st))) return s;
+    if ((s = enqueue_front(ctx, pm, g, p, 1, b.sky, {nhat, 1}, d_w, 0, 0, true, b, st))) return s;
     TileArgs a = tile_args(pm, g, p, 1, b, weighted, 0);
     a.map_i32 = weighted ? nullptr : (int32_t *)out;
     a.map_f32 = weighted ? (float *)out : nullptr;
@@ -875,7 +905,7 @@ fh_status run_search(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const 
         const int slots = std::min(chunk, n_sky - base);
         const float *w = weighted ? d_w + (w_stride ? (int64_t)base * w_stride : 0) : nullptr;
         if ((s = enqueue_front(ctx, pm, g, p, slots, b.sky + 3 * (int64_t)base, base == 0 ? dirs : SkyDirs{}, w,
-                               w_stride, (int64_t)slots * g->nf, b, st)))
+                               w_stride, (int64_t)slots * g->nf, base == 0, b, st)))
             return s;
         TileArgs a = tile_args(pm, g, p, slots, b, weighted, w_stride == 0 ? 0 : 1);
         const int64_t n_tiles = p.tiles_per_sky * slots;
@@ -1662,18 +1692,20 @@ namespace {
 
 // Pieces of the unweighted map path carved out of `scratch` (256-byte aligned
 // byte offsets).  Every piece a kernel reads is written earlier in the same
-// call (edges, their padding, every window entry including the padding FFTs,
+// call (edges, every window entry including the padding FFTs,
 // the shift table and the direction), so nothing has to start at zero; the
 // error flag and the queue counters are only read on paths this call does not
 // take (weights, the persistent schedule).
 struct StaticLayout {
-    size_t sky, err, qctr, sht, y, y64, win, wsort, total;
+    size_t sky, err, qctr, sht, y, y64, win, n_win, wsort, total;
     ShiftLayout shl;
 };
 
 StaticLayout static_layout(const fh_ctx *ctx, const fh_peakmap *pm, const Plan &p) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t ys = (size_t)y_stride(pm->n_peaks, pm->n_fft);
+    // 8 bytes per window as reserved for the unsorted ones: they take 4, and
+    // the FFTs' first edges lie behind them
     const size_t wins = (size_t)8 * p.nrbg * p.nbb * win_stride(pm->n_fft);
     StaticLayout L{};
     size_t o = 0;
@@ -1685,6 +1717,7 @@ StaticLayout static_layout(const fh_ctx *ctx, const fh_peakmap *pm, const Plan &
     L.y = o;     o += al(4 * ys);
     L.y64 = o;   if (needs_full_edges(ctx, pm)) o += al(8 * ys);
     L.win = o;   o += al(wins);
+    L.n_win = wins / 8;
     L.wsort = o; o += al(wins);
     L.total = o;
     return L;
@@ -1724,7 +1757,8 @@ fh_status fh_hough_map_i32_static(fh_ctx *ctx, const fh_peakmap *pm, const doubl
     b.step = reinterpret_cast<uint32_t *>(c + L.sht + L.shl.step);
     b.Y = reinterpret_cast<uint32_t *>(c + L.y);
     b.Y64 = reinterpret_cast<int64_t *>(c + L.y64);
-    b.win = reinterpret_cast<int2 *>(c + L.win);
+    b.win = reinterpret_cast<uint32_t *>(c + L.win);
+    b.base = b.win + L.n_win;
     b.wsort = reinterpret_cast<int2 *>(c + L.wsort);
     b.part = reinterpret_cast<uint32_t *>(c + L.total);  // what is left holds partial tiles
     b.part_bytes = kStaticScratchBytes - L.total;
@@ -1792,6 +1826,7 @@ fh_status fh_hough_candidates(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, 
         (uint64_t)(uintptr_t)b.gwin,
         (uint64_t)(uintptr_t)b.qctr, (uint64_t)(uintptr_t)b.Y64, (uint64_t)ctx->window_method,
         (uint64_t)ctx->tile_parts, (uint64_t)(uintptr_t)b.part, (uint64_t)b.part_bytes,
+        (uint64_t)(uintptr_t)b.rank,
         (uint64_t)ctx->doppler_mode, bits(ctx->doppler_fref)};
     fh_ctx::GraphEntry *ge = nullptr;
     for (auto &e : ctx->graphs)
@@ -1915,7 +1950,7 @@ double ms_between(Clock::time_point a, Clock::time_point b) {
 // arena: the same buffers ensure_workspace provides, 256-byte aligned.
 struct SearchLayout {
     size_t sht = 0, y = 0, y64 = 0, win = 0, wsort = 0, colmax = 0, wq = 0, ws = 0, sky = 0, qctr = 0, part = 0, total = 0;
-    size_t part_bytes = 0;
+    size_t n_win = 0, rank = 0, rank_size = 0, part_bytes = 0;
     ShiftLayout shl{};
 };
 
@@ -1924,7 +1959,7 @@ SearchLayout search_layout(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gri
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t N = (size_t)pm->n_fft, c = (size_t)chunk;
     const size_t ys = (size_t)y_stride(pm->n_peaks, pm->n_fft);
-    const size_t wins = (size_t)8 * c * p.nrbg * p.nbb * win_stride(pm->n_fft);
+    const size_t wins = (size_t)8 * c * p.nrbg * p.nbb * win_stride(pm->n_fft);  // (as static_layout)
     SearchLayout L;
     size_t o = 0;
     L.shl = shift_layout((int64_t)N, p.nrb_tab, p.nrbg);
@@ -1932,12 +1967,15 @@ SearchLayout search_layout(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gri
     L.y = o;      o += al(4 * ys * c);
     L.y64 = o;    if (needs_full_edges(ctx, pm)) o += al(8 * ys * c);
     L.win = o;    o += al(wins);
+    L.n_win = wins / 8;
     L.wsort = o;  o += al(wins);
     L.colmax = o; o += al(8 * c * (size_t)g->nf);
     L.wq = o;     o += al(weighted ? 4 * c * N : 4);
     L.ws = o;     o += al(sizeof(WeightStats) * c);
     L.sky = o;    o += al(24 * (size_t)n_sky);
     L.qctr = o;   o += al(4 * kXcds);
+    L.rank_size = rank_bytes(ctx, pm, p, chunk);
+    L.rank = o;   o += al(L.rank_size);
     L.total = o;
     return L;
 }
@@ -1946,12 +1984,14 @@ ChunkBufs carve(char *base, const SearchLayout &L, int32_t *err) {
     ChunkBufs b{};
     b.part = reinterpret_cast<uint32_t *>(base + L.part);
     b.part_bytes = L.part_bytes;
+    b.rank = L.rank_size ? reinterpret_cast<uint2 *>(base + L.rank) : nullptr;
     b.gwin = reinterpret_cast<int64_t *>(base + L.sht + L.shl.gwin);
     b.rec = reinterpret_cast<uint2 *>(base + L.sht + L.shl.rec);
     b.step = reinterpret_cast<uint32_t *>(base + L.sht + L.shl.step);
     b.Y = reinterpret_cast<uint32_t *>(base + L.y);
     b.Y64 = reinterpret_cast<int64_t *>(base + L.y64);
-    b.win = reinterpret_cast<int2 *>(base + L.win);
+    b.win = reinterpret_cast<uint32_t *>(base + L.win);
+    b.base = b.win + L.n_win;
     b.wsort = reinterpret_cast<int2 *>(base + L.wsort);
     b.colmax = reinterpret_cast<unsigned long long *>(base + L.colmax);
     b.wq = reinterpret_cast<uint32_t *>(base + L.wq);

@@ -624,3 +624,54 @@ def test_tiles_shared_by_several_workgroups(ctx, kf, ns, parts, weighted, nf):
     else:
         assert np.all(np.abs(m - ref) <= 1e-5 * np.maximum(np.abs(ref), w.mean()))
     dpm.release()
+
+
+@pytest.mark.parametrize("kf,k_lo,span,density,min_gap,fd_scale,mode", [
+    (10, 50000, 700, 0.07, 2, 1.0, "exact"),    # the usual band
+    (10, 50000, 700, 0.07, 2, -20.0, "shift"),  # steep descending rows, per-FFT shift
+    (1, 0, 640, 0.6, 1, 1.0, "exact"),          # from natural bin 0, adjacent peaks, K_f = 1
+    (64, 90000, 65, 0.5, 1, 3.0, "exact"),      # three words of a table, the largest K_f
+    (7, 31, 33, 0.9, 1, 0.0, "exact"),          # flat rows, words that start inside a table's word
+    (10, 1000, 98000, 0.05, 2, 1.0, "exact"),   # the widest table ...
+    (10, 1000, 98500, 0.05, 2, 1.0, "shift"),   # ... and a band past it
+    (3, 200000, 30000, 0.001, 2, 1.0, "exact"), # too sparse for a table
+])
+def test_window_tables_agree_with_searches(ctx, kf, k_lo, span, density, min_gap, fd_scale, mode):
+    """Windows of many directions from rank tables equal those of the sweep
+    over the stripe edges, with several row groups and bin blocks, empty and
+    padding FFTs, and one direction against the oracle."""
+    import torch
+    from paper_1407_8333_amd import api
+    rng = synth.rng_for(kf * 1000 + span)
+    n, t_fft = 41 if span > 5000 else 205, 1024.0
+    pm = synth.random_peakmap(n, t_fft, k_lo, k_lo + span, density, rng, min_gap=min_gap)
+    cnt = np.diff(pm.offsets)
+    cnt[7] = 0  # an FFT without peaks
+    keep = np.ones(pm.bins.shape[0], bool)
+    keep[pm.offsets[7]:pm.offsets[8]] = False
+    pm = synth.Peakmap(t_fft, pm.t, pm.v, np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64), pm.bins[keep],
+                       pm.k_lo, pm.k_hi)
+    dfdot = fd_scale / (t_fft * 0.5 * n * t_fft)
+    nf = min(kf * (span - 10), 2600)
+    grid = synth.Grid(kf=kf, b0=kf * (k_lo + span // 2) - nf // 2, nf=nf, ns=83, fdot0=-30 * dfdot, dfdot=dfdot,
+                      t0=0.5 * (pm.t[0] + pm.t[-1]))
+    sky = synth.sky_uniform(5, rng)
+    wt = torch.as_tensor(synth.fft_weights(n, rng), device="cuda")
+    dpm = ctx.upload(pm)
+    ctx.set_doppler(mode)
+    try:
+        got = []
+        for method in (2, 1):
+            ctx.set_option("window_method", method)
+            got.append([*api.fh_hough_colmax(ctx, dpm, sky, grid, tile_bins=256),
+                        *api.fh_hough_colmax(ctx, dpm, sky, grid, weights=wt),
+                        *api.fh_hough_colmax(ctx, dpm, sky, grid, weights=wt, sky_chunk=3)])
+    finally:
+        ctx.set_option("window_method", 2)
+        ctx.set_doppler("exact")
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    ref = oracle.hough_map(pm, grid, sky[2], doppler=mode)
+    np.testing.assert_array_equal(got[0][0][2].cpu().numpy(), ref.max(0).astype(np.float32))
+    np.testing.assert_array_equal(got[0][1][2].cpu().numpy(), ref.argmax(0))
+    dpm.release()
