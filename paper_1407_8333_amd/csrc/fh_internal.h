@@ -190,21 +190,22 @@ hipError_t launch_slice(int32_t n_fft, const int64_t *offsets, const int32_t *bi
                         int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
                         int64_t *meta, hipStream_t st);
 // one coarse candidate's refined grid: fine bin 0, first row's spin-down, shift
-// reference (shift mode), natural bins [k_lo, k_hi) whose peaks can reach it
+// reference (shift mode), largest distance of a direction from the middle one,
+// natural bins [k_lo, k_hi) whose peaks can reach it
 struct RefineCand {
     int64_t b0;
-    double fdot0, q;
+    double fdot0, q, spread;
     int32_t k_lo, k_hi;
 };
 // first candidate of every (candidate, direction) in out[2 (cand n_dir + dir)];
-// runs: scratch [n_cand][N].  refine_cell_bytes: LDS bytes of a refined volume,
+// runs, firsts: scratch [n_cand][N].  refine_cell_bytes: LDS bytes of a refined volume,
 // 0 when it does not fit (then the volume is searched with the tiles)
 int refine_cell_bytes(int kf, int nf, int ns);
 hipError_t launch_refine_cells(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const double *t,
                                const double *v, int32_t n_cand, int32_t n_dir, const double *sky,
-                               const RefineCand *rc, int2 *runs, int32_t kf, int32_t nf, int32_t ns, double dfdot,
-                               double t0, double t_fft, double theta, const float *w, const WeightStats *ws,
-                               int32_t shift_mode, fh_candidate *out, hipStream_t st);
+                               const RefineCand *rc, int2 *runs, int4 *firsts, int32_t kf, int32_t nf, int32_t ns,
+                               double dfdot, double t0, double t_fft, double theta, const float *w,
+                               const WeightStats *ws, int32_t shift_mode, fh_candidate *out, hipStream_t st);
 // best of the first candidates of each refined direction, per coarse candidate
 hipError_t launch_refine_pick(int32_t n_cand, int32_t n_dir, const fh_candidate *cands, const double *params,
                               const double *lamb, fh_refined *out, hipStream_t st);

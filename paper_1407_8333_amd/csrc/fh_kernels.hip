@@ -2330,51 +2330,88 @@ __global__ void k_slice_pack(const int64_t *__restrict__ first, const int32_t *_
 // peakmap, sorted windows, tiles) costs eleven launches per candidate, each
 // far too small for the GPU.  Here all candidates run in two launches.
 
-// Per (candidate, FFT): the run of peaks with natural bin in [klo, khi).
-// grid.y = candidate.
-__global__ void __launch_bounds__(256) k_refine_runs(int32_t n_fft, const int64_t *__restrict__ offsets,
-                                                     const int32_t *__restrict__ bins,
-                                                     const RefineCand *__restrict__ rc, int2 *__restrict__ runs) {
+// Per (candidate, FFT): the run of peaks that can meet the volume in any of the
+// candidate's directions, and its first four natural bins.  The directions lie
+// within `spread` of the middle one, so their Doppler factors within |v| spread
+// of its: a run is a few natural bins (0.3-1 peaks on average), and the cells
+// kernel, which reads it once per direction, needs no search.  grid.y =
+// candidate.
+__global__ void __launch_bounds__(256) k_refine_runs(
+    int32_t n_fft, const int64_t *__restrict__ offsets, const int32_t *__restrict__ bins, const double *__restrict__ t,
+    const double *__restrict__ v, const double *__restrict__ sky, const RefineCand *__restrict__ rc, int32_t n_dir,
+    int32_t kf, int32_t nf, int32_t ns, double dfdot, double t0, double S, int32_t shift_mode, int2 *__restrict__ runs,
+    int4 *__restrict__ firsts) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_fft) return;
     const RefineCand q = rc[blockIdx.y];
+    const double *n = sky + 3 * ((int64_t)blockIdx.y * n_dir + n_dir / 2);
+    const double *vi = v + 3 * (int64_t)i;
+    const double d = 1.0 + (vi[0] * n[0] + vi[1] * n[1] + vi[2] * n[2]);
+    // largest change of the Doppler factor (and of its inverse) over the
+    // directions; the factor 1.1 covers 1 / D and every rounding
+    const double dd = 1.1 * q.spread * sqrt(vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2]) + 1e-14;
+    const double tau = t[i] - t0;
+    const double ga = rint(((q.fdot0 + 0.0 * dfdot) * tau) * S), gb = rint(((q.fdot0 + (double)(ns - 1) * dfdot) * tau) * S);
+    // edges (without their Doppler term) of the volume's ends, in fine bins
+    const double off = (double)q.b0 + 0.5 * (double)kf;
+    const double z_lo = off + (double)(1 - kf) + fmin(ga, gb) * (1.0 / kQd) - 2.0;
+    const double z_hi = off + (double)nf + fmax(ga, gb) * (1.0 / kQd) + 2.0;
+    double lo, hi;
+    if (shift_mode) {
+        const double sh = q.q * (1.0 - 1.0 / d), m = fabs(q.q) * dd + 1.0;
+        lo = z_lo + sh - m;
+        hi = z_hi + sh + m;
+    } else {
+        lo = fmin(z_lo * (d - dd), z_lo * (d + dd));
+        hi = fmax(z_hi * (d - dd), z_hi * (d + dd));
+    }
+    const int32_t k1 = max(q.k_lo, (int32_t)fmin(fmax(floor(lo / (double)kf) - 1.0, -2e9), 2e9));
+    const int32_t k2 = min(q.k_hi, (int32_t)fmin(fmax(ceil(hi / (double)kf) + 2.0, -2e9), 2e9));
     const int32_t p0 = (int32_t)offsets[i], p1 = (int32_t)offsets[i + 1];
-    // both lower bounds in lockstep
+    // first peaks with natural bin >= k1 and >= k2, in lockstep
     int32_t a = p0, b = p0;
     int32_t top = 1;
     while (top <= (p1 - p0) >> 1) top <<= 1;
     for (int32_t st = top; st > 0; st >>= 1) {
         const int32_t ta = a + st - 1, tb = b + st - 1;
         const int32_t va = ta < p1 ? bins[ta] : 0x7fffffff, vb = tb < p1 ? bins[tb] : 0x7fffffff;
-        if (va < q.k_lo) a += st;
-        if (vb < q.k_hi) b += st;
+        if (va < k1) a += st;
+        if (vb < k2) b += st;
     }
-    runs[(int64_t)blockIdx.y * n_fft + i] = make_int2(a, b);
+    const int32_t c = max(b - a, 0);
+    const int64_t at = (int64_t)blockIdx.y * n_fft + i;
+    runs[at] = make_int2(a, c);
+    firsts[at] = make_int4(c > 0 ? bins[a] : 0, c > 1 ? bins[a + 1] : 0, c > 2 ? bins[a + 2] : 0, c > 3 ? bins[a + 3] : 0);
 }
 
 // One workgroup per (direction, candidate): grid (n_dir, n_cand).  Threads
-// own FFTs: the FFT's peaks whose stripes meet the volume are a contiguous
-// part of its run (Y ascends; the shifts' extremes over the rows are those of
-// the first and last row).  These peaks (0.1-2 per FFT) are compacted into an
-// LDS list, so that the (peak, row) pairs then spread evenly over the
-// threads, one LDS atomic each; window sums and the maximum follow in LDS.
-// Bound by the chain of dependent loads per FFT (run, then the edges of its
-// binary search), which several workgroups per CU hide.  Measured on 22
-// candidates x 25 directions (3140 FFTs of 8192 s at 100 Hz, 20 rows): the
-// whole call 2290 us with a slice and a tile search per candidate, 133 us so.
+// own FFTs and test the peaks of their runs against the volume's bounds (the
+// shifts' extremes over the rows are those of the first and last row).  The
+// peaks that meet it are compacted into an LDS list, so that the (peak, row)
+// pairs then spread evenly over the threads, one LDS atomic each; a thread
+// keeps its row and its row's spin-down.  Window sums and the maximum follow in
+// LDS.  Edges and shifts stay doubles: they are whole numbers below 2^53
+// wherever a start can lie in the volume, so their difference is exact.
+// Measured on 22 candidates x 25 directions (3140 FFTs of 8192 s at 100 Hz, 20
+// rows): the whole call 2290 us with a slice and a tile search per candidate;
+// 133 us while every direction searched runs as wide as the year's Doppler
+// shift (their scattered lines, fetched at every step of the searches, bound
+// it); lanes in groups of 16 over such runs, without a search, 143 us; 66 us with
+// runs narrowed to the candidate's directions.
 constexpr int kRefineThreads = 512;
 constexpr int kRefineList = 1024;  // listed peaks per pass
 
 struct RefinePeak {
-    int64_t y;    // stripe edge Y
+    double y;     // stripe edge, from column 0 (fine bin 1 - K_f)
     double tau;   // t_i - t0
 };
 
 __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
     int32_t n_fft, const int32_t *__restrict__ bins, const double *__restrict__ t, const double *__restrict__ v,
-    const double *__restrict__ sky, const RefineCand *__restrict__ rc, const int2 *__restrict__ runs, int32_t kf,
-    int32_t nf, int32_t ns, double dfdot, double t0, double S, double theta, const float *__restrict__ w,
-    const WeightStats *__restrict__ ws, int32_t shift_mode, fh_candidate *__restrict__ out) {
+    const double *__restrict__ sky, const RefineCand *__restrict__ rc, const int2 *__restrict__ runs,
+    const int4 *__restrict__ firsts, int32_t kf, int32_t nf, int32_t ns, double dfdot, double t0, double S,
+    double theta, const float *__restrict__ w, const WeightStats *__restrict__ ws, int32_t shift_mode,
+    fh_candidate *__restrict__ out) {
     extern __shared__ uint32_t cells[];  // [ns][nf + kf - 1] stripe starts
     __shared__ RefinePeak s_peak[kRefineList];
     __shared__ uint32_t s_w[kRefineList];
@@ -2395,45 +2432,52 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
         bad = ws->bad != 0;
         frac = ws->frac_bits;
     }
-    const int2 *__restrict__ run = runs + (int64_t)cand * n_fft;
     const int64_t ybase = -q.b0 * kQ - (int64_t)kf * (kQ / 2) + (kQ - 1);
+    // the pairs of this thread: rows s0, s0 + n_rows, ... of peaks p0, p0 + step, ...
+    const int n_rows = min(ns, kRefineThreads);
+    const int step = kRefineThreads / n_rows;
+    const int p_first = tid / n_rows, s_first = tid - p_first * n_rows;
+    // spin-downs of the first and last row (row_shift's steps)
+    const double fd_first = q.fdot0 + 0.0 * dfdot, fd_last = q.fdot0 + (double)(ns - 1) * dfdot;
     for (int i0 = 0; i0 < n_fft; i0 += kRefineThreads) {
         const int i = i0 + tid;
-        int pa = 0, pe = 0;
-        double r = 1.0, tau = 0.0;
-        int64_t c = ybase;
-        auto edge = [&](int p) -> int64_t {
-            const int32_t k = bins[p];
-            if (shift_mode) return (int64_t)(kf * k) * kQ + c;
+        int cnt = 0, most = 0;  // peaks that meet the volume; peaks of the run
+        int2 run = make_int2(0, 0);
+        int4 fk = make_int4(0, 0, 0, 0);
+        double r = 1.0, tau = 0.0, c = 0.0, y_lo = 0.0, y_hi = 0.0;
+        // edge of the run's u-th peak, and whether it meets the volume
+        auto edge = [&](int u, double *y) {
+            const int32_t k = u == 0 ? fk.x : u == 1 ? fk.y : u == 2 ? fk.z : u == 3 ? fk.w : bins[run.x + u];
             double x = (double)(kf * k) * r;
             x = x * kQd;
-            return (int64_t)floor(x) + c;
+            *y = floor(x) + c;
+            return u < most && *y >= y_lo && *y < y_hi;
         };
         if (i < n_fft) {
-            const int2 ab = run[i];
+            run = runs[(int64_t)cand * n_fft + i];
+            fk = firsts[(int64_t)cand * n_fft + i];
+            most = run.y;
             const double *vi = v + 3 * (int64_t)i;
             double d = vi[0] * n0;
             d = d + vi[1] * n1;
             d = d + vi[2] * n2;
             d = 1.0 + d;
             r = 1.0 / d;
-            if (shift_mode) c -= llrint((q.q * (1.0 - r)) * kQd);
-            tau = t[i] - t0;
-            const int64_t ga = row_shift(tau, S, q.fdot0, dfdot, 0), gb = row_shift(tau, S, q.fdot0, dfdot, ns - 1);
-            // some row's start lies in columns [0, wc), column = start + K_f - 1
-            const int64_t y_lo = -(int64_t)(kf - 1) * kQ + (ga < gb ? ga : gb);
-            const int64_t y_hi = (int64_t)nf * kQ + (ga < gb ? gb : ga);
-            pa = pe = ab.x;
-            int top = 1;
-            while (top <= (ab.y - ab.x) >> 1) top <<= 1;
-            for (int st = top; st > 0; st >>= 1) {
-                const int ta = pa + st - 1, te = pe + st - 1;
-                if (ta < ab.y && edge(ta) < y_lo) pa += st;
-                if (te < ab.y && edge(te) < y_hi) pe += st;
+            int64_t ci = ybase;
+            if (shift_mode) {
+                ci -= llrint((q.q * (1.0 - r)) * kQd);
+                r = 1.0;  // (the product above is then exact)
             }
+            c = (double)ci;
+            tau = t[i] - t0;
+            const double ga = rint((fd_first * tau) * S), gb = rint((fd_last * tau) * S);
+            // some row's start lies in columns [0, wc), column = start + K_f - 1
+            y_lo = (double)(1 - kf) * kQd + fmin(ga, gb);
+            y_hi = (double)nf * kQd + fmax(ga, gb);
         }
+        double y;
+        for (int u = 0; u < most; ++u) cnt += edge(u, &y) ? 1 : 0;
         // places of the thread's peaks in the list: exclusive scan of the counts
-        const int cnt = pe - pa;
         int incl = cnt;
         for (int o = 1; o < 64; o <<= 1) {
             const int u = __shfl_up(incl, o);
@@ -2450,19 +2494,27 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
         uint32_t wq = 1u;
         if (w != nullptr && cnt > 0) wq = bad ? 0u : (uint32_t)rint(ldexp((double)w[i], frac));
         for (int base = 0; base < total; base += kRefineList) {
-            const int b0 = max(0, base - first), b1 = min(cnt, base + kRefineList - first);
-            for (int u = b0; u < b1; ++u) {
-                s_peak[first + u - base] = {edge(pa + u), tau};
-                s_w[first + u - base] = wq;
+            int at = first - base;
+            for (int u = 0; cnt > 0 && u < most; ++u) {
+                if (!edge(u, &y)) continue;
+                if (at >= 0 && at < kRefineList) {
+                    s_peak[at] = {y + (double)(kf - 1) * kQd, tau};
+                    s_w[at] = wq;
+                }
+                ++at;
             }
             __syncthreads();
-            const int n_pairs = min(total - base, kRefineList) * ns;
-            for (int e = tid; e < n_pairs; e += kRefineThreads) {
-                const int p = e / ns, s = e - p * ns;
-                const RefinePeak pk = s_peak[p];
-                const int64_t g = row_shift(pk.tau, S, q.fdot0, dfdot, s);
-                const int64_t col = shrq(pk.y - g) + (kf - 1);
-                if (col >= 0 && col < wc) atomicAdd(&cells[s * wc + (int)col], s_w[p]);
+            const int n_list = min(total - base, kRefineList);
+            if (p_first < step) {
+                for (int s = s_first; s < ns; s += n_rows) {
+                    const double fs = q.fdot0 + (double)s * dfdot;
+                    for (int p = p_first; p < n_list; p += step) {
+                        const RefinePeak pk = s_peak[p];
+                        const double g = rint((fs * pk.tau) * S);
+                        const double col = floor((pk.y - g) * (1.0 / kQd));
+                        if (col >= 0.0 && col < (double)wc) atomicAdd(&cells[s * wc + (int)col], s_w[p]);
+                    }
+                }
             }
             __syncthreads();
         }
@@ -2503,18 +2555,31 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
 // ----------------------------------------------------------------------------
 // refined candidates: the best of the k_sky^2 directions' first candidates
 
-__global__ void k_refine_pick(int32_t n_cand, int32_t n_dir, const fh_candidate *__restrict__ cands,
-                              const double *__restrict__ params, const double *__restrict__ lamb,
-                              fh_refined *__restrict__ out) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_cand) return;
+// one wave per candidate (larger value, then smaller direction)
+__global__ void __launch_bounds__(64) k_refine_pick(int32_t n_cand, int32_t n_dir,
+                                                    const fh_candidate *__restrict__ cands,
+                                                    const double *__restrict__ params, const double *__restrict__ lamb,
+                                                    fh_refined *__restrict__ out) {
+    const int c = blockIdx.x, lane = threadIdx.x;
     const fh_candidate *cc = cands + (int64_t)c * n_dir * 2;
     int best = -1;
-    for (int s = 0; s < n_dir; ++s) {
+    float val = 0.0f;
+    for (int s = lane; s < n_dir; s += 64) {
         const fh_candidate &x = cc[2 * s];
-        if (!x.valid) continue;
-        if (best < 0 || x.value > cc[2 * best].value) best = s;
+        if (x.valid && (best < 0 || x.value > val)) {
+            best = s;
+            val = x.value;
+        }
     }
+    for (int o = 32; o >= 1; o >>= 1) {
+        const int b2 = __shfl_xor(best, o);
+        const float v2 = __shfl_xor(val, o);
+        if (b2 >= 0 && (best < 0 || v2 > val || (v2 == val && b2 < best))) {
+            best = b2;
+            val = v2;
+        }
+    }
+    if (lane != 0) return;
     fh_refined r{};
     r.cand = c;
     if (best >= 0) {
@@ -2940,24 +3005,25 @@ int refine_cell_bytes(int kf, int nf, int ns) {
 
 hipError_t launch_refine_cells(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const double *t,
                                const double *v, int32_t n_cand, int32_t n_dir, const double *sky,
-                               const RefineCand *rc, int2 *runs, int32_t kf, int32_t nf, int32_t ns, double dfdot,
-                               double t0, double t_fft, double theta, const float *w, const WeightStats *ws,
-                               int32_t shift_mode, fh_candidate *out, hipStream_t st) {
+                               const RefineCand *rc, int2 *runs, int4 *firsts, int32_t kf, int32_t nf, int32_t ns,
+                               double dfdot, double t0, double t_fft, double theta, const float *w,
+                               const WeightStats *ws, int32_t shift_mode, fh_candidate *out, hipStream_t st) {
     const int lds = refine_cell_bytes(kf, nf, ns);
     if (lds == 0 || n_cand > 65535) return hipErrorInvalidValue;
-    k_refine_runs<<<dim3(grid_for(n_fft, 256), n_cand), 256, 0, st>>>(n_fft, offsets, bins, rc, runs);
+    const double S = ((double)kf * t_fft) * kQd;
+    k_refine_runs<<<dim3(grid_for(n_fft, 256), n_cand), 256, 0, st>>>(n_fft, offsets, bins, t, v, sky, rc, n_dir, kf, nf,
+                                                                      ns, dfdot, t0, S, shift_mode, runs, firsts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const double S = ((double)kf * t_fft) * kQd;
-    k_refine_cells<<<dim3(n_dir, n_cand), kRefineThreads, lds, st>>>(n_fft, bins, t, v, sky, rc, runs, kf, nf, ns,
-                                                                     dfdot, t0, S, theta, w, ws, shift_mode, out);
+    k_refine_cells<<<dim3(n_dir, n_cand), kRefineThreads, lds, st>>>(n_fft, bins, t, v, sky, rc, runs, firsts, kf, nf,
+                                                                     ns, dfdot, t0, S, theta, w, ws, shift_mode, out);
     return hipGetLastError();
 }
 
 hipError_t launch_refine_pick(int32_t n_cand, int32_t n_dir, const fh_candidate *cands, const double *params,
                               const double *lamb, fh_refined *out, hipStream_t st) {
     if (n_cand <= 0) return hipSuccess;
-    k_refine_pick<<<grid_for(n_cand, 64), 64, 0, st>>>(n_cand, n_dir, cands, params, lamb, out);
+    k_refine_pick<<<n_cand, 64, 0, st>>>(n_cand, n_dir, cands, params, lamb, out);
     return hipGetLastError();
 }
 

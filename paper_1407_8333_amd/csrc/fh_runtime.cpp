@@ -1453,24 +1453,41 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
         width = std::max(width, khi[c] - klo[c]);
         kmin = std::min(kmin, klo[c]);
         kmax = std::max(kmax, khi[c] - 1);
-        for (int j = -L; j <= L; ++j)
+        // longitudes (as they are, and turned by pi for latitudes over a pole)
+        // and their sines and cosines, once per column of the refined sky
+        struct Angle { double a, c, s; };
+        Angle lams[2][63];
+        bool turned = false;
+        auto longitudes = [&](int over) {
             for (int i = -L; i <= L; ++i) {
-                const int d = (j + L) * ks + (i + L);
-                double lam = q.lambda + i * (q.dlambda / ks), bet = q.beta + j * (q.dbeta / ks);
-                if (std::fabs(bet) > 0.5 * M_PI) {  // over a pole
-                    lam += M_PI;
-                    bet = (bet > 0 ? M_PI : -M_PI) - bet;
-                }
+                double lam = q.lambda + i * (q.dlambda / ks);
+                if (over) lam += M_PI;
                 lam = std::fmod(lam, 2.0 * M_PI);
                 if (lam < 0) lam += 2.0 * M_PI;
-                lamb[2 * ((size_t)c * n_dir + d)] = lam;
+                lams[over][i + L] = {lam, std::cos(lam), std::sin(lam)};
+            }
+        };
+        longitudes(0);
+        for (int j = -L; j <= L; ++j) {
+            double bet = q.beta + j * (q.dbeta / ks);
+            const bool over = std::fabs(bet) > 0.5 * M_PI;  // over a pole
+            if (over) {
+                if (!turned) longitudes(1);
+                turned = true;
+                bet = (bet > 0 ? M_PI : -M_PI) - bet;
+            }
+            const double cb = std::cos(bet), ze = std::sin(bet);
+            for (int i = -L; i <= L; ++i) {
+                const int d = (j + L) * ks + (i + L);
+                const Angle &lam = lams[over ? 1 : 0][i + L];
+                lamb[2 * ((size_t)c * n_dir + d)] = lam.a;
                 lamb[2 * ((size_t)c * n_dir + d) + 1] = bet;
-                const double x = std::cos(bet) * std::cos(lam), ye = std::cos(bet) * std::sin(lam),
-                             ze = std::sin(bet);
+                const double x = cb * lam.c, ye = cb * lam.s;
                 double n[3] = {x, ye * ce - ze * se, ye * se + ze * ce};
                 const double r = std::sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
                 for (int k = 0; k < 3; ++k) sky[3 * ((size_t)c * n_dir + d) + k] = n[k] / r;
             }
+        }
     }
     const int32_t N = pm->n_fft;
     const int64_t cap = std::min<int64_t>((int64_t)N * width, pm->n_peaks);
@@ -1485,9 +1502,17 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
     // one upload: parameters and sky points of the pick, refined directions,
     // and the candidates' grids
     std::vector<RefineCand> rc((size_t)n_cand);
-    for (int c = 0; c < n_cand; ++c)
+    for (int c = 0; c < n_cand; ++c) {
+        double far2 = 0.0;  // squared distance of the farthest direction from the middle one
+        const double *n = sky.data() + 3 * (size_t)c * n_dir, *m = n + 3 * (n_dir / 2);
+        for (int d = 0; d < n_dir; ++d) {
+            double x2 = 0.0;
+            for (int k = 0; k < 3; ++k) x2 += (n[3 * d + k] - m[k]) * (n[3 * d + k] - m[k]);
+            far2 = std::max(far2, x2);
+        }
         rc[c] = {grids[c].b0, grids[c].fdot0, ctx->doppler_mode ? shift_reference_bins(ctx, &sub, &grids[c]) : 0.0,
-                 klo[c], khi[c]};
+                 std::sqrt(far2), klo[c], khi[c]};
+    }
     const size_t b_aux = 8 * aux.size(), b_sky = 8 * sky.size(), b_rc = sizeof(RefineCand) * rc.size();
     if ((s = ctx->rf_cands.ensure(sizeof(fh_candidate) * 2 * (size_t)n_cand * n_dir, st)) ||
         (s = ctx->rf_aux.ensure(b_aux + b_sky + b_rc, st)))
@@ -1506,8 +1531,8 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
         // a volume that fits the LDS: all candidates at once (in chunks whose
         // peak runs take at most 64 MiB)
         const int chunk = (int)std::min<int64_t>(std::min(n_cand, 65535),
-                                                 std::max<int64_t>(1, ((int64_t)64 << 20) / (8 * (int64_t)N)));
-        if ((s = ctx->rf_first.ensure(8 * (size_t)chunk * N, st)) ||
+                                                 std::max<int64_t>(1, ((int64_t)64 << 20) / (24 * (int64_t)N)));
+        if ((s = ctx->rf_first.ensure(24 * (size_t)chunk * N, st)) ||
             (s = ctx->cur->ws.ensure(sizeof(WeightStats), st)))
             return s;
         WeightStats *ws = weighted ? (WeightStats *)ctx->cur->ws.ptr : nullptr;
@@ -1516,9 +1541,10 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
             HIP_OK(launch_weight_stats(N, d_w, pm->adjacent ? 2 : 1, ws, (int32_t *)ctx->err.ptr, st));
         for (int c = 0; c < n_cand; c += chunk) {
             const int nc = std::min(chunk, n_cand - c);
+            int4 *firsts = (int4 *)ctx->rf_first.ptr;
             HIP_OK(launch_refine_cells(N, pm->d_offsets, pm->d_bins, pm->d_t, pm->d_v, nc, n_dir,
-                                       d_sky + 3 * (size_t)c * n_dir, d_rc + c, (int2 *)ctx->rf_first.ptr, kf, nf, ns,
-                                       dfd, o->t0, T, o->theta, d_w, ws, ctx->doppler_mode,
+                                       d_sky + 3 * (size_t)c * n_dir, d_rc + c, (int2 *)(firsts + (size_t)chunk * N),
+                                       firsts, kf, nf, ns, dfd, o->t0, T, o->theta, d_w, ws, ctx->doppler_mode,
                                        dc + 2 * (size_t)c * n_dir, st));
         }
         if (ctx->profiling) ctx->prof_updates += cap * (int64_t)ns * n_dir * n_cand;
