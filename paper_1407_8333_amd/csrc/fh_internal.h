@@ -120,7 +120,30 @@ struct SetupArgs {
     double *sky;
     double sky_arg[3 * kArgSky];
 };
-hipError_t launch_setup(const SetupArgs &a, hipStream_t st);
+// k_setup's rank table (n_blocks = 0: none) and k_setup_front's front
+struct RankArgs {
+    const int32_t *bins;
+    int32_t k_min, nw, n_blocks;
+    uint2 *rank;
+};
+struct FrontArgs {
+    int64_t n_peaks, b0;
+    const int32_t *bins;
+    const double *v, *sky;
+    int32_t n_slots, kf, nrbg, nbb, W, F, search_top, shift_mode;
+    double q;
+    uint32_t *Y, *win;
+};
+// fixed-point weights of every slot, left to the window sort (w = nullptr: none)
+struct WeightArgs {
+    const float *w;
+    const WeightStats *ws;
+    uint32_t *wq;
+    int32_t w_stride, ws_stride;
+};
+// with the rank table of launch_front_rank (rank = nullptr: without)
+hipError_t launch_setup(const SetupArgs &a, const int32_t *bins, int32_t k_min, int32_t k_max, uint2 *rank,
+                        hipStream_t st);
 hipError_t launch_weight_stats(int32_t n_fft, const float *w, int32_t mult, WeightStats *ws, int32_t *err_flag,
                                hipStream_t st);
 hipError_t launch_prep(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
@@ -128,7 +151,7 @@ hipError_t launch_prep(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, c
                        int64_t *Y, const float *w, int32_t w_stride,
                        const WeightStats *ws, int32_t ws_stride, uint32_t *wq, uint32_t *Y32,
                        int32_t shift_mode, double q, hipStream_t st);
-// fused stripe edges + weights + windows (LDS-staged edges of F FFTs per
+// setup with the fused stripe edges + windows (LDS-staged edges of F FFTs per
 // workgroup); F = front_ffts_per_block(max peaks of one FFT), 0 when even one
 // FFT's edges do not fit (then use launch_prep + launch_windows).  FFTs of
 // kFrontBigFft peaks or more go at most four to a workgroup: the front is
@@ -137,22 +160,15 @@ constexpr int kFrontLdsBytes = 48 * 1024;
 constexpr int kFrontBigFft = 256;
 constexpr int kFrontMaxF = 16;
 int front_ffts_per_block(int32_t max_per_fft);
-hipError_t launch_front(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
-                        const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
-                        const int64_t *gwin, uint32_t *Y, const float *w,
-                        int32_t w_stride, const WeightStats *ws, int32_t ws_stride, uint32_t *wq,
-                        int32_t ns, int32_t nrbg, int32_t nbb, int32_t W, int32_t F, int32_t max_per_fft,
-                        uint32_t *win, int32_t shift_mode, double q, hipStream_t st);
-// The same for many directions: window ends from a table of the FFTs' peaks
-// (launch_rank, uint2 [N][rank_words], once per call; 0 words when the natural
+hipError_t launch_setup_front(const SetupArgs &a, FrontArgs r, int32_t max_per_fft, hipStream_t st);
+// The front of many directions: window ends from a table of the FFTs' peaks
+// (launch_setup's, uint2 [N][rank_words], once per call; 0 words when the natural
 // bins span too far for it) instead of searches.
 constexpr int kRankMaxWords = 3072;
 constexpr int kRankLdsBytes = 24 * 1024;
 constexpr int kRankDirs = 4;  // directions per workgroup, at most
 int32_t rank_words(int32_t k_min, int32_t k_max);
 bool rank_front_fits(int32_t k_min, int32_t k_max, int32_t nrbg);
-hipError_t launch_rank(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_min, int32_t k_max,
-                       uint2 *rank, hipStream_t st);
 hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
                              const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
                              const int64_t *gwin, uint32_t *Y, const float *w, int32_t w_stride,
@@ -164,7 +180,7 @@ hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offs
 // window rows sorted by window size per tile-wave run (see k_sort_windows)
 // (win: packed, see window(); base: u32 [win_stride(N)], see SetupArgs)
 hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t n_slots, const uint32_t *win,
-                               const uint32_t *base, int2 *wsorted, hipStream_t st);
+                               const uint32_t *base, int2 *wsorted, const WeightArgs &wa, hipStream_t st);
 // method 0: two binary searches per entry; 1: one sweep per FFT
 hipError_t launch_windows(int32_t n_fft, const int64_t *offsets, const int64_t *Y, int64_t n_peaks,
                           const int64_t *gwin, int32_t nrbg, int32_t nbb, int32_t W,

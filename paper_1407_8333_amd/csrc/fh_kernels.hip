@@ -181,22 +181,10 @@ __global__ void __launch_bounds__(256) k_weight_stats(int32_t n, const float *__
     weight_stats(n, w, mult, ws, err_flag);
 }
 
-// ----------------------------------------------------------------------------
-// Everything a search needs before its front, in one launch: the weight
-// statistics (one workgroup per vector), the shift tables, cleared column
-// maxima and queue counters, and the directions of a small call, which come
-// as kernel arguments.  All of it is latency: it replaces a copy, behind which
-// the host waited for the stream, and four kernels.  A 0.1 Hz map of 200 FFTs
-// went from 36 to 23 us, the column maxima of five directions (4096 s, own
-// weights) from 153 to 126 us.
-__global__ void __launch_bounds__(256) k_setup(SetupArgs A) {
-    int b = blockIdx.x;
-    if (b < A.n_vec) {
-        weight_stats(A.n_fft, A.w + (int64_t)b * A.w_stride, A.mult, A.ws + b, A.err);
-        return;
-    }
-    b -= A.n_vec;
-    const int64_t x = b * (int64_t)256 + threadIdx.x, stride = (int64_t)(gridDim.x - A.n_vec) * 256;
+// Block b of the n_blocks that hold the shift tables, the cleared buffers and
+// the directions.
+__device__ __forceinline__ void setup_block(const SetupArgs &A, int b, int n_blocks) {
+    const int64_t x = b * (int64_t)256 + threadIdx.x, stride = (int64_t)n_blocks * 256;
     shift_tables(A, x, stride);
     for (int64_t y = x; y < A.n_colmax; y += stride) A.colmax[y] = 0ull;
     if (b == 0) {
@@ -285,28 +273,25 @@ __global__ void __launch_bounds__(256) k_prep(
 // first and last row).  Consecutive threads write consecutive FFTs of a
 // window row.
 
-__global__ void __launch_bounds__(256) k_front(
-    int32_t n_fft, int64_t n_peaks, const int64_t *__restrict__ offsets,
-    const int32_t *__restrict__ bins, const double *__restrict__ v,
-    const double *__restrict__ sky, int32_t kf, int64_t b0, const int64_t *__restrict__ gwin,
-    uint32_t *__restrict__ Y, const float *__restrict__ w,
-    int32_t w_stride, const WeightStats *__restrict__ ws, int32_t ws_stride,
-    uint32_t *__restrict__ wq, int32_t ns, int32_t nrbg, int32_t nbb, int32_t W, int32_t F,
-    int32_t search_top, uint32_t *__restrict__ win, int32_t shift_mode, double q) {
+__device__ __forceinline__ void front_block(const SetupArgs &A, const FrontArgs &R, int block, int slot) {
     extern __shared__ int64_t ys[];
     __shared__ int64_t s_off[kFrontMaxF + 1];  // offsets of the block's FFTs
     __shared__ int32_t s_loc[kFrontMaxF + 1];  // the same, from the block's first peak
     __shared__ int64_t s_c[kFrontMaxF];        // per-FFT constant of the edge
     __shared__ double s_r[kFrontMaxF];         // per-FFT inverse Doppler factor
-    const int slot = blockIdx.y;
-    const int f0 = blockIdx.x * F;
+    const int32_t n_fft = A.n_fft, kf = R.kf, F = R.F, nrbg = R.nrbg, nbb = R.nbb, W = R.W;
+    const int32_t search_top = R.search_top, shift_mode = R.shift_mode;
+    const int64_t *__restrict__ offsets = A.offsets;
+    const int32_t *__restrict__ bins = R.bins;
+    const int f0 = block * F;
     const int fe = min(f0 + F, n_fft);
     const int nfl = fe - f0;  // FFTs of this block (<= 0 for padding blocks)
     const int32_t n_pad = win_stride(n_fft);
-    uint32_t *Yslot = Y + (int64_t)slot * y_stride(n_peaks, n_fft);
+    uint32_t *Yslot = R.Y + (int64_t)slot * y_stride(R.n_peaks, n_fft);
 
-    // per-FFT terms (r, constant, weight), one thread per FFT
-    const double *n = sky + 3 * (int64_t)slot;
+    // per-FFT terms (r, constant), one thread per FFT; the directions of a
+    // small call are read from the arguments (k_setup's copy may not be there)
+    const double *n = slot < A.n_sky ? A.sky_arg + 3 * slot : R.sky + 3 * (int64_t)slot;
     if ((int)threadIdx.x <= nfl) {
         const int64_t o = offsets[f0 + threadIdx.x];
         s_off[threadIdx.x] = o;
@@ -314,21 +299,16 @@ __global__ void __launch_bounds__(256) k_front(
     }
     if ((int)threadIdx.x < nfl) {
         const int i = f0 + threadIdx.x;
-        const double *vi = v + 3 * (int64_t)i;
+        const double *vi = R.v + 3 * (int64_t)i;
         double d = vi[0] * n[0];
         d = d + vi[1] * n[1];
         d = d + vi[2] * n[2];
         d = 1.0 + d;
         const double r = 1.0 / d;
         s_r[threadIdx.x] = r;
-        int64_t c = -b0 * kQ - (int64_t)kf * (kQ / 2) + (kQ - 1);
-        if (shift_mode) c -= llrint((q * (1.0 - r)) * kQd);  // per-FFT shift at the reference
+        int64_t c = -R.b0 * kQ - (int64_t)kf * (kQ / 2) + (kQ - 1);
+        if (shift_mode) c -= llrint((R.q * (1.0 - r)) * kQd);  // per-FFT shift at the reference
         s_c[threadIdx.x] = c;
-        if (w != nullptr) {
-            const WeightStats wst = ws[(int64_t)slot * ws_stride];
-            double wi = (double)w[(int64_t)slot * w_stride + i];
-            wq[(int64_t)slot * n_fft + i] = wst.bad ? 0u : (uint32_t)rint(ldexp(wi, wst.frac_bits));
-        }
     }
     __syncthreads();
 
@@ -396,13 +376,18 @@ __global__ void __launch_bounds__(256) k_front(
         a0 = s_loc[fl] + kYPad * fl;
         end = s_loc[fl + 1] + kYPad * fl;
     }
-    const int64_t *__restrict__ gq = gwin + (int64_t)f * nrbg * 2;
-    uint32_t *__restrict__ wp = win + (int64_t)slot * n_rows * n_pad + f;
-    for (; rest < n_rows; rest += step_r) {
+    const double tau = live ? A.t[f] - A.t0 : 0.0;
+    uint32_t *__restrict__ wp = R.win + (int64_t)slot * n_rows * n_pad + f;
+    int64_t q_lo = 0, q_hi = 0;  // shifts of the group's first and last grid rows
+    for (int g_of = -1; rest < n_rows; rest += step_r) {
         uint32_t out = 0u;
         if (live) {
-            // shifts of the group's first and last grid rows
-            const int64_t q_lo = gq[2 * g], q_hi = gq[2 * g + 1];
+            if (g != g_of) {  // worked out here: the tables come from the same launch
+                constexpr int kGroupRows = kTileRows * kRowBlocksPerGroup;
+                q_lo = row_shift(tau, A.S, A.fdot0, A.dfdot, g * kGroupRows);
+                q_hi = row_shift(tau, A.S, A.fdot0, A.dfdot, g == nrbg - 1 ? A.ns - 1 : (g + 1) * kGroupRows - 1);
+                g_of = g;
+            }
             // max_s a_s = floor((Y - min G) / kQ) >= t  <=>  Y >= t kQ + min G
             // min_s a_s = floor((Y - max G) / kQ) >= t  <=>  Y >= t kQ + max G
             const int64_t y_lo = ((int64_t)jb * W - (kf - 1)) * kQ + (q_lo < q_hi ? q_lo : q_hi);
@@ -427,21 +412,15 @@ __global__ void __launch_bounds__(256) k_front(
 }
 
 // ----------------------------------------------------------------------------
-// Front of many directions.  A window's ends are found without a search: the
-// edge bound of an entry gives the least natural bin whose edge reaches it
-// (an estimate and one exact test, since edges ascend with the bin), and a
-// table of the FFT's peaks, 32 natural bins to a word with the number of peaks
-// before it, gives that bin's place among them.  The table does not depend on
-// the direction and is built once per call.
-
+// The front's table of an FFT's peaks (see k_front_rank):
 // rank[i][w] = (bits of natural bins k_min + 32 w .. + 31, peaks of FFT i below
 // them), nw words per FFT; one wave per FFT.
-__global__ void __launch_bounds__(256) k_rank(int32_t n_fft, const int64_t *__restrict__ offsets,
-                                              const int32_t *__restrict__ bins, int32_t k_min, int32_t nw,
-                                              uint2 *__restrict__ rank) {
+__device__ __forceinline__ void rank_block(int32_t n_fft, const int64_t *__restrict__ offsets,
+                                           const int32_t *__restrict__ bins, int32_t k_min, int32_t nw,
+                                           uint2 *__restrict__ rank, int block) {
     extern __shared__ uint32_t s_bits[];  // [4][nw]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i = blockIdx.x * 4 + wave;
+    const int i = block * 4 + wave;
     uint32_t *b = s_bits + wave * nw;
     for (int w = lane; w < nw; w += 64) b[w] = 0u;
     __syncthreads();
@@ -468,6 +447,56 @@ __global__ void __launch_bounds__(256) k_rank(int32_t n_fft, const int64_t *__re
         carry += __shfl(incl, 63);
     }
 }
+
+// ----------------------------------------------------------------------------
+// Everything a search needs before its front (or beside it), in one launch: the
+// weight statistics (one workgroup per vector), the shift tables, cleared
+// column maxima and queue counters, and the directions of a small call, which
+// come as kernel arguments.  All of it is latency: it replaces a copy, behind
+// which the host waited for the stream, and four kernels.  A 0.1 Hz map of 200 FFTs
+// went from 36 to 23 us, the column maxima of five directions (4096 s, own
+// weights) from 153 to 126 us.
+// With the rank table of launch_front_rank:
+__global__ void __launch_bounds__(256) k_setup(SetupArgs A, RankArgs R) {
+    int b = blockIdx.x;
+    if (b < A.n_vec) {
+        weight_stats(A.n_fft, A.w + (int64_t)b * A.w_stride, A.mult, A.ws + b, A.err);
+        return;
+    }
+    b -= A.n_vec;
+    if (b < R.n_blocks) {
+        rank_block(A.n_fft, A.offsets, R.bins, R.k_min, R.nw, R.rank, b);
+        return;
+    }
+    setup_block(A, b - R.n_blocks, (int)gridDim.x - A.n_vec - R.n_blocks);
+}
+
+// With the front of one or a few directions, which needs nothing of the rest
+// (the window sort, the next launch, takes the fixed-point weights): 3 us less
+// per call, 23 -> 20 us on a 0.1 Hz map of 200 FFTs.
+__global__ void __launch_bounds__(256) k_setup_front(SetupArgs A, FrontArgs R) {
+    int b = blockIdx.x;
+    if (b < A.n_vec) {
+        weight_stats(A.n_fft, A.w + (int64_t)b * A.w_stride, A.mult, A.ws + b, A.err);
+        return;
+    }
+    b -= A.n_vec;
+    const int per_slot = win_stride(A.n_fft) / R.F;
+    if (b < per_slot * R.n_slots) {
+        const int slot = b / per_slot;
+        front_block(A, R, b - slot * per_slot, slot);
+        return;
+    }
+    setup_block(A, b - per_slot * R.n_slots, (int)gridDim.x - A.n_vec - per_slot * R.n_slots);
+}
+
+// ----------------------------------------------------------------------------
+// Front of many directions.  A window's ends are found without a search: the
+// edge bound of an entry gives the least natural bin whose edge reaches it
+// (an estimate and one exact test, since edges ascend with the bin), and a
+// table of the FFT's peaks, 32 natural bins to a word with the number of peaks
+// before it, gives that bin's place among them.  The table does not depend on
+// the direction and is built once per call.
 
 // For up to D direction slots and F consecutive FFTs f0 .. f0+F-1: the stripe
 // edges of their peaks, their fixed-point weights and every window entry.  The
@@ -791,6 +820,18 @@ __device__ __forceinline__ int big_window_rank(int c, int e, int per, Size size)
 // entries that a wave stores together lie in 64 banks.
 __host__ __device__ inline int sort_run_stride(int per) { return per + ((4 - per) & 15); }
 
+// The slot's fixed-point weights, when the front left them to the sort (its
+// statistics came from the same launch); grid.x workgroups share them.
+__device__ __forceinline__ void fixed_weights(int32_t n_fft, const WeightArgs &A) {
+    if (A.w == nullptr) return;
+    const int64_t slot = blockIdx.y;
+    const WeightStats st = A.ws[slot * A.ws_stride];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_fft; i += gridDim.x * blockDim.x) {
+        const double wi = (double)A.w[slot * A.w_stride + i];
+        A.wq[slot * n_fft + i] = st.bad ? 0u : (uint32_t)rint(ldexp(wi, st.frac_bits));
+    }
+}
+
 __device__ __forceinline__ int window_size(uint32_t w) { return (int)(w >> 16) - (int)(w & 0xFFFFu); }
 
 // Exclusive prefix sums over a run's buckets (lane L holds buckets 2L, 2L+1).
@@ -811,7 +852,8 @@ __device__ __forceinline__ void scan_buckets(int *h, int lane) {
 __global__ void __launch_bounds__(kTileThreads) k_sort_windows(int32_t n_fft, int32_t nrows,
                                                                const uint32_t *__restrict__ win,
                                                                const uint32_t *__restrict__ base,
-                                                               int2 *__restrict__ wsorted) {
+                                                               int2 *__restrict__ wsorted, WeightArgs wa) {
+    fixed_weights(n_fft, wa);
     extern __shared__ uint32_t s_run[];  // the row, run by run, then the entries' ranks in their buckets (16-bit)
     __shared__ int hist[kTileWaves][kSortBuckets];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -880,7 +922,8 @@ constexpr int kSortPiece = 32768;
 __global__ void __launch_bounds__(kTileThreads) k_sort_windows_long(int32_t n_fft, int32_t nrows,
                                                                     const uint32_t *__restrict__ win,
                                                                     const uint32_t *__restrict__ base,
-                                                                    int2 *__restrict__ wsorted) {
+                                                                    int2 *__restrict__ wsorted, WeightArgs wa) {
+    fixed_weights(n_fft, wa);
     extern __shared__ uint4 s_row4[];
     __shared__ int hist[kTileWaves][kSortBuckets];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -2079,11 +2122,27 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_setup(const SetupArgs &a, hipStream_t st) {
-    if (a.n_fft < 1 || a.nrb < 1 || a.nrb_run < 1 || a.nrb_run > a.nrb || a.n_sky > kArgSky) return hipErrorInvalidValue;
+// workgroups for the shift tables and the cleared buffers; 0: invalid
+static int setup_blocks(const SetupArgs &a) {
+    if (a.n_fft < 1 || a.nrb < 1 || a.nrb_run < 1 || a.nrb_run > a.nrb || a.n_sky > kArgSky) return 0;
     const int64_t work = std::max((int64_t)a.n_fft * a.nrb, a.n_colmax / 4);
-    const unsigned blocks = (unsigned)std::min<int64_t>((work + 255) / 256, 8192);
-    k_setup<<<a.n_vec + blocks, 256, 0, st>>>(a);
+    return (int)std::min<int64_t>((work + 255) / 256, 8192);
+}
+
+hipError_t launch_setup(const SetupArgs &a, const int32_t *bins, int32_t k_min, int32_t k_max, uint2 *rank,
+                        hipStream_t st) {
+    const int blocks = setup_blocks(a);
+    if (blocks == 0) return hipErrorInvalidValue;
+    RankArgs r{};
+    if (rank != nullptr) {
+        r.bins = bins;
+        r.k_min = k_min;
+        r.nw = rank_words(k_min, k_max);
+        r.rank = rank;
+        r.n_blocks = (a.n_fft + 3) / 4;
+        if (r.nw == 0) return hipErrorInvalidValue;
+    }
+    k_setup<<<a.n_vec + r.n_blocks + blocks, 256, (size_t)16 * r.nw, st>>>(a, r);
     return hipGetLastError();
 }
 
@@ -2116,21 +2175,16 @@ int front_ffts_per_block(int32_t max_per_fft) {
     return 0;
 }
 
-hipError_t launch_front(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
-                        const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
-                        const int64_t *gwin, uint32_t *Y, const float *w,
-                        int32_t w_stride, const WeightStats *ws, int32_t ws_stride, uint32_t *wq,
-                        int32_t ns, int32_t nrbg, int32_t nbb, int32_t W, int32_t F, int32_t max_per_fft,
-                        uint32_t *win, int32_t shift_mode, double q, hipStream_t st) {
-    if (F < 1 || win_stride(n_fft) % F != 0) return hipErrorInvalidValue;
-    dim3 grid(win_stride(n_fft) / F, n_slots);
-    const size_t lds = ((size_t)F * (max_per_fft + kYPad) * 8 + 255) / 256 * 256;
-    if (F > kFrontMaxF || lds > (size_t)kFrontLdsBytes) return hipErrorInvalidValue;
-    int32_t top = 0;  // largest power of two up to max_per_fft (0 when no FFT has a peak)
-    while (top * 2 <= max_per_fft && top < (1 << 30)) top = top ? 2 * top : 1;
-    k_front<<<grid, 256, lds, st>>>(n_fft, n_peaks, offsets, bins, v, sky, kf, b0, gwin, Y,
-                                               w, w_stride, ws, ws_stride, wq, ns, nrbg, nbb, W, F, top, win,
-                                               shift_mode, q);
+hipError_t launch_setup_front(const SetupArgs &a, FrontArgs r, int32_t max_per_fft, hipStream_t st) {
+    const int blocks = setup_blocks(a);
+    if (blocks == 0 || r.F < 1 || r.F > kFrontMaxF || win_stride(a.n_fft) % r.F != 0) return hipErrorInvalidValue;
+    const size_t lds = ((size_t)r.F * (max_per_fft + kYPad) * 8 + 255) / 256 * 256;
+    if (lds > (size_t)kFrontLdsBytes) return hipErrorInvalidValue;
+    r.search_top = 0;  // largest power of two up to max_per_fft (0 when no FFT has a peak)
+    while (r.search_top * 2 <= max_per_fft && r.search_top < (1 << 30)) r.search_top = r.search_top ? 2 * r.search_top : 1;
+    const int64_t front = (int64_t)(win_stride(a.n_fft) / r.F) * r.n_slots;
+    if (front + a.n_vec + blocks >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    k_setup_front<<<(unsigned)(a.n_vec + front + blocks), 256, lds, st>>>(a, r);
     return hipGetLastError();
 }
 
@@ -2154,14 +2208,6 @@ bool rank_front_fits(int32_t k_min, int32_t k_max, int32_t nrbg) {
     return nw > 0 && rank_ffts_per_block(nw, nrbg) > 0;
 }
 
-hipError_t launch_rank(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_min, int32_t k_max,
-                       uint2 *rank, hipStream_t st) {
-    const int32_t nw = rank_words(k_min, k_max);
-    if (nw == 0) return hipErrorInvalidValue;
-    k_rank<<<(n_fft + 3) / 4, 256, (size_t)16 * nw, st>>>(n_fft, offsets, bins, k_min, nw, rank);
-    return hipGetLastError();
-}
-
 hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
                              const double *v, const double *sky, int32_t n_slots, int32_t kf, int64_t b0,
                              const int64_t *gwin, uint32_t *Y, const float *w, int32_t w_stride,
@@ -2183,14 +2229,14 @@ hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offs
 }
 
 hipError_t launch_sort_windows(int32_t n_fft, int32_t nrbg, int32_t nbb, int32_t n_slots, const uint32_t *win,
-                               const uint32_t *base, int2 *wsorted, hipStream_t st) {
+                               const uint32_t *base, int2 *wsorted, const WeightArgs &wa, hipStream_t st) {
     dim3 grid(nrbg * nbb, n_slots);
     const size_t lds = (size_t)kTileWaves * (4 * (size_t)sort_run_stride(wave_ffts(n_fft)) + 2 * (size_t)wave_ffts(n_fft));
     if (lds <= (size_t)kSortLdsBytes)
-        k_sort_windows<<<grid, kTileThreads, lds, st>>>(n_fft, nrbg * nbb, win, base, wsorted);
+        k_sort_windows<<<grid, kTileThreads, lds, st>>>(n_fft, nrbg * nbb, win, base, wsorted, wa);
     else
         k_sort_windows_long<<<grid, kTileThreads, (size_t)kSortPiece * sizeof(uint32_t), st>>>(n_fft, nrbg * nbb, win,
-                                                                                              base, wsorted);
+                                                                                              base, wsorted, wa);
     return hipGetLastError();
 }
 

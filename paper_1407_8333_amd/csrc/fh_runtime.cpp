@@ -805,32 +805,44 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
     a.n_sky = dirs.n;
     a.sky = b.sky;
     if (dirs.n) std::memcpy(a.sky_arg, dirs.arg, (size_t)24 * dirs.n);
-    HIP_OK(launch_setup(a, st));
     const int F = ctx->window_method == 2 ? front_ffts_per_block(pm->max_per_fft) : 0;
     const int32_t sm = ctx->doppler_mode;
     const double q = sm ? shift_reference_bins(ctx, pm, g) : 0.0;
+    const int ws_stride = w_stride == 0 ? 0 : 1;
+    WeightArgs wa{};  // the front writes the fixed-point weights itself, or leaves them to the sort
     if (b.rank && rank_bytes(ctx, pm, p, slots) > 0) {
         // (the first chunk is the largest; later ones find its table)
-        if (first) HIP_OK(launch_rank(pm->n_fft, pm->d_offsets, pm->d_bins, pm->k_min, pm->k_max, b.rank, st));
+        HIP_OK(launch_setup(a, pm->d_bins, pm->k_min, pm->k_max, first ? b.rank : nullptr, st));
         HIP_OK(launch_front_rank(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots, g->kf, g->b0,
-                                 b.gwin, b.Y, d_w, w_stride, b.ws, w_stride == 0 ? 0 : 1, b.wq, p.nrbg, p.nbb, p.W,
-                                 pm->k_min, pm->k_max, b.rank, b.win, sm, q, st));
-        HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, st));
-        return FH_OK;
+                                 b.gwin, b.Y, d_w, w_stride, b.ws, ws_stride, b.wq, p.nrbg, p.nbb, p.W, pm->k_min,
+                                 pm->k_max, b.rank, b.win, sm, q, st));
+    } else if (F > 0) {
+        FrontArgs r{};
+        r.n_peaks = pm->n_peaks;
+        r.b0 = g->b0;
+        r.bins = pm->d_bins;
+        r.v = pm->d_v;
+        r.sky = d_sky;
+        r.n_slots = slots;
+        r.kf = g->kf;
+        r.nrbg = p.nrbg;
+        r.nbb = p.nbb;
+        r.W = p.W;
+        r.F = F;
+        r.shift_mode = sm;
+        r.q = q;
+        r.Y = b.Y;
+        r.win = b.win;
+        HIP_OK(launch_setup_front(a, r, pm->max_per_fft, st));
+        if (weighted) wa = {d_w, b.ws, b.wq, w_stride, ws_stride};
+    } else {
+        HIP_OK(launch_setup(a, nullptr, 0, 0, nullptr, st));
+        HIP_OK(launch_prep(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots, g->kf, g->b0, b.Y64,
+                           d_w, w_stride, b.ws, ws_stride, b.wq, b.Y, sm, q, st));
+        HIP_OK(launch_windows(pm->n_fft, pm->d_offsets, b.Y64, pm->n_peaks, b.gwin, p.nrbg, p.nbb, p.W, g->kf, slots,
+                              b.win, ctx->window_method == 0 ? 0 : 1, st));
     }
-    if (F > 0) {
-        HIP_OK(launch_front(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots, g->kf,
-                            g->b0, b.gwin, b.Y, d_w, w_stride, b.ws, w_stride == 0 ? 0 : 1, b.wq, g->ns,
-                            p.nrbg, p.nbb, p.W, F, pm->max_per_fft, b.win, sm, q, st));
-        HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, st));
-        return FH_OK;
-    }
-    HIP_OK(launch_prep(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots,
-                       g->kf, g->b0, b.Y64, d_w, w_stride, b.ws, w_stride == 0 ? 0 : 1, b.wq, b.Y, sm, q,
-                       st));
-    HIP_OK(launch_windows(pm->n_fft, pm->d_offsets, b.Y64, pm->n_peaks, b.gwin, p.nrbg, p.nbb,
-                          p.W, g->kf, slots, b.win, ctx->window_method == 0 ? 0 : 1, st));
-    HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, st));
+    HIP_OK(launch_sort_windows(pm->n_fft, p.nrbg, p.nbb, slots, b.win, b.base, b.wsort, wa, st));
     return FH_OK;
 }
 
