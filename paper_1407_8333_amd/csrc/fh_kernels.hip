@@ -1826,116 +1826,141 @@ __global__ void __launch_bounds__(kMergeThreads) k_tiles_merge(TileArgs A) {
 // ----------------------------------------------------------------------------
 // candidates per (sky, sub-band)
 
-struct Best {
-    uint32_t val;
-    int32_t bin;
-    int32_t row;
-};
-
-__device__ __forceinline__ bool better(const Best &a, const Best &b) {
-    if (a.val != b.val) return a.val > b.val;
-    if (a.bin != b.bin) return a.bin < b.bin;
-    return a.row < b.row;
+// A column as a key: larger value first, then smaller bin (its row is the
+// smallest holding the value already); 0 is no column.
+__device__ __forceinline__ unsigned long long column_key(uint32_t val, int bin) {
+    return ((unsigned long long)val << 32) | (0xFFFFFFFFull - (unsigned)bin);
 }
+__device__ __forceinline__ int key_bin(unsigned long long k) { return (int)(0xFFFFFFFFu - (uint32_t)k); }
 
-__device__ Best block_best(Best m, Best *red) {
+__device__ unsigned long long block_best(unsigned long long m, unsigned long long *red) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        Best o2;
-        o2.val = __shfl_xor(m.val, o);
-        o2.bin = __shfl_xor(m.bin, o);
-        o2.row = __shfl_xor(m.row, o);
-        if (better(o2, m)) m = o2;
+        const unsigned long long o2 = __shfl_xor(m, o);
+        m = o2 > m ? o2 : m;
     }
     const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if ((threadIdx.x & 63) == 0) red[wave] = m;
     __syncthreads();
-    Best r = red[0];
-    for (int k = 1; k < nw; ++k)
-        if (better(red[k], r)) r = red[k];
-    __syncthreads();
+    unsigned long long r = red[0];
+    for (int k = 1; k < nw; ++k) r = red[k] > r ? red[k] : r;
     return r;
 }
 
-// Value and critical ratio of a cell holding `val` (a count, or a fixed-point
-// weighted sum when ws is given).
-__device__ __forceinline__ void cell_value(uint32_t val, int32_t n_fft, double theta,
-                                           const WeightStats *__restrict__ ws, float *value, float *cr) {
+// Mean and deviation of a cell's noise value, and the value's scale: a count,
+// or a fixed-point weighted sum when ws is given.
+struct CellStats {
+    double mu, sd;
+    float scale;
+};
+__device__ __forceinline__ CellStats cell_stats(int32_t n_fft, double theta, const WeightStats *__restrict__ ws) {
     const double p0 = exp(-theta) - exp(-2.0 * theta) + exp(-3.0 * theta) / 3.0;
-    double mu, sd, v;
+    CellStats c;
     if (ws != nullptr) {
         const WeightStats st = *ws;
-        const double scale = ldexp(1.0, -st.frac_bits);
-        mu = p0 * st.sum_w;
-        sd = sqrt(p0 * (1.0 - p0) * st.sum_w2);
-        v = (double)(float)((float)val * (float)scale);
+        c.scale = (float)ldexp(1.0, -st.frac_bits);
+        c.mu = p0 * st.sum_w;
+        c.sd = sqrt(p0 * (1.0 - p0) * st.sum_w2);
     } else {
-        mu = (double)n_fft * p0;
-        sd = sqrt((double)n_fft * p0 * (1.0 - p0));
-        v = (double)val;
+        c.scale = 1.0f;
+        c.mu = (double)n_fft * p0;
+        c.sd = sqrt((double)n_fft * p0 * (1.0 - p0));
     }
-    *value = (float)v;
-    *cr = (float)((v - mu) / sd);
+    return c;
 }
 
-__global__ void __launch_bounds__(256) k_select(const unsigned long long *__restrict__ colmax,
-                                                int32_t nf, fh_select sel, int32_t sky_base,
-                                                int32_t n_fft, const WeightStats *__restrict__ ws,
-                                                int32_t ws_stride, fh_candidate *__restrict__ out) {
-    __shared__ Best red[16];
+// Value and critical ratio of a cell holding `val`.
+__device__ __forceinline__ void cell_value(uint32_t val, const CellStats &c, bool weighted, float *value, float *cr) {
+    const double v = weighted ? (double)((float)val * c.scale) : (double)val;
+    *value = (float)v;
+    *cr = (float)((v - c.mu) / c.sd);
+}
+
+// One workgroup per (sub-band, direction).  Every column is read once: a thread
+// holds up to kHeld of them for the second search, all requested before the
+// first is used; only sub-bands of more than kHeld columns per thread read the
+// rest again.  Bound by latency: with 256 threads reading each column twice, one
+// at a time, the ten sub-bands of 8192 columns of a 1 Hz band took 24 us, now
+// launch_select.
+constexpr int kHeld = 8;
+
+__global__ void __launch_bounds__(1024) k_select(const unsigned long long *__restrict__ colmax,
+                                                 int32_t nf, fh_select sel, int32_t sky_base,
+                                                 int32_t n_fft, const WeightStats *__restrict__ ws,
+                                                 int32_t ws_stride, fh_candidate *__restrict__ out) {
+    __shared__ unsigned long long red[2][16];
     const int sb = blockIdx.x, slot = blockIdx.y;
     const int n_sb = gridDim.x;
     const int lo = sb * sel.width;
     const int hi = lo + sel.width < nf ? lo + sel.width : nf;
     const unsigned long long *cm = colmax + (int64_t)slot * nf;
-    const Best none = {0u, 0x7fffffff, 0x7fffffff};
-    Best m = none;
-    bool any = false;
-    for (int b = lo + threadIdx.x; b < hi; b += blockDim.x) {
-        const unsigned long long k = cm[b];
-        Best c = {(uint32_t)(k >> 32), b, (int32_t)(0xFFFFFFFFu - (uint32_t)k)};
-        if (!any || better(c, m)) { m = c; any = true; }
+    const int step = blockDim.x;
+    unsigned long long held[kHeld];
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const int b = lo + (int)threadIdx.x + u * step;
+        held[u] = b < hi ? cm[b] : 0ull;
     }
-    const Best b1 = block_best(m, red);
-    m = none;
-    any = false;
+    // (two threads write the two candidates; their cells' statistics are
+    // worked out while the columns are on their way)
+    CellStats stats{};
+    if (threadIdx.x < 2)
+        stats = cell_stats(n_fft, sel.theta, ws != nullptr ? ws + (int64_t)slot * ws_stride : nullptr);
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const int b = lo + (int)threadIdx.x + u * step;
+        const unsigned long long k = column_key((uint32_t)(held[u] >> 32), b);
+        m = b < hi && k > m ? k : m;
+    }
+    for (int b = lo + (int)threadIdx.x + kHeld * step; b < hi; b += step) {
+        const unsigned long long k = column_key((uint32_t)(cm[b] >> 32), b);
+        m = k > m ? k : m;
+    }
+    const unsigned long long b1 = block_best(m, red[0]);
+    unsigned long long b2 = 0ull;
     if (sel.sep >= 0) {
-        for (int b = lo + threadIdx.x; b < hi; b += blockDim.x) {
-            const int d = b > b1.bin ? b - b1.bin : b1.bin - b;
+        const int first = key_bin(b1);
+        m = 0ull;
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) {
+            const int b = lo + (int)threadIdx.x + u * step;
+            const int d = b > first ? b - first : first - b;
+            const unsigned long long k = column_key((uint32_t)(held[u] >> 32), b);
+            m = b < hi && d > sel.excl && k > m ? k : m;
+        }
+        for (int b = lo + (int)threadIdx.x + kHeld * step; b < hi; b += step) {
+            const int d = b > first ? b - first : first - b;
             if (d <= sel.excl) continue;
-            const unsigned long long k = cm[b];
-            Best c = {(uint32_t)(k >> 32), b, (int32_t)(0xFFFFFFFFu - (uint32_t)k)};
-            if (!any || better(c, m)) { m = c; any = true; }
+            const unsigned long long k = column_key((uint32_t)(cm[b] >> 32), b);
+            m = k > m ? k : m;
         }
+        b2 = block_best(m, red[1]);
     }
-    const Best b2 = block_best(m, red);
-    if (threadIdx.x == 0) {
-        fh_candidate *o = out + ((int64_t)(sky_base + slot) * n_sb + sb) * 2;
-        const Best bs[2] = {b1, b2};
-        for (int r = 0; r < 2; ++r) {
-            fh_candidate c;
-            c.sky = sky_base + slot;
-            c.subband = sb;
-            c.rank = r;
-            bool valid = bs[r].bin != 0x7fffffff && hi > lo;
-            if (r == 1) {
-                const int d = bs[1].bin > b1.bin ? bs[1].bin - b1.bin : b1.bin - bs[1].bin;
-                valid = valid && sel.sep >= 0 && d >= sel.sep;
-            }
-            c.valid = valid ? 1 : 0;
-            if (valid) {
-                c.bin = bs[r].bin;
-                c.row = bs[r].row;
-                cell_value(bs[r].val, n_fft, sel.theta, ws != nullptr ? ws + (int64_t)slot * ws_stride : nullptr,
-                           &c.value, &c.cr);
-            } else {
-                c.bin = -1;
-                c.row = -1;
-                c.value = 0.0f;
-                c.cr = 0.0f;
-            }
-            o[r] = c;
+    if (threadIdx.x < 2) {
+        const int r = threadIdx.x;
+        const unsigned long long best = r == 0 ? b1 : b2;
+        fh_candidate c;
+        c.sky = sky_base + slot;
+        c.subband = sb;
+        c.rank = r;
+        bool valid = best != 0ull;
+        if (r == 1 && valid) {
+            const int d = key_bin(b2) > key_bin(b1) ? key_bin(b2) - key_bin(b1) : key_bin(b1) - key_bin(b2);
+            valid = d >= sel.sep;
         }
+        c.valid = valid ? 1 : 0;
+        if (valid) {
+            c.bin = key_bin(best);
+            c.row = (int32_t)(0xFFFFFFFFu - (uint32_t)cm[c.bin]);
+            cell_value((uint32_t)(best >> 32), stats, ws != nullptr, &c.value, &c.cr);
+        } else {
+            c.bin = -1;
+            c.row = -1;
+            c.value = 0.0f;
+            c.cr = 0.0f;
+        }
+        out[((int64_t)(sky_base + slot) * n_sb + sb) * 2 + r] = c;
     }
 }
 
@@ -2324,7 +2349,12 @@ hipError_t launch_select(const unsigned long long *colmax, int32_t nf, int32_t n
                          hipStream_t st) {
     const int n_sb = (nf + sel.width - 1) / sel.width;
     dim3 grid(n_sb, n_slots);
-    k_select<<<grid, 256, 0, st>>>(colmax, nf, sel, sky_base, n_fft, ws, ws_stride, out);
+    // threads for four columns each where the launch leaves CUs idle, else for
+    // the eight that a thread holds (1120 sub-bands of 4096 columns: 25 and
+    // 11 us); a wider sub-band gets them all
+    const int held = (int64_t)n_sb * n_slots <= 256 ? kHeld / 2 : kHeld;
+    const int threads = std::min(1024, std::max(64, (std::min(sel.width, nf) + held * 64 - 1) / (held * 64) * 64));
+    k_select<<<grid, threads, 0, st>>>(colmax, nf, sel, sky_base, n_fft, ws, ws_stride, out);
     return hipGetLastError();
 }
 
@@ -2592,7 +2622,7 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
         x.rank = 0;
         x.bin = (int32_t)(at / (uint32_t)ns);
         x.row = (int32_t)(at % (uint32_t)ns);
-        cell_value((uint32_t)(k >> 32), n_fft, theta, ws, &x.value, &x.cr);
+        cell_value((uint32_t)(k >> 32), cell_stats(n_fft, theta, ws), ws != nullptr, &x.value, &x.cr);
         x.valid = 1;
         out[2 * ((int64_t)cand * n_dir + dir)] = x;
     }

@@ -675,3 +675,26 @@ def test_window_tables_agree_with_searches(ctx, kf, k_lo, span, density, min_gap
     np.testing.assert_array_equal(got[0][0][2].cpu().numpy(), ref.max(0).astype(np.float32))
     np.testing.assert_array_equal(got[0][1][2].cpu().numpy(), ref.argmax(0))
     dpm.release()
+
+
+@pytest.mark.parametrize("width", [1, 5, 64, 255, 257, 2047, 2049, 8191, 8192, 8193, 20000])
+def test_selection_at_the_edges_of_the_held_columns(ctx, width):
+    """Sub-bands around the columns that a workgroup's threads hold, on a map
+    of few values (ties in bin and row), with exclusion and separation."""
+    import torch
+    from paper_1407_8333_amd import api
+    rng = synth.rng_for(width)
+    n, t_fft = 30, 1024.0
+    pm = synth.random_peakmap(n, t_fft, 60000, 62100, 0.05, rng)
+    dfdot = 1.0 / (t_fft * 0.5 * n * t_fft)
+    grid = synth.Grid(kf=10, b0=600300, nf=20000, ns=6, fdot0=-3 * dfdot, dfdot=dfdot, t0=0.5 * (pm.t[0] + pm.t[-1]))
+    sky = synth.sky_uniform(1, rng)
+    ref = oracle.hough_map(pm, grid, sky[0])
+    dpm = ctx.upload(pm)
+    for excl, sep in ((4, 8), (0, 0), (width, 8), (4, -1)):
+        sel = synth.Selection(width=width, excl=excl, sep=sep)
+        raw = api.fh_hough_candidates(ctx, dpm, sky, grid, sel)
+        torch.cuda.synchronize()
+        idx, val = oracle.candidates(ref, width, excl, sep)
+        _check_candidates(api.decode_candidates(raw), 0, idx, val, n, sel.theta)
+    dpm.release()
