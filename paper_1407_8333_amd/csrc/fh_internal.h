@@ -202,8 +202,9 @@ hipError_t launch_pm_scan(int32_t n_fft, const int32_t *counts, int64_t *offsets
 hipError_t launch_pm_pack(int32_t n_fft, int32_t cap, const int32_t *scratch, const int64_t *offsets,
                           int32_t *bins, hipStream_t st);
 // peaks of each FFT with natural bin in [k_lo, k_hi) into a new CSR
+// (tv: times [N] and velocities [N][3], copied to tv_out unless that is nullptr)
 hipError_t launch_slice(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_lo, int32_t k_hi,
-                        int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
+                        const double *tv, double *tv_out, int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
                         int64_t *meta, hipStream_t st);
 // one coarse candidate's refined grid: fine bin 0, first row's spin-down, shift
 // reference (shift mode), largest distance of a direction from the middle one,
@@ -230,7 +231,8 @@ hipError_t launch_gross_hist(int32_t n_fft, const int64_t *offsets, const int32_
                              double t_fft, const fh_gross &geo, int32_t *hist, hipStream_t st);
 // filter of the peaks of a peakmap (mode 0: gross cells over thr; mode 1:
 // natural bins whose statistic exceeds thr); phase 0 counts survivors per
-// FFT and scans them into out_offsets, phase 1 packs the survivors
+// FFT, copies times and velocities and scans the counts into out_offsets,
+// phase 1 packs the survivors
 struct FilterSpec {
     int mode;
     const double *t;
@@ -243,7 +245,7 @@ struct FilterSpec {
     double thr;
 };
 hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const FilterSpec &spec,
-                         int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, int64_t *meta,
+                         const double *tv, double *tv_out, int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, int64_t *meta,
                          hipStream_t st);
 hipError_t launch_bin_counts(int32_t n_fft, int64_t n_peaks, const int64_t *offsets, const int32_t *bins,
                              int32_t k_lo, int32_t k_hi, int32_t *counts, hipStream_t st);

@@ -2372,9 +2372,12 @@ namespace {
 
 __global__ void k_slice_count(int32_t n_fft, const int64_t *__restrict__ offsets,
                               const int32_t *__restrict__ bins, int32_t k_lo, int32_t k_hi,
+                              const double *__restrict__ tv, double *__restrict__ tv_out,
                               int64_t *__restrict__ first, int32_t *__restrict__ counts) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_fft) return;
+    if (tv_out != nullptr)  // the head's times [N] and velocities [N][3]
+        for (int c = 0; c < 4; ++c) tv_out[(int64_t)c * n_fft + i] = tv[(int64_t)c * n_fft + i];
     const int64_t p0 = offsets[i], p1 = offsets[i + 1];
     int64_t a = p0, b = p1;
     while (a < b) {  // first bin >= k_lo
@@ -2782,10 +2785,13 @@ __global__ void __launch_bounds__(1024) k_gross_rows(int32_t n_fft, const int64_
 // one wave per FFT: surviving peaks counted
 __global__ void __launch_bounds__(256) k_filter_count(int32_t n_fft, const int64_t *__restrict__ offsets,
                                                       const int32_t *__restrict__ bins, PeakFilter f,
+                                                      const double *__restrict__ tv, double *__restrict__ tv_out,
                                                       int32_t *__restrict__ counts) {
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= n_fft) return;
+    // the head's times [N] and velocities [N][3]
+    if (lane < 4) tv_out[(int64_t)lane * n_fft + i] = tv[(int64_t)lane * n_fft + i];
     const int ct = f.mode == 0 ? gross_time_cell(f, i) : 0;
     int kept = 0;
     for (int64_t p = offsets[i] + lane; p < offsets[i + 1]; p += 64) kept += filter_drop(f, ct, bins[p]) ? 0 : 1;
@@ -3053,9 +3059,9 @@ hipError_t launch_colmax_decode(const unsigned long long *colmax, int32_t nf, in
 }
 
 hipError_t launch_slice(int32_t n_fft, const int64_t *offsets, const int32_t *bins, int32_t k_lo, int32_t k_hi,
-                        int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
+                        const double *tv, double *tv_out, int64_t *first, int32_t *counts, int64_t *out_offsets, int32_t *out_bins,
                         int64_t *meta, hipStream_t st) {
-    k_slice_count<<<grid_for(n_fft, 256), 256, 0, st>>>(n_fft, offsets, bins, k_lo, k_hi, first, counts);
+    k_slice_count<<<grid_for(n_fft, 256), 256, 0, st>>>(n_fft, offsets, bins, k_lo, k_hi, tv, tv_out, first, counts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets, meta);
@@ -3134,7 +3140,7 @@ hipError_t launch_gross_hist(int32_t n_fft, const int64_t *offsets, const int32_
 }
 
 hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *bins, const FilterSpec &spec,
-                         int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, int64_t *meta,
+                         const double *tv, double *tv_out, int32_t *counts, int64_t *out_offsets, int32_t *out_bins, int phase, int64_t *meta,
                          hipStream_t st) {
     PeakFilter f{};
     f.mode = spec.mode;
@@ -3155,7 +3161,7 @@ hipError_t launch_filter(int32_t n_fft, const int64_t *offsets, const int32_t *b
     f.thr = spec.thr;
     if (n_fft == 0) return hipSuccess;
     if (phase == 0) {
-        k_filter_count<<<(n_fft + 3) / 4, 256, 0, st>>>(n_fft, offsets, bins, f, counts);
+        k_filter_count<<<(n_fft + 3) / 4, 256, 0, st>>>(n_fft, offsets, bins, f, tv, tv_out, counts);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         k_pm_scan<<<1, 1024, 0, st>>>(n_fft, counts, out_offsets, meta);

@@ -239,11 +239,12 @@ struct fh_ctx {
     DevBuf err;
     // refinement: sliced peakmap (volumes larger than the LDS) and per-call scratch
     DevBuf rf_offsets, rf_bins, rf_first, rf_counts, rf_cands, rf_aux;
-    // cleaning: robust-statistic histogram, its rank sum and results
-    DevBuf cl_hist, cl_s2, cl_out;
-    // peakmap construction: row scratch, peaks per FFT, {total, largest} of the
-    // counts; pinned memory for small results and staged times and velocities
-    DevBuf pm_rows, pm_counts, pm_meta;
+    // cleaning: robust-statistic histogram and its rank sum
+    DevBuf cl_hist, cl_s2;
+    // peakmap construction: row scratch and peaks per FFT; pinned memory for
+    // small results, which kernels write in place (a copy of their own cost
+    // 8 us), and for staged times and velocities
+    DevBuf pm_rows, pm_counts;
     PinnedBuf h_small, h_stage;
     BlockPool blocks;
     // autotuned tile width per problem shape (shared by weighted and
@@ -326,6 +327,35 @@ fh_status check_ctx(fh_ctx *ctx) {
     return FH_OK;
 }
 
+// Checks the times and velocities of pm->n_fft FFTs and takes their extremes
+// into pm: one pass without branches, and a second one that names the first
+// bad FFT.
+fh_status check_times(fh_peakmap *pm, const double *t, const double *v) {
+    const int32_t N = pm->n_fft;
+    double t_min = t[0], t_max = t[0], v2 = 0.0, sum = 0.0;
+    for (int32_t i = 0; i < N; ++i) {
+        const double *vi = v + 3 * (int64_t)i;
+        const double n2 = vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2];
+        t_min = t[i] < t_min ? t[i] : t_min;
+        t_max = t[i] > t_max ? t[i] : t_max;
+        v2 = n2 > v2 ? n2 : v2;
+        sum += 0.0 * t[i] + 0.0 * n2;  // NaN as soon as a value is not finite
+    }
+    pm->t_min = t_min;
+    pm->t_max = t_max;
+    pm->v_max = std::sqrt(v2);
+    if (sum == 0.0 && pm->v_max < 1e-2) return FH_OK;
+    for (int32_t i = 0; i < N; ++i) {
+        if (!std::isfinite(t[i])) return fail(FH_E_INVALID, "t[%d] is not finite", i);
+        const double *vi = v + 3 * (int64_t)i;
+        if (!std::isfinite(vi[0]) || !std::isfinite(vi[1]) || !std::isfinite(vi[2]))
+            return fail(FH_E_INVALID, "v[%d] is not finite", i);
+        const double vn = std::sqrt(vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2]);
+        if (vn >= 1e-2) return fail(FH_E_INVALID, "|v[%d]| = %g >= 1e-2", i, vn);
+    }
+    return FH_OK;
+}
+
 // The head block of a peakmap of pm->n_fft FFTs.
 bool alloc_head(fh_ctx *ctx, fh_peakmap *pm) {
     const size_t N = (size_t)pm->n_fft;
@@ -354,12 +384,11 @@ fh_peakmap *like(const fh_peakmap *pm) {
     return q;
 }
 
-// {total, largest} of a scan's counts, read back from ctx->pm_meta; waits for
-// the stream.
+// {total, largest} of a scan's counts, which the scan writes to pinned memory;
+// waits for the stream.
 hipError_t read_meta(fh_ctx *ctx, hipStream_t st, int64_t *total, int32_t *most) {
-    int64_t *h = (int64_t *)ctx->h_small.ptr;
-    hipError_t e = hipMemcpyAsync(h, ctx->pm_meta.ptr, 16, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const int64_t *h = (const int64_t *)ctx->h_small.ptr;
+    const hipError_t e = hipStreamSynchronize(st);
     if (e == hipSuccess) {
         *total = h[0];
         *most = (int32_t)h[1];
@@ -1054,16 +1083,15 @@ fh_status filter_peakmap(fh_ctx *ctx, const fh_peakmap *pm, const FilterSpec &sp
         fh_peakmap_release(ctx, q);
         return fail(FH_E_NOMEM, "device allocation for the cleaned peakmap failed");
     }
-    // times and velocities lie next to each other in both heads
-    hipError_t e = hipMemcpyAsync(q->d_t, pm->d_t, 32 * (size_t)N, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess)
-        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, (int32_t *)ctx->rf_counts.ptr, q->d_offsets, nullptr, 0,
-                          (int64_t *)ctx->pm_meta.ptr, st);
+    // (the count also copies the times and velocities)
+    hipError_t e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, pm->d_t, q->d_t, (int32_t *)ctx->rf_counts.ptr,
+                                 q->d_offsets, nullptr, 0, (int64_t *)ctx->h_small.ptr, st);
     int64_t P = 0;
     if (e == hipSuccess) e = read_meta(ctx, st, &P, &q->max_per_fft);
     if (e == hipSuccess && !alloc_bins(ctx, q, P)) e = hipErrorOutOfMemory;
     if (e == hipSuccess)
-        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, nullptr, q->d_offsets, q->d_bins, 1, nullptr, st);
+        e = launch_filter(N, pm->d_offsets, pm->d_bins, spec, nullptr, nullptr, nullptr, q->d_offsets, q->d_bins, 1,
+                          nullptr, st);
     if (e != hipSuccess) {
         fh_peakmap_release(ctx, q);
         return fail(e == hipErrorOutOfMemory ? FH_E_NOMEM : FH_E_DEVICE, "filtering the peakmap failed: %s",
@@ -1102,17 +1130,14 @@ fh_status fh_ctx_create(int32_t device, fh_ctx **out) {
     c->device = device;
     c->n_cu = prop.multiProcessorCount;
     fh_status s = c->err.ensure(4, nullptr);
-    if (!s) s = c->pm_meta.ensure(16, nullptr);
     if (!s) s = c->h_small.ensure(256, nullptr);
     if (s) {
         c->err.release();
-        c->pm_meta.release();
         delete c;
         return s;
     }
     if (hipMemset(c->err.ptr, 0, 4) != hipSuccess) {
         c->err.release();
-        c->pm_meta.release();
         c->h_small.release();
         delete c;
         return fail(FH_E_DEVICE, "hipMemset failed");
@@ -1133,8 +1158,7 @@ void fh_ctx_destroy(fh_ctx *ctx) {
     ctx->main_ws.release();
     ctx->err.release();
     for (DevBuf *b : {&ctx->rf_offsets, &ctx->rf_bins, &ctx->rf_first, &ctx->rf_counts,
-                      &ctx->rf_cands, &ctx->rf_aux, &ctx->cl_hist, &ctx->cl_s2, &ctx->cl_out, &ctx->pm_rows, &ctx->pm_counts,
-                      &ctx->pm_meta})
+                      &ctx->rf_cands, &ctx->rf_aux, &ctx->cl_hist, &ctx->cl_s2, &ctx->pm_rows, &ctx->pm_counts})
         b->release();
     ctx->h_small.release();
     ctx->h_stage.release();
@@ -1201,24 +1225,15 @@ fh_status fh_peakmap_upload(fh_ctx *ctx, const fh_peakmap_desc *d, void *stream,
     pm->n_fft = N;
     pm->n_peaks = d->n_peaks;
     pm->t_fft = d->t_fft;
-    pm->t_min = d->t[0];
-    pm->t_max = d->t[0];
+    if ((s = check_times(pm, d->t, d->v))) {
+        delete pm;
+        return s;
+    }
     pm->k_min = 0x7fffffff;
     pm->k_max = 0;
     for (int32_t i = 0; i < N; ++i) {
         const int64_t a = d->offsets[i], e = d->offsets[i + 1];
         if (e < a) { delete pm; return fail(FH_E_INVALID, "offsets decrease at FFT %d", i); }
-        if (!std::isfinite(d->t[i])) { delete pm; return fail(FH_E_INVALID, "t[%d] is not finite", i); }
-        pm->t_min = std::min(pm->t_min, d->t[i]);
-        pm->t_max = std::max(pm->t_max, d->t[i]);
-        const double *v = d->v + 3 * (int64_t)i;
-        if (!std::isfinite(v[0]) || !std::isfinite(v[1]) || !std::isfinite(v[2])) {
-            delete pm;
-            return fail(FH_E_INVALID, "v[%d] is not finite", i);
-        }
-        const double vn = std::sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-        if (vn >= 1e-2) { delete pm; return fail(FH_E_INVALID, "|v[%d]| = %g >= 1e-2", i, vn); }
-        pm->v_max = std::max(pm->v_max, vn);
         pm->max_per_fft = std::max<int32_t>(pm->max_per_fft, (int32_t)(e - a));
         if (e == a) continue;
         // ascending bins: the first is the least, the last the largest
@@ -1280,19 +1295,9 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
     fh_peakmap *pm = new fh_peakmap();
     pm->n_fft = n_fft;
     pm->t_fft = t_fft;
-    pm->t_min = pm->t_max = t[0];
-    for (int32_t i = 0; i < n_fft; ++i) {
-        if (!std::isfinite(t[i])) { delete pm; return fail(FH_E_INVALID, "t[%d] is not finite", i); }
-        pm->t_min = std::min(pm->t_min, t[i]);
-        pm->t_max = std::max(pm->t_max, t[i]);
-        const double *vi = v + 3 * (int64_t)i;
-        if (!std::isfinite(vi[0]) || !std::isfinite(vi[1]) || !std::isfinite(vi[2])) {
-            delete pm;
-            return fail(FH_E_INVALID, "v[%d] is not finite", i);
-        }
-        const double vn = std::sqrt(vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2]);
-        if (vn >= 1e-2) { delete pm; return fail(FH_E_INVALID, "|v[%d]| = %g >= 1e-2", i, vn); }
-        pm->v_max = std::max(pm->v_max, vn);
+    if ((s = check_times(pm, t, v))) {
+        delete pm;
+        return s;
     }
     hipStream_t st = (hipStream_t)stream;
     const int32_t cap = n_bins / 2 + 1;  // strict local maxima are never adjacent
@@ -1317,7 +1322,7 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
     int32_t *rows_buf = (int32_t *)ctx->pm_rows.ptr, *counts = (int32_t *)ctx->pm_counts.ptr;
     int64_t P = 0;
     hipError_t e = launch_pm_rows(n_fft, n_bins, ld, d_sp, d_sar, k0, theta, cap, rows_buf, counts, st);
-    if (e == hipSuccess) e = launch_pm_scan(n_fft, counts, pm->d_offsets, (int64_t *)ctx->pm_meta.ptr, st);
+    if (e == hipSuccess) e = launch_pm_scan(n_fft, counts, pm->d_offsets, (int64_t *)ctx->h_small.ptr, st);
     if (e == hipSuccess) e = hipMemcpyAsync(pm->d_t, ctx->h_stage.ptr, b_t + b_v, hipMemcpyHostToDevice, st);
     const hipError_t e2 = read_meta(ctx, st, &P, &pm->max_per_fft);
     if (e == hipSuccess) e = e2;
@@ -1400,10 +1405,9 @@ fh_status fh_peakmap_slice(fh_ctx *ctx, const fh_peakmap *pm, int32_t k_lo, int3
         return fail(FH_E_NOMEM, "device allocation for the sliced peakmap failed");
     }
     q->bytes = (int64_t)(b_off + b_bins + 32 * (size_t)N);
-    hipError_t e = hipMemcpyAsync(q->d_t, pm->d_t, 32 * (size_t)N, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess)
-        e = launch_slice(N, pm->d_offsets, pm->d_bins, k_lo, k_hi, (int64_t *)ctx->rf_first.ptr,
-                         (int32_t *)ctx->rf_counts.ptr, q->d_offsets, q->d_bins, (int64_t *)ctx->pm_meta.ptr, st);
+    hipError_t e = launch_slice(N, pm->d_offsets, pm->d_bins, k_lo, k_hi, pm->d_t, q->d_t, (int64_t *)ctx->rf_first.ptr,
+                                (int32_t *)ctx->rf_counts.ptr, q->d_offsets, q->d_bins, (int64_t *)ctx->h_small.ptr,
+                                st);
     // exact peak count and longest FFT of the slice (the allocation keeps the bound)
     if (e == hipSuccess) e = read_meta(ctx, st, &q->n_peaks, &q->max_per_fft);
     if (e != hipSuccess) {
@@ -1573,7 +1577,7 @@ fh_status fh_refine(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_cand, const fh_
         if ((s = ensure_workspace(ctx, &sub, &grids[0], p, n_dir, 1, weighted, st, b))) return s;
         fh_select sel{nf, nf, -1, o->theta};
         for (int c = 0; c < n_cand; ++c) {
-            HIP_OK(launch_slice(N, pm->d_offsets, pm->d_bins, klo[c], khi[c], (int64_t *)ctx->rf_first.ptr,
+            HIP_OK(launch_slice(N, pm->d_offsets, pm->d_bins, klo[c], khi[c], nullptr, nullptr, (int64_t *)ctx->rf_first.ptr,
                                 (int32_t *)ctx->rf_counts.ptr, sub.d_offsets, sub.d_bins, nullptr, st));
             ChunkBufs bc = b;
             bc.sky = d_sky + 3 * (size_t)c * n_dir;
@@ -1639,12 +1643,11 @@ fh_status fh_robust_stats(fh_ctx *ctx, const int32_t *d_x, int32_t n, int32_t x_
     if (x_max < 0 || x_max > (1 << 28)) return fail(FH_E_INVALID, "x_max=%d outside 0..2^28", x_max);
     hipStream_t st = (hipStream_t)stream;
     if ((s = ctx->cl_hist.ensure(4 * (2 * (size_t)x_max + 1), st)) || (s = ctx->cl_s2.ensure(8, st)) ||
-        (s = ctx->cl_out.ensure(24, st)) || (s = ctx->err.ensure(4, st)))
+        (s = ctx->err.ensure(4, st)))
         return s;
-    HIP_OK(launch_robust(d_x, n, x_max, (int32_t *)ctx->cl_hist.ptr, (int64_t *)ctx->cl_s2.ptr,
-                         (double *)ctx->cl_out.ptr, (int32_t *)ctx->err.ptr, st));
     double *h = (double *)ctx->h_small.ptr;  // m1, m2, error flag
-    HIP_OK(hipMemcpyAsync(h, ctx->cl_out.ptr, 24, hipMemcpyDeviceToHost, st));
+    HIP_OK(launch_robust(d_x, n, x_max, (int32_t *)ctx->cl_hist.ptr, (int64_t *)ctx->cl_s2.ptr, h,
+                         (int32_t *)ctx->err.ptr, st));
     HIP_OK(hipStreamSynchronize(st));
     if (h[2] != 0.0) return fail(FH_E_INVALID, "a value lies outside [0, x_max=%d]", x_max);
     out[0] = h[0];

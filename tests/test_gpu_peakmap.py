@@ -118,3 +118,25 @@ def test_blocks_of_released_peakmaps_are_handed_on_safely():
                 np.testing.assert_array_equal(got[1], bins)
         for p, _ in live:
             p.release()
+
+
+@pytest.mark.parametrize("what,value", [("t", np.nan), ("t", np.inf), ("v", np.nan), ("v", -np.inf), ("v", 1e-2),
+                                        ("v", 1e200)])
+@pytest.mark.parametrize("at", [0, 36])
+def test_bad_times_and_velocities_are_refused(what, value, at):
+    import torch
+    from paper_1407_8333_amd import api
+    from paper_1407_8333_amd._lib import FH_E_INVALID, FHError
+    n = 37
+    t, v = synth.fft_times(n, 1024.0), np.zeros((n, 3))
+    if what == "t":
+        t[at] = value
+    else:
+        v[at, 1] = value
+    pm = synth.Peakmap(1024.0, t, v, np.arange(n + 1, dtype=np.int64), np.full(n, 5, np.int32))
+    with api.Context(0) as ctx:
+        for build in (lambda: ctx.upload(pm),
+                      lambda: api.DevicePeakmap.from_spectra(ctx, torch.ones((n, 8), device="cuda"), 5, 2.5, t, v, 1024.0)):
+            with pytest.raises(FHError) as e:
+                build()
+            assert e.value.status == FH_E_INVALID and "%s[%d]" % (what, at) in str(e.value)
