@@ -67,7 +67,7 @@ struct TileArgs {
     const uint32_t *Y;            // [slot][P] low words of the stripe edges (2^-16 fine bins)
     const int2 *win;              // [slot][nrbg][nbb][win_stride(N)] sorted windows
     const uint2 *rec;             // [nrb][N] low word of G_{i,s0} and the rows' residual codes
-    const uint32_t *step;         // [N][16] floor(j q_i / 2^16): the rows' linear steps
+    const uint32_t *step;         // [N][16] 1 - floor(j q_i / 2^16): the rows' linear steps
     const uint32_t *wq;           // [slot][N] fixed-point weights or nullptr
     const WeightStats *ws;        // [slot * ws_stride] or nullptr
     int32_t ws_stride;            // 0: one shared weight vector, 1: one per slot

@@ -84,7 +84,7 @@ __device__ __forceinline__ int64_t row_shift(double tau, double S, double fdot0,
 // of j's exact step, and each G within 0.5 of its exact value, so
 //   c_ij = G_{i,s0+j} - G_{i,s0} - floor(j q_i / 2^16)  lies in {-1, 0, 1, 2}.
 // Tables (all sky independent):
-//   step[i][j]  = low word of floor(j q_i / 2^16)                  [N][16]
+//   step[i][j]  = low word of 1 - floor(j q_i / 2^16)              [N][16]
 //   rec[rb][i]  = (low word of G_{i,s0}, sum_j (c_ij + 1) << 2j)   [nrb][N]
 //   gwin[i][g]  = (G_is at the first and at the last grid row of row
 //                 group g), for the peak windows                   [N][nrbg][2]
@@ -114,7 +114,7 @@ __device__ __forceinline__ void shift_tables(const SetupArgs &A, int64_t first, 
             const int64_t c = row_shift(tau, A.S, A.fdot0, A.dfdot, s0 + j) - g0 - lin;
             bad = bad || c < -1 || c > 2;
             codes |= (uint32_t)((c + 1) & 3) << (2 * j);
-            if (rb == 0) A.step[(int64_t)i * kTileRows + j] = (uint32_t)(uint64_t)lin;
+            if (rb == 0) A.step[(int64_t)i * kTileRows + j] = 1u - (uint32_t)(uint64_t)lin;
         }
         A.rec[(int64_t)rb * n_fft + i] = make_uint2((uint32_t)(uint64_t)g0, codes);
         if (bad) atomicOr(A.err, 2);
@@ -816,6 +816,11 @@ __device__ __forceinline__ int big_window_rank(int c, int e, int per, Size size)
     return pos;
 }
 
+// A sorted entry as the tiles take it: the byte offset of the window's first
+// stripe edge in the slot's edges, and FFT place in the run << 16 | peak
+// count.  Entries past the last FFT (no peaks) name place 0, so that their
+// table reads stay inside the tables.
+
 // Words between the staged runs: 4 modulo 16, so that the four quarters of 16
 // entries that a wave stores together lie in 64 banks.
 __host__ __device__ inline int sort_run_stride(int per) { return per + ((4 - per) & 15); }
@@ -909,7 +914,8 @@ __global__ void __launch_bounds__(kTileThreads) k_sort_windows(int32_t n_fft, in
             const int pos = c >= kSortBuckets - 1
                                 ? big_window_rank(c, e, per, [&](int j) { return window_size(src[j]); })
                                 : h[kSortBuckets - 1 - c] + rk[e];
-            dst[pos] = make_int2((int)(b[u] + (w[u] & 0xFFFFu)), (e << 16) | c);
+            const int place = e * kTileWaves + wave < n_fft ? e : 0;
+            dst[pos] = make_int2((int)((b[u] + (w[u] & 0xFFFFu)) << 2), (place << 16) | c);
         }
     }
 }
@@ -958,7 +964,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sort_windows_long(int32_t n_ff
                     pos = atomicAdd(&h[kSortBuckets - 1 - c], 1);
                 const int i = e * kTileWaves + wave;
                 const uint32_t b = i < n_fft ? base[wave * per + e] : 0u;
-                dst[pos] = make_int2((int)(b + (w & 0xFFFFu)), (e << 16) | c);
+                dst[pos] = make_int2((int)((b + (w & 0xFFFFu)) << 2), ((i < n_fft ? e : 0) << 16) | c);
             }
         }
         __syncthreads();
@@ -994,70 +1000,61 @@ __device__ __forceinline__ void lds_barrier() {
 // conflicts with itself (the four groups of a wave can still collide on the
 // bank halves that their columns map to).
 // One step of the accumulation.  Lane (group g, row j) adds the stripe of the
-// peak held by lane (g, U): its edge, already made relative to the tile
-// (v = Y - c0 kQ - G_{i,s0}, exact in 32 bits for every peak of a window),
-// reaches the group's 16 lanes through DPP row_newbcast:U fused into the add
-// of the lane's row term t = G_{i,s0} - G_{i,s0+j}.  col = floor((v + t) / kQ) is the tile
-// column of the stripe start in row s0 + j; columns outside
-// [0, W + K_f - 1) (negative ones wrap to large unsigned values) go to the
-// group's dump column.
-template <int U>
-__device__ __forceinline__ uint32_t stripe_word(uint32_t v, uint32_t t, uint32_t dump, uint32_t lane_off) {
-    const uint32_t b = __builtin_amdgcn_update_dpp(0u, v, 0x150 + U, 0xF, 0xF, true);
-    // the column is the upper half-word (negative columns read as 2^15 and
-    // more); one SDWA min takes it and clamps it to the dump column
-    const uint16_t col = (uint16_t)((b + t) >> kFrac);
-    const uint32_t cu = col < (uint16_t)dump ? col : (uint16_t)dump;
-    return cu * kTileRows + lane_off;
-}
-
-// Steps U .. E-1, two at a time (independent address chains interleave).
-template <int U, int E>
-__device__ __forceinline__ void stripe_run(uint32_t v, uint32_t t, uint32_t dump,
-                                           uint32_t lane_off, uint32_t val,
-                                           uint32_t *__restrict__ lds) {
-    if constexpr (U + 1 < E) {
-        const uint32_t a0 = stripe_word<U>(v, t, dump, lane_off);
-        const uint32_t a1 = stripe_word<U + 1>(v, t, dump, lane_off);
-        atomicAdd(lds + a0, val);
-        atomicAdd(lds + a1, val);
-        stripe_run<U + 2, E>(v, t, dump, lane_off, val, lds);
-    } else if constexpr (U < E) {
-        atomicAdd(lds + stripe_word<U>(v, t, dump, lane_off), val);
-    }
-}
-
-// A chunk of up to 16 peaks of each group's FFT occupies the lanes named by
-// a 16-bit pattern m(n), n = min(peaks left in the block's largest window,
-// 16), built from fixed runs so that each run is one straight sequence of
-// steps: lanes 0-7 (n & 8), 8-11 (n & 4), 12-13 (n & 2), 14 (n & 1); n = 16
-// uses all 16.  Pattern lane j of a group holds its FFT's peak q (plus the
-// chunk's first peak), q = the number of pattern lanes below j; lanes
-// outside the pattern take part in the steps only as rows.
-__device__ __forceinline__ uint32_t chunk_pattern(int n) {
-    if (n >= 16) return 0xFFFFu;
-    return ((1u << (n & 8)) - 1u) | (((1u << (n & 4)) - 1u) << 8) |
-           (((1u << (n & 2)) - 1u) << 12) | (((1u << (n & 1)) - 1u) << 14);
-}
-
-__device__ __forceinline__ void stripe_chunk(uint32_t m, uint32_t v, uint32_t t, uint32_t dump,
-                                             uint32_t lane_off, uint32_t val,
-                                             uint32_t *__restrict__ lds) {
-    if (m & 0x00FFu) stripe_run<0, 8>(v, t, dump, lane_off, val, lds);
-    if (m & 0x0F00u) stripe_run<8, 12>(v, t, dump, lane_off, val, lds);
-    if (m & 0x3000u) stripe_run<12, 14>(v, t, dump, lane_off, val, lds);
-    if (m & 0x4000u) stripe_run<14, 15>(v, t, dump, lane_off, val, lds);
-    if (m & 0x8000u) stripe_run<15, 16>(v, t, dump, lane_off, val, lds);
+// peak held by lane (g, U): its edge v = Y reaches the group's 16 lanes
+// through DPP row_newbcast:U fused into the add of the lane's row term
+// t = -c0 kQ - G_{i,s0+j} (the sum is exact in 32 bits for every peak of a
+// window).  The upper half-word of the sum is the tile column of the stripe
+// start in row s0 + j; columns outside [0, W + K_f - 1) (negative ones read
+// as 2^15 and more) go to the group's dump column.
+//
+// stripe_steps runs steps n-1 .. 0 of up to 32 peaks of each group's FFT:
+// lane j of a group holds the edges of its peaks j (v0) and 16 + j (v1).  The
+// steps are one straight sequence, entered by a computed jump n steps before
+// its end, so a block of four FFTs takes one jump.  With the peaks in
+// patterns of 8, 4, 2, 1 and 1 lanes and a scalar test before each run a block
+// issued 14 branches, 36 scalar and 98 vector instructions for its ~20 steps;
+// now 3, about 30 and 80.  The step itself was never the limit (alone, its
+// three vector instructions and its LDS update take 4.13 clocks per CU, the
+// update's own 4.1): the branches were, each one a gap in its wave's issue,
+// and with four waves per SIMD the gaps reached the LDS.  Tile kernel, 112
+// directions of the 256 Hz batch: 21.7 -> 18.7 ms, 69 -> 80 % of the LDS
+// rate; 13 directions of a 1162-row grid 5.36 -> 4.48 ms; 24 of a 10 Hz band
+// 11.6 -> 10.7 ms.  The LDS updates are outside the compiler's count: who
+// waits for them says so.
+#define FH_STEP(U, V)                                                                       \
+    "v_add_u32_dpp %[a], " V ", %[t] row_newbcast:" #U " row_mask:0xf bank_mask:0xf\n"      \
+    "v_min_u32_sdwa %[a], %[a], %[dump] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n" \
+    "v_lshl_add_u32 %[a], %[a], 6, %[lane]\n"                                               \
+    "ds_add_u32 %[a], %[val]\n"
+#define FH_STEPS16(V)                                                                       \
+    FH_STEP(15, V) FH_STEP(14, V) FH_STEP(13, V) FH_STEP(12, V) FH_STEP(11, V) FH_STEP(10, V) \
+    FH_STEP(9, V) FH_STEP(8, V) FH_STEP(7, V) FH_STEP(6, V) FH_STEP(5, V) FH_STEP(4, V)      \
+    FH_STEP(3, V) FH_STEP(2, V) FH_STEP(1, V) FH_STEP(0, V)
+__device__ __forceinline__ void stripe_steps(int n, uint32_t v0, uint32_t v1, uint32_t t, uint32_t dump,
+                                             uint32_t lane_addr, uint32_t val) {
+    const int skip = 12 + (32 - n) * 32;  // bytes from the instruction after s_getpc; 0 <= n <= 32
+    uint32_t a;
+    asm volatile(
+        "s_getpc_b64 s[98:99]\n"
+        "s_add_u32 s98, s98, %[skip]\n"
+        "s_addc_u32 s99, s99, 0\n"
+        "s_setpc_b64 s[98:99]\n"
+        ".Lsteps%=:\n" FH_STEPS16("%[v1]") FH_STEPS16("%[v0]")
+        ".if (. - .Lsteps%=) != 1024\n.error \"a step is not 32 bytes\"\n.endif\n"
+        : [a] "=&v"(a)
+        : [skip] "s"(skip), [v0] "v"(v0), [v1] "v"(v1), [t] "v"(t), [dump] "v"(dump), [lane] "v"(lane_addr),
+          [val] "v"(val)
+        : "memory", "scc", "s98", "s99");
 }
 
 // Tail rows (rows 16 .. 16 + A.tail - 1 of the tiles of the last run row
-// block): every pattern lane adds its own peak's stripe start in each tail
-// row, one atomic per peak and row, in the row-major tail region `lt` (row
-// stride `stride` words).  Lane r of a group holds the group's tail row term
-// of row 16 + r, broadcast to the group by DPP row_newbcast:r fused into the
-// add; lanes outside the chunk's pattern (which may repeat a pattern lane's
-// peak) and starts outside the tile go to the lane's own dump word, so that
-// no two lanes of an atomic update one word.
+// block): every lane adds its own peak's stripe start in each tail row, one
+// atomic per peak and row, in the row-major tail region `lt` (row stride
+// `stride` words).  Lane r of a group holds the group's tail row term of row
+// 16 + r, broadcast to the group by DPP row_newbcast:r fused into the add;
+// lanes past the window (whose edge lies far away) and starts outside the
+// tile go to the lane's own dump word, so that no two lanes of an atomic
+// update one word.
 template <int R>
 __device__ __forceinline__ void tail_row(uint32_t v, uint32_t tt, uint32_t dump, uint32_t val,
                                          uint32_t *__restrict__ lt) {
@@ -1067,29 +1064,27 @@ __device__ __forceinline__ void tail_row(uint32_t v, uint32_t tt, uint32_t dump,
     atomicAdd(lt + cu, val);
 }
 
-__device__ __forceinline__ void tail_steps(int rows, uint32_t m, uint32_t j, uint32_t v, uint32_t tt,
-                                           uint32_t dump, uint32_t stride, uint32_t val,
-                                           uint32_t *__restrict__ lt) {
+__device__ __forceinline__ void tail_steps(int rows, uint32_t v, uint32_t tt, uint32_t dump, uint32_t stride,
+                                           uint32_t val, uint32_t *__restrict__ lt) {
     static_assert(kTailRows == 3, "tail_steps unrolls kTailRows rows");
-    const uint32_t vv = (m >> j) & 1u ? v : kFarEdge;
-    tail_row<0>(vv, tt, dump, val, lt);
-    if (rows > 1) tail_row<1>(vv, tt, dump, val, lt + stride);
-    if (rows > 2) tail_row<2>(vv, tt, dump, val, lt + 2 * stride);
+    tail_row<0>(v, tt, dump, val, lt);
+    if (rows > 1) tail_row<1>(v, tt, dump, val, lt + stride);
+    if (rows > 2) tail_row<2>(v, tt, dump, val, lt + 2 * stride);
 }
 
 // One block: four consecutive FFTs of a sorted run, entry 4 b + g in lane
 // group g.  Lane (g, j) holds its group's window, row term and weight, and
-// the stripe edges of its peaks in up to two chunks of 16.
+// the stripe edges of peaks j and 16 + j.
 struct Quad {
     int g, run;          // block id claimed from the tile's counter; its run g % 16
-    int lo, pk;          // window start; FFT place in the run << 16 | peak count
-    uint32_t gb;         // G_{i,s0} of the group's FFT i (mod 2^32)
-    uint32_t t, wq;      // row term G_{i,s0} - G_{i,s0+j} (mod 2^32); fixed-point weight
-    uint32_t tt;         // tail row term G_{i,s0} - G_{i,s0+16+j} (mod 2^32), tiles with tail rows
-    int cnt;             // peaks in the window (0 past the tile's blocks)
-    int32_t q1, q2;      // chunk positions of the lane's peaks
-    uint32_t y0, y1;     // low words of their stripe edges
-    uint32_t m1, m2;     // lane patterns of the two chunks
+    uint32_t lo;         // byte offset of the window's first stripe edge
+    uint32_t pk;         // FFT place in the run << 16 | peak count
+    uint32_t gb, codes;  // G_{i,s0} of the group's FFT i (mod 2^32); residual codes of its rows
+    uint32_t step;       // 1 - floor(j q_i / 2^16) (mod 2^32)
+    uint32_t gb2, codes2;  // record of the tail rows (tiles with tail rows)
+    uint32_t wq;         // fixed-point weight
+    int cnt;             // peaks in the window
+    uint32_t y0, y1;     // low words of the stripe edges of peaks j and 16 + j
     int cmax;            // largest window of the four groups
 };
 
@@ -1461,16 +1456,23 @@ __device__ __forceinline__ void tail_output(const TileArgs &A, int slot, int rb,
 // of a sorted run, one per lane group; windows past the last FFT are empty)
 // from a counter in LDS, so that each wave takes as many as it can process.
 // A block's window data are loaded two blocks ahead and its stripe edges one
-// block ahead (a ring of three blocks), so that the accumulation of a block
+// block ahead (a ring of kRing blocks), so that the accumulation of a block
 // never waits for memory; the first two blocks of the next tile are loaded
-// during the output phase of the current one.  Every load is issued on every
-// path so that the wait counts stay exact.  PERSISTENT: tiles come from the
+// during the output phase of the current one.  Every load of the ring is
+// issued on every path so that the wait counts stay exact.  Rings of four and
+// five blocks, with the edges one or two blocks ahead, ran 0.5 to 2 % slower
+// (256 Hz batch, 1162 rows) and no faster on a 10 Hz band, whose edges miss
+// the L2 most.  Dealing the first 60 % of the blocks in turn instead of from
+// the counter was no faster either.  PERSISTENT: tiles come from the
 // XCD queues until all are exhausted; otherwise the workgroup runs tile
 // tile_base + blockIdx.x only.  OUT says what becomes of the tile: a map,
 // column maxima, or (kOutPart, not persistent) one of A.parts partial tiles:
 // workgroup u takes every A.parts-th block of tile u / A.parts, starting at
 // block u % A.parts, and copies its LDS tile to A.part for k_tiles_merge.
 enum { kOutColmax = 0, kOutMap = 1, kOutPart = 2 };
+
+constexpr int kRing = 3;
+constexpr int kEdge = 1;  // blocks ahead of a block that the stripe edges are requested
 
 template <bool WEIGHTED, int OUT, bool PERSISTENT, bool TAIL>
 __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restrict__ lds, int *s_next,
@@ -1484,9 +1486,9 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     // LDS column c holds fine bin c0 + c, c in [0, wc); columns wc + g are
     // the dumps of the four lane groups.
     const uint32_t dump = (uint32_t)(wc + grp);
-    const uint32_t lane_off = (uint32_t)j;
-    const uint32_t below = (1u << j) - 1u;           // pattern lanes below j
-    const uint32_t mtab = chunk_pattern(lane);       // lane n holds m(n), n <= 16
+    // LDS byte address of column 0 in this lane's row
+    const uint32_t lane_addr =
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t *)(lds + j);
     const int32_t n_pad = win_stride(A.n_fft);
     const int per = wave_ffts(A.n_fft);
     const int nblk = per >> 2;
@@ -1497,6 +1499,7 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     const int part = OUT == kOutPart ? (int)blockIdx.x % parts : 0;
     const __amdgpu_buffer_rsrc_t r_rec = buf(A.rec), r_step = buf(A.step);
     const uint32_t lane_code = 2u * (uint32_t)j;  // bit offset of this row's residual code
+    const uint32_t lane_byte = 4u * (uint32_t)j;
     // tail rows after the 16-row tile (row-major, rows of wc + kTailDump
     // words; every lane of a wave has its own dump word in each row)
     const uint32_t t_stride = (uint32_t)(wc + kTailDump);
@@ -1506,7 +1509,7 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     // per-tile buffers: window row, stripe edges and weights of the slot
     struct Bufs {
         __amdgpu_buffer_rsrc_t win, y, wq;
-        uint32_t rb;  // row block of the tile
+        int rb;  // row block of the tile
     };
     auto tile_bufs = [&](int t) {
         int slot, rb, jb;
@@ -1514,10 +1517,10 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         const int g = rb / kRowBlocksPerGroup;
         Bufs b;
         b.win = buf(A.win + (((int64_t)slot * A.nrbg + g) * A.nbb + jb) * n_pad);
-        // low 32 bits of the stripe edges (all the tile needs: see stripe_word)
+        // low 32 bits of the stripe edges (all the tile needs: see stripe_steps)
         b.y = buf(A.Y + (int64_t)slot * y_stride(A.n_peaks, A.n_fft));
         b.wq = buf(WEIGHTED ? (const void *)(A.wq + (int64_t)slot * A.n_fft) : (const void *)A.step);
-        b.rb = (uint32_t)rb;
+        b.rb = rb;
         return b;
     };
     // Blocks are handed out dynamically: block g of a tile is block g / 16 of
@@ -1532,51 +1535,47 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         return g;
     };
     // window data of block g (stage 1).  Blocks past the last one (claims
-    // after the counter ran out) read the row's last entry, an empty window.
-    auto stage_w = [&](Quad &Q, int gv, const Bufs &B) {
-        Q.g = __builtin_amdgcn_readfirstlane(gv);
+    // after the counter ran out) read the row's last entries and are not run.
+    // All but the lane group's part of the offset is scalar.
+    auto stage_w = [&](Quad &Q, int g, const Bufs &B) {
+        Q.g = g;
         if (OUT == kOutPart) Q.g = Q.g * parts + part;
         Q.run = Q.g & (kTileWaves - 1);
-        const uint32_t e = (uint32_t)(Q.run * per + 4 * (Q.g >> 4) + grp);
-        const auto w2 = __builtin_amdgcn_raw_buffer_load_b64(
-            B.win, (Q.g < total ? e : (uint32_t)(n_pad - 1)) * 8u, 0, 0);
-        Q.lo = (int)w2[0];
-        Q.pk = (int)w2[1];
+        const int e = Q.g < total ? Q.run * per + 4 * (Q.g >> 4) : n_pad - 4;
+        const auto w2 = __builtin_amdgcn_raw_buffer_load_b64(B.win, (uint32_t)grp * 8u, e * 8, 0);
+        Q.lo = w2[0];
+        Q.pk = w2[1];
     };
-    // stripe edges, row terms and weights of block bb (stage 2): the chunk
-    // sizes follow the largest window of the four groups, group 0's (the runs
+    // stripe edges, row terms and weights of a block (stage 2): the number of
+    // steps follows the largest window of the four groups, group 0's (the runs
     // are sorted by window size, exactly).  The row term of row s0 + j,
-    // G_{i,s0} - G_{i,s0+j} = 1 - step[i][j] - code_j (mod 2^32), comes from the
+    // G_{i,s0} - G_{i,s0+j} = step[i][j] - code_j (mod 2^32) comes from the
     // FFT's step table and the row block's record (the host keeps N nrb below
-    // 2^28, so the byte offsets fit 31 bits).
+    // 2^28, so the byte offsets fit 31 bits).  FFT i = place * 16 + run: the
+    // run's part of an offset is scalar; windows past the last FFT name place
+    // 0, whose run is clamped where N < 16.
     auto stage_y = [&](Quad &Q, const Bufs &B) {
-        Q.cnt = Q.pk & 0xFFFF;
-        const uint32_t fc = min((uint32_t)((Q.pk >> 16) * kTileWaves + Q.run), (uint32_t)i_last);
-        const auto r = __builtin_amdgcn_raw_buffer_load_b64(r_rec, (B.rb * (uint32_t)A.n_fft + fc) * 8u, 0, 0);
-        Q.gb = (uint32_t)r[0];
-        const uint32_t code = __builtin_amdgcn_ubfe((uint32_t)r[1], lane_code, 2u);
-        Q.t = (1u - ld_u32(r_step, (fc * kTileRows + (uint32_t)j) * 4u)) - code;
-        // tiles with tail rows: G_{i,s0} - G_{i,s0+16+j} from the next row
-        // block's record, whose rows share this block's linear steps (other
-        // row blocks read their own record and leave the term unused; no
-        // branch, so that nothing here waits for the loads)
-        Q.tt = 0u;
+        Q.cnt = (int)(Q.pk & 0xFFFFu);
+        const uint32_t place = Q.pk >> 16;
+        const int run = min(Q.run, i_last);
+        const auto r = __builtin_amdgcn_raw_buffer_load_b64(r_rec, place << 7, (B.rb * A.n_fft + run) * 8, 0);
+        Q.gb = r[0];
+        Q.codes = r[1];
+        Q.step = __builtin_amdgcn_raw_buffer_load_b32(r_step, (place << 10) | lane_byte, run * (kTileRows * 4), 0);
+        // tiles with tail rows: the next row block's record, whose rows share
+        // this block's linear steps (other row blocks read their own record
+        // and leave the term unused; no branch, so that nothing here waits
+        // for the loads)
         if (TAIL) {
-            const uint32_t rb2 = B.rb + (B.rb == (uint32_t)(A.nrb - 1) ? 1u : 0u);
-            const auto r2 = __builtin_amdgcn_raw_buffer_load_b64(r_rec, (rb2 * (uint32_t)A.n_fft + fc) * 8u, 0, 0);
-            const uint32_t code2 = __builtin_amdgcn_ubfe((uint32_t)r2[1], lane_code, 2u);
-            Q.tt = Q.t + code - code2 + (Q.gb - (uint32_t)r2[0]);
+            const int rb2 = B.rb + (B.rb == A.nrb - 1 ? 1 : 0);
+            const auto r2 = __builtin_amdgcn_raw_buffer_load_b64(r_rec, place << 7, (rb2 * A.n_fft + run) * 8, 0);
+            Q.gb2 = r2[0];
+            Q.codes2 = r2[1];
         }
-        Q.wq = WEIGHTED ? ld_u32(B.wq, fc * 4u) : 1u;
+        Q.wq = WEIGHTED ? __builtin_amdgcn_raw_buffer_load_b32(B.wq, place << 6, run * 4, 0) : 1u;
         Q.cmax = __builtin_amdgcn_readlane(Q.cnt, 0);
-        const int n1 = min(Q.cmax, 16);
-        const int n2 = min(max(Q.cmax - 16, 0), 16);
-        Q.m1 = __builtin_amdgcn_readlane(mtab, n1);
-        Q.m2 = __builtin_amdgcn_readlane(mtab, n2);
-        Q.q1 = (int32_t)__builtin_popcount(Q.m1 & below);
-        Q.q2 = 16 + (int32_t)__builtin_popcount(Q.m2 & below);
-        Q.y0 = ld_u32(B.y, (uint32_t)(Q.lo + Q.q1) * 4u);
-        Q.y1 = ld_u32(B.y, (uint32_t)(Q.lo + Q.q2) * 4u);
+        Q.y0 = ld_u32(B.y, Q.lo + lane_byte);
+        Q.y1 = ld_u32(B.y, Q.lo + lane_byte + 64u);
     };
 
     // (thread 0) position of the current tile in the home queue
@@ -1590,11 +1589,15 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     lds_barrier();
     t = PERSISTENT ? s_next[0] : OUT == kOutPart ? (int)blockIdx.x / parts : A.tile_base + (int)blockIdx.x;
     if (t < 0 || nblk == 0) return;  // nblk > 0 whenever there is an FFT
-    Quad qa, qb, qc;
+    Quad q[kRing];
     Bufs cur = tile_bufs(t);
-    stage_w(qa, claim(0, 1), cur);
-    stage_w(qb, claim(0, 1), cur);
-    stage_y(qa, cur);
+    {
+        const int g0 = __builtin_amdgcn_readfirstlane(claim(0, kRing - 1));
+#pragma unroll
+        for (int u = 0; u < kRing - 1; ++u) stage_w(q[u], g0 + u, cur);
+#pragma unroll
+        for (int u = 0; u < kEdge; ++u) stage_y(q[u], cur);
+    }
     for (int it = 0;; ++it) {
         const int par = it & 1;  // block counter of this tile; the other is the next tile's
         // The next tile is claimed ahead while the home queue holds two more
@@ -1612,48 +1615,51 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         const uint32_t c0q = (uint32_t)(jb * W - (kf - 1)) << kFrac;
         const bool tailed = TAIL && rb == A.nrb - 1;  // this tile also does the tail rows
         auto consume = [&](const Quad &Q) {
+            // the edges stay as loaded: the tile's origin and G_{i,s0} go into
+            // the row term, and lanes past the window hold an edge far from it
             const uint32_t base = c0q + Q.gb;
+            const uint32_t code = __builtin_amdgcn_ubfe(Q.codes, lane_code, 2u);
+            const uint32_t t = Q.step - code - base;
+            const uint32_t far = base + kFarEdge;
+            uint32_t tt = 0;
+            if (TAIL)
+                tt = t + code - __builtin_amdgcn_ubfe(Q.codes2, lane_code, 2u) + (Q.gb - Q.gb2);
             uint32_t val = Q.wq;
             asm volatile("" : "+v"(val));
-            const uint32_t v0 = Q.q1 < Q.cnt ? Q.y0 - base : kFarEdge;
-            stripe_chunk(Q.m1, v0, Q.t, dump, lane_off, val, lds);
-            if (tailed) tail_steps(A.tail, Q.m1, lane_off, v0, Q.tt, t_dump, t_stride, val, ltail);
-            if (Q.cmax > 16) {
-                const uint32_t v1 = Q.q2 < Q.cnt ? Q.y1 - base : kFarEdge;
-                stripe_chunk(Q.m2, v1, Q.t, dump, lane_off, val, lds);
-                if (tailed) tail_steps(A.tail, Q.m2, lane_off, v1, Q.tt, t_dump, t_stride, val, ltail);
+            const uint32_t v0 = j < Q.cnt ? Q.y0 : far;
+            const uint32_t v1 = j + 16 < Q.cnt ? Q.y1 : far;
+            stripe_steps(min(Q.cmax, 32), v0, v1, t, dump, lane_addr, val);
+            if (tailed) {
+                tail_steps(A.tail, v0, tt, t_dump, t_stride, val, ltail);
+                if (Q.cmax > 16) tail_steps(A.tail, v1, tt, t_dump, t_stride, val, ltail);
             }
             // windows longer than 32 peaks: further chunks, loaded here
             for (int off = 32; off < Q.cmax; off += 16) {
-                const uint32_t m = __builtin_amdgcn_readlane(mtab, min(Q.cmax - off, 16));
-                const int32_t q = off + (int32_t)__builtin_popcount(m & below);
-                uint32_t v = kFarEdge;
-                if (q < Q.cnt) v = ld_u32(cur.y, (uint32_t)(Q.lo + q) * 4u) - base;
-                stripe_chunk(m, v, Q.t, dump, lane_off, val, lds);
-                if (tailed) tail_steps(A.tail, m, lane_off, v, Q.tt, t_dump, t_stride, val, ltail);
+                uint32_t v = far;
+                if (off + j < Q.cnt) v = ld_u32(cur.y, Q.lo + lane_byte + 4u * (uint32_t)off);
+                stripe_steps(min(Q.cmax - off, 16), v, far, t, dump, lane_addr, val);
+                if (tailed) tail_steps(A.tail, v, tt, t_dump, t_stride, val, ltail);
             }
         };
-        // Ring of three blocks: a block's window is loaded two blocks ahead,
-        // its stripe edges one block ahead.  Blocks are claimed three at a
-        // time, one round ahead, so a wave drains its LDS queue to read a
-        // claim once per three blocks.  A wave's claims grow, so once one
-        // block is past the end, so are the blocks staged after it.
-        int gv = claim(par, 3);
-        for (;;) {
+        // Blocks are claimed kRing at a time, one round ahead, so a wave
+        // drains its LDS queue to read a claim once per round.  A wave's
+        // claims grow, so once one block is past the end, so are the blocks
+        // staged after it; it is left before it stages more (staging first
+        // made the last wave of a tile wait for loads nobody uses: 1 %).
+        int gv = claim(par, kRing);
+        for (bool more = true; more;) {
             const int g3 = __builtin_amdgcn_readfirstlane(gv);
-            gv = claim(par, 3);
-            stage_w(qc, g3, cur);
-            stage_y(qb, cur);
-            if (qa.g >= total) break;
-            consume(qa);
-            stage_w(qa, g3 + 1, cur);
-            stage_y(qc, cur);
-            if (qb.g >= total) break;
-            consume(qb);
-            stage_w(qb, g3 + 2, cur);
-            stage_y(qa, cur);
-            if (qc.g >= total) break;
-            consume(qc);
+            gv = claim(par, kRing);
+#pragma unroll
+            for (int u = 0; u < kRing; ++u) {
+                if (q[u].g >= total) {
+                    more = false;
+                    break;
+                }
+                stage_w(q[(u + kRing - 1) % kRing], g3 + u, cur);
+                stage_y(q[(u + kEdge) % kRing], cur);
+                consume(q[u]);
+            }
         }
         int tn = -1;
         if (PERSISTENT) {
@@ -1670,14 +1676,18 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         // waits anyway: otherwise the compiler cannot tell that the tile
         // claim above has returned on every path, and the output phase would
         // open with a full wait that also covers the next tile's prefetch.
+        // The LDS updates of stripe_steps are waited for by name, too: the
+        // compiler does not count them.
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         lds_barrier();
         if (PERSISTENT) tn = s_next[(it + 1) & 1];
         Bufs nxt = cur;
         if (tn >= 0) {
             nxt = tile_bufs(tn);
-            stage_w(qa, claim(par ^ 1, 1), nxt);
-            stage_w(qb, claim(par ^ 1, 1), nxt);
+            const int g0 = __builtin_amdgcn_readfirstlane(claim(par ^ 1, kRing - 1));
+#pragma unroll
+            for (int u = 0; u < kRing - 1; ++u) stage_w(q[u], g0 + u, nxt);
         }
         if (OUT == kOutPart) {
             uint32_t *__restrict__ dst = A.part + (int64_t)blockIdx.x * A.part_stride;
@@ -1696,14 +1706,20 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         const bool fused = kf <= kHold + 1;
         if (fused) {
             tile_windows<WEIGHTED, OUT == kOutMap, PERSISTENT>(A, slot, rb, jb, lds, [&] {
-                if (tn >= 0) stage_y(qa, nxt);
+                if (tn >= 0) {
+#pragma unroll
+                    for (int u = 0; u < kEdge; ++u) stage_y(q[u], nxt);
+                }
             });
         } else {
             tile_output<WEIGHTED, OUT == kOutMap>(A, slot, rb, jb, lds);
         }
         if (TAIL && tailed) tail_output<WEIGHTED, OUT == kOutMap>(A, slot, rb, jb, ltail);
         if (tn < 0) break;
-        if (!fused) stage_y(qa, nxt);
+        if (!fused) {
+#pragma unroll
+            for (int u = 0; u < kEdge; ++u) stage_y(q[u], nxt);
+        }
         lds_barrier();
         if (!fused) {
             tile_zero(A, lds);

@@ -698,3 +698,51 @@ def test_selection_at_the_edges_of_the_held_columns(ctx, width):
         idx, val = oracle.candidates(ref, width, excl, sep)
         _check_candidates(api.decode_candidates(raw), 0, idx, val, n, sel.theta)
     dpm.release()
+
+
+@pytest.mark.parametrize("n_fft", [1, 15, 16, 17, 300])
+@pytest.mark.parametrize("ns", [34, 40])  # two row blocks and two tail rows; three row blocks
+@pytest.mark.parametrize("weighted", [False, True])
+def test_blocks_of_every_window_size(ctx, n_fft, ns, weighted):
+    """Windows of 0 to 70 peaks per FFT, so that blocks run every number of
+    steps of the accumulation's straight sequence and the chunks after it, in
+    runs with and without FFTs of their own: maps (one workgroup per tile) and
+    column maxima (130 directions, more tiles than CUs) against the oracle."""
+    import torch
+    api = _api()
+    rng = synth.rng_for(1000 + n_fft)
+    t_fft, k_lo = 1024.0, 400_000
+    t = synth.fft_times(n_fft, t_fft)
+    segs = [np.sort(rng.choice(75, size=(i * 7 + 3) % 71, replace=False)).astype(np.int32) * 2 + k_lo
+            for i in range(n_fft)]
+    off = np.zeros(n_fft + 1, np.int64)
+    off[1:] = np.cumsum([len(x) for x in segs])
+    pm = synth.Peakmap(t_fft, t, synth.random_peakmap(n_fft, t_fft, k_lo, k_lo + 10, 0.5, rng).v, off,
+                       np.concatenate(segs).astype(np.int32))
+    dfdot = 1.0 / (t_fft * 0.5 * max(n_fft, 2) * t_fft)
+    grid = synth.Grid(kf=10, b0=10 * k_lo - 100, nf=1700, ns=ns, fdot0=-0.5 * ns * dfdot, dfdot=dfdot,
+                      t0=0.5 * float(t[0] + t[-1]))
+    sky = synth.sky_uniform(130, rng)
+    w = rng.uniform(0.5, 1.5, n_fft).astype(np.float32) if weighted else None
+    got = _gpu_map(ctx, pm, grid, sky[0], weights=w)
+    refs = [oracle.hough_map(pm, grid, sky[s], weights=None if w is None else w.astype(np.float64)) for s in (0, 129)]
+    dpm = ctx.upload(pm)
+    val, row = api.fh_hough_colmax(ctx, dpm, sky, grid,
+                                   weights=None if w is None else torch.as_tensor(w, device="cuda"))
+    torch.cuda.synchronize()
+    ctx.check()
+    val, row = val.cpu().numpy(), row.cpu().numpy()
+    if w is None:
+        np.testing.assert_array_equal(got, refs[0].astype(np.int32))
+    else:
+        _assert_weighted_close(got, refs[0], w)
+    for s, m in zip((0, 129), refs):
+        top, arg = _colmax_ref(m)
+        if w is None:
+            np.testing.assert_array_equal(val[s], top.astype(np.float32))
+            np.testing.assert_array_equal(row[s], arg)
+        else:
+            tol = REL_TOL * np.maximum(top, float(np.mean(w)))
+            assert np.all(np.abs(val[s].astype(np.float64) - top) <= tol)
+            assert np.all(m[row[s], np.arange(grid.nf)] >= top - 2 * tol)
+    dpm.release()
