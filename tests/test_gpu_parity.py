@@ -746,3 +746,32 @@ def test_blocks_of_every_window_size(ctx, n_fft, ns, weighted):
             assert np.all(np.abs(val[s].astype(np.float64) - top) <= tol)
             assert np.all(m[row[s], np.arange(grid.nf)] >= top - 2 * tol)
     dpm.release()
+
+
+@pytest.mark.parametrize("tile_bins", [64, 192, 704, 1280, 2496])
+@pytest.mark.parametrize("nf", [1, 64, 705, 2700])
+@pytest.mark.parametrize("n_dir,ns", [(1, 21), (140, 21), (140, 35)])  # one workgroup per tile; persistent; tail rows
+def test_unweighted_column_maxima_equal_those_of_unit_weights(ctx, tile_bins, nf, n_dir, ns):
+    """The unweighted column maxima (sums in registers, K_f = 10) against the
+    weighted ones (the general output) with every weight 1, in every two bins
+    of bands that end inside, at and past segments and tiles."""
+    import torch
+    api = _api()
+    rng = synth.rng_for(nf)
+    n, t_fft, k_lo = 120, 1024.0, 70_000
+    pm = synth.random_peakmap(n, t_fft, k_lo, k_lo + 300, 0.08, rng)
+    dfdot = 1.0 / (t_fft * 0.5 * n * t_fft)
+    grid = synth.Grid(kf=10, b0=10 * (k_lo + 8), nf=nf, ns=ns, fdot0=-0.3 * ns * dfdot, dfdot=dfdot,
+                      t0=0.5 * float(pm.t[0] + pm.t[-1]))
+    sel = synth.Selection(width=2)
+    sky = synth.sky_uniform(n_dir, rng)
+    dpm = ctx.upload(pm)
+    raw = [api.fh_hough_candidates(ctx, dpm, sky, grid, sel, weights=w, tile_bins=tile_bins)
+           for w in (None, torch.ones(n, dtype=torch.float32, device="cuda"))]
+    torch.cuda.synchronize()
+    ctx.check()
+    a, b = (api.decode_candidates(r) for r in raw)
+    for field in ("valid", "bin", "row", "value"):
+        np.testing.assert_array_equal(a[field], b[field])
+    assert a["valid"].any()
+    dpm.release()
