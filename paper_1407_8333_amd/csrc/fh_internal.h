@@ -64,7 +64,9 @@ struct TileArgs {
     int32_t nrb, nbb, nrbg;       // row blocks run by the tiles, bin blocks, row-block groups
     int32_t tail;                 // grid rows past the last run row block (0..kTailRows), done by its tiles
     int32_t n_slots;              // sky directions in this chunk
-    const uint32_t *Y;            // [slot][P] low words of the stripe edges (2^-16 fine bins)
+    const uint32_t *Y;            // [slot][y_stride] low words of the stripe edges (2^-16 fine bins), or,
+                                  // with bins, what the tiles compute them from (see k_front_rank)
+    const int32_t *bins;          // natural bins of the peaks, or nullptr: edges from Y
     const int2 *win;              // [slot][nrbg][nbb][win_stride(N)] sorted windows
     const uint2 *rec;             // [nrb][N] low word of G_{i,s0} and the rows' residual codes
     const uint32_t *step;         // [N][16] 1 - floor(j q_i / 2^16): the rows' linear steps
@@ -109,6 +111,7 @@ struct SetupArgs {
     int64_t *gwin;
     uint2 *rec;
     uint32_t *step, *base;
+    int32_t y_pad;  // entries after each FFT's edges that base counts: kYPad, or 0 (edges in the tiles)
     int32_t *err;
     int32_t n_vec, w_stride, mult;
     const float *w;
@@ -174,7 +177,8 @@ hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offs
                              const int64_t *gwin, uint32_t *Y, const float *w, int32_t w_stride,
                              const WeightStats *ws, int32_t ws_stride, uint32_t *wq, int32_t nrbg, int32_t nbb,
                              int32_t W, int32_t k_min, int32_t k_max, const uint2 *rank, uint32_t *win,
-                             int32_t shift_mode, double q, hipStream_t st);
+                             int32_t shift_mode, double q, bool terms_only, hipStream_t st);
+// terms_only: no stripe edges, but the terms that the tiles compute them from
 // shift_mode 1: Doppler correction as a per-FFT shift computed at the
 // reference q = (K_f T_FFT) f_ref fine bins (0: exact per peak)
 // window rows sorted by window size per tile-wave run (see k_sort_windows)

@@ -100,7 +100,7 @@ __device__ __forceinline__ void shift_tables(const SetupArgs &A, int64_t first, 
         const int32_t rb = (int32_t)(x / n_fft);
         const int32_t i = (int32_t)(x - (int64_t)rb * n_fft);
         if (rb == 0)  // run by run, as the window sort reads them
-            A.base[(i % kTileWaves) * wave_ffts(n_fft) + i / kTileWaves] = (uint32_t)(A.offsets[i] + (int64_t)kYPad * i);
+            A.base[(i % kTileWaves) * wave_ffts(n_fft) + i / kTileWaves] = (uint32_t)(A.offsets[i] + (int64_t)A.y_pad * i);
         const double tau = A.t[i] - A.t0;
         double sig = A.dfdot * tau;
         sig = sig * A.S;
@@ -509,6 +509,9 @@ __global__ void __launch_bounds__(256) k_setup_front(SetupArgs A, FrontArgs R) {
 // z = (y - c) 2^-16, which a double holds exactly wherever an edge can lie; z
 // d / K_f (d = 1 / r before rounding) is within 2^-23 of the real bound, so the
 // least bin is the nearest whole number or the next one.
+// With few row blocks the tiles compute the edges from the natural bins, and
+// the front stores only each FFT's terms (terms_only): the multiplier fl(r)
+// 2^16 and the low word of c, 16 B apart, where the slot's edges would begin.
 // Bound by its stores (the edges, 4 B per peak, and 4 B per window entry).
 // Against k_front: 112 directions of the 256 Hz band 1050 -> 464 us (3.2 TB/s
 // written), 24 of the 10 Hz band at 1 kHz 1440 -> 900 us, 97 narrow ones at
@@ -519,7 +522,7 @@ __global__ void __launch_bounds__(256) k_front_rank(
     const int64_t *__restrict__ gwin, uint32_t *__restrict__ Y, const float *__restrict__ w, int32_t w_stride,
     const WeightStats *__restrict__ ws, int32_t ws_stride, uint32_t *__restrict__ wq, int32_t nrbg, int32_t nbb,
     int32_t W, int32_t F, int32_t D, int32_t k_min, int32_t k_max, int32_t nw, const uint2 *__restrict__ rank,
-    uint32_t *__restrict__ win, int32_t shift_mode, double q) {
+    uint32_t *__restrict__ win, int32_t shift_mode, double q, bool terms_only) {
     extern __shared__ double s_dyn[];
     double *s_g = s_dyn;  // [nrbg][F][2]: least and largest shift of the group's rows, in fine bins
     const int ts = nw | 1;  // table stride (odd: the FFTs' words spread over the banks)
@@ -550,6 +553,13 @@ __global__ void __launch_bounds__(256) k_front_rank(
         s_r[x] = shift_mode ? 1.0 : r;
         s_d[x] = (shift_mode ? 1.0 : d) / (double)kf;
         s_c[x] = c;
+        if (terms_only) {
+            uint32_t *e = Y + (int64_t)slot * y_stride(n_peaks, n_fft) + 4 * (int64_t)i;
+            const uint64_t rq = (uint64_t)__double_as_longlong(s_r[x] * kQd);
+            e[0] = (uint32_t)rq;
+            e[1] = (uint32_t)(rq >> 32);
+            e[2] = (uint32_t)(uint64_t)c;
+        }
         if (w != nullptr) {
             const WeightStats wst = ws[(int64_t)slot * ws_stride];
             double wi = (double)w[(int64_t)slot * w_stride + i];
@@ -574,7 +584,7 @@ __global__ void __launch_bounds__(256) k_front_rank(
     // stripe edges: wave w takes FFTs w, w + 4, ..., its lanes their
     // consecutive peaks; the entries between two FFTs' runs stay unwritten
     // (the tiles read past a window's end but do not use what they read)
-    {
+    if (!terms_only) {
         const int64_t ys = y_stride(n_peaks, n_fft);
         const int lane = (int)threadIdx.x & 63;
         constexpr int kU = 4;  // peaks per lane and round, their natural bins requested together
@@ -1084,7 +1094,8 @@ struct Quad {
     uint32_t gb2, codes2;  // record of the tail rows (tiles with tail rows)
     uint32_t wq;         // fixed-point weight
     int cnt;             // peaks in the window
-    uint32_t y0, y1;     // low words of the stripe edges of peaks j and 16 + j
+    uint32_t y0, y1;     // low words of the stripe edges of peaks j and 16 + j, or their natural bins
+    uint32_t rl, rh, c;  // (natural bins) the FFT's edge terms
     int cmax;            // largest window of the four groups
 };
 
@@ -1582,7 +1593,8 @@ __device__ __forceinline__ void tail_output(const TileArgs &A, int slot, int rb,
 // the L2 most.  Dealing the first 60 % of the blocks in turn instead of from
 // the counter was no faster either.  PERSISTENT: tiles come from the
 // XCD queues until all are exhausted; otherwise the workgroup runs tile
-// tile_base + blockIdx.x only.  OUT says what becomes of the tile: a map,
+// tile_base + blockIdx.x only.  BINS: the lanes hold natural bins and compute
+// the edges.  OUT says what becomes of the tile: a map,
 // column maxima, or (kOutPart, not persistent) one of A.parts partial tiles:
 // workgroup u takes every A.parts-th block of tile u / A.parts, starting at
 // block u % A.parts, and copies its LDS tile to A.part for k_tiles_merge.
@@ -1591,7 +1603,7 @@ enum { kOutColmax = 0, kOutMap = 1, kOutPart = 2 };
 constexpr int kRing = 3;
 constexpr int kEdge = 1;  // blocks ahead of a block that the stripe edges are requested
 
-template <bool WEIGHTED, int OUT, bool PERSISTENT, bool TAIL>
+template <bool WEIGHTED, int OUT, bool PERSISTENT, bool TAIL, bool BINS>
 __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restrict__ lds, int4 *s_next,
                                           int *s_cnt) {
     const int tid = threadIdx.x;
@@ -1615,6 +1627,10 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
     const int parts = OUT == kOutPart ? A.parts : 1;
     const int part = OUT == kOutPart ? (int)blockIdx.x % parts : 0;
     const __amdgpu_buffer_rsrc_t r_rec = buf(A.rec), r_step = buf(A.step);
+    // natural bins: reads past the last peak return 0 (the records end there)
+    const __amdgpu_buffer_rsrc_t r_bins =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(A.bins), 0, BINS ? (int)(4 * A.n_peaks) : 0, 0x00020000);
+    const double kf_d = (double)kf;
     const uint32_t lane_code = 2u * (uint32_t)j;  // bit offset of this row's residual code
     const uint32_t lane_byte = 4u * (uint32_t)j;
     // tail rows after the 16-row tile (row-major, rows of wc + kTailDump
@@ -1693,8 +1709,14 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         }
         Q.wq = WEIGHTED ? __builtin_amdgcn_raw_buffer_load_b32(B.wq, place << 6, run * 4, 0) : 1u;
         Q.cmax = __builtin_amdgcn_readlane(Q.cnt, 0);
-        Q.y0 = ld_u32(B.y, Q.lo + lane_byte);
-        Q.y1 = ld_u32(B.y, Q.lo + lane_byte + 64u);
+        if (BINS) {
+            const auto e = __builtin_amdgcn_raw_buffer_load_b96(B.y, place << 8, run * 16, 0);
+            Q.rl = e[0];
+            Q.rh = e[1];
+            Q.c = e[2];
+        }
+        Q.y0 = ld_u32(BINS ? r_bins : B.y, Q.lo + lane_byte);
+        Q.y1 = ld_u32(BINS ? r_bins : B.y, Q.lo + lane_byte + 64u);
     };
 
     // (thread 0) position of the current tile in the home queue
@@ -1735,7 +1757,14 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
         auto consume = [&](const Quad &Q) {
             // the edges stay as loaded: the tile's origin and G_{i,s0} go into
             // the row term, and lanes past the window hold an edge far from it
-            const uint32_t base = c0q + Q.gb;
+            const uint32_t base = c0q + Q.gb - (BINS ? Q.c : 0u);
+            // BINS: the edge without its constant, floor(fl(K_f k r) 2^16), whose
+            // low word is that of its sum with 2^52 (0 <= edge < 2^45)
+            auto edge = [&](uint32_t k) -> uint32_t {
+                if (!BINS) return k;
+                const double r = __hiloint2double((int)Q.rh, (int)Q.rl);
+                return (uint32_t)__double2loint(floor((double)k * kf_d * r) + 4503599627370496.0);
+            };
             const uint32_t code = __builtin_amdgcn_ubfe(Q.codes, lane_code, 2u);
             const uint32_t t = Q.step - code - base;
             const uint32_t far = base + kFarEdge;
@@ -1744,8 +1773,8 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
                 tt = t + code - __builtin_amdgcn_ubfe(Q.codes2, lane_code, 2u) + (Q.gb - Q.gb2);
             uint32_t val = Q.wq;
             asm volatile("" : "+v"(val));
-            const uint32_t v0 = j < Q.cnt ? Q.y0 : far;
-            const uint32_t v1 = j + 16 < Q.cnt ? Q.y1 : far;
+            const uint32_t v0 = j < Q.cnt ? edge(Q.y0) : far;
+            const uint32_t v1 = j + 16 < Q.cnt ? edge(Q.y1) : far;
             stripe_steps(min(Q.cmax, 32), v0, v1, t, dump, lane_addr, val);
             if (tailed) {
                 tail_steps(A.tail, v0, tt, t_dump, t_stride, val, ltail);
@@ -1754,7 +1783,8 @@ __device__ __forceinline__ void run_tiles(const TileArgs &A, uint32_t *__restric
             // windows longer than 32 peaks: further chunks, loaded here
             for (int off = 32; off < Q.cmax; off += 16) {
                 uint32_t v = far;
-                if (off + j < Q.cnt) v = ld_u32(cur.y, Q.lo + lane_byte + 4u * (uint32_t)off);
+                if (off + j < Q.cnt)
+                    v = edge(ld_u32(BINS ? r_bins : cur.y, Q.lo + lane_byte + 4u * (uint32_t)off));
                 stripe_steps(min(Q.cmax - off, 16), v, far, t, dump, lane_addr, val);
                 if (tailed) tail_steps(A.tail, v, tt, t_dump, t_stride, val, ltail);
             }
@@ -1849,19 +1879,19 @@ template <bool WEIGHTED, int OUT, bool TAIL>
 __global__ void __launch_bounds__(kTileThreads) k_tiles_plain(TileArgs A) {
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ int s_cnt[2];
-    run_tiles<WEIGHTED, OUT, false, TAIL>(A, lds, nullptr, s_cnt);
+    run_tiles<WEIGHTED, OUT, false, TAIL, false>(A, lds, nullptr, s_cnt);
 }
 
 // One workgroup per CU.  The next tile of the home queue is claimed when a
 // tile starts (its counter update overlaps the tile's work) and used when it
 // ends; an exhausted home queue sends the workgroup to the others.  Every
 // workgroup leaves the loop once all queues are exhausted.
-template <bool WEIGHTED, bool TAIL>
+template <bool WEIGHTED, bool TAIL, bool BINS>
 __global__ void __launch_bounds__(kTileThreads) k_tiles_persistent(TileArgs A) {
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ int4 s_next[2];
     __shared__ int s_cnt[2];
-    run_tiles<WEIGHTED, kOutColmax, true, TAIL>(A, lds, s_next, s_cnt);
+    run_tiles<WEIGHTED, kOutColmax, true, TAIL, BINS>(A, lds, s_next, s_cnt);
 }
 
 // Sums of the partial tiles and their output: grid (column chunks of a tile,
@@ -2369,7 +2399,7 @@ hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offs
                              const int64_t *gwin, uint32_t *Y, const float *w, int32_t w_stride,
                              const WeightStats *ws, int32_t ws_stride, uint32_t *wq, int32_t nrbg, int32_t nbb,
                              int32_t W, int32_t k_min, int32_t k_max, const uint2 *rank, uint32_t *win,
-                             int32_t shift_mode, double q, hipStream_t st) {
+                             int32_t shift_mode, double q, bool terms_only, hipStream_t st) {
     const int32_t nw = rank_words(k_min, k_max);
     const int F = nw ? rank_ffts_per_block(nw, nrbg) : 0;
     if (F < 1 || win_stride(n_fft) % F != 0) return hipErrorInvalidValue;
@@ -2380,7 +2410,7 @@ hipError_t launch_front_rank(int32_t n_fft, int64_t n_peaks, const int64_t *offs
     const int D = (int)std::max<int64_t>(1, std::min<int64_t>(kRankDirs, blocks / (4 * 8 * 256)));
     k_front_rank<<<dim3(win_stride(n_fft) / F, (n_slots + D - 1) / D), 256, lds, st>>>(
         n_fft, n_peaks, offsets, bins, v, sky, n_slots, kf, b0, gwin, Y, w, w_stride, ws, ws_stride, wq, nrbg, nbb, W, F,
-        D, k_min, k_max, nw, rank, win, shift_mode, q);
+        D, k_min, k_max, nw, rank, win, shift_mode, q, terms_only);
     return hipGetLastError();
 }
 
@@ -2412,7 +2442,8 @@ hipError_t launch_windows(int32_t n_fft, const int64_t *offsets, const int64_t *
 template <bool Wt, bool T>
 static hipError_t set_tile_attrs() {
     const int lds = kLdsBytes - kLdsReserve;
-    for (const void *f : {(const void *)k_tiles_persistent<Wt, T>, (const void *)k_tiles_plain<Wt, kOutColmax, T>,
+    for (const void *f : {(const void *)k_tiles_persistent<Wt, T, false>, (const void *)k_tiles_persistent<Wt, T, true>,
+                          (const void *)k_tiles_plain<Wt, kOutColmax, T>,
                           (const void *)k_tiles_plain<Wt, kOutMap, T>, (const void *)k_tiles_plain<Wt, kOutPart, T>}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
@@ -2428,6 +2459,7 @@ static hipError_t launch_tiles_t(const TileArgs &a, bool map, bool persistent, i
     if (a.tail < 0 || a.tail > kTailRows) return hipErrorInvalidValue;
     const int lds = tile_lds_bytes(a.W, a.kf, a.tail);
     if (lds > kLdsBytes - kLdsReserve) return hipErrorInvalidValue;
+    if (a.bins && (map || !persistent || a.parts > 1)) return hipErrorInvalidValue;
     if (a.parts > 1) {
         // (the launch grid below holds 65535 tiles)
         if (a.part == nullptr || a.part_stride < part_words(a.W, a.kf, a.tail) || n_tiles > 65535)
@@ -2441,7 +2473,8 @@ static hipError_t launch_tiles_t(const TileArgs &a, bool map, bool persistent, i
         return hipGetLastError();
     }
     if (map) k_tiles_plain<Wt, kOutMap, T><<<n_tiles, kTileThreads, lds, st>>>(a);
-    else if (persistent) k_tiles_persistent<Wt, T><<<grid_blocks, kTileThreads, lds, st>>>(a);
+    else if (persistent && a.bins) k_tiles_persistent<Wt, T, true><<<grid_blocks, kTileThreads, lds, st>>>(a);
+    else if (persistent) k_tiles_persistent<Wt, T, false><<<grid_blocks, kTileThreads, lds, st>>>(a);
     else k_tiles_plain<Wt, kOutColmax, T><<<n_tiles, kTileThreads, lds, st>>>(a);
     return hipGetLastError();
 }

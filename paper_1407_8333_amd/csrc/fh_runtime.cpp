@@ -650,6 +650,18 @@ bool needs_full_edges(const fh_ctx *ctx, const fh_peakmap *pm) {
 // than four directions' stripe edges.
 constexpr int kRankMinDirs = 3;
 
+// Row blocks up to which the tiles of such a launch compute the stripe edges
+// from the natural bins instead of reading them.  Each peak's edge is then
+// computed once per row block, and the front neither computes nor stores it:
+// with few row blocks the edges' way through memory (4 bytes per peak and
+// direction written, and lines of them read that two bin blocks share) costs
+// more than ten FP64 instructions per block of the tiles.  Whole calls of 128
+// directions (97 of 17 rows, 64 of 147), edges read -> computed: 1 row block
+// (17 rows) 1170 -> 815 us, weighted 1805 -> 1352; 2 (31 rows) 1654 -> 1418;
+// 4 (60 rows) 2692 -> 2591; 8 (118 rows) 5218 -> 5353; 10 (147 rows) 3498 ->
+// 3626.
+constexpr int kTermRowBlocks = 4;
+
 size_t rank_bytes(const fh_ctx *ctx, const fh_peakmap *pm, const Plan &p, int slots) {
     if (slots < kRankMinDirs || needs_full_edges(ctx, pm) || !rank_front_fits(pm->k_min, pm->k_max, p.nrbg)) return 0;
     const int64_t bytes = 8 * (int64_t)rank_words(pm->k_min, pm->k_max) * pm->n_fft;
@@ -804,7 +816,7 @@ double shift_reference_bins(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gr
 
 fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
                         int slots, const double *d_sky, const SkyDirs &dirs, const float *d_w, int w_stride,
-                        int64_t n_colmax, bool first, const ChunkBufs &b, hipStream_t st) {
+                        int64_t n_colmax, bool first, const ChunkBufs &b, hipStream_t st, bool terms_only = false) {
     Timed timed(ctx, st, kSpanFront);
     const bool weighted = d_w != nullptr;
     SetupArgs a{};
@@ -821,6 +833,7 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
     a.rec = b.rec;
     a.step = b.step;
     a.base = b.base;
+    a.y_pad = terms_only ? 0 : kYPad;
     a.offsets = pm->d_offsets;
     a.err = b.err;
     a.n_vec = weighted ? (w_stride == 0 ? 1 : slots) : 0;
@@ -844,7 +857,7 @@ fh_status enqueue_front(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, con
         HIP_OK(launch_setup(a, pm->d_bins, pm->k_min, pm->k_max, first ? b.rank : nullptr, st));
         HIP_OK(launch_front_rank(pm->n_fft, pm->n_peaks, pm->d_offsets, pm->d_bins, pm->d_v, d_sky, slots, g->kf, g->b0,
                                  b.gwin, b.Y, d_w, w_stride, b.ws, ws_stride, b.wq, p.nrbg, p.nbb, p.W, pm->k_min,
-                                 pm->k_max, b.rank, b.win, sm, q, st));
+                                 pm->k_max, b.rank, b.win, sm, q, terms_only, st));
     } else if (F > 0) {
         FrontArgs r{};
         r.n_peaks = pm->n_peaks;
@@ -945,9 +958,6 @@ fh_status run_search(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const 
     for (int32_t base = 0; base < n_sky; base += chunk) {
         const int slots = std::min(chunk, n_sky - base);
         const float *w = weighted ? d_w + (w_stride ? (int64_t)base * w_stride : 0) : nullptr;
-        if ((s = enqueue_front(ctx, pm, g, p, slots, b.sky + 3 * (int64_t)base, base == 0 ? dirs : SkyDirs{}, w,
-                               w_stride, (int64_t)slots * g->nf, base == 0, b, st)))
-            return s;
         TileArgs a = tile_args(pm, g, p, slots, b, weighted, w_stride == 0 ? 0 : 1);
         const int64_t n_tiles = p.tiles_per_sky * slots;
         set_parts(ctx, pm, g, p, n_tiles, b, a);
@@ -956,6 +966,12 @@ fh_status run_search(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const 
         // would take two tiles and late ones none (240 tiles of a 4096 s band:
         // 165 us, against 90 us).
         const bool persistent = schedule == FH_SCHED_PERSISTENT && a.parts == 1 && n_tiles > ctx->n_cu;
+        const bool terms_only = persistent && p.nrb <= kTermRowBlocks && b.rank &&
+                                rank_bytes(ctx, pm, p, slots) > 0 && pm->n_peaks < ((int64_t)1 << 29);
+        if (terms_only) a.bins = pm->d_bins;
+        if ((s = enqueue_front(ctx, pm, g, p, slots, b.sky + 3 * (int64_t)base, base == 0 ? dirs : SkyDirs{}, w,
+                               w_stride, (int64_t)slots * g->nf, base == 0, b, st, terms_only)))
+            return s;
         {
             const int grid_blocks = (int)std::min<int64_t>(ctx->n_cu, n_tiles);
             Timed timed(ctx, st, kSpanTiles);

@@ -775,3 +775,45 @@ def test_unweighted_column_maxima_equal_those_of_unit_weights(ctx, tile_bins, nf
         np.testing.assert_array_equal(a[field], b[field])
     assert a["valid"].any()
     dpm.release()
+
+
+@pytest.mark.parametrize("ns", [5, 18, 64, 67, 80])  # one block; tail rows; four blocks, and four with a tail; five
+@pytest.mark.parametrize("kf,k_lo,mode,density,min_gap", [
+    (10, 50_000, "exact", 0.08, 2),
+    (10, 50_000, "shift", 0.08, 2),
+    (1, 0, "exact", 0.6, 1),        # from natural bin 0, adjacent peaks
+    (37, 3_000_000, "exact", 0.3, 1),  # windows of more than 32 peaks, large natural bins
+])
+def test_edges_computed_in_the_tiles_equal_stored_ones(ctx, ns, kf, k_lo, mode, density, min_gap):
+    """Persistent searches of few row blocks (edges from the natural bins)
+    against the search of the same windows by sweeps over stored edges, with
+    and without weights of each direction; one direction against the oracle;
+    the last peaks of the peakmap inside the band."""
+    import torch
+    api = _api()
+    rng = synth.rng_for(kf * 10 + ns)
+    n, t_fft, span, n_dir = 77, 1024.0, 260, 150
+    pm = synth.random_peakmap(n, t_fft, k_lo, k_lo + span, density, rng, min_gap=min_gap)
+    dfdot = 1.0 / (t_fft * 0.5 * n * t_fft)
+    grid = synth.Grid(kf=kf, b0=kf * (k_lo + 4), nf=kf * (span - 4), ns=ns, fdot0=-0.5 * ns * dfdot, dfdot=dfdot,
+                      t0=0.5 * float(pm.t[0] + pm.t[-1]))
+    sky = synth.sky_uniform(n_dir, rng)
+    wt = torch.as_tensor(np.stack([synth.fft_weights(n, rng) for _ in range(n_dir)]), device="cuda")
+    dpm = ctx.upload(pm)
+    ctx.set_doppler(mode)
+    try:
+        got = []
+        for method in (2, 1):
+            ctx.set_option("window_method", method)
+            got.append([x for w in (None, wt) for tb in (64, 128)
+                        for x in api.fh_hough_colmax(ctx, dpm, sky, grid, weights=w, tile_bins=tb)])
+        ctx.check()
+    finally:
+        ctx.set_option("window_method", 2)
+        ctx.set_doppler("exact")
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    ref = oracle.hough_map(pm, grid, sky[3], doppler=mode)
+    np.testing.assert_array_equal(got[0][0][3].cpu().numpy(), ref.max(0).astype(np.float32))
+    np.testing.assert_array_equal(got[0][1][3].cpu().numpy(), ref.argmax(0))
+    dpm.release()
