@@ -530,7 +530,9 @@ struct ChunkBufs {
 
 // Cost model of the tiles of small launches, in us, fitted to timed launches of
 // one and five directions at T_FFT = 1024 .. 8192 s, W = 256 .. 2496 and 1 .. 16
-// parts (single rounds; the model is within about 20 % of them).
+// parts (single rounds).  Fitted to tiles whose blocks took more set-up; timed
+// against the present ones it is within 40 % (20 % rms), and a refit to 6 % rms
+// chose widths that moved calls by -2 to +3 % with no gain over all of them.
 //   a tile's clearing, first loads and output: 4.2 + 2.5 per 1000 columns;
 //   its FFTs: 3.05 ns each (a quarter of a block's window, term and pattern
 //   set-up) and 0.43 ns per peak of the FFT's window, which is wider than the
@@ -557,8 +559,8 @@ double tiles_us(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const
 // parts-th block of FFTs; a merge adds the partial tiles): more than one only
 // where the launch leaves CUs idle and the model finds the shorter
 // accumulation worth the partial tiles' way through memory.  One direction of
-// 31 rows at T_FFT = 2048 s (32 tiles of 1280 bins): 103 us by one workgroup
-// each, 35 us by eight.
+// 31 rows at T_FFT = 2048 s (32 tiles of 1280 bins): 84 us by one workgroup
+// each, 29 us by eight.
 int plan_parts(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int64_t n_tiles) {
     // a part keeps one round of the ring of blocks for each of its waves
     const int64_t blocks = (int64_t)kTileWaves * (wave_ffts(pm->n_fft) / 4);
