@@ -787,8 +787,9 @@ def test_unweighted_column_maxima_equal_those_of_unit_weights(ctx, tile_bins, nf
 def test_edges_computed_in_the_tiles_equal_stored_ones(ctx, ns, kf, k_lo, mode, density, min_gap):
     """Persistent searches of few row blocks (edges from the natural bins)
     against the search of the same windows by sweeps over stored edges, with
-    and without weights of each direction; one direction against the oracle;
-    the last peaks of the peakmap inside the band."""
+    and without weights of each direction, and in chunks whose last is too
+    small for it; one direction against the oracle; the last peaks of the
+    peakmap inside the band."""
     import torch
     api = _api()
     rng = synth.rng_for(kf * 10 + ns)
@@ -805,8 +806,9 @@ def test_edges_computed_in_the_tiles_equal_stored_ones(ctx, ns, kf, k_lo, mode, 
         got = []
         for method in (2, 1):
             ctx.set_option("window_method", method)
-            got.append([x for w in (None, wt) for tb in (64, 128)
-                        for x in api.fh_hough_colmax(ctx, dpm, sky, grid, weights=w, tile_bins=tb)])
+            got.append([x for w in (None, wt) for tb, chunk in ((64, 0), (128, 0), (128, 148))
+                        for x in api.fh_hough_colmax(ctx, dpm, sky, grid, weights=w, tile_bins=tb,
+                                                     sky_chunk=chunk)])
         ctx.check()
     finally:
         ctx.set_option("window_method", 2)
