@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <deque>
 #include <cmath>
@@ -182,9 +183,24 @@ struct BlockPool {
     }
 };
 
+// Number of a peakmap, never given twice in a process (a copy is another
+// peakmap).  What a context keeps for a peakmap past a call is kept by it: a
+// released peakmap's address is soon another one's.
+struct Serial {
+    uint64_t id = next();
+    Serial() = default;
+    Serial(const Serial &) {}
+    Serial &operator=(const Serial &) = delete;
+    static uint64_t next() {
+        static std::atomic<uint64_t> n{0};
+        return ++n;
+    }
+};
+
 }  // namespace
 
 struct fh_peakmap {
+    Serial serial;
     int32_t n_fft = 0;
     int64_t n_peaks = 0;
     double t_fft = 0;
@@ -253,8 +269,8 @@ struct fh_ctx {
     // width of a shape's last search where that was a small launch, which
     // chooses its own (reported by fh_plan_query)
     std::map<std::tuple<int, int, int, int>, int> used;
-    // captured searches (fh_options.use_graph), keyed by every argument and
-    // workspace pointer they bake in
+    // captured searches (fh_options.use_graph), keyed by the peakmap's serial
+    // number and every argument and workspace pointer they bake in
     struct GraphEntry {
         std::vector<uint64_t> key;
         hipGraph_t graph = nullptr;
@@ -1870,12 +1886,13 @@ fh_status fh_hough_candidates(fh_ctx *ctx, const fh_peakmap *pm, int32_t n_sky, 
         HIP_OK(launch_set_sky(arg, dirs.n, b.sky, st));
     }
 
-    // hipGraph: capture the whole search once, replay it while every argument
-    // and workspace pointer it bakes in is unchanged (sky vectors and weights
-    // are read from device memory at replay time, so their contents may change).
+    // hipGraph: capture the whole search once, replay it while the peakmap and
+    // every argument and workspace pointer it bakes in is unchanged (sky vectors
+    // and weights are read from device memory at replay time, so their contents
+    // may change).
     auto bits = [](double x) { uint64_t u; std::memcpy(&u, &x, 8); return u; };
     std::vector<uint64_t> key = {
-        (uint64_t)(uintptr_t)pm, (uint64_t)g->kf, (uint64_t)g->b0, (uint64_t)g->nf, (uint64_t)g->ns,
+        pm->serial.id, (uint64_t)g->kf, (uint64_t)g->b0, (uint64_t)g->nf, (uint64_t)g->ns,
         bits(g->fdot0), bits(g->dfdot), bits(g->t0), (uint64_t)sel->width, (uint64_t)(uint32_t)sel->excl,
         (uint64_t)(uint32_t)sel->sep, bits(sel->theta), (uint64_t)o.schedule, (uint64_t)p.W,
         (uint64_t)chunk, (uint64_t)n_sky, (uint64_t)(uintptr_t)d_w, (uint64_t)(uint32_t)w_stride,

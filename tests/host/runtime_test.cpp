@@ -1,0 +1,96 @@
+// Checks of the library's host runtime without a GPU: fh_runtime.cpp itself,
+// compiled for the host against a stand-in HIP runtime, so that allocations
+// can fail, addresses be reused and threads meet.  Usage: runtime_test NAME;
+// exit status 0 passed, 1 failed, 77 not applicable here.
+#include "../../paper_1407_8333_amd/csrc/fh_runtime.cpp"
+#include "launches.h"
+
+#include <thread>
+
+#define CHECK(x)                                                              \
+    do {                                                                      \
+        if (!(x)) {                                                           \
+            std::printf("line %d: %s (%s)\n", __LINE__, #x, fh_last_error()); \
+            std::exit(1);                                                     \
+        }                                                                     \
+    } while (0)
+
+namespace {
+
+const double kSky[3 * 4] = {1, 0, 0, 0, 1, 0, 0, 0, 1, 0, 1, 0};
+const fh_select kSel{1000, 4, 8, 2.5};
+
+fh_ctx *make_ctx() {
+    fh_ctx *c = nullptr;
+    CHECK(fh_ctx_create(0, &c) == FH_OK);
+    return c;
+}
+
+// n_fft FFTs of `per` peaks each at natural bins 1000, 1002, ...
+fh_peakmap *upload(fh_ctx *c, int n_fft, int per) {
+    std::vector<int64_t> off(n_fft + 1);
+    std::vector<int32_t> bins((size_t)n_fft * per);
+    std::vector<double> t(n_fft), v(3 * (size_t)n_fft, 1e-5);
+    for (int i = 0; i < n_fft; ++i) {
+        off[i + 1] = off[i] + per;
+        t[i] = 1000.0 * i;
+        for (int k = 0; k < per; ++k) bins[(size_t)i * per + k] = 1000 + 2 * k;
+    }
+    const fh_peakmap_desc d{n_fft, off[n_fft], off.data(), bins.data(), t.data(), v.data(), 1024.0};
+    fh_peakmap *pm = nullptr;
+    CHECK(fh_peakmap_upload(c, &d, nullptr, &pm) == FH_OK);
+    return pm;
+}
+
+fh_grid grid(int nf, int ns) { return fh_grid{10, 10000, nf, ns, -1e-12, 1e-13, 0.0}; }
+
+const fake::Launch *last(const char *what) {
+    for (size_t k = fake::launches.size(); k-- > 0;)
+        if (!std::strcmp(fake::launches[k].what, what)) return &fake::launches[k];
+    return nullptr;
+}
+
+fh_candidate g_out[4096];
+int g_stream;  // its address stands for a created stream
+
+fh_status search(fh_ctx *c, fh_peakmap *pm, const fh_grid &g, int n_sky, bool graph) {
+    const fh_options o{FH_SCHED_PERSISTENT, 0, 0, graph ? 1 : 0};
+    return fh_hough_candidates(c, pm, n_sky, kSky, nullptr, 0, &g, &kSel, &o, g_out, (hipStream_t)&g_stream);
+}
+
+// A captured search belongs to its peakmap, not to the address: another
+// peakmap that takes a released one's address is captured anew.
+void captured_search_of_a_released_peakmap() {
+    fh_ctx *c = make_ctx();
+    const fh_grid g = grid(4000, 17);
+    fh_peakmap *a = upload(c, 200, 50);
+    CHECK(search(c, a, g, 2, true) == FH_OK && fake::graphs == 1);
+    CHECK(search(c, a, g, 2, true) == FH_OK && fake::graphs == 1);
+    fh_peakmap_release(c, a);
+    fh_peakmap *b = upload(c, 200, 40);
+    if (b != a) std::exit(77);
+    CHECK(search(c, b, g, 2, true) == FH_OK && fake::graphs == 2);
+    CHECK(last("tiles")->n_peaks == 200 * 40);
+    fh_peakmap_release(c, b);
+    fh_ctx_destroy(c);
+}
+
+struct Case {
+    const char *name;
+    void (*run)();
+};
+const Case kCases[] = {
+    {"captured_search_of_a_released_peakmap", captured_search_of_a_released_peakmap},
+};
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    for (const Case &k : kCases)
+        if (argc > 1 && !std::strcmp(argv[1], k.name)) {
+            k.run();
+            return 0;
+        }
+    std::printf("no such case\n");
+    return 1;
+}
