@@ -70,6 +70,23 @@ fh_status scratch_init(int device) {
     return FH_OK;
 }
 
+// Device and pinned host memory, nullptr when there is none.  HIP keeps the
+// error of a failed call until it is asked for, and every launch asks for it:
+// an allocation that may fail without its caller failing takes its error along.
+void *device_alloc(size_t n) {
+    void *p = nullptr;
+    if (hipMalloc(&p, n) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+void *pinned_alloc(size_t n) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, n, hipHostMallocDefault) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
 // A device buffer that only grows.  Growing synchronises the stream first so
 // that no enqueued kernel still uses the old allocation.
 struct DevBuf {
@@ -85,10 +102,7 @@ struct DevBuf {
             bytes = 0;
         }
         size_t n = std::max(want, (size_t)256);
-        if (hipMalloc(&ptr, n) != hipSuccess) {
-            ptr = nullptr;
-            return fail(FH_E_NOMEM, "hipMalloc of %zu bytes failed", n);
-        }
+        if (!(ptr = device_alloc(n))) return fail(FH_E_NOMEM, "hipMalloc of %zu bytes failed", n);
         bytes = n;
         return FH_OK;
     }
@@ -109,13 +123,10 @@ struct PinnedBuf {
             if (e != hipSuccess) return fail(FH_E_DEVICE, "hipStreamSynchronize: %s", hipGetErrorString(e));
             (void)hipHostFree(ptr);
             ptr = nullptr;
+            bytes = 0;
         }
         size_t n = std::max(want, (size_t)4096);
-        if (hipHostMalloc(&ptr, n, hipHostMallocDefault) != hipSuccess) {
-            ptr = nullptr;
-            bytes = 0;
-            return fail(FH_E_NOMEM, "hipHostMalloc of %zu bytes failed", n);
-        }
+        if (!(ptr = pinned_alloc(n))) return fail(FH_E_NOMEM, "hipHostMalloc of %zu bytes failed", n);
         bytes = n;
         return FH_OK;
     }
@@ -153,10 +164,10 @@ struct BlockPool {
             *bytes = b.bytes;
             return b.ptr;
         }
-        void *p = nullptr;
-        if (hipMalloc(&p, n) != hipSuccess) {
+        void *p = device_alloc(n);
+        if (!p) {
             trim();
-            if (hipMalloc(&p, n) != hipSuccess) return nullptr;
+            if (!(p = device_alloc(n))) return nullptr;
         }
         *bytes = n;
         return p;
@@ -2233,13 +2244,12 @@ fh_status fh_server_create(fh_ctx *ctx, int64_t hbm_budget, int32_t lanes, int32
     // the arena is carved in 256-byte pieces
     const int64_t budget = hbm_budget / 256 * 256;
     if (budget <= 0) return fail(FH_E_INVALID, "hbm_budget must be at least 256 bytes");
-    void *mem = nullptr;
-    if (hipMalloc(&mem, (size_t)budget) != hipSuccess) {
+    void *mem = device_alloc((size_t)budget);
+    if (!mem) {
         ctx->blocks.trim();
-        mem = nullptr;
+        mem = device_alloc((size_t)budget);
     }
-    if (!mem && hipMalloc(&mem, (size_t)budget) != hipSuccess)
-        return fail(FH_E_NOMEM, "allocating the server's %lld-byte arena failed", (long long)budget);
+    if (!mem) return fail(FH_E_NOMEM, "allocating the server's %lld-byte arena failed", (long long)budget);
     fh_server *srv = new fh_server();
     srv->ctx = ctx;
     srv->budget = budget;

@@ -75,12 +75,66 @@ void captured_search_of_a_released_peakmap() {
     fh_ctx_destroy(c);
 }
 
+// A peakmap built from n_fft spectra, of `total` peaks.
+fh_status from_spectra(fh_ctx *c, int n_fft, int n_bins, int64_t total, fh_peakmap **pm) {
+    static const float sp[1] = {0.0f};
+    std::vector<double> t(n_fft), v(3 * (size_t)n_fft, 1e-5);
+    for (int i = 0; i < n_fft; ++i) t[i] = 1000.0 * i;
+    fake::meta_total = total;
+    fake::meta_most = total / n_fft + 1;
+    return fh_peakmap_from_spectra(c, n_fft, n_bins, n_bins, sp, nullptr, 1000, 2.5f, t.data(), v.data(), 1024.0,
+                                   nullptr, pm);
+}
+
+constexpr int64_t kMB = 1 << 20;
+
+// An allocation that succeeds once the released peakmaps' blocks are given
+// back leaves no error for the launches after it.
+void allocation_after_trimming() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *a = upload(c, 1000, 4000), *b = nullptr;  // 16 MB
+    fh_peakmap_release(c, a);
+    fake::limit = fake::used.load() + 8 * kMB;
+    CHECK(from_spectra(c, 1000, 8000, 100000, &b) == FH_OK);  // 16 MB of rows; pool given back
+    fake::limit = INT64_MAX;
+    fh_peakmap_release(c, b);
+    a = upload(c, 1000, 4000);
+    fh_peakmap_release(c, a);
+    fh_peakmap *d = upload(c, 100, 100);
+    fake::limit = fake::used.load() + 8 * kMB;
+    fh_server *srv = nullptr;
+    CHECK(fh_server_create(c, 16 * kMB, 2, 16, &srv) == FH_OK);
+    fake::limit = INT64_MAX;
+    CHECK(search(c, d, grid(2000, 17), 2, false) == FH_OK);
+    fh_server_destroy(srv);
+    fh_peakmap_release(c, d);
+    fh_ctx_destroy(c);
+}
+
+// A refused allocation fails its own call, not the next one.
+void search_after_a_failed_allocation() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *d = upload(c, 100, 100);
+    fh_server *srv = nullptr;
+    fake::limit = fake::used.load() + 8 * kMB;
+    CHECK(fh_server_create(c, 16 * kMB, 2, 16, &srv) == FH_E_NOMEM);
+    CHECK(search(c, d, grid(2000, 17), 2, false) == FH_OK);
+    fake::limit = fake::used.load();
+    CHECK(search(c, d, grid(400000, 17), 2, false) == FH_E_NOMEM);
+    fake::limit = INT64_MAX;
+    CHECK(search(c, d, grid(2000, 17), 2, false) == FH_OK);
+    fh_peakmap_release(c, d);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
 };
 const Case kCases[] = {
     {"captured_search_of_a_released_peakmap", captured_search_of_a_released_peakmap},
+    {"allocation_after_trimming", allocation_after_trimming},
+    {"search_after_a_failed_allocation", search_after_a_failed_allocation},
 };
 
 }  // namespace

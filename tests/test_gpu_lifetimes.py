@@ -54,3 +54,21 @@ def test_captured_searches_of_successive_peakmaps(ctx):
         np.testing.assert_array_equal(api.decode_candidates(out)["bin"][2][idx[..., 0] == 1],
                                       idx[..., 1][idx[..., 0] == 1])
         dpm.release()
+
+
+def test_map_after_a_refused_allocation(ctx):
+    """An allocation that the device has no room for fails its own call only:
+    HIP keeps the error of a failed call, and launches report it."""
+    import torch
+    from paper_1407_8333_amd import api
+    from paper_1407_8333_amd._lib import FHError
+    pm, grid = _band(510, 0.08)
+    dpm = ctx.upload(pm)
+    nhat = synth.sky_uniform(1, synth.rng_for(4))[0]
+    with pytest.raises(FHError) as e:
+        api.Server(ctx, 1 << 46)
+    assert e.value.status == -2  # FH_E_NOMEM
+    got = api.fh_hough_map_i32(ctx, dpm, nhat, grid)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(got.cpu().numpy(), oracle.hough_map(pm, grid, nhat).astype(np.int32))
+    dpm.release()

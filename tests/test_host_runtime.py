@@ -36,6 +36,8 @@ def _run(exe, name):
 
 @pytest.mark.parametrize("name", [
     "captured_search_of_a_released_peakmap",
+    "allocation_after_trimming",
+    "search_after_a_failed_allocation",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
