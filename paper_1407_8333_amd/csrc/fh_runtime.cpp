@@ -721,12 +721,14 @@ fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, co
     if ((s = ctx->cur->sky.ensure((size_t)24 * n_sky, st))) return s;
     if ((s = ctx->cur->qctr.ensure(4 * kXcds, st))) return s;
     if ((s = ctx->err.ensure(4, st))) return s;
+    // Partial tiles and the rank table only save time: where there is no room
+    // for them, the tiles are not shared and the windows are searched for.
     const size_t pb = search_parts_bytes(ctx, pm, g, p, slots, n_sky);
-    if (pb && (s = ctx->cur->part.ensure(pb, st))) return s;
+    if (pb && (s = ctx->cur->part.ensure(pb, st)) && s != FH_E_NOMEM) return s;
     b.part = (uint32_t *)ctx->cur->part.ptr;
     b.part_bytes = ctx->cur->part.bytes;
     const size_t rb = rank_bytes(ctx, pm, p, slots);
-    if (rb && (s = ctx->cur->rank.ensure(rb, st))) return s;
+    if (rb && (s = ctx->cur->rank.ensure(rb, st)) && s != FH_E_NOMEM) return s;
     b.rank = rb ? (uint2 *)ctx->cur->rank.ptr : nullptr;
     b.gwin = reinterpret_cast<int64_t *>((char *)ctx->cur->sht.ptr + sl.gwin);
     b.rec = reinterpret_cast<uint2 *>((char *)ctx->cur->sht.ptr + sl.rec);

@@ -127,6 +127,35 @@ void search_after_a_failed_allocation() {
     fh_ctx_destroy(c);
 }
 
+// Partial tiles and the rank table are left out where there is no room for
+// them; the search runs all the same.
+void search_without_room_for_optional_buffers() {
+    fh_ctx *c = make_ctx();
+    const fh_grid g = grid(4000, 17);
+    fh_peakmap *pm = upload(c, 3000, 80);
+    const int64_t before = fake::used;
+    CHECK(search(c, pm, g, 4, false) == FH_OK);
+    CHECK(last("tiles")->parts > 1 && last("front")->rank);
+    const int64_t all = fake::used - before, part = (int64_t)c->main_ws.part.bytes, rank = (int64_t)c->main_ws.rank.bytes;
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+    c = make_ctx();
+    pm = upload(c, 3000, 80);
+    fake::limit = fake::used + all - part - rank;
+    for (const bool graph : {false, true}) {
+        CHECK(search(c, pm, g, 4, graph) == FH_OK);
+        CHECK(last("tiles")->parts == 1 && !last("front")->rank);
+    }
+    fake::limit = fake::used + rank;
+    CHECK(search(c, pm, g, 4, false) == FH_OK);
+    CHECK(last("tiles")->parts == 1 && last("front")->rank);
+    fake::limit = fake::used + part;
+    CHECK(search(c, pm, g, 4, true) == FH_OK);
+    CHECK(last("tiles")->parts > 1 && last("front")->rank);
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -135,6 +164,7 @@ const Case kCases[] = {
     {"captured_search_of_a_released_peakmap", captured_search_of_a_released_peakmap},
     {"allocation_after_trimming", allocation_after_trimming},
     {"search_after_a_failed_allocation", search_after_a_failed_allocation},
+    {"search_without_room_for_optional_buffers", search_without_room_for_optional_buffers},
 };
 
 }  // namespace

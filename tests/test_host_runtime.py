@@ -38,6 +38,7 @@ def _run(exe, name):
     "captured_search_of_a_released_peakmap",
     "allocation_after_trimming",
     "search_after_a_failed_allocation",
+    "search_without_room_for_optional_buffers",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
