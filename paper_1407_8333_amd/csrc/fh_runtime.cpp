@@ -87,11 +87,15 @@ void *pinned_alloc(size_t n) {
     return nullptr;
 }
 
+struct Spare;
+
 // A device buffer that only grows.  Growing synchronises the stream first so
 // that no enqueued kernel still uses the old allocation.
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    Spare *spare = nullptr;  // given back when there is no room to grow
+    bool allocate(size_t n);
     fh_status ensure(size_t want, hipStream_t st) {
         if (want <= bytes) return FH_OK;
         if (ptr) {
@@ -102,7 +106,7 @@ struct DevBuf {
             bytes = 0;
         }
         size_t n = std::max(want, (size_t)256);
-        if (!(ptr = device_alloc(n))) return fail(FH_E_NOMEM, "hipMalloc of %zu bytes failed", n);
+        if (!allocate(n)) return fail(FH_E_NOMEM, "hipMalloc of %zu bytes failed", n);
         bytes = n;
         return FH_OK;
     }
@@ -142,35 +146,29 @@ struct PinnedBuf {
 // hipMalloc and hipFree (which maps and unmaps the pages): 700 us of calls
 // around 70 us of kernels for a band of 2.1 M peaks.  At most kMaxBlocks
 // blocks of kMaxBytes together; a block serves requests of half its size or
-// more; given back when an allocation fails and with the context.
+// more; given back when an allocation fails (Spare) and with the context.
 struct BlockPool {
     static constexpr size_t kMaxBlocks = 8;
     static constexpr size_t kMaxBytes = (size_t)256 << 20;
     struct Block { void *ptr; size_t bytes; };
     std::vector<Block> free_;
     size_t held = 0;
-    // a block of at least n bytes and its size, or nullptr
+    // the size that a request of n bytes is allocated with
+    static size_t block_bytes(size_t n) { return (std::max(n, (size_t)1) + 4095) / 4096 * 4096; }
+    // a kept block of at least n bytes and its size, or nullptr
     void *take(size_t n, size_t *bytes) {
-        n = (std::max(n, (size_t)1) + 4095) / 4096 * 4096;
+        n = block_bytes(n);
         size_t at = free_.size();
         for (size_t k = 0; k < free_.size(); ++k)
             if (free_[k].bytes >= n && free_[k].bytes <= 2 * n &&
                 (at == free_.size() || free_[k].bytes < free_[at].bytes))
                 at = k;
-        if (at < free_.size()) {
-            const Block b = free_[at];
-            free_.erase(free_.begin() + (long)at);
-            held -= b.bytes;
-            *bytes = b.bytes;
-            return b.ptr;
-        }
-        void *p = device_alloc(n);
-        if (!p) {
-            trim();
-            if (!(p = device_alloc(n))) return nullptr;
-        }
-        *bytes = n;
-        return p;
+        if (at == free_.size()) return nullptr;
+        const Block b = free_[at];
+        free_.erase(free_.begin() + (long)at);
+        held -= b.bytes;
+        *bytes = b.bytes;
+        return b.ptr;
     }
     // no enqueued work uses the block any more
     void give(void *p, size_t bytes) {
@@ -187,12 +185,53 @@ struct BlockPool {
             free_.erase(free_.begin());
         }
     }
-    void trim() {
+    // whether there was a block
+    bool trim() {
+        const bool any = !free_.empty();
         for (const Block &b : free_) (void)hipFree(b.ptr);
         free_.clear();
         held = 0;
+        return any;
     }
 };
+
+// Device memory that a context keeps past a call only to save time: the blocks
+// of released peakmaps, the row scratch of peakmap construction, partial tiles
+// and rank tables.  Any allocation of the context that finds no room has it
+// given back and is tried again.
+struct Spare {
+    BlockPool blocks;
+    DevBuf *rows = nullptr;  // the row scratch, and
+    bool rows_busy = false;  // whether a call is using it
+    std::vector<DevBuf *> other;
+    // frees it all; false: there was nothing
+    bool give_back() {
+        bool any = blocks.trim();
+        if (hipDeviceSynchronize() != hipSuccess) {  // (a stream is being captured: the rest may be in use)
+            (void)hipGetLastError();
+            return any;
+        }
+        auto drop = [&](DevBuf *b) {
+            any = any || b->ptr;
+            b->release();
+        };
+        if (!rows_busy) drop(rows);
+        for (DevBuf *b : other) drop(b);
+        return any;
+    }
+    void *allocate(size_t n) {
+        void *p = device_alloc(n);
+        return p || !give_back() ? p : device_alloc(n);
+    }
+    // a block of at least n bytes and its size, or nullptr
+    void *block(size_t n, size_t *bytes) {
+        if (void *p = blocks.take(n, bytes)) return p;
+        *bytes = BlockPool::block_bytes(n);
+        return allocate(*bytes);
+    }
+};
+
+bool DevBuf::allocate(size_t n) { return (ptr = spare ? spare->allocate(n) : device_alloc(n)) != nullptr; }
 
 // Number of a peakmap, never given twice in a process (a copy is another
 // peakmap).  What a context keeps for a peakmap past a call is kept by it: a
@@ -273,7 +312,7 @@ struct fh_ctx {
     // 8 us), and for staged times and velocities
     DevBuf pm_rows, pm_counts;
     PinnedBuf h_small, h_stage;
-    BlockPool blocks;
+    Spare spare;
     // autotuned tile width per problem shape (shared by weighted and
     // unweighted searches: the two kernels differ only in the added value)
     std::map<std::tuple<int, int, int, int>, int> tuned;
@@ -295,6 +334,15 @@ struct fh_ctx {
     struct Span { hipEvent_t a, b; int kind; };
     std::vector<Span> spans;
     int64_t prof_updates = 0;
+
+    fh_ctx() {
+        spare.rows = &pm_rows;
+        spare.other = {&main_ws.part, &main_ws.rank};
+        for (DevBuf *b : {&main_ws.sht, &main_ws.Y, &main_ws.Y64, &main_ws.win, &main_ws.wsort, &main_ws.colmax,
+                          &main_ws.wq, &main_ws.ws, &main_ws.sky, &main_ws.qctr, &err, &rf_offsets, &rf_bins,
+                          &rf_first, &rf_counts, &rf_cands, &rf_aux, &cl_hist, &cl_s2, &pm_rows, &pm_counts})
+            b->spare = &spare;
+    }
 };
 
 namespace {
@@ -387,7 +435,7 @@ fh_status check_times(fh_peakmap *pm, const double *t, const double *v) {
 bool alloc_head(fh_ctx *ctx, fh_peakmap *pm) {
     const size_t N = (size_t)pm->n_fft;
     pm->device = ctx->device;
-    pm->head = ctx->blocks.take(32 * N + 8 * (N + 1), &pm->head_bytes);
+    pm->head = ctx->spare.block(32 * N + 8 * (N + 1), &pm->head_bytes);
     if (!pm->head) return false;
     pm->d_t = (double *)pm->head;
     pm->d_v = pm->d_t + N;
@@ -396,7 +444,7 @@ bool alloc_head(fh_ctx *ctx, fh_peakmap *pm) {
 }
 
 bool alloc_bins(fh_ctx *ctx, fh_peakmap *pm, int64_t n) {
-    pm->d_bins = (int32_t *)ctx->blocks.take(4 * (size_t)std::max<int64_t>(1, n), &pm->bins_bytes);
+    pm->d_bins = (int32_t *)ctx->spare.block(4 * (size_t)std::max<int64_t>(1, n), &pm->bins_bytes);
     return pm->d_bins != nullptr;
 }
 
@@ -702,10 +750,21 @@ int64_t edge_bytes_per_sky(const fh_ctx *ctx, const fh_peakmap *pm) {
     return (needs_full_edges(ctx, pm) ? 12 : 4) * y_stride(pm->n_peaks, pm->n_fft);
 }
 
-fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
-                         int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
+// Calls that use the context's buffers are not captured by the caller: a
+// later call may move the buffers under the graph (the static map is made
+// for that).
+fh_status refuse_capture(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (st && hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
+        return fail(FH_E_DEVICE, "the stream is being captured");
+    return FH_OK;
+}
+
+fh_status ensure_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
+                           int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
     const int64_t N = pm->n_fft;
     fh_status s;
+    if ((s = refuse_capture(st))) return s;
     const ShiftLayout sl = shift_layout(N, p.nrb_tab, p.nrbg);
     if ((s = ctx->cur->sht.ensure(sl.total, st))) return s;
     if ((s = ctx->cur->Y.ensure((size_t)4 * y_stride(pm->n_peaks, pm->n_fft) * slots, st))) return s;
@@ -745,25 +804,6 @@ fh_status grow_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, co
     b.qctr = (int32_t *)ctx->cur->qctr.ptr;
     b.err = (int32_t *)ctx->err.ptr;
     return FH_OK;
-}
-
-// Calls that use the context's buffers are not captured by the caller: a
-// later call may move the buffers under the graph (the static map is made
-// for that).
-fh_status refuse_capture(hipStream_t st) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (st && hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
-        return fail(FH_E_DEVICE, "the stream is being captured");
-    return FH_OK;
-}
-
-fh_status ensure_workspace(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p,
-                           int slots, int n_sky, bool weighted, hipStream_t st, ChunkBufs &b) {
-    if (const fh_status c = refuse_capture(st)) return c;
-    const fh_status s = grow_workspace(ctx, pm, g, p, slots, n_sky, weighted, st, b);
-    if (s != FH_E_NOMEM || ctx->blocks.held == 0) return s;
-    ctx->blocks.trim();
-    return grow_workspace(ctx, pm, g, p, slots, n_sky, weighted, st, b);
 }
 
 TileArgs tile_args(const fh_peakmap *pm, const fh_grid *g, const Plan &p, int slots,
@@ -1209,7 +1249,7 @@ void fh_ctx_destroy(fh_ctx *ctx) {
         b->release();
     ctx->h_small.release();
     ctx->h_stage.release();
-    ctx->blocks.trim();
+    ctx->spare.blocks.trim();
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
     delete ctx;
 }
@@ -1349,16 +1389,16 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
     hipStream_t st = (hipStream_t)stream;
     const int32_t cap = n_bins / 2 + 1;  // strict local maxima are never adjacent
     const size_t b_off = 8 * (size_t)(n_fft + 1), b_t = 8 * (size_t)n_fft, b_v = 24 * (size_t)n_fft;
-    s = ctx->pm_rows.ensure(4 * (size_t)n_fft * cap, st);
-    if (s == FH_E_NOMEM && ctx->blocks.held) {
-        ctx->blocks.trim();
-        s = ctx->pm_rows.ensure(4 * (size_t)n_fft * cap, st);
-    }
-    if (s || (s = ctx->pm_counts.ensure(4 * (size_t)n_fft, st)) ||
-        (s = ctx->h_stage.ensure(b_t + b_v, st))) {
+    struct Busy {  // the rows stay while this call uses them
+        bool &f;
+        ~Busy() { f = false; }
+    } busy{ctx->spare.rows_busy};
+    if ((s = ctx->pm_counts.ensure(4 * (size_t)n_fft, st)) || (s = ctx->h_stage.ensure(b_t + b_v, st)) ||
+        (s = ctx->pm_rows.ensure(4 * (size_t)n_fft * cap, st))) {
         delete pm;
         return s;
     }
+    ctx->spare.rows_busy = true;
     if (!alloc_head(ctx, pm)) {
         fh_peakmap_release(ctx, pm);
         return fail(FH_E_NOMEM, "device allocation for the peakmap failed");
@@ -1419,8 +1459,8 @@ void fh_peakmap_release(fh_ctx *ctx, fh_peakmap *pm) {
     if (ctx && ctx->device == pm->device) {
         // as hipFree does: no block is handed on while the device may use it
         if (pm->head || pm->d_bins) (void)hipDeviceSynchronize();
-        ctx->blocks.give(pm->head, pm->head_bytes);
-        ctx->blocks.give(pm->d_bins, pm->bins_bytes);
+        ctx->spare.blocks.give(pm->head, pm->head_bytes);
+        ctx->spare.blocks.give(pm->d_bins, pm->bins_bytes);
     } else {
         if (pm->head) (void)hipFree(pm->head);
         if (pm->d_bins) (void)hipFree(pm->d_bins);
@@ -2246,11 +2286,7 @@ fh_status fh_server_create(fh_ctx *ctx, int64_t hbm_budget, int32_t lanes, int32
     // the arena is carved in 256-byte pieces
     const int64_t budget = hbm_budget / 256 * 256;
     if (budget <= 0) return fail(FH_E_INVALID, "hbm_budget must be at least 256 bytes");
-    void *mem = device_alloc((size_t)budget);
-    if (!mem) {
-        ctx->blocks.trim();
-        mem = device_alloc((size_t)budget);
-    }
+    void *mem = ctx->spare.allocate((size_t)budget);
     if (!mem) return fail(FH_E_NOMEM, "allocating the server's %lld-byte arena failed", (long long)budget);
     fh_server *srv = new fh_server();
     srv->ctx = ctx;

@@ -156,6 +156,43 @@ void search_without_room_for_optional_buffers() {
     fh_ctx_destroy(c);
 }
 
+// Whatever a context keeps only to save time makes room for a call that needs
+// it: the row scratch of peakmap construction (16 MB here), partial tiles and
+// the rank table, released peakmaps' blocks.
+void kept_memory_makes_room() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *a = nullptr, *b = nullptr, *pm = upload(c, 3000, 80);
+    CHECK(from_spectra(c, 1000, 8000, 100000, &a) == FH_OK);
+    const int64_t rows = (int64_t)c->pm_rows.bytes;
+    CHECK(rows >= 15 * kMB);
+    // a search of more memory than is left without the rows
+    fake::limit = fake::used + rows / 2;
+    CHECK(search(c, pm, grid(200000, 17), 1, false) == FH_OK);
+    CHECK(c->pm_rows.ptr == nullptr);
+    // a histogram that takes the place of partial tiles
+    fake::limit = INT64_MAX;
+    CHECK(search(c, pm, grid(4000, 17), 4, false) == FH_OK && last("tiles")->parts > 1);
+    const int64_t part = (int64_t)c->main_ws.part.bytes;
+    fake::limit = fake::used + part / 2;
+    double stats[2];
+    CHECK(fh_robust_stats(c, (const int32_t *)g_out, 100, (int32_t)(part / 8 * 3 / 4), stats, nullptr) == FH_OK);
+    CHECK(c->main_ws.part.ptr == nullptr);
+    // a peakmap's bins, which do the same while the rows are in use
+    fake::limit = INT64_MAX;
+    CHECK(from_spectra(c, 1000, 8000, 100000, &b) == FH_OK);
+    fh_peakmap_release(c, b);
+    CHECK(search(c, pm, grid(4000, 17), 4, false) == FH_OK && last("tiles")->parts > 1);
+    fake::limit = fake::used + part / 2;
+    CHECK(from_spectra(c, 1000, 8000, part / 4 * 3 / 4, &b) == FH_OK);
+    CHECK(c->main_ws.part.ptr == nullptr && c->pm_rows.ptr != nullptr);
+    fake::limit = INT64_MAX;
+    fh_peakmap_release(c, a);
+    fh_peakmap_release(c, b);
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+    CHECK(fake::used == 0);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -165,6 +202,7 @@ const Case kCases[] = {
     {"allocation_after_trimming", allocation_after_trimming},
     {"search_after_a_failed_allocation", search_after_a_failed_allocation},
     {"search_without_room_for_optional_buffers", search_without_room_for_optional_buffers},
+    {"kept_memory_makes_room", kept_memory_makes_room},
 };
 
 }  // namespace

@@ -39,6 +39,7 @@ def _run(exe, name):
     "allocation_after_trimming",
     "search_after_a_failed_allocation",
     "search_without_room_for_optional_buffers",
+    "kept_memory_makes_room",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
