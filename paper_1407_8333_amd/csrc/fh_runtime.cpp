@@ -2083,8 +2083,9 @@ struct SearchLayout {
     ShiftLayout shl{};
 };
 
+// (with_rank: room for the rank table, which only saves time)
 SearchLayout search_layout(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const Plan &p, int chunk,
-                           int n_sky, bool weighted) {
+                           int n_sky, bool weighted, bool with_rank = true) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t N = (size_t)pm->n_fft, c = (size_t)chunk;
     const size_t ys = (size_t)y_stride(pm->n_peaks, pm->n_fft);
@@ -2103,7 +2104,7 @@ SearchLayout search_layout(const fh_ctx *ctx, const fh_peakmap *pm, const fh_gri
     L.ws = o;     o += al(sizeof(WeightStats) * c);
     L.sky = o;    o += al(24 * (size_t)n_sky);
     L.qctr = o;   o += al(4 * kXcds);
-    L.rank_size = rank_bytes(ctx, pm, p, chunk);
+    L.rank_size = with_rank ? rank_bytes(ctx, pm, p, chunk) : 0;
     L.rank = o;   o += al(L.rank_size);
     L.total = o;
     return L;
@@ -2328,29 +2329,31 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
     R.sky.assign(req->sky, req->sky + 3 * (int64_t)req->n_sky);
     R.r.sky = nullptr;
     R.t_submit = Clock::now();
-    // the largest chunk whose footprint fits one lane's share of the budget,
-    // with the tile width and partial tiles of a launch of that many directions
+    // the largest chunk whose footprint fits one lane's share of the budget.
+    // What only saves time is left out before the chunk is halved: the partial
+    // tiles, the rank table, and then the tile width of a launch of that many
+    // directions (the default one has fewer windows).
     const bool weighted = req->d_w != nullptr;
     const int64_t share = srv->budget / (int64_t)srv->lanes.size();
-    auto plan = [&](int chunk, int width, bool parts) {
+    auto fits = [&](int chunk, int width, bool parts, bool rank) {
         const Plan p = make_plan(req->grid, width);
         R.W = width;
         R.chunk = (int)std::min<int64_t>(chunk, chunk_by_tiles(p));
-        R.layout = search_layout(ctx, req->pm, &req->grid, p, R.chunk, req->n_sky, weighted);
+        R.layout = search_layout(ctx, req->pm, &req->grid, p, R.chunk, req->n_sky, weighted, rank);
         if (parts) {
             R.layout.part = R.layout.total;
             R.layout.part_bytes =
                 (search_parts_bytes(ctx, req->pm, &req->grid, p, R.chunk, req->n_sky) + 255) / 256 * 256;
             R.layout.total += R.layout.part_bytes;
         }
-        return (int64_t)R.layout.total;
+        return (int64_t)R.layout.total <= share;
     };
-    int chunk = std::min<int>(req->n_sky, 256);
-    while (plan(chunk, search_tile_bins(ctx, req->pm, &req->grid, chunk), true) > share && R.chunk > 1)
-        chunk = (R.chunk + 1) / 2;
-    // one direction at a time, in the least memory
-    if ((int64_t)R.layout.total > srv->budget) plan(1, R.W, false);
-    if ((int64_t)R.layout.total > srv->budget) plan(1, choose_tile_bins(ctx, req->pm, &req->grid, 0), false);
+    for (int chunk = std::min<int>(req->n_sky, 256);; chunk = (R.chunk + 1) / 2) {
+        const int w = search_tile_bins(ctx, req->pm, &req->grid, chunk);
+        if (fits(chunk, w, true, true) || fits(chunk, w, false, true) || fits(chunk, w, false, false) ||
+            fits(chunk, choose_tile_bins(ctx, req->pm, &req->grid, 0), false, false) || R.chunk == 1)
+            break;  // (one direction in the least memory may take more than a share)
+    }
     R.footprint = (int64_t)R.layout.total;
     if (R.footprint > srv->budget) {
         srv->next_id--;

@@ -193,6 +193,49 @@ void kept_memory_makes_room() {
     CHECK(fake::used == 0);
 }
 
+// A request's directions run in one launch when a lane's share of the budget
+// holds the search itself: what only saves time is left out first.
+void request_in_a_tight_budget() {
+    fh_ctx *c = make_ctx();
+    const fh_grid g = grid(4000, 17);
+    fh_peakmap *pm = upload(c, 3000, 80);
+    double sky[3 * 16];
+    for (int k = 0; k < 3 * 16; ++k) sky[k] = kSky[k % 3];
+    const fh_request q{pm, g, kSel, 16, sky, nullptr, 0, g_out, 0};
+    auto served = [&](int64_t budget, int lanes) {
+        fh_server *srv = nullptr;
+        uint64_t id = 0;
+        fh_completion done{};
+        int32_t n = 0;
+        CHECK(fh_server_create(c, budget, lanes, 16, &srv) == FH_OK);
+        CHECK(fh_server_submit(srv, &q, &id) == FH_OK);
+        fake::launches.clear();
+        CHECK(fh_server_drain(srv) == FH_OK);
+        CHECK(fh_server_poll(srv, &done, 1, &n) == FH_OK && n == 1 && done.status == FH_OK);
+        CHECK(done.footprint <= budget);
+        fh_server_destroy(srv);
+    };
+    // (the rank table is the last piece of a layout)
+    auto bare = [&](int width, int chunk) {
+        return (int64_t)search_layout(c, pm, &g, make_plan(g, width), chunk, 16, false).rank;
+    };
+    const int wide = choose_tile_bins(c, pm, &g, 0), narrow = search_tile_bins(c, pm, &g, 16);
+    CHECK(wide > narrow && bare(wide, 16) < bare(narrow, 16));
+    served(64 * kMB, 2);
+    CHECK(last("tiles")->slots == 16 && last("front")->rank);
+    for (const int width : {narrow, wide}) {
+        served(2 * bare(width, 16), 2);
+        CHECK(last("tiles")->slots == 16 && last("tiles")->parts == 1 && !last("front")->rank);
+    }
+    served(2 * (bare(wide, 16) - 256), 2);
+    CHECK(last("tiles")->slots == 8);
+    // the least that one direction takes, with a share of half of it
+    served(bare(wide, 1), 2);
+    CHECK(last("tiles")->slots == 1);
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -203,6 +246,7 @@ const Case kCases[] = {
     {"search_after_a_failed_allocation", search_after_a_failed_allocation},
     {"search_without_room_for_optional_buffers", search_without_room_for_optional_buffers},
     {"kept_memory_makes_room", kept_memory_makes_room},
+    {"request_in_a_tight_budget", request_in_a_tight_budget},
 };
 
 }  // namespace

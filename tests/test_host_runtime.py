@@ -40,6 +40,7 @@ def _run(exe, name):
     "search_after_a_failed_allocation",
     "search_without_room_for_optional_buffers",
     "kept_memory_makes_room",
+    "request_in_a_tight_budget",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
