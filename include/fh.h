@@ -43,7 +43,8 @@
  *     arguments, enqueue kernels on `stream` and return.
  *   - Library workspaces are owned by the context and grow on demand; a call
  *     that has to grow one first synchronises `stream`.
- *   - A context may be used by one host thread at a time.
+ *   - A context may be used by one host thread at a time; peakmaps may be
+ *     released on any thread meanwhile.
  *   - Errors: functions return a negative fh_status and set a thread-local
  *     message read with fh_last_error().  Nothing is enqueued after a failed
  *     validation.  Conditions that can only be seen on the device (invalid

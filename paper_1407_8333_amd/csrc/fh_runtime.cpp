@@ -147,17 +147,22 @@ struct PinnedBuf {
 // around 70 us of kernels for a band of 2.1 M peaks.  At most kMaxBlocks
 // blocks of kMaxBytes together; a block serves requests of half its size or
 // more; given back when an allocation fails (Spare) and with the context.
+// Locked: a peakmap may be released on another thread than the context's (a
+// garbage collector's) while the context's is building one.
 struct BlockPool {
     static constexpr size_t kMaxBlocks = 8;
     static constexpr size_t kMaxBytes = (size_t)256 << 20;
     struct Block { void *ptr; size_t bytes; };
+    std::mutex mu;
     std::vector<Block> free_;
     size_t held = 0;
+    BlockPool() { free_.reserve(kMaxBlocks + 1); }
     // the size that a request of n bytes is allocated with
     static size_t block_bytes(size_t n) { return (std::max(n, (size_t)1) + 4095) / 4096 * 4096; }
     // a kept block of at least n bytes and its size, or nullptr
     void *take(size_t n, size_t *bytes) {
         n = block_bytes(n);
+        std::lock_guard<std::mutex> lock(mu);
         size_t at = free_.size();
         for (size_t k = 0; k < free_.size(); ++k)
             if (free_[k].bytes >= n && free_[k].bytes <= 2 * n &&
@@ -177,6 +182,7 @@ struct BlockPool {
             (void)hipFree(p);
             return;
         }
+        std::lock_guard<std::mutex> lock(mu);
         free_.push_back({p, bytes});
         held += bytes;
         while (held > kMaxBytes || free_.size() > kMaxBlocks) {
@@ -187,6 +193,7 @@ struct BlockPool {
     }
     // whether there was a block
     bool trim() {
+        std::lock_guard<std::mutex> lock(mu);
         const bool any = !free_.empty();
         for (const Block &b : free_) (void)hipFree(b.ptr);
         free_.clear();

@@ -236,6 +236,29 @@ void request_in_a_tight_budget() {
     fh_ctx_destroy(c);
 }
 
+// Peakmaps released on another thread (as a garbage collector does) while the
+// context's own thread builds others: for the thread sanitizer.
+void peakmaps_released_on_another_thread() {
+    fh_ctx *c = make_ctx();
+    for (int rep = 0; rep < 20; ++rep) {
+        std::vector<fh_peakmap *> old;
+        for (int k = 0; k < 6; ++k) old.push_back(upload(c, 100, 10 + 20 * k));
+        std::thread other([&] {
+            for (fh_peakmap *p : old) fh_peakmap_release(c, p);
+        });
+        std::vector<fh_peakmap *> made;
+        for (int k = 0; k < 6; ++k) made.push_back(upload(c, 100, 12 + 20 * k));
+        fake::limit = fake::used.load();
+        fh_server *srv = nullptr;
+        CHECK(fh_server_create(c, 64 * kMB, 1, 1, &srv) == FH_E_NOMEM);  // gives the blocks back
+        fake::limit = INT64_MAX;
+        other.join();
+        for (fh_peakmap *p : made) fh_peakmap_release(c, p);
+    }
+    fh_ctx_destroy(c);
+    CHECK(fake::used == 0);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -247,6 +270,7 @@ const Case kCases[] = {
     {"search_without_room_for_optional_buffers", search_without_room_for_optional_buffers},
     {"kept_memory_makes_room", kept_memory_makes_room},
     {"request_in_a_tight_budget", request_in_a_tight_budget},
+    {"peakmaps_released_on_another_thread", peakmaps_released_on_another_thread},
 };
 
 }  // namespace
