@@ -416,7 +416,7 @@ fh_status fh_veto_bins(fh_ctx *ctx, const fh_peakmap *pm, int32_t k_lo, int32_t 
 /* A continuous-batching request server over one context.  Requests
  * (band = a resident peakmap + grid, sky patch, spin-down range) queue on the
  * host; fh_server_poll admits queued requests in arrival order whenever a lane
- * (a HIP stream) is free and a block of the request's HBM footprint is free in
+ * (a HIP stream) is free and a block for the request's workspace is free in
  * the server's arena, launches them, and returns finished ones.  The arena
  * is hbm_budget bytes of device memory allocated once by fh_server_create;
  * each running request's workspace is a block of it, returned when the
@@ -449,7 +449,9 @@ typedef struct {
     double queue_ms;       /* submit -> admission                               */
     double latency_ms;     /* submit -> completion seen by fh_server_poll       */
     double device_ms;      /* device time of the request's launches             */
-    int64_t footprint;     /* HBM bytes charged against the budget              */
+    int64_t footprint;     /* HBM bytes of workspace that the request needs; its
+                              block of the arena also holds what saves time,
+                              as far as budget / lanes has room for it         */
     int64_t cell_updates;
 } fh_completion;
 
@@ -461,8 +463,8 @@ fh_status fh_server_create(fh_ctx *ctx, int64_t hbm_budget, int32_t lanes, int32
                            fh_server **out);
 
 /* Validate and queue a request; *id receives its id.  Its directions run in
- * chunks sized so that one chunk's workspace fits budget / lanes where it
- * can.  FH_E_BUSY when the queue is full; FH_E_UNSUPPORTED when the request's
+ * chunks sized so that what one chunk's search needs fits budget / lanes where
+ * it can.  FH_E_BUSY when the queue is full; FH_E_UNSUPPORTED when the request's
  * workspace for one direction at a time exceeds the budget. */
 fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id);
 

@@ -2185,7 +2185,7 @@ struct ServerRequest {
     std::vector<double> sky;
     Clock::time_point t_submit, t_admit;
     SearchLayout layout;
-    int64_t footprint = 0;
+    int64_t footprint = 0;  // bytes that the search needs; its block holds layout.total
     size_t arena_off = 0;
     int32_t chunk = 1;
     int32_t W = 64;
@@ -2232,8 +2232,8 @@ void retire_lanes(fh_server *srv) {
             if (hipEventElapsedTime(&ms, L.ev_start, L.ev_done) == hipSuccess) R.device_ms = ms;
         }
         R.latency_ms = ms_between(R.t_submit, now);
-        srv->arena.release(R.arena_off, (size_t)R.footprint);
-        srv->in_flight -= R.footprint;
+        srv->arena.release(R.arena_off, R.layout.total);
+        srv->in_flight -= (int64_t)R.layout.total;
         srv->finished.push_back(R.id);
         L.req = 0;
     }
@@ -2248,9 +2248,9 @@ void admit(fh_server *srv) {
         for (size_t k = 0; k < srv->lanes.size(); ++k)
             if (!srv->lanes[k].req) { li = (int)k; break; }
         if (li < 0) break;  // wait for a lane
-        // arrival order: the head waits until a block of its footprint is free
+        // arrival order: the head waits until a block for its workspace is free
         size_t off = 0;
-        if (!srv->arena.alloc((size_t)R.footprint, &off)) break;
+        if (!srv->arena.alloc(R.layout.total, &off)) break;
         srv->queue.pop_front();
         Lane &L = srv->lanes[li];
         R.lane = li;
@@ -2273,7 +2273,7 @@ void admit(fh_server *srv) {
                            FH_SCHED_PERSISTENT, &q.sel, q.d_out, b, L.st, dirs);
         if (hipEventRecord(L.ev_done, L.st) != hipSuccess && !s) s = fail(FH_E_DEVICE, "hipEventRecord");
         R.status = s;
-        srv->in_flight += R.footprint;
+        srv->in_flight += (int64_t)R.layout.total;
         L.req = id;
     }
 }
@@ -2336,10 +2336,8 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
     R.sky.assign(req->sky, req->sky + 3 * (int64_t)req->n_sky);
     R.r.sky = nullptr;
     R.t_submit = Clock::now();
-    // the largest chunk whose footprint fits one lane's share of the budget.
-    // What only saves time is left out before the chunk is halved: the partial
-    // tiles, the rank table, and then the tile width of a launch of that many
-    // directions (the default one has fewer windows).
+    // the largest chunk whose search fits one lane's share of the budget, with
+    // the default tile width and without what only saves time
     const bool weighted = req->d_w != nullptr;
     const int64_t share = srv->budget / (int64_t)srv->lanes.size();
     auto fits = [&](int chunk, int width, bool parts, bool rank) {
@@ -2353,14 +2351,11 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
                 (search_parts_bytes(ctx, req->pm, &req->grid, p, R.chunk, req->n_sky) + 255) / 256 * 256;
             R.layout.total += R.layout.part_bytes;
         }
-        return (int64_t)R.layout.total <= share;
+        return (int64_t)R.layout.total;
     };
-    for (int chunk = std::min<int>(req->n_sky, 256);; chunk = (R.chunk + 1) / 2) {
-        const int w = search_tile_bins(ctx, req->pm, &req->grid, chunk);
-        if (fits(chunk, w, true, true) || fits(chunk, w, false, true) || fits(chunk, w, false, false) ||
-            fits(chunk, choose_tile_bins(ctx, req->pm, &req->grid, 0), false, false) || R.chunk == 1)
-            break;  // (one direction in the least memory may take more than a share)
-    }
+    const int wide = choose_tile_bins(ctx, req->pm, &req->grid, 0);
+    for (int chunk = std::min<int>(req->n_sky, 256); plan(chunk, wide, false, false) > share && R.chunk > 1;)
+        chunk = (R.chunk + 1) / 2;
     R.footprint = (int64_t)R.layout.total;
     if (R.footprint > srv->budget) {
         srv->next_id--;
@@ -2382,6 +2377,13 @@ fh_status fh_server_poll(fh_server *srv, fh_completion *out, int32_t max, int32_
     retire_lanes(srv);
     admit(srv);
     int32_t k = 0;
+    // and of what saves time, as much as the share has room for: the tile width
+    // of a launch of that many directions (more windows), the rank table and
+    // partial tiles
+    const int chunk = R.chunk, narrow = search_tile_bins(ctx, req->pm, &req->grid, chunk);
+    auto fits = [&](int width, bool parts, bool rank) { return plan(chunk, width, parts, rank) <= share && R.chunk == chunk; };
+    if (!fits(narrow, true, true) && !fits(narrow, false, true) && !fits(narrow, false, false) && !fits(wide, false, true))
+        plan(chunk, wide, false, false);
     while (k < max && !srv->finished.empty()) {
         const uint64_t id = srv->finished.front();
         srv->finished.pop_front();

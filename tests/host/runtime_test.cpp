@@ -214,6 +214,7 @@ void request_in_a_tight_budget() {
         CHECK(fh_server_poll(srv, &done, 1, &n) == FH_OK && n == 1 && done.status == FH_OK);
         CHECK(done.footprint <= budget);
         fh_server_destroy(srv);
+        return done.footprint;
     };
     // (the rank table is the last piece of a layout)
     auto bare = [&](int width, int chunk) {
@@ -221,16 +222,16 @@ void request_in_a_tight_budget() {
     };
     const int wide = choose_tile_bins(c, pm, &g, 0), narrow = search_tile_bins(c, pm, &g, 16);
     CHECK(wide > narrow && bare(wide, 16) < bare(narrow, 16));
-    served(64 * kMB, 2);
-    CHECK(last("tiles")->slots == 16 && last("front")->rank);
+    CHECK(served(256 * kMB, 2) == bare(wide, 16));
+    CHECK(last("tiles")->slots == 16 && last("tiles")->parts > 1 && last("front")->rank);
     for (const int width : {narrow, wide}) {
-        served(2 * bare(width, 16), 2);
+        CHECK(served(2 * bare(width, 16), 2) == bare(wide, 16));
         CHECK(last("tiles")->slots == 16 && last("tiles")->parts == 1 && !last("front")->rank);
     }
-    served(2 * (bare(wide, 16) - 256), 2);
+    CHECK(served(2 * (bare(wide, 16) - 256), 2) == bare(wide, 8));
     CHECK(last("tiles")->slots == 8);
     // the least that one direction takes, with a share of half of it
-    served(bare(wide, 1), 2);
+    CHECK(served(bare(wide, 1), 2) == bare(wide, 1));
     CHECK(last("tiles")->slots == 1);
     fh_peakmap_release(c, pm);
     fh_ctx_destroy(c);
