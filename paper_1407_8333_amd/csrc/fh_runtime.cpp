@@ -73,11 +73,30 @@ fh_status scratch_init(int device) {
 // Device and pinned host memory, nullptr when there is none.  HIP keeps the
 // error of a failed call until it is asked for, and every launch asks for it:
 // an allocation that may fail without its caller failing takes its error along.
-void *device_alloc(size_t n) {
+// *full: whether it failed for want of memory (and not, say, in a capture).
+void *device_alloc(size_t n, bool *full = nullptr) {
     void *p = nullptr;
-    if (hipMalloc(&p, n) == hipSuccess) return p;
+    const hipError_t e = hipMalloc(&p, n);
+    if (full) *full = e == hipErrorOutOfMemory;
+    if (e == hipSuccess) return p;
     (void)hipGetLastError();
     return nullptr;
+}
+
+void device_free(void *p) {
+    if (p && hipFree(p) != hipSuccess) (void)hipGetLastError();
+}
+
+// Waits for the device's work as hipFree does, by freeing a small block (1.2 us
+// when the device is idle): hipDeviceSynchronize() breaks every capture that is
+// under way on the device, also in other threads, where hipFree is harmless.
+// False when it cannot (this thread is capturing).
+bool wait_as_free() {
+    void *p = device_alloc(256);
+    if (!p) return false;
+    const bool ok = hipFree(p) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    return ok;
 }
 
 void *pinned_alloc(size_t n) {
@@ -211,13 +230,9 @@ struct Spare {
     DevBuf *rows = nullptr;  // the row scratch, and
     bool rows_busy = false;  // whether a call is using it
     std::vector<DevBuf *> other;
-    // frees it all; false: there was nothing
+    // frees it all (hipFree waits for the work that uses it); false: there was nothing
     bool give_back() {
         bool any = blocks.trim();
-        if (hipDeviceSynchronize() != hipSuccess) {  // (a stream is being captured: the rest may be in use)
-            (void)hipGetLastError();
-            return any;
-        }
         auto drop = [&](DevBuf *b) {
             any = any || b->ptr;
             b->release();
@@ -227,8 +242,9 @@ struct Spare {
         return any;
     }
     void *allocate(size_t n) {
-        void *p = device_alloc(n);
-        return p || !give_back() ? p : device_alloc(n);
+        bool full;
+        void *p = device_alloc(n, &full);
+        return p || !full || !give_back() ? p : device_alloc(n);
     }
     // a block of at least n bytes and its size, or nullptr
     void *block(size_t n, size_t *bytes) {
@@ -1463,14 +1479,13 @@ fh_status fh_peakmap_shape(const fh_peakmap *pm, int32_t *n_fft, int64_t *n_peak
 void fh_peakmap_release(fh_ctx *ctx, fh_peakmap *pm) {
     if (!pm) return;
     if (ctx) (void)hipSetDevice(ctx->device);
-    if (ctx && ctx->device == pm->device) {
-        // as hipFree does: no block is handed on while the device may use it
-        if (pm->head || pm->d_bins) (void)hipDeviceSynchronize();
+    // no block is handed on while the device may use it
+    if (ctx && ctx->device == pm->device && (pm->head || pm->d_bins) && wait_as_free()) {
         ctx->spare.blocks.give(pm->head, pm->head_bytes);
         ctx->spare.blocks.give(pm->d_bins, pm->bins_bytes);
     } else {
-        if (pm->head) (void)hipFree(pm->head);
-        if (pm->d_bins) (void)hipFree(pm->d_bins);
+        device_free(pm->head);
+        device_free(pm->d_bins);
     }
     delete pm;
 }
@@ -2340,7 +2355,7 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
     // the default tile width and without what only saves time
     const bool weighted = req->d_w != nullptr;
     const int64_t share = srv->budget / (int64_t)srv->lanes.size();
-    auto fits = [&](int chunk, int width, bool parts, bool rank) {
+    auto plan = [&](int chunk, int width, bool parts, bool rank) {
         const Plan p = make_plan(req->grid, width);
         R.W = width;
         R.chunk = (int)std::min<int64_t>(chunk, chunk_by_tiles(p));
@@ -2362,6 +2377,13 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
         return fail(FH_E_UNSUPPORTED, "request needs %lld workspace bytes, over the %lld-byte budget",
                     (long long)R.footprint, (long long)srv->budget);
     }
+    // and of what saves time, as much as the share has room for: the tile width
+    // of a launch of that many directions (more windows), the rank table and
+    // partial tiles
+    const int chunk = R.chunk, narrow = search_tile_bins(ctx, req->pm, &req->grid, chunk);
+    auto fits = [&](int width, bool parts, bool rank) { return plan(chunk, width, parts, rank) <= share && R.chunk == chunk; };
+    if (!fits(narrow, true, true) && !fits(narrow, false, true) && !fits(narrow, false, false) && !fits(wide, false, true))
+        plan(chunk, wide, false, false);
     *id = R.id;
     srv->reqs[R.id] = std::move(R);
     srv->queue.push_back(*id);
@@ -2377,13 +2399,6 @@ fh_status fh_server_poll(fh_server *srv, fh_completion *out, int32_t max, int32_
     retire_lanes(srv);
     admit(srv);
     int32_t k = 0;
-    // and of what saves time, as much as the share has room for: the tile width
-    // of a launch of that many directions (more windows), the rank table and
-    // partial tiles
-    const int chunk = R.chunk, narrow = search_tile_bins(ctx, req->pm, &req->grid, chunk);
-    auto fits = [&](int width, bool parts, bool rank) { return plan(chunk, width, parts, rank) <= share && R.chunk == chunk; };
-    if (!fits(narrow, true, true) && !fits(narrow, false, true) && !fits(narrow, false, false) && !fits(wide, false, true))
-        plan(chunk, wide, false, false);
     while (k < max && !srv->finished.empty()) {
         const uint64_t id = srv->finished.front();
         srv->finished.pop_front();

@@ -47,9 +47,19 @@ inline thread_local hipError_t last_error = hipSuccess;
 inline std::atomic<int64_t> used{0}, limit{INT64_MAX};          // device memory
 inline std::atomic<int64_t> pinned{0}, pinned_limit{INT64_MAX};  // pinned host memory
 inline std::atomic<int> graphs{0};                               // graphs instantiated
-inline std::atomic<bool> sync_fails{false};  // hipDeviceSynchronize, as while a stream is captured
+// a capture under way: on another thread, where hipMalloc and hipFree are
+// harmless and hipDeviceSynchronize breaks it, or on this one, where all three do
+inline std::atomic<bool> capturing_elsewhere{false}, capturing_here{false};
+inline std::atomic<int> captures_broken{0};
 
 inline hipError_t fail(hipError_t e) { return last_error = e; }
+inline hipError_t in_capture(bool elsewhere) {
+    if (!capturing_here.load(std::memory_order_relaxed) &&
+        !(elsewhere && capturing_elsewhere.load(std::memory_order_relaxed)))
+        return hipSuccess;
+    captures_broken.fetch_add(1, std::memory_order_relaxed);
+    return fail(hipErrorStreamCaptureUnsupported);
+}
 
 // blocks carry their size in front
 inline hipError_t alloc(void **p, size_t n, std::atomic<int64_t> &sum, std::atomic<int64_t> &most) {
@@ -79,10 +89,15 @@ inline hipError_t hipGetLastError() {
 }
 inline const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 
-inline hipError_t hipMalloc(void **p, size_t n) { return fake::alloc(p, n, fake::used, fake::limit); }
+inline hipError_t hipMalloc(void **p, size_t n) {
+    const hipError_t e = fake::in_capture(false);
+    return e != hipSuccess ? e : fake::alloc(p, n, fake::used, fake::limit);
+}
 template <typename T>
 hipError_t hipMalloc(T **p, size_t n) { return hipMalloc((void **)p, n); }
 inline hipError_t hipFree(void *p) {
+    const hipError_t e = fake::in_capture(false);
+    if (e != hipSuccess) return e;
     fake::release(p, fake::used);
     return hipSuccess;
 }
@@ -119,9 +134,7 @@ inline hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
     p->multiProcessorCount = 256;
     return hipSuccess;
 }
-inline hipError_t hipDeviceSynchronize() {
-    return fake::sync_fails.load(std::memory_order_relaxed) ? fake::fail(hipErrorStreamCaptureUnsupported) : hipSuccess;
-}
+inline hipError_t hipDeviceSynchronize() { return fake::in_capture(true); }
 
 inline hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
     *s = (hipStream_t)std::calloc(1, 8);

@@ -260,6 +260,33 @@ void peakmaps_released_on_another_thread() {
     CHECK(fake::used == 0);
 }
 
+// Releasing a peakmap leaves a capture of another thread alone, as freeing
+// memory does; during one of its own thread, no block is handed on (the device
+// could not be waited for), and no error stays behind.
+void peakmap_released_during_a_capture() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *a = upload(c, 100, 100), *b = upload(c, 100, 100), *d = upload(c, 100, 100);
+    const void *bins = b->d_bins;
+    fake::capturing_elsewhere = true;
+    fh_peakmap_release(c, a);
+    a = upload(c, 200, 200);
+    fake::limit = fake::used.load();
+    fh_server *srv = nullptr;
+    CHECK(fh_server_create(c, 64 * kMB, 1, 1, &srv) == FH_E_NOMEM);  // gives the blocks back
+    fake::limit = INT64_MAX;
+    CHECK(fake::captures_broken == 0);
+    fake::capturing_elsewhere = false;
+    fake::capturing_here = true;
+    fh_peakmap_release(c, b);
+    fake::capturing_here = false;
+    CHECK(fake::last_error == hipSuccess);
+    b = upload(c, 100, 100);
+    CHECK(b->d_bins != bins);
+    CHECK(search(c, d, grid(2000, 17), 2, false) == FH_OK);
+    for (fh_peakmap *p : {a, b, d}) fh_peakmap_release(c, p);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -272,6 +299,7 @@ const Case kCases[] = {
     {"kept_memory_makes_room", kept_memory_makes_room},
     {"request_in_a_tight_budget", request_in_a_tight_budget},
     {"peakmaps_released_on_another_thread", peakmaps_released_on_another_thread},
+    {"peakmap_released_during_a_capture", peakmap_released_during_a_capture},
 };
 
 }  // namespace

@@ -72,3 +72,33 @@ def test_map_after_a_refused_allocation(ctx):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(got.cpu().numpy(), oracle.hough_map(pm, grid, nhat).astype(np.int32))
     dpm.release()
+
+
+def test_release_beside_a_capture(ctx):
+    """A peakmap released on one thread while another thread captures the
+    static map of another peakmap: the capture stands, and its replays are
+    right, also with another peakmap built in between."""
+    import threading
+
+    import torch
+    from paper_1407_8333_amd import _lib, api
+    pm, grid = _band(520, 0.08)
+    nhat = synth.sky_uniform(1, synth.rng_for(5))[0]
+    ref = oracle.hough_map(pm, grid, nhat).astype(np.int32)
+    dpm, other = ctx.upload(pm), ctx.upload(_band(521, 0.05)[0])
+    out = torch.empty((grid.ns, grid.nf), dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        t = threading.Thread(target=_lib.fh_peakmap_release, args=(ctx.handle, other.handle))
+        t.start()
+        t.join()
+        other.handle = None
+        api.fh_hough_map_i32_static(ctx, dpm, nhat, grid, out)
+    for rep in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy(), ref)
+        ctx.upload(_band(522 + rep, 0.05)[0]).release()
+    dpm.release()

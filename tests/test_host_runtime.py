@@ -41,6 +41,7 @@ def _run(exe, name):
     "search_without_room_for_optional_buffers",
     "kept_memory_makes_room",
     "request_in_a_tight_budget",
+    "peakmap_released_during_a_capture",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
