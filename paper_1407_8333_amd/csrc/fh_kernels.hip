@@ -2574,7 +2574,9 @@ __global__ void k_slice_pack(const int64_t *__restrict__ first, const int32_t *_
 // far too small for the GPU.  Here all candidates run in two launches.
 
 // Per (candidate, FFT): the run of peaks that can meet the volume in any of the
-// candidate's directions, and its first four natural bins.  The directions lie
+// candidate's directions (its place in the FFT: the peakmap, of which the volume
+// needs a few bins, may hold more peaks than 32 bits count), and its first four
+// natural bins.  The directions lie
 // within `spread` of the middle one, so their Doppler factors within |v| spread
 // of its: a run is a few natural bins (0.3-1 peaks on average), and the cells
 // kernel, which reads it once per direction, needs no search.  grid.y =
@@ -2610,21 +2612,22 @@ __global__ void __launch_bounds__(256) k_refine_runs(
     }
     const int32_t k1 = max(q.k_lo, (int32_t)fmin(fmax(floor(lo / (double)kf) - 1.0, -2e9), 2e9));
     const int32_t k2 = min(q.k_hi, (int32_t)fmin(fmax(ceil(hi / (double)kf) + 2.0, -2e9), 2e9));
-    const int32_t p0 = (int32_t)offsets[i], p1 = (int32_t)offsets[i + 1];
+    const int32_t *__restrict__ k = bins + offsets[i];
+    const uint32_t n_i = (uint32_t)(offsets[i + 1] - offsets[i]);  // < 2^31
     // first peaks with natural bin >= k1 and >= k2, in lockstep
-    int32_t a = p0, b = p0;
-    int32_t top = 1;
-    while (top <= (p1 - p0) >> 1) top <<= 1;
-    for (int32_t st = top; st > 0; st >>= 1) {
-        const int32_t ta = a + st - 1, tb = b + st - 1;
-        const int32_t va = ta < p1 ? bins[ta] : 0x7fffffff, vb = tb < p1 ? bins[tb] : 0x7fffffff;
+    uint32_t a = 0, b = 0;
+    uint32_t top = 1;
+    while (top <= n_i >> 1) top <<= 1;
+    for (uint32_t st = top; st > 0; st >>= 1) {
+        const uint32_t ta = a + st - 1, tb = b + st - 1;
+        const int32_t va = ta < n_i ? k[ta] : 0x7fffffff, vb = tb < n_i ? k[tb] : 0x7fffffff;
         if (va < k1) a += st;
         if (vb < k2) b += st;
     }
-    const int32_t c = max(b - a, 0);
+    const int32_t c = b > a ? (int32_t)(b - a) : 0;
     const int64_t at = (int64_t)blockIdx.y * n_fft + i;
-    runs[at] = make_int2(a, c);
-    firsts[at] = make_int4(c > 0 ? bins[a] : 0, c > 1 ? bins[a + 1] : 0, c > 2 ? bins[a + 2] : 0, c > 3 ? bins[a + 3] : 0);
+    runs[at] = make_int2((int32_t)a, c);
+    firsts[at] = make_int4(c > 0 ? k[a] : 0, c > 1 ? k[a + 1] : 0, c > 2 ? k[a + 2] : 0, c > 3 ? k[a + 3] : 0);
 }
 
 // One workgroup per (direction, candidate): grid (n_dir, n_cand).  Threads
@@ -2650,8 +2653,9 @@ struct RefinePeak {
 };
 
 __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
-    int32_t n_fft, const int32_t *__restrict__ bins, const double *__restrict__ t, const double *__restrict__ v,
-    const double *__restrict__ sky, const RefineCand *__restrict__ rc, const int2 *__restrict__ runs,
+    int32_t n_fft, const int64_t *__restrict__ offsets, const int32_t *__restrict__ bins,
+    const double *__restrict__ t, const double *__restrict__ v, const double *__restrict__ sky,
+    const RefineCand *__restrict__ rc, const int2 *__restrict__ runs,
     const int4 *__restrict__ firsts, int32_t kf, int32_t nf, int32_t ns, double dfdot, double t0, double S,
     double theta, const float *__restrict__ w, const WeightStats *__restrict__ ws, int32_t shift_mode,
     fh_candidate *__restrict__ out) {
@@ -2690,7 +2694,7 @@ __global__ void __launch_bounds__(kRefineThreads) k_refine_cells(
         double r = 1.0, tau = 0.0, c = 0.0, y_lo = 0.0, y_hi = 0.0;
         // edge of the run's u-th peak, and whether it meets the volume
         auto edge = [&](int u, double *y) {
-            const int32_t k = u == 0 ? fk.x : u == 1 ? fk.y : u == 2 ? fk.z : u == 3 ? fk.w : bins[run.x + u];
+            const int32_t k = u == 0 ? fk.x : u == 1 ? fk.y : u == 2 ? fk.z : u == 3 ? fk.w : bins[offsets[i] + run.x + u];
             double x = (double)(kf * k) * r;
             x = x * kQd;
             *y = floor(x) + c;
@@ -3261,8 +3265,9 @@ hipError_t launch_refine_cells(int32_t n_fft, const int64_t *offsets, const int3
                                                                       ns, dfdot, t0, S, shift_mode, runs, firsts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_refine_cells<<<dim3(n_dir, n_cand), kRefineThreads, lds, st>>>(n_fft, bins, t, v, sky, rc, runs, firsts, kf, nf,
-                                                                     ns, dfdot, t0, S, theta, w, ws, shift_mode, out);
+    k_refine_cells<<<dim3(n_dir, n_cand), kRefineThreads, lds, st>>>(n_fft, offsets, bins, t, v, sky, rc, runs, firsts,
+                                                                     kf, nf, ns, dfdot, t0, S, theta, w, ws, shift_mode,
+                                                                     out);
     return hipGetLastError();
 }
 

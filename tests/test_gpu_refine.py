@@ -234,3 +234,39 @@ def test_refined_volumes_of_every_route(ctx, kf, k_fdot, k_sky, n_fft, t_fft, de
             # within twice that of the best
             assert float(o["value"]) == pytest.approx(best[0], abs=2e-5 * max(best[0], float(np.mean(w))))
     dpm.release()
+
+
+def test_refinement_in_a_peakmap_of_more_peaks_than_32_bits_count(ctx):
+    """A peakmap of more than 2^31 peaks, built on the GPU: the volumes, which
+    need a few bins of it, equal those refined in a slice around them (the last
+    32 FFTs and more lie past 2^31)."""
+    import torch
+    from paper_1407_8333_amd import api
+    n_fft, n_bins, t_fft, k0 = 16_416, 400_000, 1024.0, 50_000
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GiB of device memory")
+    print("case: refinement past 2^31 peaks", flush=True)
+    rng = synth.rng_for(2031)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    sp = torch.rand((n_fft, n_bins), generator=g, device="cuda")  # a third of the bins are local maxima
+    t = synth.fft_times(n_fft, t_fft)
+    dpm = api.DevicePeakmap.from_spectra(ctx, sp, k0, 0.0, t, synth.detector_velocity(t, rng), t_fft)
+    del sp
+    torch.cuda.empty_cache()
+    assert dpm.n_peaks > (1 << 31) + 40 * n_bins // 3
+    k_c = k0 + n_bins // 2
+    part = dpm.slice(k_c - 2000, k_c + 2000)
+    dfdot = 1.0 / (t_fft * 0.5 * n_fft * t_fft)
+    t0 = 0.5 * (t[0] + t[-1])
+    f_c = k_c / t_fft
+    cands = [[f_c, -1.5 * dfdot, 1.0, 0.3, 0.05, 0.04], [f_c + 0.3, 2.0 * dfdot, 4.0, -1.1, 0.03, 0.02]]
+    for mode in ("exact", "shift"):
+        ctx.set_doppler(mode)
+        try:
+            got, ref = (api.decode_refined(api.refine(ctx, d, cands, 10, 5, 3, dfdot, t0)) for d in (dpm, part))
+        finally:
+            ctx.set_doppler("exact")
+        assert got["valid"].all() and (got["value"] > 0.25 * n_fft).all()
+        np.testing.assert_array_equal(got, ref)
+    part.release()
+    dpm.release()
