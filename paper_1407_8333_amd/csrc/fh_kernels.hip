@@ -982,10 +982,10 @@ __global__ void __launch_bounds__(kTileThreads) k_sort_windows_long(int32_t n_ff
     }
 }
 
-// Raw buffer access with 32-bit byte offsets (no 64-bit address arithmetic
-// per load); the records limit is never reached by the offsets used here.
+// Raw buffer access with unsigned 32-bit byte offsets (no 64-bit address
+// arithmetic per load), unlimited: a direction's stripe edges may fill 4 GiB.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void *p) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, 0x7FFFFFFF, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)0xFFFFFFFFu, 0x00020000);
 }
 __device__ __forceinline__ uint32_t ld_u32(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
     return __builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, 0);
