@@ -177,7 +177,8 @@ fh_status fh_ctx_check(fh_ctx *ctx, void *stream);
  * with the edges of a few FFTs staged in LDS, default 2; it falls back to 1
  * when one FFT holds too many peaks for the LDS); "tile_parts" (workgroups
  * that share each tile of searches and maps with few tiles, 1 .. 64, capped
- * by the peakmap's FFTs; 0, the default, chooses by a cost model).
+ * by the peakmap's FFTs and at eight workgroups per CU in all; 0, the default,
+ * chooses by a cost model).
  * FH_E_INVALID for an unknown name or value. */
 fh_status fh_ctx_set_option(fh_ctx *ctx, const char *name, int64_t value);
 

@@ -653,6 +653,11 @@ double tiles_us(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const
                       : us + 6.0 + 4.0e-6 * (double)part_words(p.W, g->kf, p.tail) * (double)(n_tiles * parts) / 2.6;
 }
 
+// "tile_parts" asks for at most this many rounds of workgroups over the CUs: it
+// is for searches with few tiles, and a partial tile takes up to 160 KB (335 MB
+// in all on 256 CUs).
+constexpr int64_t kForcedRounds = 8;
+
 // Workgroups that share each of n_tiles tiles (each accumulates every
 // parts-th block of FFTs; a merge adds the partial tiles): more than one only
 // where the launch leaves CUs idle and the model finds the shorter
@@ -664,7 +669,8 @@ int plan_parts(const fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, const 
     const int64_t blocks = (int64_t)kTileWaves * (wave_ffts(pm->n_fft) / 4);
     const int64_t most = std::min<int64_t>(64, std::max<int64_t>(1, blocks / (3 * kTileWaves)));
     if (n_tiles < 1 || n_tiles > 65535) return 1;
-    if (ctx->tile_parts > 0) return (int)std::min<int64_t>(ctx->tile_parts, most);
+    if (ctx->tile_parts > 0)
+        return (int)std::max<int64_t>(1, std::min<int64_t>({ctx->tile_parts, most, kForcedRounds * ctx->n_cu / n_tiles}));
     int best = 1;
     double best_us = tiles_us(ctx, pm, g, p, n_tiles, 1);
     for (int64_t s = 2; s <= most && s * n_tiles <= 2 * ctx->n_cu; ++s) {
@@ -1104,6 +1110,13 @@ fh_status autotune(fh_ctx *ctx, const fh_peakmap *pm, const fh_grid *g, int n_sk
     const int w16 = std::min(max_tile_bins(g->kf, row_step_bins(pm, g), kTileRows), wmap);
     if (w16 > wcap) cands.push_back(w16);
     const int sample = std::min(n_sky, 128);
+    // (the width outlives the "tile_parts" option: it is tuned without)
+    struct Options {
+        fh_ctx *ctx;
+        const int32_t parts;
+        ~Options() { ctx->tile_parts = parts; }
+    } options{ctx, ctx->tile_parts};
+    ctx->tile_parts = 0;
     const bool was = ctx->profiling;
     ctx->profiling = false;
     hipEvent_t e0, e1;

@@ -287,6 +287,36 @@ void peakmap_released_during_a_capture() {
     fh_ctx_destroy(c);
 }
 
+// "tile_parts" is for searches with few tiles: it asks for no gigabytes of
+// partial tiles, and a width tuned meanwhile is tuned without it.
+void forced_tile_parts() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *pm = upload(c, 3000, 80);
+    CHECK(fh_ctx_set_option(c, "tile_parts", 16) == FH_OK);
+    const fh_options narrow{FH_SCHED_PERSISTENT, 64, 0, 0};
+    for (const int nf : {64 * 100, 64 * 1000, 64 * 20000}) {  // tiles of one direction
+        const fh_grid g = grid(nf, 15);
+        CHECK(fh_hough_candidates(c, pm, 1, kSky, nullptr, 0, &g, &kSel, &narrow, g_out, nullptr) == FH_OK);
+        CHECK(last("tiles")->parts == (nf == 64 * 100 ? 16 : nf == 64 * 1000 ? 2 : 1));
+        CHECK(c->main_ws.part.bytes < 400 * kMB);
+    }
+    std::vector<double> sky(3 * 2000);
+    for (size_t k = 0; k < sky.size(); ++k) sky[k] = kSky[k % 3];
+    std::vector<fh_candidate> out(2 * 7 * 2000);
+    const fh_grid g = grid(7000, 15);
+    fake::launches.clear();
+    CHECK(fh_hough_candidates(c, pm, 2000, sky.data(), nullptr, 0, &g, &kSel, nullptr, out.data(), nullptr) == FH_OK);
+    int tuning = 0;
+    for (const fake::Launch &l : fake::launches) {
+        if (std::strcmp(l.what, "tiles") || l.slots != 128) continue;
+        CHECK(l.parts == 1);
+        ++tuning;
+    }
+    CHECK(tuning > 1 && c->tile_parts == 16);
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -300,6 +330,7 @@ const Case kCases[] = {
     {"request_in_a_tight_budget", request_in_a_tight_budget},
     {"peakmaps_released_on_another_thread", peakmaps_released_on_another_thread},
     {"peakmap_released_during_a_capture", peakmap_released_during_a_capture},
+    {"forced_tile_parts", forced_tile_parts},
 };
 
 }  // namespace

@@ -42,6 +42,7 @@ def _run(exe, name):
     "kept_memory_makes_room",
     "request_in_a_tight_budget",
     "peakmap_released_during_a_capture",
+    "forced_tile_parts",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
