@@ -1508,14 +1508,17 @@ __device__ __forceinline__ void tile_colmax(const TileArgs &A, int slot, int rb,
     }
     // Clearing: a wave reads the kWaveCols columns of its segments and the
     // kColKf - 1 after them, so the columns past its first kColKf - 1 are its
-    // own, and its LDS accesses are in order: it clears them as soon as it has
-    // read them.  The columns that two waves read, and those after the tile,
-    // wait for the barrier.
+    // own (W % 64 == 0, see launch_tiles_t), and its LDS accesses are in order:
+    // it clears them as soon as it has read them.  A lane clears what others
+    // have read, so the order is stated for the compiler.  The columns that two
+    // waves read, and those after the tile, wait for the barrier.
     constexpr int kQ = kTileRows / 4;  // 16-byte quarters of a column
     uint4 *q4 = reinterpret_cast<uint4 *>(lds);
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     const int lane = tid & 63, wave = tid >> 6;
     if (CLEAR) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
         const int c1 = min((wave + 1) * kWaveCols, W);
         for (int x = (wave * kWaveCols + kColKf - 1) * kQ + lane; x < c1 * kQ; x += 64) q4[x] = z;
     }
@@ -2456,7 +2459,7 @@ static hipError_t set_tile_attrs() {
 template <bool Wt, bool T>
 static hipError_t launch_tiles_t(const TileArgs &a, bool map, bool persistent, int32_t n_tiles,
                                  int32_t grid_blocks, hipStream_t st) {
-    if (a.tail < 0 || a.tail > kTailRows) return hipErrorInvalidValue;
+    if (a.tail < 0 || a.tail > kTailRows || a.W < 64 || a.W % 64 != 0) return hipErrorInvalidValue;
     const int lds = tile_lds_bytes(a.W, a.kf, a.tail);
     if (lds > kLdsBytes - kLdsReserve) return hipErrorInvalidValue;
     if (a.bins && (map || !persistent || a.parts > 1)) return hipErrorInvalidValue;
