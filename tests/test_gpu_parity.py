@@ -258,6 +258,46 @@ def test_windows_of_more_than_127_peaks(ctx, n_fft, n_bins, nf, ns):
     dpm.release()
 
 
+@pytest.mark.parametrize("n_fft,peaks", [(25_728, "many"),   # the last length whose rows are sorted in one piece
+                                         (25_729, "many"), (25_750, "few"),
+                                         (32_641, "many")])  # the first of two pieces
+def test_window_rows_sorted_in_pieces(ctx, n_fft, peaks):
+    """Observations whose window rows are too long for the sort in one piece,
+    with windows of some peaks and of more than 127 (ranked apart): maps of one
+    direction, whose weights the sort writes, and searches of one and of several
+    directions, against the oracle."""
+    import torch
+    api = _api()
+    rng = synth.rng_for(n_fft)
+    print("case: window rows of %d FFTs, %s peaks" % (n_fft, peaks), flush=True)
+    t_fft = 1024.0
+    kf, n_bins, density = (1, 700, 0.4) if peaks == "many" else (10, 300, 0.07)
+    pm = synth.random_peakmap(n_fft, t_fft, 60_000, 60_000 + n_bins, density, rng)
+    if peaks == "many":
+        assert np.diff(pm.offsets).min() > 150
+    dfd = (1.0 / t_fft) / (n_fft * t_fft / 2)
+    grid = synth.Grid(kf=kf, b0=kf * 60_050, nf=kf * (n_bins - 100), ns=4, fdot0=-2 * dfd, dfdot=dfd,
+                      t0=float(pm.t[n_fft // 2]))
+    sky = synth.sky_uniform(4, rng)
+    ref = oracle.hough_map(pm, grid, sky[0])
+    np.testing.assert_array_equal(_gpu_map(ctx, pm, grid, sky[0]), ref.astype(np.int32))
+    wts = rng.uniform(0.5, 1.5, pm.n_fft).astype(np.float32)
+    refw = oracle.hough_map(pm, grid, sky[0], weights=wts.astype(np.float64))
+    _assert_weighted_close(_gpu_map(ctx, pm, grid, sky[0], weights=wts), refw, wts)
+    dpm = ctx.upload(pm)
+    sel = synth.Selection(width=max(1, grid.nf // 8))
+    idx, val = oracle.candidates(ref, sel.width, sel.excl, sel.sep)
+    idxw, valw = oracle.candidates(refw, sel.width, sel.excl, sel.sep)
+    for n in (1, 4):  # windows searched for, and from rank tables
+        raw = api.fh_hough_candidates(ctx, dpm, sky[:n], grid, sel)
+        raw_w = api.fh_hough_candidates(ctx, dpm, sky[:n], grid, sel, weights=torch.as_tensor(wts, device="cuda"))
+        torch.cuda.synchronize()
+        _check_candidates(api.decode_candidates(raw), 0, idx, val, pm.n_fft, sel.theta)
+        _check_candidates(api.decode_candidates(raw_w), 0, idxw, valw, pm.n_fft, sel.theta, weighted_map=refw,
+                          weights=wts)
+    dpm.release()
+
+
 @pytest.mark.parametrize("sign,ns", [(-1.0, 19), (-1.0, 40), (0.0, 17), (0.0, 3)])
 def test_descending_and_flat_spin_down_rows(ctx, sign, ns):
     """Rows whose spin-down decreases (dfdot < 0, the row terms change sign)
