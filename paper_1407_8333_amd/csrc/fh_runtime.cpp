@@ -482,6 +482,10 @@ fh_peakmap *like(const fh_peakmap *pm) {
     return q;
 }
 
+// Times and velocities of up to this many bytes (524 288 FFTs) are staged in
+// pinned memory, which stays with the context; more are copied from the caller's.
+constexpr size_t kMaxStage = (size_t)16 << 20;
+
 // {total, largest} of a scan's counts, which the scan writes to pinned memory;
 // waits for the stream.
 hipError_t read_meta(fh_ctx *ctx, hipStream_t st, int64_t *total, int32_t *most) {
@@ -1429,7 +1433,7 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
         bool &f;
         ~Busy() { f = false; }
     } busy{ctx->spare.rows_busy};
-    if ((s = ctx->pm_counts.ensure(4 * (size_t)n_fft, st)) || (s = ctx->h_stage.ensure(b_t + b_v, st)) ||
+    if ((s = ctx->pm_counts.ensure(4 * (size_t)n_fft, st)) ||
         (s = ctx->pm_rows.ensure(4 * (size_t)n_fft * cap, st))) {
         delete pm;
         return s;
@@ -1440,13 +1444,19 @@ fh_status fh_peakmap_from_spectra(fh_ctx *ctx, int32_t n_fft, int32_t n_bins, in
         return fail(FH_E_NOMEM, "device allocation for the peakmap failed");
     }
     // (every use of the staging buffer ends with a wait for its copy)
-    std::memcpy(ctx->h_stage.ptr, t, b_t);
-    std::memcpy((char *)ctx->h_stage.ptr + b_t, v, b_v);
+    const bool staged = b_t + b_v <= kMaxStage && ctx->h_stage.ensure(b_t + b_v, st) == FH_OK;
+    if (staged) {
+        std::memcpy(ctx->h_stage.ptr, t, b_t);
+        std::memcpy((char *)ctx->h_stage.ptr + b_t, v, b_v);
+    }
     int32_t *rows_buf = (int32_t *)ctx->pm_rows.ptr, *counts = (int32_t *)ctx->pm_counts.ptr;
     int64_t P = 0;
     hipError_t e = launch_pm_rows(n_fft, n_bins, ld, d_sp, d_sar, k0, theta, cap, rows_buf, counts, st);
     if (e == hipSuccess) e = launch_pm_scan(n_fft, counts, pm->d_offsets, (int64_t *)ctx->h_small.ptr, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(pm->d_t, ctx->h_stage.ptr, b_t + b_v, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess)
+        e = staged ? hipMemcpyAsync(pm->d_t, ctx->h_stage.ptr, b_t + b_v, hipMemcpyHostToDevice, st)
+                   : hipMemcpyAsync(pm->d_t, t, b_t, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && !staged) e = hipMemcpyAsync(pm->d_v, v, b_v, hipMemcpyHostToDevice, st);
     const hipError_t e2 = read_meta(ctx, st, &P, &pm->max_per_fft);
     if (e == hipSuccess) e = e2;
     if (e == hipSuccess && !alloc_bins(ctx, pm, P)) e = hipErrorOutOfMemory;

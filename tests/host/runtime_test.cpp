@@ -317,6 +317,23 @@ void forced_tile_parts() {
     fh_ctx_destroy(c);
 }
 
+// Pinned memory that stages a peakmap's times and velocities is bounded, and
+// done without where there is none.
+void spectra_without_pinned_memory() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *pm = nullptr;
+    const int64_t pinned = fake::pinned;
+    for (const int n_fft : {1000, 600000}) {  // 32 KB and 19 MB
+        fake::pinned_limit = n_fft == 1000 ? pinned : INT64_MAX;
+        CHECK(from_spectra(c, n_fft, 8, 100, &pm) == FH_OK);
+        CHECK(fake::pinned < 16 * kMB);
+        for (int i = 0; i < n_fft; i += 999)
+            CHECK(pm->d_t[i] == 1000.0 * i && pm->d_v[3 * i] == 1e-5 && pm->d_v[3 * i + 2] == 1e-5);
+        fh_peakmap_release(c, pm);
+    }
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -331,6 +348,7 @@ const Case kCases[] = {
     {"peakmaps_released_on_another_thread", peakmaps_released_on_another_thread},
     {"peakmap_released_during_a_capture", peakmap_released_during_a_capture},
     {"forced_tile_parts", forced_tile_parts},
+    {"spectra_without_pinned_memory", spectra_without_pinned_memory},
 };
 
 }  // namespace

@@ -43,6 +43,7 @@ def _run(exe, name):
     "request_in_a_tight_budget",
     "peakmap_released_during_a_capture",
     "forced_tile_parts",
+    "spectra_without_pinned_memory",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
