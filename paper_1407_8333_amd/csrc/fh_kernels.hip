@@ -2371,10 +2371,28 @@ hipError_t launch_setup_front(const SetupArgs &a, FrontArgs r, int32_t max_per_f
     if (lds > (size_t)kFrontLdsBytes) return hipErrorInvalidValue;
     r.search_top = 0;  // largest power of two up to max_per_fft (0 when no FFT has a peak)
     while (r.search_top * 2 <= max_per_fft && r.search_top < (1 << 30)) r.search_top = r.search_top ? 2 * r.search_top : 1;
-    const int64_t front = (int64_t)(win_stride(a.n_fft) / r.F) * r.n_slots;
-    if (front + a.n_vec + blocks >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    k_setup_front<<<(unsigned)(a.n_vec + front + blocks), 256, lds, st>>>(a, r);
-    return hipGetLastError();
+    // a launch holds fewer than 2^32 threads: fronts past that follow the setup
+    // in launches of their own, as many directions at a time as fit
+    constexpr int64_t kMaxBlocks = (((int64_t)1 << 32) - 1) / 256;
+    const int64_t per_slot = win_stride(a.n_fft) / r.F;
+    if (per_slot * r.n_slots + a.n_vec + blocks <= kMaxBlocks) {
+        k_setup_front<<<(unsigned)(a.n_vec + per_slot * r.n_slots + blocks), 256, lds, st>>>(a, r);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_setup(a, nullptr, 0, 0, nullptr, st);
+    SetupArgs b = a;
+    b.n_vec = 0;
+    b.n_sky = 0;  // (the setup has written the directions)
+    FrontArgs p = r;
+    for (int s0 = 0; s0 < r.n_slots && e == hipSuccess; s0 += p.n_slots) {
+        p.n_slots = (int32_t)std::min<int64_t>(r.n_slots - s0, kMaxBlocks / per_slot);
+        p.sky = r.sky + 3 * (int64_t)s0;
+        p.Y = r.Y + (int64_t)s0 * y_stride(r.n_peaks, a.n_fft);
+        p.win = r.win + (int64_t)s0 * r.nrbg * r.nbb * win_stride(a.n_fft);
+        k_setup_front<<<(unsigned)(per_slot * p.n_slots), 256, lds, st>>>(b, p);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 // Words of an FFT's rank table.

@@ -49,3 +49,34 @@ def test_stripe_edges_past_2_gib(ctx):
         assert torch.equal(got, ref[:n]), n
     part.release()
     dpm.release()
+
+
+def test_front_of_more_threads_than_a_launch_holds(ctx):
+    """A long, sparse observation (too sparse for rank tables) in one chunk of
+    so many directions that their fronts need more than one launch: the
+    candidates, also weighted, equal those of small chunks."""
+    import torch
+    from paper_1407_8333_amd import api
+    n_fft, n_sky, t_fft = 120_000, 2_300, 1024.0
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GiB of device memory")
+    assert 1024 * 118 * n_sky // 16 > (1 << 32) // 256  # workgroups of 16 FFTs per direction
+    print("case: front of %d directions, %d FFTs" % (n_sky, n_fft), flush=True)
+    rng = synth.rng_for(232)
+    t = synth.fft_times(n_fft, t_fft)
+    bins = np.sort(rng.integers(100_000, 103_000, n_fft * 2).reshape(n_fft, 2), axis=1).astype(np.int32)
+    bins[:, 1] += 1
+    pm = synth.Peakmap(t_fft, t, synth.detector_velocity(t, rng), np.arange(0, 2 * n_fft + 1, 2, dtype=np.int64),
+                       bins.reshape(-1), 100_000, 103_001)
+    dfd = (1.0 / t_fft) / (n_fft * t_fft / 2)
+    grid = synth.Grid(kf=10, b0=10 * 101_500, nf=640, ns=4, fdot0=-2 * dfd, dfdot=dfd, t0=float(t[n_fft // 2]))
+    sky = synth.sky_uniform(n_sky, rng)
+    sel = synth.Selection(width=64)
+    dpm = ctx.upload(pm)
+    for w in (None, torch.as_tensor(synth.fft_weights(n_fft, rng), device="cuda")):
+        got = [api.fh_hough_candidates(ctx, dpm, sky, grid, sel, weights=w, tile_bins=640, sky_chunk=c)
+               for c in (n_sky, 500)]
+        torch.cuda.synchronize()
+        assert torch.equal(*got)
+        assert (api.decode_candidates(got[0])["value"][:, :, 0] > 0).all()
+    dpm.release()
