@@ -33,7 +33,11 @@ namespace {
 
 thread_local std::string g_err = "no error";
 
+// The status of a failed call.  HIP keeps the error of a failed call until it
+// is asked for, whatever succeeds in between, and every launch asks for it: a
+// call that fails takes its error along, or the next one would report it.
 fh_status fail(fh_status s, const char *fmt, ...) {
+    if (s == FH_E_DEVICE) (void)hipGetLastError();
     char buf[512];
     va_list ap;
     va_start(ap, fmt);
@@ -70,9 +74,8 @@ fh_status scratch_init(int device) {
     return FH_OK;
 }
 
-// Device and pinned host memory, nullptr when there is none.  HIP keeps the
-// error of a failed call until it is asked for, and every launch asks for it:
-// an allocation that may fail without its caller failing takes its error along.
+// Device and pinned host memory, nullptr when there is none; the error of a
+// failure goes no further (the caller may do without).
 // *full: whether it failed for want of memory (and not, say, in a capture).
 void *device_alloc(size_t n, bool *full = nullptr) {
     void *p = nullptr;

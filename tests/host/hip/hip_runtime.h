@@ -144,7 +144,7 @@ inline hipError_t hipStreamDestroy(hipStream_t s) {
     std::free(s);
     return hipSuccess;
 }
-inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+inline hipError_t hipStreamSynchronize(hipStream_t) { return fake::in_capture(false); }
 inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
     *s = hipStreamCaptureStatusNone;
     return hipSuccess;

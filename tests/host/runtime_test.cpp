@@ -334,6 +334,22 @@ void spectra_without_pinned_memory() {
     fh_ctx_destroy(c);
 }
 
+// A call that the device refuses (here: one that waits, in a capture) fails
+// alone: the next one's launches do not report its error.
+void search_after_a_refused_call() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *pm = upload(c, 100, 100);
+    double stats[2];
+    for (const bool capturing : {false, true}) {  // (the first grows the buffers)
+        fake::capturing_here = capturing;
+        CHECK(fh_robust_stats(c, (const int32_t *)g_out, 10, 100, stats, nullptr) == (capturing ? FH_E_DEVICE : FH_OK));
+    }
+    fake::capturing_here = false;
+    CHECK(search(c, pm, grid(2000, 17), 2, false) == FH_OK);
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -349,6 +365,7 @@ const Case kCases[] = {
     {"peakmap_released_during_a_capture", peakmap_released_during_a_capture},
     {"forced_tile_parts", forced_tile_parts},
     {"spectra_without_pinned_memory", spectra_without_pinned_memory},
+    {"search_after_a_refused_call", search_after_a_refused_call},
 };
 
 }  // namespace

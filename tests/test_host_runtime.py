@@ -44,6 +44,7 @@ def _run(exe, name):
     "peakmap_released_during_a_capture",
     "forced_tile_parts",
     "spectra_without_pinned_memory",
+    "search_after_a_refused_call",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
