@@ -930,7 +930,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sort_windows(int32_t n_fft, in
     }
 }
 
-// Rows whose entries and ranks do not fit the LDS: the same sort, the
+// Rows whose entries and ranks do not fit the LDS (more than 25 728 FFTs): the same sort, the
 // row copied into LDS in pieces of kSortPiece entries (128 KB), once per pass,
 // and the entries written where they belong.
 constexpr int kSortPiece = 32768;
