@@ -102,7 +102,7 @@ VALU_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 4
 def committed_field(path, key, workload, n_sky, tile_bins, weighted):
     """A `key = value` figure of a committed rocprofv3 summary, when it was
     taken on this workload and on the current kernel source; None otherwise.
-    The autotuner's choice falls between two tile widths that tie: the plain
+    The autotuner's choice falls on either of two tile widths, by the card: the plain
     key is at W = 2496, the key with `_w2176` at that width."""
     import hashlib
     if not (workload == "batch-256hz" and n_sky == 1024 and tile_bins in (2176, 2496) and weighted):

@@ -760,15 +760,21 @@ bool needs_full_edges(const fh_ctx *ctx, const fh_peakmap *pm) {
 // Bytes of the rank table with which a launch of `slots` directions finds its
 // windows (k_front_rank), 0 when it searches them (k_front): few directions do
 // not repay the table, and wide, sparsely filled bands would make it larger
-// than four directions' stripe edges.
+// than four directions' stripe edges.  Whole calls with tiles of 1280 bins,
+// windows searched for -> from the table, in us: 6300 FFTs of 4096 s, 584 rows:
+// 1 direction 317 -> 323, 2: 581 -> 575, 3: 726 -> 725, 8: 1790 -> 1771; 25 144
+// of 1024 s, 17 rows: 1: 98 -> 109, 3: 117 -> 128, 8: 185 -> 191 (and 97: 463 ->
+// 334 of front); 3143 of 8192 s, 118 rows: 1: 112 -> 121, 3: 222 -> 228, 8: 473
+// -> 472.  Where the lines cross lies between 2 directions and some ten, by the
+// rows; at 3 no shape loses more than 11 us.
 constexpr int kRankMinDirs = 3;
 
 // Row blocks up to which the tiles of such a launch compute the stripe edges
 // from the natural bins instead of reading them.  Each peak's edge is then
 // computed once per row block, and the front neither computes nor stores it:
-// with few row blocks the edges' way through memory (4 bytes per peak and
-// direction written, and lines of them read that two bin blocks share) costs
-// more than ten FP64 instructions per block of the tiles.  Whole calls of 128
+// with few row blocks what the front saves (4 bytes per peak and direction
+// written) is more than the tiles spend on ten FP64 instructions per block (17
+// rows, 128 directions: front 793 -> 233 us, tiles 942 -> 949).  Whole calls of 128
 // directions (97 of 17 rows, 64 of 147), edges read -> computed: 1 row block
 // (17 rows) 1170 -> 815 us, weighted 1805 -> 1352; 2 (31 rows) 1654 -> 1418;
 // 4 (60 rows) 2692 -> 2591; 8 (118 rows) 5218 -> 5353; 10 (147 rows) 3498 ->
