@@ -2236,6 +2236,7 @@ struct ServerRequest {
     size_t arena_off = 0;
     int32_t chunk = 1;
     int32_t W = 64;
+    int32_t window_method = 2;  // the context's, for which the block is laid out
     int32_t lane = -1;
     int32_t status = FH_OK;
     double device_ms = 0.0, latency_ms = 0.0, queue_ms = 0.0;
@@ -2315,9 +2316,12 @@ void admit(fh_server *srv) {
         else if (hipMemcpyAsync(b.sky, R.sky.data(), (size_t)24 * q.n_sky, hipMemcpyHostToDevice, L.st) != hipSuccess)
             s = fail(FH_E_DEVICE, "copying the request's sky vectors failed");
         if (!s && hipEventRecord(L.ev_start, L.st) != hipSuccess) s = fail(FH_E_DEVICE, "hipEventRecord");
+        const int32_t method = ctx->window_method;
+        ctx->window_method = R.window_method;
         if (!s)
             s = run_search(ctx, q.pm, &q.grid, p, R.chunk, q.n_sky, q.d_w, q.w_stride,
                            FH_SCHED_PERSISTENT, &q.sel, q.d_out, b, L.st, dirs);
+        ctx->window_method = method;
         if (hipEventRecord(L.ev_done, L.st) != hipSuccess && !s) s = fail(FH_E_DEVICE, "hipEventRecord");
         R.status = s;
         srv->in_flight += (int64_t)R.layout.total;
@@ -2382,6 +2386,7 @@ fh_status fh_server_submit(fh_server *srv, const fh_request *req, uint64_t *id) 
     R.r = *req;
     R.sky.assign(req->sky, req->sky + 3 * (int64_t)req->n_sky);
     R.r.sky = nullptr;
+    R.window_method = ctx->window_method;
     R.t_submit = Clock::now();
     // the largest chunk whose search fits one lane's share of the budget, with
     // the default tile width and without what only saves time

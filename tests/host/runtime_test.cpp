@@ -350,6 +350,28 @@ void search_after_a_refused_call() {
     fh_ctx_destroy(c);
 }
 
+// A queued request runs with the window method that its block was laid out
+// for: another one needs the full edges, for which there is no place.
+void option_changed_behind_a_queued_request() {
+    fh_ctx *c = make_ctx();
+    fh_peakmap *pm = upload(c, 100, 100);
+    const fh_request q{pm, grid(2000, 17), kSel, 2, kSky, nullptr, 0, g_out, 0};
+    fh_server *srv = nullptr;
+    uint64_t id = 0;
+    CHECK(fh_server_create(c, 64 * kMB, 1, 4, &srv) == FH_OK);
+    for (const int method : {2, 0}) {
+        CHECK(fh_ctx_set_option(c, "window_method", method) == FH_OK);
+        CHECK(fh_server_submit(srv, &q, &id) == FH_OK);
+        CHECK(fh_ctx_set_option(c, "window_method", 2 - method) == FH_OK);
+        fake::launches.clear();
+        CHECK(fh_server_drain(srv) == FH_OK);
+        CHECK((last("prep") != nullptr) == (method == 0) && c->window_method == 2 - method);
+    }
+    fh_server_destroy(srv);
+    fh_peakmap_release(c, pm);
+    fh_ctx_destroy(c);
+}
+
 struct Case {
     const char *name;
     void (*run)();
@@ -366,6 +388,7 @@ const Case kCases[] = {
     {"forced_tile_parts", forced_tile_parts},
     {"spectra_without_pinned_memory", spectra_without_pinned_memory},
     {"search_after_a_refused_call", search_after_a_refused_call},
+    {"option_changed_behind_a_queued_request", option_changed_behind_a_queued_request},
 };
 
 }  // namespace

@@ -45,6 +45,7 @@ def _run(exe, name):
     "forced_tile_parts",
     "spectra_without_pinned_memory",
     "search_after_a_refused_call",
+    "option_changed_behind_a_queued_request",
 ])
 def test_host_runtime(build, name):
     _run(build(), name)
